@@ -229,3 +229,46 @@ def tolerance(case):
         return {"rel": 1.5e-6, "max": 1.6e-5}
     causal = case.get("causal") or case.get("diag") or case["path"] == "at"
     return {"rel": 9e-3 if case.get("block") == "bf16" else 6.5e-3, "max": 0.4 if causal else 8e-2}
+
+
+def exact(case, seed):
+    """out and lse in 64 bits from the definitions: attention over every key a row sees, and partial results weighted by
+    exp(lse_i - lse).  Row blocks keep the score matrix near a gigabyte."""
+    st = prepare(case, seed)
+    if case["path"] in ("merge", "nary"):
+        outs, lses = list(st["outs"]), list(st["lses"])
+        if case.get("acc"):
+            outs, lses = outs + [st["held"]], lses + [st["seen"]]
+        lse = torch.logsumexp(torch.stack([x.double() for x in lses]), 0)
+        out = torch.zeros(st["out"].shape, dtype=torch.float64, device="cuda")
+        for o, x in zip(outs, lses):
+            out += torch.exp(x.double() - lse)[..., None] * o.double()
+        return out, lse
+    B, Hq, Hkv, D, scale = case["B"], case["Hq"], case["Hkv"], case["D"], st["scale"]
+    kv = st["kv"] if "kv" in st else [(st["k"], st["v"])]
+    Sq = st["q"].shape[2]
+    out = torch.empty((B, Hq, Sq, D), dtype=torch.float64, device="cuda")
+    lse = torch.empty((B, Hq, Sq), dtype=torch.float64, device="cuda")
+    causal = case.get("causal") or case.get("diag") or case["path"] == "at"
+    first = case.get("q0", 0) - case.get("k0", 0)          # Query row r sees the keys up to r + first of the chunk that holds the diagonal
+    own = kv[0][0].shape[2]                                # keys of that chunk; those behind it are seen by every row
+    rows = torch.arange(Sq, device="cuda")
+    for b in range(B):
+        for g in range(Hkv):
+            k = torch.cat([x[b, g].double() for x, _ in kv])
+            v = torch.cat([x[b, g].double() for _, x in kv])
+            step = max(64, min(Sq, (1 << 27) // k.shape[0]))
+            for h in range(g * (Hq // Hkv), (g + 1) * (Hq // Hkv)):
+                for r0 in range(0, Sq, step):
+                    r1 = min(Sq, r0 + step)
+                    n = min(k.shape[0], r1 + first) if causal and len(kv) == 1 else k.shape[0]
+                    s = (st["q"][b, h, r0:r1].double() * scale) @ k[:n].t()
+                    if causal:
+                        m = min(n, own)
+                        s[:, :m].masked_fill_(torch.arange(m, device="cuda")[None, :] > rows[r0:r1, None] + first, float("-inf"))
+                    top = s.amax(1, keepdim=True)
+                    s.sub_(top).exp_()
+                    total = s.sum(1)
+                    out[b, h, r0:r1] = (s @ v[:n]) / total[:, None]
+                    lse[b, h, r0:r1] = top[:, 0] + total.log()
+    return out, lse
