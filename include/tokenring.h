@@ -144,17 +144,15 @@ tr_status tr_merge_n(const tr_tensor* out, const tr_tensor* lse,
  * steps with j > c are skipped and j == c uses the diagonal mask.
  *   q [B,Hq,S,D] bf16   k, v [B,Hkv,S,D] bf16   out [B,Hq,S,D] fp32   lse [B,Hq,S] fp32
  *   S must be a multiple of n_chunks; n_chunks >= 1; scale <= 0 selects 1/sqrt(D).
- *   workspace == NULL (workspace_bytes ignored): every step after a Query chunk's first one
- *   runs as tr_block_attn_merge, i.e. the Update happens in the attention kernel's epilogue;
- *   consecutive steps on distinct Query chunks (what different devices do at the same time)
- *   share one kernel launch (tr_schedule_steps shows the grouping).
- *   workspace != NULL: the two-kernel form of Algorithm 1 - tr_block_attn writes one fp32
- *   block result (block_out, block_lse) into the workspace and tr_merge folds it into
- *   out/lse.  It needs at least tr_ring_attn_workspace_bytes(q, n_chunks) bytes, 256-byte
- *   aligned; its contents on return are unspecified.
- * Both forms apply the same Update arithmetic in the same order.  The first block of every
- * Query chunk is written straight into out/lse, so the caller need not initialise them.  All
- * launches go to `hip_stream` in a fixed order, hence the result is bitwise reproducible.
+ *   One GPU holds every K/V chunk, and the Update is associative and commutative: the blocks a
+ *   Query row meets are folded in registers by the softmax that runs over all its keys, so the
+ *   whole schedule is one attention kernel (one launch per 65535 * 256 Query rows) and no block result
+ *   reaches memory.  The result is that of the steps one by one up to fp32 rounding.
+ *   workspace == NULL: workspace_bytes is ignored.  workspace != NULL: checked - at least
+ *   tr_ring_attn_workspace_bytes(q, n_chunks) bytes, 256-byte aligned, apart from the tensors - and
+ *   left alone; the result is bitwise the same.
+ * out and lse are written once, the caller need not initialise them.  The result is bitwise
+ * reproducible.
  */
 tr_status tr_ring_attn(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v,
                        int n_chunks, int causal,
@@ -162,7 +160,7 @@ tr_status tr_ring_attn(const tr_tensor* q, const tr_tensor* k, const tr_tensor* 
                        void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /*
- * Algorithm 1 in its literal two-kernel form with a chosen format for the block result that
+ * Algorithm 1 with a chosen format for the block result that
  * travels between the Attention and the Update (Sec. 3.1 notes the volume of block_out and
  * block_lse): block_dtype = TR_F32 is tr_ring_attn with a workspace; TR_BF16 halves block_out
  * (what a multi-device run would put on the wire) at the cost of one bf16 rounding (at most 2^-8
@@ -177,18 +175,12 @@ tr_status tr_ring_attn_blocks(const tr_tensor* q, const tr_tensor* k, const tr_t
 size_t tr_ring_attn_blocks_workspace_bytes(const tr_tensor* q, int n_chunks, int block_dtype);
 
 /*
- * tr_ring_attn in its two-kernel form for callers that cannot allocate device memory: code under
- * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The block result that
- * travels from tr_block_attn to tr_merge (fp32 block_out + block_lse of one step) lives in a
- * device array inside the library (TR_NOALLOC_SCRATCH_BYTES, held by every GPU the library runs on
- * until the process ends) instead of a caller workspace; the call allocates and frees nothing on
- * the device and calls no allocating library routine.  Limit: one block result,
+ * tr_ring_attn for callers that cannot allocate device memory: code under
+ * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The call allocates and
+ * frees nothing on the device and calls no allocating library routine.  Limit: one block result,
  *   align256(B * Hq * (S / n_chunks) * D * 4) + align256(B * Hq * (S / n_chunks) * 4) bytes,
- * must fit the array; larger problems return TR_ERR_WORKSPACE (use tr_ring_attn with a workspace).
- * Arguments, checks, arithmetic and results are those of tr_ring_attn with a workspace (bitwise).
- * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different
- * streams or threads) race and must be serialised by the caller.  Nothing in the array needs
- * clearing: every step overwrites the block result before the Update reads it.
+ * must not exceed TR_NOALLOC_SCRATCH_BYTES; larger problems return TR_ERR_WORKSPACE (use
+ * tr_ring_attn).  Arguments, checks, arithmetic and results are those of tr_ring_attn (bitwise).
  */
 #define TR_NOALLOC_SCRATCH_BYTES (8 * 1024 * 1024 + 64 * 1024)
 tr_status tr_ring_attn_noalloc(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v,
@@ -204,44 +196,40 @@ typedef enum {
 } tr_schedule;
 
 /*
- * tr_ring_attn with a selectable schedule; the Update always runs in the attention epilogue
- * (no workspace).  The sequence is cut into n_devices equal chunks (2 * n_devices segments for
- * TR_SCHED_ZIGZAG, which requires causal != 0); S must be a multiple of that.
+ * tr_ring_attn with a selectable schedule (no workspace).  The sequence is cut into n_devices equal
+ * chunks (2 * n_devices segments for TR_SCHED_ZIGZAG, which requires causal != 0); S must be a
+ * multiple of that.  The schedules partition the same work among devices; on one GPU the parts a
+ * Query segment meets are folded in registers as in tr_ring_attn.
  *   TR_SCHED_TOKENRING      for i, for j: Q chunk (j-i) mod n  x  K/V chunk j       (bitwise equal to
  *                           tr_ring_attn with workspace == NULL)
  *   TR_SCHED_RING_ATTENTION for i, for j: Q chunk j  x  K/V chunk (j-i) mod n
  *   TR_SCHED_ZIGZAG         for i, for j: the Query pair {c, 2n-1-c}, c = (j-i) mod n, against the K/V pair
  *                           {j, 2n-1-j}; of the four segment pairs the causal rule keeps two full ones
- *                           (three on i == 0, two of them diagonal), so every (i, j) carries the same work.  When the
- *                           later Query segment meets both K/V segments of the device and the segment length is a
- *                           multiple of 128, the two are attended in ONE block step over the device's whole K/V (one
- *                           softmax over both, one Update), which leaves the result of Sec. 3.1's Update unchanged; an iteration is then
- *                           a single launch of at most two steps per device.  Otherwise the devices' pairs are issued
- *                           slot by slot (all first pairs, then all second, ...)
+ *                           (three on i == 0, two of them diagonal), so every (i, j) carries the same work
  *   TR_SCHED_HYBRID         n_devices = nodes x n_inner; for t < nodes, for i < n_inner, for node, for p:
  *                           Q chunk node*n_inner + (p-i) mod n_inner  x  K/V chunk ((node-t) mod nodes)*n_inner + p
  *                           (n_inner is ignored by the other schedules)
  * With causal != 0 a step whose K/V segment lies after its Query segment is dropped and equal
- * segments use the diagonal mask.  Every schedule reaches the same result up to fp32 rounding of
- * the merge order; each is bitwise reproducible.  Tensors, scale and stream as in tr_ring_attn.
+ * segments use the diagonal mask.  Every schedule reaches the same result and is bitwise
+ * reproducible.  Tensors, scale and stream as in tr_ring_attn.
  */
 tr_status tr_ring_attn_sched(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v,
                              int n_devices, int causal, int schedule, int n_inner,
                              const tr_tensor* out, const tr_tensor* lse, float scale, void* hip_stream);
 
 /*
- * Host-only view of what tr_ring_attn_sched (and the fused tr_ring_attn, schedule
- * TR_SCHED_TOKENRING) will run: the block steps of a schedule in execution order.  Returns
+ * Host-only view of a schedule (tr_ring_attn: TR_SCHED_TOKENRING): its block steps in the order in
+ * which devices would run them.  Returns
  * the number of steps, or -1 on invalid arguments (tr_last_error() says why).  If steps_out
  * (HOST memory, 3 * capacity int32) is given, step i < capacity is written as
  *   steps_out[3i] = Query segment, steps_out[3i+1] = K/V segment, steps_out[3i+2] = index of
- *   the attention launch that carries the step
- * (steps of one launch touch distinct Query segments and run concurrently; launches run in
- * order).  Segments are n_devices equal chunks of S, 2 * n_devices for TR_SCHED_ZIGZAG; with
+ *   the group of concurrent steps it belongs to
+ * (steps of one group touch distinct Query segments; each group's Updates need the groups before
+ * it).  Segments are n_devices equal chunks of S, 2 * n_devices for TR_SCHED_ZIGZAG; with
  * causal != 0 a step with equal segments is the diagonal-masked one.  For TR_SCHED_ZIGZAG the
- * list is the one for segment lengths that are multiples of 128: a block step over a pair of
- * K/V segments appears as its two (Query segment, K/V segment) entries, adjacent and in the
- * same launch, the only case of a Query segment occurring twice in a launch.  Touches no device.
+ * later Query segment of a device meets both K/V segments of the device as one block step, which
+ * appears as its two (Query segment, K/V segment) entries, adjacent and in the
+ * same group, the only case of a Query segment occurring twice in a group.  Touches no device.
  */
 int64_t tr_schedule_steps(int schedule, int n_devices, int n_inner, int causal, int32_t* steps_out, int64_t capacity);
 

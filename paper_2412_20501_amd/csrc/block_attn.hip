@@ -93,14 +93,14 @@ __device__ __forceinline__ int v_lds_off(int row, int c) {
   return row * RB + ((slot ^ swz) << 5) + ((c & 1) << 4);
 }
 
-// Which (batch*head, query tile, block step) a workgroup computes.  The grid is three-dimensional
-// - x: batch*head, y: query tile, z: block step of the launch - so the indices come from the
+// Which (batch*head, query tile) a workgroup computes.  The grid is two-dimensional - x: batch*head,
+// y: query tile - so the indices come from the
 // hardware instead of integer divisions (a division costs ~40 dependent instructions and the
 // decoding sits in front of every workgroup's first load).  Workgroups are dealt round-robin to
 // the 8 XCDs in the order of their linear id, which is x-fastest, and the x extent is a multiple
 // of 8 whenever xcd_map is set: XCD = blockIdx.x mod 8.  XCD x gets the K/V heads x, x+8, ... and
 // all query heads and query tiles that read them, so a head's K/V stays in one L2.
-__device__ __forceinline__ void decode_block(const AttnParams& p, int& qt, int& b, int& hq, int& hk, int& prob) {
+__device__ __forceinline__ void decode_block(const AttnParams& p, int& qt, int& b, int& hq, int& hk) {
   const int gq = p.gq, sh = p.gq_log2;   // query heads per K/V head; its log2, or -1 if not a power of two
   int bh = (int)blockIdx.x, qi = (int)blockIdx.y;
   if (p.xcd_map) {
@@ -117,7 +117,6 @@ __device__ __forceinline__ void decode_block(const AttnParams& p, int& qt, int& 
   hq = bh - b * p.Hq;
   hk = sh >= 0 ? hq >> sh : hq / gq;
   qt = p.n_qtiles - 1 - qi;  // late query tiles (most keys under a causal mask) first
-  prob = (int)blockIdx.z;
 }
 
 typedef __attribute__((address_space(1))) const void* gptr_t;
@@ -162,19 +161,11 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in an SGPR
   const int ql = lane & 31, hf = lane >> 5;
 
-  // which block step of the launch, batch, head and query tile this workgroup computes (wave-uniform)
-  int qt, b, hq, hk, prob;
-  decode_block(p, qt, b, hq, hk, prob);
-  const AttnParams::Step sg = p.step[prob];
-  const int64_t qseg = sg.q_seg, kseg = sg.k_seg;
-  const bool causal = (p.causal_bits >> prob) & 1u;
-  // A block step may attend a pair of K/V segments as one key range (the two segments a device of
-  // the zigzag partition holds): keys 0 .. p.Sk-1 are segment kseg, keys p.Sk .. 2 p.Sk-1 segment
-  // kseg2, which lies p.Sk positions later in the causal rule.  p.Sk is then a multiple of the
-  // tile, so the tile stream changes segment between two tiles.
-  const int kseg2 = sg.k_seg2;
-  const int Sk = kseg2 >= 0 ? 2 * p.Sk : p.Sk;
-  const int causal_off = kseg2 >= 0 ? p.Sk : p.causal_off;
+  // which batch, head and query tile this workgroup computes (wave-uniform)
+  int qt, b, hq, hk;
+  decode_block(p, qt, b, hq, hk);
+  const bool causal = p.causal != 0;
+  const int Sk = p.Sk, causal_off = p.causal_off;
   const int q0 = qt * kBM, qw0 = q0 + wave * 32;
   const int qrow = qw0 + ql;
   const int qrow_ld = min(qrow, p.Sq - 1);
@@ -185,8 +176,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   if (causal) kv_end = max(0, min(Sk, q_last_wg + causal_off + 1));
   const int n_tiles = (kv_end + BN - 1) / BN;
 
-  const __bf16* kg = p.k + kseg * p.k_seg_elems + (int64_t)b * p.k_sb + (int64_t)hk * p.k_sh;
-  const __bf16* vg = p.v + kseg * p.v_seg_elems + (int64_t)b * p.v_sb + (int64_t)hk * p.v_sh;
+  const __bf16* kg = p.k + (int64_t)b * p.k_sb + (int64_t)hk * p.k_sh;
+  const __bf16* vg = p.v + (int64_t)b * p.v_sb + (int64_t)hk * p.v_sh;
 
   // Direct global -> LDS staging (no VGPRs, no ds_write): one wave-wide instruction deposits
   // lane l's 16 bytes at lds_base + 16*l, i.e. RPI consecutive tile rows.  The swizzle is
@@ -228,16 +219,12 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   const __bf16* v_next = uniform_ptr(vg);
   const int64_t k_tile_stride = (int64_t)BN * p.k_ss, v_tile_stride = (int64_t)BN * p.v_ss;
   int k_left = last_tile, v_left = last_tile;  // tiles still ahead of the pointer
-  // with a segment pair: the pointer leaves the first segment when jump_left tiles are still ahead
-  // (the counters run below zero when the ring issues past the last tile, so "never" is a value they cannot take)
-  const int jump_left = kseg2 >= 0 ? last_tile + 1 - p.Sk / BN : 0x7fffffff;
-  const int64_t k_jump = (int64_t)(kseg2 - (int)kseg - 1) * p.k_seg_elems, v_jump = (int64_t)(kseg2 - (int)kseg - 1) * p.v_seg_elems;
   auto issue_k = [&](int slot) __attribute__((always_inline)) {
     const bool last = k_left <= 0;
 #pragma unroll
     for (int i = 0; i < IPW; i++)
       dma16(k_next, last ? k_off_last[i] : k_off[i], slot * TILE_BYTES + (wave * IPW + i) * 1024);
-    k_next = uniform_ptr(k_next + (last ? 0 : k_tile_stride) + (k_left == jump_left ? k_jump : 0));
+    k_next = uniform_ptr(k_next + (last ? 0 : k_tile_stride));
     k_left--;
   };
   auto issue_v = [&](int slot) __attribute__((always_inline)) {
@@ -245,7 +232,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
 #pragma unroll
     for (int i = 0; i < IPW; i++)
       dma16(v_next, last ? v_off_last[i] : v_off[i], (NS + slot) * TILE_BYTES + (wave * IPW + i) * 1024);
-    v_next = uniform_ptr(v_next + (last ? 0 : v_tile_stride) + (v_left == jump_left ? v_jump : 0));
+    v_next = uniform_ptr(v_next + (last ? 0 : v_tile_stride));
     v_left--;
   };
 
@@ -262,7 +249,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step.
   bf16x8 qf[KS];
   {
-    const __bf16* qp = p.q + qseg * p.q_seg_elems + (int64_t)b * p.q_sb + (int64_t)hq * p.q_sh + (int64_t)qrow_ld * p.q_ss;
+    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)hq * p.q_sh + (int64_t)qrow_ld * p.q_ss;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * hf);
   }
@@ -309,8 +296,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     for (int i = 0; i < 16; i++) o_acc[db][i] = 0.f;
   // Largest sub-tile sum (16 weights of one row) the fast path accepts: 2^80.  The weights, their
   // bf16 roundings and the fp32 accumulators all carry an 8-bit exponent, so precision does not
-  // depend on the magnitude; the cap only has to keep sums over a whole K/V chunk (up to 2^20 keys,
-  // |v| up to 2^7) below 2^127.  A score must therefore exceed the reference by 55 (in natural
+  // depend on the magnitude; the cap only has to keep sums over all keys (up to 2^30, i.e. 2^25
+  // sub-tiles, |v| up to 2^7) below 2^127.  A score must therefore exceed the reference by 55 (in natural
   // units) before the reference is moved: on all but pathological inputs that happens once, at
   // the row's first keys.
   constexpr float kSumCap = 0x1p80f;
@@ -471,9 +458,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     for (int i = 0; i < NQK; i++) pre[i] = nxt[i];
   };
 
-  // Tiles that are certain to lie before the last tile of the K/V segment (and not at the end of
-  // the first segment of a pair) need neither the choice between the two offset sets nor the
-  // end-of-stream and change-of-segment tests.
+  // Tiles that are certain to lie before the last tile of the keys need neither the choice between
+  // the two offset sets nor the end-of-stream test.
   auto issue_k_inner = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < IPW; i++) dma16(k_next, k_off[i], slot * TILE_BYTES + (wave * IPW + i) * 1024);
@@ -573,27 +559,19 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   if (1 <= n_tiles) tile_body(1, IC<1 % NS>{}, IC<0>{});
   if (2 <= n_tiles) tile_body(2, IC<2 % NS>{}, IC<0>{});
   if (3 <= n_tiles) tile_body(3, IC<3 % NS>{}, IC<0>{});
-  // Groups of NS tiles: first the groups of inner tiles, then general ones to the end.  With a pair
-  // of segments the sequence runs twice: the groups whose loads (K_{u0+3} .. K_{u0+6}, V_{u0+2} ..
-  // V_{u0+5}) include the last tile of the first segment, after which the stream changes segment,
-  // take the general bodies, and the inner ones resume behind them.
-  const int jump_tile = kseg2 >= 0 ? p.Sk / BN - 1 : 0x40000000;
+  // Groups of NS tiles: first the groups of inner tiles, then general ones to the end.
   int u0 = NS;
-  for (int half = 0; half < 2; half++) {
-    const int inner_end = half == 0 ? min(u_inner, jump_tile - 4) : u_inner;
-    const int general_end = half == 0 ? min(n_tiles, jump_tile - 2) : n_tiles;
-    for (; u0 + NS - 1 <= inner_end; u0 += NS) {
-      tile_body(u0, IC<0>{}, IC<1>{});
-      tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{});
-      tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{});
-      tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{});
-    }
-    for (; u0 <= general_end; u0 += NS) {
-      tile_body(u0, IC<0>{}, IC<0>{});
-      if (u0 + 1 <= n_tiles) tile_body(u0 + 1, IC<1 % NS>{}, IC<0>{});
-      if (u0 + 2 <= n_tiles) tile_body(u0 + 2, IC<2 % NS>{}, IC<0>{});
-      if (u0 + 3 <= n_tiles) tile_body(u0 + 3, IC<3 % NS>{}, IC<0>{});
-    }
+  for (; u0 + NS - 1 <= u_inner; u0 += NS) {
+    tile_body(u0, IC<0>{}, IC<1>{});
+    tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{});
+    tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{});
+    tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{});
+  }
+  for (; u0 <= n_tiles; u0 += NS) {
+    tile_body(u0, IC<0>{}, IC<0>{});
+    if (u0 + 1 <= n_tiles) tile_body(u0 + 1, IC<1 % NS>{}, IC<0>{});
+    if (u0 + 2 <= n_tiles) tile_body(u0 + 2, IC<2 % NS>{}, IC<0>{});
+    if (u0 + 3 <= n_tiles) tile_body(u0 + 3, IC<3 % NS>{}, IC<0>{});
   }
   __builtin_amdgcn_s_waitcnt(0);  // no LDS write of this workgroup may still be in flight at exit
 
@@ -625,11 +603,11 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     }
   if (EPI != kEpiMerge) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
   if (EPI != kEpiMerge && hf == 0 && qrow < p.Sq)
-    p.lse[qseg * p.l_seg_elems + (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (int64_t)qrow * p.l_ss] = lse_blk;
+    p.lse[(int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (int64_t)qrow * p.l_ss] = lse_blk;
   const int rr = lane / CPRF, cc = lane % CPRF;
   constexpr int NIT = 32 / RPI_OUT;
-  const int64_t o_bh = qseg * p.o_seg_elems + (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + 4 * cc;
-  const int64_t l_bh = qseg * p.l_seg_elems + (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh;
+  const int64_t o_bh = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + 4 * cc;
+  const int64_t l_bh = (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh;
   if (EPI == kEpiMerge) {
     // Out, Lse <- Update(block_out, block_lse) on the accumulators p.out / p.lse.  All of the
     // wave's accumulator rows are fetched first (the O registers are free by now), so their
@@ -696,7 +674,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     constexpr int RPI_B = 64 / LPR;     // rows one wave-wide store covers
     constexpr int NIT_B = 32 / RPI_B;
     const int rb = lane / LPR, cb = lane % LPR;
-    const int64_t ob_bh = qseg * p.o_seg_elems + (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + 8 * cb;
+    const int64_t ob_bh = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + 8 * cb;
     f32x4 o0[NIT_B], o1[NIT_B];
 #pragma unroll
     for (int it = 0; it < NIT_B; it++) {
@@ -747,10 +725,10 @@ hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
 
 hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream) {
   const int64_t nbh = (int64_t)p.B * p.Hq;
-  if (nbh * p.n_qtiles * p.n_prob == 0) return hipSuccess;
-  if (p.n_qtiles > 65535 || p.n_prob > 65535) return hipErrorInvalidValue;   // grid y / z limits
-  dim3 grid((unsigned)nbh, (unsigned)p.n_qtiles, (unsigned)p.n_prob);
-  if (p.xcd_map == 2) grid = dim3(8u * (unsigned)p.n_qtiles, (unsigned)(nbh / 8), (unsigned)p.n_prob);
+  if (nbh * p.n_qtiles == 0) return hipSuccess;
+  if (p.n_qtiles > 65535) return hipErrorInvalidValue;   // grid y limit
+  dim3 grid((unsigned)nbh, (unsigned)p.n_qtiles);
+  if (p.xcd_map == 2) grid = dim3(8u * (unsigned)p.n_qtiles, (unsigned)(nbh / 8));
   if (D == 128) {
     if (epilogue == kEpiBf16) return launch_one<128, kEpiBf16>(p, grid, stream);
     if (epilogue == kEpiF32) return launch_one<128, kEpiF32>(p, grid, stream);
