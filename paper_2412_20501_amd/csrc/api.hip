@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <vector>
 
 #include "tr_internal.h"
@@ -93,6 +94,170 @@ struct RingStep {
   int ks2 = -1;
 };
 
+// View of `rows` rows of a tensor along S, from row r0 on.
+tr_tensor rows_view(const tr_tensor* t, int64_t r0, int64_t rows) {
+  tr_tensor r = *t;
+  r.ptr = (char*)t->ptr + r0 * t->stride_s * elem_bytes(t->dtype);
+  r.S = rows;
+  return r;
+}
+
+// ---- partitioned attention launches: which calls, how many parts, and where the partial results go.
+
+constexpr int kCUs = 256;
+constexpr int kPartStreams = 4;
+constexpr int64_t kPartBytes = (int64_t)33 << 20;   // 256 workgroups' partials of 256 rows at D = 128
+constexpr int64_t kPartAlign = 128;   // parts begin on whole tiles of either head dim
+
+struct PartPlan {
+  int pack = 0, parts = 1, members = 0, row_tiles = 0, part_rows = 0;
+  int64_t part_keys = 0, out_elems = 0;   // out_elems: floats of block_out in the scratch
+};
+
+// Chooses the form of a launch; false: the plain one.
+//
+// Heads are packed when that leaves at most four fifths of the row tiles: the rows that fill a tile up cost
+// their share of the loads and of the time of its slowest wave all the same.  (Where the plain form fits the
+// chip at once and the keys are too few to be cut, packing only idles compute units: 75 rows x 32 heads on
+// 75 keys 18.2 against 17.6 us.)
+//
+// The keys are cut where an estimate of the call's time (us) says so, over rounds of one workgroup per compute
+// unit.  Measured: a tile of keys takes 0.65 while at most four waves of a workgroup have rows, else 1.0 on an
+// idle chip and 1.7 on a full one (the clock gives way); a workgroup's set-up and epilogue 8; the fold 5,
+// 0.25 for each part in a row's chain, and its partials at 3.5 TB/s; nothing is faster than K and V at 5 TB/s.
+// Both sides of the line, us: 500 rows x 32 heads on 12500 keys 213 in one part, 106 in 4; 96 rows x 8
+// heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 1777 rows x 24
+// heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 88 and 38 in 6.
+bool plan_parts(const tr::AttnParams& p, int D, PartPlan& best) {
+  const int bm = tr::attn_rows_per_block();
+  const int64_t rows = (int64_t)p.gq * p.Sq, kv = (int64_t)p.B * p.Hkv;
+  if (p.Sk == 0 || p.Sq == 0 || kv == 0 || rows > ((int64_t)1 << 24)) return false;
+  const int64_t packed = (rows + bm - 1) / bm, plain = (int64_t)p.gq * p.n_qtiles;
+  PartPlan c;
+  c.pack = 5 * packed <= 4 * plain;
+  c.row_tiles = c.pack ? (int)packed : p.n_qtiles;
+  c.members = (int)(c.pack ? packed : plain);
+  const int64_t space = c.pack ? rows : p.Sq, tiles = kv * c.members;
+  c.part_rows = space > bm ? bm : (int)((space + 31) / 32 * 32);
+  c.part_keys = ((int64_t)p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
+  best = c;
+  if (tiles * tr::kMaxParts >= ((int64_t)1 << 31)) return false;
+  if (tiles > 2 * kCUs) return c.pack;
+  // keys that some row of row tile t sees
+  auto seen = [&](int t) -> int64_t {
+    if (!p.causal) return p.Sk;
+    const int64_t last = c.pack ? p.Sq - 1 : std::min<int64_t>((int64_t)(t + 1) * bm, p.Sq) - 1;
+    return std::max<int64_t>(0, std::min<int64_t>(p.Sk, last + p.causal_off + 1));
+  };
+  const double tile_keys = D == 64 ? 128.0 : 64.0, heads = (double)tiles / c.row_tiles;
+  const int64_t all = seen(c.row_tiles - 1);
+  const double stream = (double)kv * all * D * 4 / 5e6, fix = 8.0;
+  auto estimate = [&](int64_t part_keys) {
+    double n = 0, keys = 0;
+    for (int t = 0; t < c.row_tiles; t++) {
+      n += heads * (double)std::max<int64_t>(1, (seen(t) + part_keys - 1) / part_keys);
+      keys += heads * (double)seen(t);
+    }
+    const double tile = c.part_rows <= 128 ? 0.65 : 1.0 + 0.7 * std::min(1.0, n / kCUs);
+    const double longest = (double)std::min(all, part_keys) / tile_keys * tile + fix;
+    double t = longest;
+    if (n > kCUs) t = p.causal ? (keys / tile_keys * tile + n * fix) / kCUs + 0.5 * longest : (double)(((int64_t)n + kCUs - 1) / kCUs) * longest;
+    return std::max(t, stream + fix);
+  };
+  double t_best = 0.95 * estimate(std::max<int64_t>(all, 1));
+  for (int n = 2; n <= tr::kMaxParts; n++) {
+    const int64_t part_keys = std::max<int64_t>(512, ((all + n - 1) / n + kPartAlign - 1) / kPartAlign * kPartAlign);
+    const int64_t parts = (all + part_keys - 1) / part_keys, slot_rows = tiles * parts * c.part_rows;
+    if (parts != n || slot_rows * (D + 1) * 4 > kPartBytes) continue;
+    const double t = estimate(part_keys) + 5.0 + 0.25 * (double)parts + (double)slot_rows * D * 4 / 3.5e6;
+    if (t >= t_best) continue;
+    t_best = t;
+    best.parts = (int)parts;
+    best.part_keys = part_keys;
+    best.out_elems = slot_rows * D;
+  }
+  return best.parts > 1 || (c.pack && kv * plain > kCUs);
+}
+
+// Scratch of the partitioned launches: device arrays of the library itself (nothing is allocated), one
+// region per stream for up to kPartStreams streams of a device.  Launches on one stream run one after
+// the other, so a region is in use by one launch at a time; a region stays with its stream (a
+// destroyed stream has finished its work before its handle can come back).  No region: for a stream
+// beyond the first kPartStreams, for the per-thread default stream, whose handle stands for several, for
+// a stream of another device than the current one, and under capture, because a graph may be replayed
+// on any stream.
+__device__ __align__(256) static unsigned char part_scratch[kPartStreams][kPartBytes];
+std::mutex g_part_lock;   // held from the choice of a region until the launches that use it are enqueued
+
+// The region of a stream, or NULL.  Called with g_part_lock held.
+char* part_scratch_for(hipStream_t stream) {
+  constexpr int kDevices = 64;
+  struct Device { char* bytes = nullptr; int n = 0; hipStream_t owner[kPartStreams]; };
+  static Device devices[kDevices];
+  if (stream == hipStreamPerThread || stream == (hipStream_t)1) return nullptr;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (capture != hipStreamCaptureStatusNone) return nullptr;
+  int dev = -1, stream_dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return nullptr;
+  if (stream != nullptr && (hipStreamGetDevice(stream, &stream_dev) != hipSuccess || stream_dev != dev)) return nullptr;
+  Device& d = devices[dev];
+  if (!d.bytes) {
+    void* a = nullptr;
+    if (hipGetSymbolAddress(&a, HIP_SYMBOL(part_scratch)) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    d.bytes = (char*)a;
+  }
+  int i = 0;
+  while (i < d.n && d.owner[i] != stream) i++;
+  if (i == d.n) {
+    if (d.n == kPartStreams) return nullptr;
+    d.owner[d.n++] = stream;
+  }
+  return d.bytes + (size_t)i * kPartBytes;
+}
+
+hipError_t launch_parts(tr::AttnParams p, const PartPlan& plan, int D, int epilogue, hipStream_t stream) {
+  p.pack = plan.pack;
+  p.members = plan.members;
+  p.n_qtiles = plan.row_tiles;
+  p.part_rows = plan.part_rows;
+  p.part_keys = (int)plan.part_keys;
+  if (plan.parts > 1) {
+    std::lock_guard<std::mutex> hold(g_part_lock);   // another thread on this stream must not enqueue between attention and fold
+    if (char* scratch = part_scratch_for(stream)) {
+      p.n_parts = plan.parts;
+      p.units = p.B * p.Hkv * p.n_parts;
+      p.part_out = (float*)scratch;
+      p.part_lse = p.part_out + plan.out_elems;
+      return tr::launch_block_attn(p, D, epilogue, stream);
+    }
+  }
+  p.n_parts = 1;
+  p.units = p.B * p.Hkv;
+  // Without scratch: fp32 results are folded part by part in out / lse themselves, one launch after the
+  // other, which gives the same bits; a bf16 result has no room for that and takes all keys at once.
+  const int parts = epilogue == 0 ? 1 : plan.parts;
+  const __bf16 *k = p.k, *v = p.v;
+  const int sk = p.Sk, off = p.causal_off;
+  for (int i = 0; i < parts; i++) {
+    const int64_t k0 = i * plan.part_keys;
+    p.k = k + k0 * p.k_ss;
+    p.v = v + k0 * p.v_ss;
+    p.Sk = (int)(parts == 1 ? sk : std::min<int64_t>(sk - k0, plan.part_keys));
+    p.part_keys = (p.Sk + 127) / 128 * 128;
+    p.causal_off = off - (int)k0;
+    const hipError_t e = tr::launch_block_attn(p, D, i > 0 ? 2 : epilogue, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // fuse_update: out/lse are fp32 accumulators and the block is merged into them by the kernel's epilogue
 tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int causal, int64_t off64, float scale,
                       const tr_tensor* out, const tr_tensor* lse, void* stream, bool fuse_update = false) {
@@ -147,17 +312,11 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   if (p.xcd_map && !p.causal && (int64_t)p.B * p.Hq / 8 <= 65535) p.xcd_map = 2;
   if (p.B == 0 || p.Hq == 0 || p.Sq == 0) return TR_OK;
   const int epilogue = fuse_update ? 2 : (out->dtype == TR_F32 ? 1 : 0);
-  const hipError_t e = tr::launch_block_attn(p, (int)q->D, epilogue, (hipStream_t)stream);
+  PartPlan plan;
+  const hipError_t e = plan_parts(p, (int)q->D, plan) ? launch_parts(p, plan, (int)q->D, epilogue, (hipStream_t)stream)
+                                                      : tr::launch_block_attn(p, (int)q->D, epilogue, (hipStream_t)stream);
   if (e != hipSuccess) return fail(TR_ERR_HIP, "block attention launch failed: %s", hipGetErrorString(e));
   return TR_OK;
-}
-
-// View of `rows` rows of a tensor along S, from row r0 on.
-tr_tensor rows_view(const tr_tensor* t, int64_t r0, int64_t rows) {
-  tr_tensor r = *t;
-  r.ptr = (char*)t->ptr + r0 * t->stride_s * elem_bytes(t->dtype);
-  r.S = rows;
-  return r;
 }
 
 // View of chunk `c` (of length C along S) of a tensor.

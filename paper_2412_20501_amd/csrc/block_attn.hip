@@ -134,12 +134,188 @@ __device__ __forceinline__ const __bf16* uniform_ptr(const __bf16* ptr) {
 // ordered by explicit s_waitcnt vmcnt() on the direct-to-LDS loads instead.
 __device__ __forceinline__ void wg_barrier() { __builtin_amdgcn_s_barrier(); }
 
+// The same for the partitioned form (PART): a one-dimensional grid over units (K/V head of a batch
+// entry, part of the keys) and, inside a unit, the row tiles that read its keys.  Unit u goes to XCD
+// u mod 8, so whatever shares keys shares an L2.  Returns false for the ids that only fill the last eight up.
+struct PartBlock { int tile, b, hk, hq0, part, group; };
+__device__ __forceinline__ bool decode_part(const AttnParams& p, PartBlock& w) {
+  const int x = (int)blockIdx.x & 7, rest = (int)blockIdx.x >> 3;
+  const int m = rest % p.members, u = rest / p.members * 8 + x;
+  if (u >= p.units) return false;
+  const int kv = u / p.n_parts;
+  w.part = u - kv * p.n_parts;
+  w.b = kv / p.Hkv;
+  w.hk = kv - w.b * p.Hkv;
+  w.group = kv * p.members + m;
+  const int head = p.pack ? 0 : m / p.n_qtiles;
+  w.hq0 = w.hk * p.gq + head;
+  w.tile = p.n_qtiles - 1 - (m - head * p.n_qtiles);
+  return true;
+}
+
 template <int N>
 using IC = std::integral_constant<int, N>;
 
+// The rows of a partitioned launch: row r of the row space of heads hq0, hq0 + 1, ... is Query row r mod Sq
+// of head hq0 + r / Sq.  pos_span: smallest and largest Query position among rows first .. first + n - 1.
+__device__ __forceinline__ int part_rows_total(const AttnParams& p) { return p.pack ? p.gq * p.Sq : p.Sq; }
+__device__ __forceinline__ void pos_span(const AttnParams& p, int first, int n, int& lo, int& hi) {
+  const int last = min(first + n, part_rows_total(p)) - 1;
+  const int ha = first / p.Sq, hb = last / p.Sq;
+  lo = ha == hb ? first - ha * p.Sq : 0;
+  hi = ha == hb ? last - hb * p.Sq : p.Sq - 1;
+}
+// Parts of the keys that any row of the tile sees, the first one always counted: parts 0 .. n - 1 are computed.
+__device__ __forceinline__ int live_parts(const AttnParams& p, int pos_last) {
+  const int seen = p.causal ? max(0, min(p.Sk, pos_last + p.causal_off + 1)) : p.Sk;
+  return max(1, (seen + p.part_keys - 1) / p.part_keys);
+}
+
+// LDS of the epilogue behind the waves' transposed 32 x D fp32 tiles (byte offsets from the start):
+// Update weight and case of each row, and for the partitioned form the rows' output offsets.
+template <int D>
+struct EpiLds {
+  static constexpr int w = kBM * 4 * D, mode = w + kBM * 4, off = mode + kBM * 4;
+  static constexpr int bytes = off, bytes_part = off + kBM * 8;
+};
+
+// Epilogue of the partitioned form.  The wave's normalised 32 x D tile lies in LDS (chunk-swizzled, written
+// by this wave), lse_blk is the log-sum-exp of the lane's row over the workgroup's part of the keys.  With
+// one live part the tile is stored or merged as it is, otherwise tile and lse go to the scratch slot of
+// (row tile, part) for the fold kernel.
+template <int D, int EPI>
+__device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, int q0, int b, int hq0, int group, int part, int n_live,
+                                              float lse_blk) {
+  constexpr int ROWB = 4 * D, CPRF = D / 4, RPI_OUT = 64 / CPRF, NIT = 32 / RPI_OUT;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ql = lane & 31, rr = lane / CPRF, cc = lane % CPRF;
+  const int n_rows = part_rows_total(p), n_valid = n_rows - (q0 + wave * 32);   // rows of this wave (32 or more: all)
+  if (n_valid <= 0) return;   // no barrier follows
+  const bool own_row = lane < 32 && ql < n_valid;
+  const char* const my = lds + wave * (32 * ROWB);
+
+  if (n_live > 1) {
+    const int64_t slot_row = ((int64_t)group * p.n_parts + part) * p.part_rows + wave * 32;
+    float* const dst = p.part_out + slot_row * D + 4 * cc;
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
+#pragma unroll
+    for (int it = 0; it < NIT; it++) {
+      const int r = it * RPI_OUT + rr;
+      const f32x4 o = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
+      if (r < n_valid) *reinterpret_cast<f32x4*>(dst + (int64_t)r * D) = o;
+    }
+    if (own_row) p.part_lse[slot_row + ql] = lse_blk;
+    return;
+  }
+  float* const tab_w = reinterpret_cast<float*>(lds + EpiLds<D>::w) + wave * 32;
+  int* const tab_mode = reinterpret_cast<int*>(lds + EpiLds<D>::mode) + wave * 32;
+  int64_t* const off = reinterpret_cast<int64_t*>(lds + EpiLds<D>::off) + wave * 32;
+  {
+    const int row = min(q0 + wave * 32 + ql, n_rows - 1), head = row / p.Sq, pos = row - head * p.Sq;
+    const int64_t l_at = (int64_t)b * p.l_sb + (int64_t)(hq0 + head) * p.l_sh + (int64_t)pos * p.l_ss;
+    const UpdatePlan pl = plan_update(EPI == kEpiMerge ? p.lse[l_at] : -INFINITY, lse_blk);
+    if (lane < 32) {
+      off[ql] = (int64_t)b * p.o_sb + (int64_t)(hq0 + head) * p.o_sh + (int64_t)pos * p.o_ss;
+      tab_w[ql] = pl.w;
+      tab_mode[ql] = pl.mode;
+    }
+    if (own_row) p.lse[l_at] = pl.new_lse;
+  }
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), as above
+#pragma unroll
+  for (int it = 0; it < NIT; it++) {
+    const int r = it * RPI_OUT + rr;
+    if (r >= n_valid) continue;
+    f32x4 o = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
+    const int64_t at = off[r] + 4 * cc;
+    if (EPI == kEpiBf16) {
+      bf16x4 ob;
+#pragma unroll
+      for (int e = 0; e < 4; e++) ob[e] = (__bf16)o[e];
+      *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + at) = ob;
+    } else {
+      f32x4* const dst = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + at);
+      if (EPI == kEpiMerge) {
+        UpdatePlan pl;
+        pl.w = tab_w[r];
+        pl.mode = tab_mode[r];
+        pl.new_lse = 0.f;
+        o = apply_update(pl, *dst, o);
+      }
+      *dst = o;
+    }
+  }
+}
+
+// Fold of a partitioned launch: out, lse <- the Update of Sec. 3.1 applied to the parts of a row in key order (with
+// kEpiMerge onto the accumulators).  A kernel of its own, because whoever finishes last would otherwise read all
+// parts of a row tile through one compute unit and pay for cache write-backs between the XCDs first:
+// 16 rows x 4 heads in 16 parts of 1024 keys 50 -> 30 us, 500 rows x 32 heads in 4 parts 119 -> 106 us (whole call).
+// A thread owns 16 bytes of a row; lse values and pieces of all its parts (MAXP at most) are requested before
+// the chain of log-sum-exps starts.
+constexpr int kFoldThreads = 256;
+template <int D, int EPI, int MAXP>
+__global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnParams p) {
+  constexpr int CPRF = D / 4;
+  const int group = (int)blockIdx.x, kv = group / p.members, m = group - kv * p.members;
+  const int b = kv / p.Hkv, hk = kv - b * p.Hkv;
+  const int head0 = p.pack ? 0 : m / p.n_qtiles;
+  const int q0 = (p.n_qtiles - 1 - (m - head0 * p.n_qtiles)) * kBM, n_tile = min(kBM, part_rows_total(p) - q0);
+  const int r = (int)blockIdx.y * (kFoldThreads / CPRF) + (int)threadIdx.x / CPRF, cc = (int)threadIdx.x % CPRF;
+  if (r >= n_tile) return;
+  int lo, hi;
+  pos_span(p, q0, kBM, lo, hi);
+  const int n_live = live_parts(p, hi);
+  if (n_live == 1) return;   // written by the attention kernel
+
+  const int head = (q0 + r) / p.Sq, pos = q0 + r - head * p.Sq, hq = hk * p.gq + head0 + head;
+  const int64_t l_at = (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (int64_t)pos * p.l_ss;
+  const int64_t o_at = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + (int64_t)pos * p.o_ss + 4 * cc;
+  const int64_t slot_row = (int64_t)group * p.n_parts * p.part_rows + r;
+  float ls[MAXP];
+  f32x4 y[MAXP];
+#pragma unroll
+  for (int i = 0; i < MAXP; i++) ls[i] = p.part_lse[slot_row + (int64_t)min(i, n_live - 1) * p.part_rows];
+#pragma unroll
+  for (int i = 0; i < MAXP; i++)
+    y[i] = *reinterpret_cast<const f32x4*>(p.part_out + (slot_row + (int64_t)min(i, n_live - 1) * p.part_rows) * D + 4 * cc);
+  float acc = -INFINITY;
+  f32x4 x = {0.f, 0.f, 0.f, 0.f};
+  if (EPI == kEpiMerge) {
+    acc = p.lse[l_at];
+    x = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.out) + o_at);
+  }
+#pragma unroll
+  for (int i = 0; i < MAXP; i++)
+    if (i < n_live) {
+      const UpdatePlan pl = plan_update(acc, ls[i]);
+      acc = pl.new_lse;
+      x = apply_update(pl, x, y[i]);
+    }
+  if (EPI == kEpiBf16) {
+    bf16x4 ob;
+#pragma unroll
+    for (int e = 0; e < 4; e++) ob[e] = (__bf16)x[e];
+    *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + o_at) = ob;
+  } else {
+    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + o_at) = x;
+  }
+  if (cc == 0) p.lse[l_at] = acc;   // a row lies within one wave, so every thread of it has read the old value
+}
+
 // EPI selects the epilogue: kEpiBf16 / kEpiF32 store block_out and block_lse; kEpiMerge folds
 // the block straight into fp32 accumulators with the Update of Sec. 3.1 (no block_out round trip).
-template <int D, int EPI>
+//
+// PART is the form for grids that would leave most of the chip idle (a decode step, a short prompt
+// behind a long cache).  (1) The rows of a workgroup are (query head of one K/V head's group, Query
+// row) pairs when that needs fewer workgroups: a decode step with grouped heads then reads every key
+// once instead of once per query head.  (2) The keys are cut into p.n_parts parts of p.part_keys
+// keys, each computed exactly as a launch over that part alone would; the block results go to a
+// scratch buffer in fp32 and fold_parts_kernel applies the Update of Sec. 3.1 to them in key order (a fixed
+// order: bitwise reproducible).  Bound: HBM for a decode step, MFMA otherwise, plus the fold.  Four decode steps
+// over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 156 us, 500 Query rows x 32 heads
+// behind 12000 keys 216 -> 105 us against the plain form.
+template <int D, int EPI, bool PART>
 __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p) {
   constexpr int RB = 2 * D;
   constexpr int KS = D / 16;               // MFMA k-steps over the head dim
@@ -163,21 +339,48 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
 
   // which batch, head and query tile this workgroup computes (wave-uniform)
   int qt, b, hq, hk;
-  decode_block(p, qt, b, hq, hk);
+  PartBlock pb = {0, 0, 0, 0, 0, 0};
+  if constexpr (PART) {
+    if (!decode_part(p, pb)) return;
+    qt = pb.tile; b = pb.b; hq = pb.hq0; hk = pb.hk;
+  } else {
+    decode_block(p, qt, b, hq, hk);
+  }
   const bool causal = p.causal != 0;
-  const int Sk = p.Sk, causal_off = p.causal_off;
+  int Sk = p.Sk, causal_off = p.causal_off;
   const int q0 = qt * kBM, qw0 = q0 + wave * 32;
   const int qrow = qw0 + ql;
-  const int qrow_ld = min(qrow, p.Sq - 1);
+  // rows of this workgroup's row space: the Query rows of one head, or of a whole group of heads
+  const int n_rows = PART ? part_rows_total(p) : p.Sq;
+  const int qrow_ld = min(qrow, n_rows - 1);
+  // Query position of this lane's row (its head is hq + lane_head), the smallest and largest position
+  // of the wave's rows, the largest of the workgroup's: what the causal rule needs
+  int lane_head = 0, lane_pos = qrow, pos_first = qw0, pos_last = min(qw0 + 31, p.Sq - 1), pos_last_wg = min(q0 + kBM, p.Sq) - 1;
+  int n_live = 1;   // parts of the keys that any row of this workgroup sees
+  if constexpr (PART) {
+    lane_head = qrow_ld / p.Sq;
+    lane_pos = qrow_ld - lane_head * p.Sq;
+    int unused;
+    pos_span(p, min(qw0, n_rows - 1), 32, pos_first, pos_last);
+    pos_span(p, q0, kBM, unused, pos_last_wg);
+    n_live = live_parts(p, pos_last_wg);
+    if (pb.part >= n_live) return;
+    const int k0 = pb.part * p.part_keys;
+    Sk = min(Sk - k0, p.part_keys);
+    causal_off -= k0;
+  }
 
   // Key range of this workgroup in tiles (needed to start the loads; the wave's own range follows below)
-  const int q_last_wg = min(q0 + kBM, p.Sq) - 1;
   int kv_end = Sk;
-  if (causal) kv_end = max(0, min(Sk, q_last_wg + causal_off + 1));
+  if (causal) kv_end = max(0, min(Sk, pos_last_wg + causal_off + 1));
   const int n_tiles = (kv_end + BN - 1) / BN;
 
   const __bf16* kg = p.k + (int64_t)b * p.k_sb + (int64_t)hk * p.k_sh;
   const __bf16* vg = p.v + (int64_t)b * p.v_sb + (int64_t)hk * p.v_sh;
+  if constexpr (PART) {
+    kg += (int64_t)pb.part * p.part_keys * p.k_ss;
+    vg += (int64_t)pb.part * p.part_keys * p.v_ss;
+  }
 
   // Direct global -> LDS staging (no VGPRs, no ds_write): one wave-wide instruction deposits
   // lane l's 16 bytes at lds_base + 16*l, i.e. RPI consecutive tile rows.  The swizzle is
@@ -249,7 +452,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step.
   bf16x8 qf[KS];
   {
-    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)hq * p.q_sh + (int64_t)qrow_ld * p.q_ss;
+    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)(PART ? hq + lane_head : hq) * p.q_sh + (int64_t)(PART ? lane_pos : qrow_ld) * p.q_ss;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * hf);
   }
@@ -257,9 +460,9 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
 
   // Key range of this wave (in 32-key sub-tiles).
   int wave_kv_end = 0;
-  if (qw0 < p.Sq) {
+  if (qw0 < n_rows) {
     wave_kv_end = Sk;
-    if (causal) wave_kv_end = max(0, min(Sk, min(qw0 + 31, p.Sq - 1) + causal_off + 1));
+    if (causal) wave_kv_end = max(0, min(Sk, pos_last + causal_off + 1));
   }
   const int jw = (wave_kv_end + SUB - 1) / SUB;  // sub-tiles this wave has visible keys in
   // wave-uniform loop bounds, forced into scalar registers so that every per-step test is one compare
@@ -267,7 +470,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   const int jw_in = __builtin_amdgcn_readfirstlane(min(jw, NSUB * n_tiles - 1));      // last allowed step inside a tile
   // a sub-tile starting at kstart needs masking iff kstart > kmask_from
   int kmask_from_v = Sk - SUB;
-  if (causal) kmask_from_v = min(kmask_from_v, qw0 + causal_off - SUB + 1);
+  if (causal) kmask_from_v = min(kmask_from_v, pos_first + causal_off - SUB + 1);
   const int kmask_from = __builtin_amdgcn_readfirstlane(kmask_from_v);
 
   // Per-lane LDS read offsets.
@@ -357,7 +560,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
 
     if (!INNER && kstart > kmask_from) {  // some key of the sub-tile is past Sk or above this wave's first diagonal
       int limit = Sk - 1;
-      if (causal) limit = min(limit, qrow + causal_off);
+      if (causal) limit = min(limit, lane_pos + causal_off);
 #pragma unroll
       for (int i = 0; i < 16; i++) {
         const int key = kstart + 8 * (i >> 2) + 4 * hf + (i & 3);
@@ -586,8 +789,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   constexpr int CPRF = D / 4;                 // 16-byte chunks per fp32 row = lanes per row when reading back
   constexpr int RPI_OUT = 64 / CPRF;          // rows one wave-wide access covers
   char* const my = lds + wave * (32 * ROWB);
-  float* const my_w = reinterpret_cast<float*>(lds + kWaves * 32 * ROWB) + wave * 32;   // Update weight of each of the wave's rows
-  int* const my_mode = reinterpret_cast<int*>(lds + kWaves * 32 * ROWB) + (kWaves + wave) * 32;   // and its case
+  float* const my_w = reinterpret_cast<float*>(lds + EpiLds<D>::w) + wave * 32;     // Update weight of each of the wave's rows
+  int* const my_mode = reinterpret_cast<int*>(lds + EpiLds<D>::mode) + wave * 32;   // and its case
   const float l_tot = half_swap_sum(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   const float lse_blk = l_tot > 0.f ? m_ref * p.scale + logf(l_tot) : -INFINITY;
@@ -601,6 +804,10 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
       for (int r = 0; r < 4; r++) o[r] = o_acc[db][4 * g + r] * inv;
       *reinterpret_cast<f32x4*>(my + ql * ROWB + ((c ^ (ql & 15)) << 4)) = o;
     }
+  if constexpr (PART) {
+    part_epilogue<D, EPI>(p, lds, q0, b, hq, pb.group, pb.part, n_live, lse_blk);
+    return;
+  }
   if (EPI != kEpiMerge) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
   if (EPI != kEpiMerge && hf == 0 && qrow < p.Sq)
     p.lse[(int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (int64_t)qrow * p.l_ss] = lse_blk;
@@ -698,11 +905,11 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   }
 }
 
-template <int D, int EPI>
+template <int D, int EPI, bool PART>
 hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
-  // K/V rings; the epilogue reuses them for kWaves private 32 x D fp32 tiles plus 32 lse each
+  // K/V rings; the epilogue reuses them for kWaves private 32 x D fp32 tiles and its row tables
   constexpr int ring_bytes = 2 * kRing * tile_keys<D>() * 2 * D;
-  constexpr int epi_bytes = kWaves * 32 * 4 * D + 2 * kWaves * 32 * 4;
+  constexpr int epi_bytes = PART ? EpiLds<D>::bytes_part : EpiLds<D>::bytes;
   constexpr int lds_bytes = ring_bytes > epi_bytes ? ring_bytes : epi_bytes;
   static_assert(lds_bytes <= 160 * 1024, "LDS budget of one CU exceeded");
   // Raising the dynamic-LDS limit is a per-function, per-device setting: done once for each
@@ -713,12 +920,40 @@ hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&block_attn_kernel<D, EPI>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&block_attn_kernel<D, EPI, PART>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
   }
-  return launch_kernel(block_attn_kernel<D, EPI>, grid, dim3(kThreads), lds_bytes, stream, p);
+  return launch_kernel(block_attn_kernel<D, EPI, PART>, grid, dim3(kThreads), lds_bytes, stream, p);
+}
+
+template <bool PART>
+hipError_t launch_typed(const AttnParams& p, int D, int epilogue, dim3 grid, hipStream_t stream) {
+  if (D == 128) {
+    if (epilogue == kEpiBf16) return launch_one<128, kEpiBf16, PART>(p, grid, stream);
+    if (epilogue == kEpiF32) return launch_one<128, kEpiF32, PART>(p, grid, stream);
+    return launch_one<128, kEpiMerge, PART>(p, grid, stream);
+  }
+  if (epilogue == kEpiBf16) return launch_one<64, kEpiBf16, PART>(p, grid, stream);
+  if (epilogue == kEpiF32) return launch_one<64, kEpiF32, PART>(p, grid, stream);
+  return launch_one<64, kEpiMerge, PART>(p, grid, stream);
+}
+
+template <int D, int EPI>
+hipError_t launch_fold_typed(const AttnParams& p, dim3 grid, hipStream_t stream) {
+  if (p.n_parts <= 4) return launch_kernel(fold_parts_kernel<D, EPI, 4>, grid, dim3(kFoldThreads), 0, stream, p);
+  if (p.n_parts <= 8) return launch_kernel(fold_parts_kernel<D, EPI, 8>, grid, dim3(kFoldThreads), 0, stream, p);
+  return launch_kernel(fold_parts_kernel<D, EPI, kMaxParts>, grid, dim3(kFoldThreads), 0, stream, p);
+}
+template <int D>
+hipError_t launch_fold(const AttnParams& p, int epilogue, hipStream_t stream) {
+  constexpr int rows = kFoldThreads / (D / 4);   // rows one block folds
+  const int tile_rows = p.part_rows < kBM ? p.part_rows : kBM;
+  const dim3 grid((unsigned)(p.B * p.Hkv * p.members), (unsigned)((tile_rows + rows - 1) / rows));
+  if (epilogue == kEpiBf16) return launch_fold_typed<D, kEpiBf16>(p, grid, stream);
+  if (epilogue == kEpiF32) return launch_fold_typed<D, kEpiF32>(p, grid, stream);
+  return launch_fold_typed<D, kEpiMerge>(p, grid, stream);
 }
 
 }  // namespace
@@ -729,14 +964,13 @@ hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream
   if (p.n_qtiles > 65535) return hipErrorInvalidValue;   // grid y limit
   dim3 grid((unsigned)nbh, (unsigned)p.n_qtiles);
   if (p.xcd_map == 2) grid = dim3(8u * (unsigned)p.n_qtiles, (unsigned)(nbh / 8));
-  if (D == 128) {
-    if (epilogue == kEpiBf16) return launch_one<128, kEpiBf16>(p, grid, stream);
-    if (epilogue == kEpiF32) return launch_one<128, kEpiF32>(p, grid, stream);
-    return launch_one<128, kEpiMerge>(p, grid, stream);
+  if (p.n_parts > 0) {
+    if ((int64_t)p.units * p.members == 0) return hipSuccess;
+    const hipError_t e = launch_typed<true>(p, D, epilogue, dim3((unsigned)((p.units + 7) / 8 * p.members * 8)), stream);
+    if (e != hipSuccess || p.n_parts == 1) return e;
+    return D == 128 ? launch_fold<128>(p, epilogue, stream) : launch_fold<64>(p, epilogue, stream);
   }
-  if (epilogue == kEpiBf16) return launch_one<64, kEpiBf16>(p, grid, stream);
-  if (epilogue == kEpiF32) return launch_one<64, kEpiF32>(p, grid, stream);
-  return launch_one<64, kEpiMerge>(p, grid, stream);
+  return launch_typed<false>(p, D, epilogue, grid, stream);
 }
 
 int attn_rows_per_block() { return kBM; }

@@ -8,6 +8,8 @@
 
 namespace tr {
 
+constexpr int kMaxParts = 16;  // parts the keys of one partitioned attention launch are cut into at most
+
 // Arguments of the block-attention kernel: raw pointers, element strides, sizes.
 struct AttnParams {
   const __bf16* q;
@@ -28,6 +30,16 @@ struct AttnParams {
   int xcd_map;    // 1: place all query tiles of a K/V head on one XCD (grid x = batch*head, y = query tile); 2: the same with grid x = XCD + 8 * query tile, y = head within the XCD
   int gq;         // query heads per K/V head (Hq / Hkv)
   int gq_log2;    // log2(gq) if gq is a power of two, else -1
+  // Partitioned form (n_parts > 0), see the kernel: n_qtiles then counts the tiles of the row space
+  // (one head's Sq rows, or with pack the gq * Sq rows of a K/V head's group).
+  int n_parts;    // parts of the keys, part_keys (a multiple of 128) each; 0: the plain form
+  int part_keys;
+  int pack;       // 1: a row space holds every query head of a K/V head
+  int units;      // B * Hkv * n_parts
+  int members;    // row tiles that read one unit's keys
+  int part_rows;  // rows of a scratch slot
+  float* part_out;       // [row tile][part][part_rows][D], if n_parts > 1
+  float* part_lse;       // [row tile][part][part_rows]
 };
 
 // Arguments of the merge kernel.
@@ -92,21 +104,19 @@ inline hipError_t launch_kernel(Kernel kernel, dim3 grid, dim3 block, size_t lds
 // (out = 0, lse = -inf) on either side is handled exactly and never produces NaN.
 typedef float tr_f32x4 __attribute__((ext_vector_type(4)));
 struct UpdatePlan {
-  int mode;  // 0: blend with weight w; 1: both empty -> 0; 2: empty accumulator -> block; 3: empty block -> keep
+  int mode;  // 0: blend with weight w (meaningless otherwise); 1: both empty -> 0; 2: empty accumulator -> block; 3: empty block -> keep
   float w, new_lse;
 };
 __device__ __forceinline__ UpdatePlan plan_update(float lse_acc, float lse_blk) {
+  // Straight-line: a chain of these (the parts of one row) then costs the latency of its logarithms only,
+  // and no lane waits for another's case.
   UpdatePlan r;
   const float m = fmaxf(lse_acc, lse_blk);
-  r.mode = 0;
-  r.w = 0.f;
-  if (m == -INFINITY) { r.mode = 1; r.new_lse = -INFINITY; }
-  else if (lse_acc == -INFINITY) { r.mode = 2; r.new_lse = lse_blk; }   // the accumulator's out may be uninitialised
-  else if (lse_blk == -INFINITY) { r.mode = 3; r.new_lse = lse_acc; }
-  else {
-    r.new_lse = m + log1pf(expf(-fabsf(lse_acc - lse_blk)));
-    r.w = expf(lse_blk - r.new_lse);
-  }
+  const bool acc_empty = lse_acc == -INFINITY, blk_empty = lse_blk == -INFINITY;   // an empty accumulator's out may be uninitialised
+  const float both = m + log1pf(expf(-fabsf(lse_acc - lse_blk)));
+  r.mode = m == -INFINITY ? 1 : (acc_empty ? 2 : (blk_empty ? 3 : 0));
+  r.new_lse = m == -INFINITY ? m : (acc_empty ? lse_blk : (blk_empty ? lse_acc : both));
+  r.w = expf(lse_blk - r.new_lse);
   return r;
 }
 // Branch-free: the blend is evaluated for every lane and bit masks made from the plan's case pick

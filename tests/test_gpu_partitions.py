@@ -1,0 +1,113 @@
+"""Attention on grids that leave the chip idle: keys cut into parts, grouped query heads packed into one row space.
+
+Sizes sit where the form can go wrong: row counts around a wave and a tile, a last part of one key, parts
+that no row of a tile sees, heads that share a wave.  Reference: the fp64 oracle, tolerances as for every
+block step.  Without scratch (under graph capture, on a stream beyond those that have a region) fp32 results
+are folded part by part in the output and must be the same bits.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import bits_to_dev, f64, max_abs, rand_bits, to_np
+
+pytestmark = pytest.mark.gpu
+OUT_TOL, LSE_TOL = 1e-2, 1e-3
+
+CASES = [
+    # B, Hq, Hkv, Sq, Sk, D, offset of the causal rule (None: no mask)
+    (1, 8, 1, 1, 4097, 128, None),        # decode: eight heads in one wave, last part of one key
+    (2, 6, 2, 11, 1500, 64, None),        # three heads, 33 rows: one row in the second wave
+    (1, 4, 1, 64, 3000, 128, None),       # 256 packed rows: exactly a tile
+    (1, 3, 1, 86, 2049, 64, None),        # 258 packed rows: two in the second tile
+    (1, 2, 2, 300, 8192, 128, None),      # no packing, two tiles, sixteen parts
+    (1, 4, 2, 40, 2600, 128, 2560),       # causal, packed heads that share waves
+    (1, 2, 2, 1030, 1030, 64, 0),         # diagonal: early tiles see one part only
+    (1, 2, 1, 20, 3000, 128, 1100),       # later parts that no row sees
+    (1, 2, 2, 600, 3000, 128, -300),      # rows without any key, and a tile with one part
+]
+
+
+def _inputs(case, seed):
+    B, Hq, Hkv, Sq, Sk, D, _ = case
+    return rand_bits((B, Hq, Sq, D), seed), rand_bits((B, Hkv, Sk, D), seed + 1), rand_bits((B, Hkv, Sk, D), seed + 2)
+
+
+def _attend(lib, case, q, k, v, scale, out, lse, stream=None):
+    off = case[6]
+    if off is None:
+        lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, scale, out, lse, stream)
+    else:
+        lib.tr_block_attn_causal_at(q, k, v, max(off, 0), max(-off, 0), scale, out, lse, stream)
+
+
+def _reference(case, qb, kb, vb, scale):
+    off = case[6]
+    if off is None:
+        return oracle.attention_block(f64(qb), f64(kb), f64(vb), scale)
+    return oracle.attention_block(f64(qb), f64(kb), f64(vb), scale, causal_diag=True, q_offset=max(off, 0), k_offset=max(-off, 0))
+
+
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_parts_reach_the_oracle(lib, case, out_dtype):
+    B, Hq, Hkv, Sq, Sk, D, _ = case
+    qb, kb, vb = _inputs(case, 300)
+    scale = 1.0 / np.sqrt(D)
+    # token-major tensors: head and row strides change places
+    q, k, v = (bits_to_dev(np.ascontiguousarray(x.transpose(0, 2, 1, 3))).permute(0, 2, 1, 3) for x in (qb, kb, vb))
+    out = torch.full((B, Sq, Hq, D), float("nan"), dtype=out_dtype, device="cuda").permute(0, 2, 1, 3)
+    lse = torch.full((B, Hq, Sq), float("nan"), dtype=torch.float32, device="cuda")
+    _attend(lib, case, q, k, v, scale, out, lse)
+    torch.cuda.synchronize()
+    ref_o, ref_l = _reference(case, qb, kb, vb, scale)
+    assert np.array_equal(np.isneginf(to_np(lse)), np.isneginf(ref_l))
+    assert max_abs(to_np(out), ref_o) <= OUT_TOL and max_abs(to_np(lse), ref_l) <= LSE_TOL
+
+
+@pytest.mark.parametrize("case", [c for c in CASES if c[6] is None], ids=str)
+def test_parts_merge_into_accumulators(lib, case):
+    B, Hq, Hkv, Sq, Sk, D, _ = case
+    qb, kb, vb = _inputs(case, 330)
+    rng = np.random.default_rng(333)
+    acc_o = rng.standard_normal((B, Hq, Sq, D)).astype(np.float32)
+    acc_l = rng.uniform(-5, 15, (B, Hq, Sq)).astype(np.float32)
+    acc_l[:, 0, 0] = -np.inf
+    clean = acc_o.copy()
+    clean[:, 0, 0] = 0.0
+    acc_o[:, 0, 0] = np.nan                                # an empty row may hold garbage
+    d_o, d_l = torch.from_numpy(acc_o).cuda(), torch.from_numpy(acc_l).cuda()
+    lib.tr_block_attn_merge(bits_to_dev(qb), bits_to_dev(kb), bits_to_dev(vb), lib.TR_MASK_NONE, 0.1, d_o, d_l)
+    torch.cuda.synchronize()
+    ref_o, ref_l = oracle.merge_pair(clean, acc_l, *oracle.attention_block(f64(qb), f64(kb), f64(vb), 0.1))
+    assert max_abs(to_np(d_o), ref_o) <= OUT_TOL and max_abs(to_np(d_l), ref_l) <= LSE_TOL
+
+
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_without_scratch_the_bits_are_the_same(lib, case):
+    B, Hq, Hkv, Sq, Sk, D, _ = case
+    q, k, v = (bits_to_dev(x) for x in _inputs(case, 360))
+    new = lambda: (torch.full((B, Hq, Sq, D), float("nan"), device="cuda"), torch.full((B, Hq, Sq), float("nan"), device="cuda"))
+    out, lse = new()
+    _attend(lib, case, q, k, v, 0.1, out, lse)
+    torch.cuda.synchronize()
+    # more streams than have a scratch region: each gives the same result
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    results = [new() for _ in streams]
+    torch.cuda.synchronize()
+    for s, (o, l) in zip(streams, results):
+        _attend(lib, case, q, k, v, 0.1, o, l, s)
+    torch.cuda.synchronize()
+    for o, l in results:
+        assert torch.equal(o, out) and torch.equal(l, lse)
+    graph_o, graph_l = new()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        _attend(lib, case, q, k, v, 0.1, graph_o, graph_l)
+    for _ in range(3):
+        graph_o.fill_(float("nan")); graph_l.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(graph_o, out) and torch.equal(graph_l, lse)
