@@ -258,9 +258,11 @@ hipError_t launch_parts(tr::AttnParams p, const PartPlan& plan, int D, int epilo
   return hipSuccess;
 }
 
-// fuse_update: out/lse are fp32 accumulators and the block is merged into them by the kernel's epilogue
+// fuse_update: out/lse are fp32 accumulators and the block is merged into them by the kernel's epilogue.
+// n_chunks > 0: all Query chunks against all K/V chunks with bf16 blocks in between; the tensors are views of chunk 0.
 tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int causal, int64_t off64, float scale,
-                      const tr_tensor* out, const tr_tensor* lse, void* stream, bool fuse_update = false) {
+                      const tr_tensor* out, const tr_tensor* lse, void* stream, bool fuse_update = false,
+                      int n_chunks = 0) {
   tr_status st;
   if ((st = check_tensor("q", q, true, false, 16)) != TR_OK) return st;
   if ((st = check_tensor("k", k, true, false, 16)) != TR_OK) return st;
@@ -309,9 +311,19 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   // Without the causal rule all query tiles cost the same, and an XCD may finish the
   // query tiles of one head before it starts the next: half as many heads' K/V are then live in
   // its L2 at a time.  (Under a causal mask that order would bunch the heavy tiles.)
-  if (p.xcd_map && !p.causal && (int64_t)p.B * p.Hq / 8 <= 65535) p.xcd_map = 2;
+  if (p.xcd_map && !p.causal && n_chunks == 0 && (int64_t)p.B * p.Hq / 8 <= 65535) p.xcd_map = 2;
   if (p.B == 0 || p.Hq == 0 || p.Sq == 0) return TR_OK;
   const int epilogue = fuse_update ? 2 : (out->dtype == TR_F32 ? 1 : 0);
+  if (n_chunks > 0) {
+    p.n_chunks = n_chunks;
+    const int step = std::max(1, 65535 / p.n_qtiles);   // chunks one grid holds; the later ones first, as inside a launch
+    for (p.chunk_end = n_chunks; p.chunk_end > 0; p.chunk_end = p.chunk_begin) {
+      p.chunk_begin = std::max(0, p.chunk_end - step);
+      const hipError_t e = tr::launch_block_attn(p, (int)q->D, 2, (hipStream_t)stream);
+      if (e != hipSuccess) return fail(TR_ERR_HIP, "chunk attention launch failed: %s", hipGetErrorString(e));
+    }
+    return TR_OK;
+  }
   PartPlan plan;
   const hipError_t e = plan_parts(p, (int)q->D, plan) ? launch_parts(p, plan, (int)q->D, epilogue, (hipStream_t)stream)
                                                       : tr::launch_block_attn(p, (int)q->D, epilogue, (hipStream_t)stream);
@@ -493,13 +505,9 @@ tr_status tr_block_attn_merge(const tr_tensor* q, const tr_tensor* k, const tr_t
   return attn_common(q, k, v, mask_kind == TR_MASK_CAUSAL_DIAG, 0, scale, out_acc, lse_acc, hip_stream, true);
 }
 
-}  // extern "C"
-
-namespace {
-// acc_streams: the caller knows that the accumulator view is part of a larger tensor that is swept
-// once between two Updates of this view (a ring replay over many Query chunks)
-tr_status merge_common(const tr_tensor* out_acc, const tr_tensor* lse_acc, const tr_tensor* block_out, const tr_tensor* block_lse,
-                       void* hip_stream, bool acc_streams) {
+tr_status tr_merge(const tr_tensor* out_acc, const tr_tensor* lse_acc, const tr_tensor* block_out, const tr_tensor* block_lse,
+                   void* hip_stream) {
+  g_err[0] = 0;
   tr_status st;
   if ((st = check_tensor("out_acc", out_acc, false, true, 16)) != TR_OK) return st;
   if ((st = check_tensor("lse_acc", lse_acc, false, true, 4)) != TR_OK) return st;
@@ -531,20 +539,10 @@ tr_status merge_common(const tr_tensor* out_acc, const tr_tensor* lse_acc, const
     return t->stride_s == t->D && t->stride_h == t->S * t->D && t->stride_b == t->H * t->S * t->D;
   };
   p.contiguous = dense(out_acc) && dense(block_out) && dense(lse_acc) && dense(block_lse);
-  p.stream_acc = acc_streams ? 1 : 0;
   if (p.B == 0 || p.H == 0 || p.S == 0 || p.D == 0) return TR_OK;
   const hipError_t e = tr::launch_merge(p, block_out->dtype == TR_BF16, (hipStream_t)hip_stream);
   if (e != hipSuccess) return fail(TR_ERR_HIP, "merge launch failed: %s", hipGetErrorString(e));
   return TR_OK;
-}
-}  // namespace
-
-extern "C" {
-
-tr_status tr_merge(const tr_tensor* out_acc, const tr_tensor* lse_acc, const tr_tensor* block_out, const tr_tensor* block_lse,
-                   void* hip_stream) {
-  g_err[0] = 0;
-  return merge_common(out_acc, lse_acc, block_out, block_lse, hip_stream, false);
 }
 
 tr_status tr_merge_n(const tr_tensor* out, const tr_tensor* lse, const tr_tensor* const* block_outs,
@@ -615,8 +613,8 @@ size_t tr_ring_attn_workspace_bytes(const tr_tensor* q, int n_chunks) {
 
 namespace {
 
-// Algorithm 1 on one device.  block_dtype TR_F32: one pass, a workspace is only checked.  TR_BF16:
-// every block result after a Query chunk's first passes through the workspace as bf16.
+// Algorithm 1 on one device.  block_dtype TR_F32: one pass over all keys.  TR_BF16: block by block, every
+// block result after a Query chunk's first rounded to bf16 before its Update.  A workspace is only checked.
 tr_status ring_attn_impl(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int n_chunks, int causal,
                          const tr_tensor* out, const tr_tensor* lse, float scale, int block_dtype, void* workspace,
                          size_t workspace_bytes, void* hip_stream) {
@@ -642,22 +640,14 @@ tr_status ring_attn_impl(const tr_tensor* q, const tr_tensor* k, const tr_tensor
 
   const size_t need = tr_ring_attn_blocks_workspace_bytes(q, n_chunks, block_dtype);
   const size_t rows = (size_t)q->B * (size_t)q->H * (size_t)C;
-  tr_tensor ws_out, ws_lse;
-  memset(&ws_out, 0, sizeof(ws_out));
   const bool given = workspace != nullptr;
   if (given && workspace_bytes == 0) return fail(TR_ERR_WORKSPACE, "workspace given with size 0 (need %zu bytes)", need);
   if (given && n_chunks > 1 && rows > 0) {
     if (((uintptr_t)workspace) % kWsAlign) return fail(TR_ERR_WORKSPACE, "workspace must be %zu-byte aligned", kWsAlign);
     if (workspace_bytes < need) return fail(TR_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", workspace_bytes, need);
-    ws_out.ptr = workspace; ws_out.dtype = block_dtype;
-    ws_out.B = q->B; ws_out.H = q->H; ws_out.S = C; ws_out.D = q->D;
-    ws_out.stride_s = q->D; ws_out.stride_h = C * q->D; ws_out.stride_b = q->H * C * q->D;
-    ws_lse = ws_out;
-    ws_lse.ptr = (char*)workspace + align_up(rows * (size_t)q->D * (size_t)elem_bytes(block_dtype));
-    ws_lse.dtype = TR_F32;
-    ws_lse.D = 1; ws_lse.stride_s = 1; ws_lse.stride_h = C; ws_lse.stride_b = q->H * C;
-    tr_tensor ws_all = ws_out;  // alias check of the whole workspace against the user tensors
-    ws_all.dtype = TR_F32;
+    tr_tensor ws_all;  // alias check of the whole workspace against the user tensors
+    memset(&ws_all, 0, sizeof(ws_all));
+    ws_all.ptr = workspace; ws_all.dtype = TR_F32;
     ws_all.B = 1; ws_all.H = 1; ws_all.S = 1; ws_all.D = (int64_t)(need / 4);
     if (overlaps(&ws_all, q) || overlaps(&ws_all, k) || overlaps(&ws_all, v) || overlaps(&ws_all, out) || overlaps(&ws_all, lse))
       return fail(TR_ERR_ALIAS, "workspace overlaps a tensor argument");
@@ -670,29 +660,9 @@ tr_status ring_attn_impl(const tr_tensor* q, const tr_tensor* k, const tr_tensor
   // fp32 blocks reach the Update unrounded, so folding them in registers is the same operation; bf16
   // blocks are rounded one by one on their way, as the caller asked.
   if (block_dtype == TR_F32) return attn_whole(q, k, v, causal != 0, scale, out, lse, hip_stream);
-  // between two Updates of one Query chunk every other chunk's accumulator is touched: if all of them
-  // together exceed the memory-side cache, none survives there and the Update streams past the caches
-  const bool out_sweeps = (int64_t)q->B * q->H * q->S * q->D * 4 > ((int64_t)128 << 20);
-  for (int i = 0; i < n_chunks; i++) {
-    for (int j = 0; j < n_chunks; j++) {
-      const int c = ((j - i) % n_chunks + n_chunks) % n_chunks;
-      if (causal && j > c) continue;
-      const tr_tensor qc = chunk_view(q, c, C), kj = chunk_view(k, j, C), vj = chunk_view(v, j, C);
-      const tr_tensor oc = chunk_view(out, c, C), lc = chunk_view(lse, c, C);
-      const int diag = causal && j == c;
-      if (i == 0) {
-        // first block of Query chunk c: it *is* the accumulator's initial value
-        st = attn_common(&qc, &kj, &vj, diag, 0, scale, &oc, &lc, hip_stream);
-        if (st != TR_OK) return st;
-      } else {
-        st = attn_common(&qc, &kj, &vj, diag, 0, scale, &ws_out, &ws_lse, hip_stream);
-        if (st != TR_OK) return st;
-        st = merge_common(&oc, &lc, &ws_out, &ws_lse, hip_stream, out_sweeps);
-        if (st != TR_OK) return st;
-      }
-    }
-  }
-  return TR_OK;
+  const tr_tensor q0 = chunk_view(q, 0, C), k0 = chunk_view(k, 0, C), v0 = chunk_view(v, 0, C);
+  const tr_tensor o0 = chunk_view(out, 0, C), l0 = chunk_view(lse, 0, C);
+  return attn_common(&q0, &k0, &v0, causal != 0, 0, scale, &o0, &l0, hip_stream, true, n_chunks);
 }
 
 }  // namespace

@@ -51,6 +51,7 @@ template <int D>
 constexpr int tile_keys() { return D == 64 ? 128 : 64; }
 constexpr int kRing = 4;          // LDS ring depth (tiles) of K and of V
 constexpr int kEpiBf16 = 0, kEpiF32 = 1, kEpiMerge = 2;
+constexpr int kPlain = 0, kPart = 1, kChunks = 2;   // forms of the kernel, see there
 
 // Exchange between the two 32-lane halves of a wave with v_permlane32_swap, which swaps the
 // upper half of its first operand with the lower half of its second: fed (x, x) it leaves
@@ -315,8 +316,18 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
 // order: bitwise reproducible).  Bound: HBM for a decode step, MFMA otherwise, plus the fold.  Four decode steps
 // over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 156 us, 500 Query rows x 32 heads
 // behind 12000 keys 216 -> 105 us against the plain form.
-template <int D, int EPI, bool PART>
+//
+// FORM kChunks replays Algorithm 1 with block results that are rounded to bf16 on their way to the Update.
+// A workgroup keeps its Query tile of chunk c and runs through the K/V chunks in the order the schedule
+// brings them, c, c + 1, ... mod n (causal: only those not after c); each block ends in the merging
+// epilogue, the first one unrounded onto an empty accumulator.  One launch instead of two per block: no
+// block result in memory, no idle tail between the blocks (chunks of 1502 rows x 16 heads fill 96 of 256
+// compute units), the longest chunks first.  Bound: as the plain form, plus an epilogue for each block.
+// Causal 6008 rows in 4 chunks, 16 heads: 400 -> 213 us, the same bits.
+template <int D, int EPI, int FORM>
 __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p) {
+  constexpr bool PART = FORM == kPart, CHUNKS = FORM == kChunks;
+  static_assert(!CHUNKS || EPI == kEpiMerge, "blocks of the chunk form are merged");
   constexpr int RB = 2 * D;
   constexpr int KS = D / 16;               // MFMA k-steps over the head dim
   constexpr int DB = D / 32;               // 32-wide d blocks of the output
@@ -333,10 +344,6 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
 
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // K ring | V ring
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in an SGPR
-  const int ql = lane & 31, hf = lane >> 5;
-
   // which batch, head and query tile this workgroup computes (wave-uniform)
   int qt, b, hq, hk;
   PartBlock pb = {0, 0, 0, 0, 0, 0};
@@ -346,7 +353,21 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   } else {
     decode_block(p, qt, b, hq, hk);
   }
-  const bool causal = p.causal != 0;
+  int chunk = 0;
+  if constexpr (CHUNKS) {   // grid y runs over (chunk, query tile), both from the last on
+    const int y = (int)blockIdx.y / p.n_qtiles;
+    chunk = p.chunk_end - 1 - y;
+    qt += y * p.n_qtiles;
+  }
+  const int64_t chunk_row = (int64_t)chunk * p.Sq;
+  for (int block = 0; block < (CHUNKS ? p.n_chunks : 1); block++) {
+  const int kv_chunk = CHUNKS ? (chunk + block < p.n_chunks ? chunk + block : chunk + block - p.n_chunks) : 0;
+  if (CHUNKS && p.causal && kv_chunk > chunk) continue;
+  int tid = threadIdx.x;
+  if constexpr (CHUNKS) asm volatile("" : "+v"(tid));   // nothing derived from it is held in registers from block to block (179 spills otherwise)
+  const int lane = tid & 63, ql = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in an SGPR
+  const bool causal = CHUNKS ? p.causal && block == 0 : p.causal != 0;
   int Sk = p.Sk, causal_off = p.causal_off;
   const int q0 = qt * kBM, qw0 = q0 + wave * 32;
   const int qrow = qw0 + ql;
@@ -377,6 +398,10 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
 
   const __bf16* kg = p.k + (int64_t)b * p.k_sb + (int64_t)hk * p.k_sh;
   const __bf16* vg = p.v + (int64_t)b * p.v_sb + (int64_t)hk * p.v_sh;
+  if constexpr (CHUNKS) {
+    kg += (int64_t)kv_chunk * p.Sk * p.k_ss;
+    vg += (int64_t)kv_chunk * p.Sk * p.v_ss;
+  }
   if constexpr (PART) {
     kg += (int64_t)pb.part * p.part_keys * p.k_ss;
     vg += (int64_t)pb.part * p.part_keys * p.v_ss;
@@ -452,7 +477,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step.
   bf16x8 qf[KS];
   {
-    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)(PART ? hq + lane_head : hq) * p.q_sh + (int64_t)(PART ? lane_pos : qrow_ld) * p.q_ss;
+    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)(PART ? hq + lane_head : hq) * p.q_sh + (PART ? lane_pos : chunk_row + qrow_ld) * p.q_ss;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * hf);
   }
@@ -813,8 +838,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     p.lse[(int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (int64_t)qrow * p.l_ss] = lse_blk;
   const int rr = lane / CPRF, cc = lane % CPRF;
   constexpr int NIT = 32 / RPI_OUT;
-  const int64_t o_bh = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + 4 * cc;
-  const int64_t l_bh = (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh;
+  const int64_t o_bh = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + chunk_row * p.o_ss + 4 * cc;
+  const int64_t l_bh = (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + chunk_row * p.l_ss;
   if (EPI == kEpiMerge) {
     // Out, Lse <- Update(block_out, block_lse) on the accumulators p.out / p.lse.  All of the
     // wave's accumulator rows are fetched first (the O registers are free by now), so their
@@ -826,7 +851,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
 #pragma unroll
     for (int it = 0; it < NIT; it++) {
       const int grow = min(qw0 + it * RPI_OUT + rr, p.Sq - 1);
-      x[it] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(acc_out + o_bh + (int64_t)grow * p.o_ss));
+      if (CHUNKS && block == 0) x[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+      else x[it] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(acc_out + o_bh + (int64_t)grow * p.o_ss));
     }
     // The Update of a row is planned once, by the lanes that own the row in the accumulator layout
     // (its two exponentials and its logarithm would otherwise be evaluated in every lane that
@@ -834,7 +860,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     // on their way.  The same lane reads the row's old lse and writes the new one.
     {
       const int64_t l_at = l_bh + (int64_t)min(qrow, p.Sq - 1) * p.l_ss;
-      const UpdatePlan plq = plan_update(p.lse[l_at], lse_blk);
+      const UpdatePlan plq = plan_update(CHUNKS && block == 0 ? -INFINITY : p.lse[l_at], lse_blk);
       if (hf == 0) {
         my_w[ql] = plq.w;
         my_mode[ql] = plq.mode;
@@ -850,6 +876,10 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     for (int it = 0; it < NIT; it++) {
       const int r = it * RPI_OUT + rr;
       ov[it] = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
+      if (CHUNKS && block > 0) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) ov[it][e] = (float)(__bf16)ov[it][e];
+      }
       pl[it].w = my_w[r];
       pl[it].mode = my_mode[r];
       pl[it].new_lse = 0.f;
@@ -903,13 +933,15 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
       dst += dst_step;
     }
   }
+  if constexpr (CHUNKS) __syncthreads();  // the next block's loads land where other waves may still read their rows
+  }
 }
 
-template <int D, int EPI, bool PART>
+template <int D, int EPI, int FORM>
 hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
   // K/V rings; the epilogue reuses them for kWaves private 32 x D fp32 tiles and its row tables
   constexpr int ring_bytes = 2 * kRing * tile_keys<D>() * 2 * D;
-  constexpr int epi_bytes = PART ? EpiLds<D>::bytes_part : EpiLds<D>::bytes;
+  constexpr int epi_bytes = FORM == kPart ? EpiLds<D>::bytes_part : EpiLds<D>::bytes;
   constexpr int lds_bytes = ring_bytes > epi_bytes ? ring_bytes : epi_bytes;
   static_assert(lds_bytes <= 160 * 1024, "LDS budget of one CU exceeded");
   // Raising the dynamic-LDS limit is a per-function, per-device setting: done once for each
@@ -920,24 +952,21 @@ hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&block_attn_kernel<D, EPI, PART>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&block_attn_kernel<D, EPI, FORM>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
   }
-  return launch_kernel(block_attn_kernel<D, EPI, PART>, grid, dim3(kThreads), lds_bytes, stream, p);
+  return launch_kernel(block_attn_kernel<D, EPI, FORM>, grid, dim3(kThreads), lds_bytes, stream, p);
 }
 
-template <bool PART>
+template <int FORM>
 hipError_t launch_typed(const AttnParams& p, int D, int epilogue, dim3 grid, hipStream_t stream) {
-  if (D == 128) {
-    if (epilogue == kEpiBf16) return launch_one<128, kEpiBf16, PART>(p, grid, stream);
-    if (epilogue == kEpiF32) return launch_one<128, kEpiF32, PART>(p, grid, stream);
-    return launch_one<128, kEpiMerge, PART>(p, grid, stream);
+  if constexpr (FORM != kChunks) {
+    if (epilogue == kEpiBf16) return D == 128 ? launch_one<128, kEpiBf16, FORM>(p, grid, stream) : launch_one<64, kEpiBf16, FORM>(p, grid, stream);
+    if (epilogue == kEpiF32) return D == 128 ? launch_one<128, kEpiF32, FORM>(p, grid, stream) : launch_one<64, kEpiF32, FORM>(p, grid, stream);
   }
-  if (epilogue == kEpiBf16) return launch_one<64, kEpiBf16, PART>(p, grid, stream);
-  if (epilogue == kEpiF32) return launch_one<64, kEpiF32, PART>(p, grid, stream);
-  return launch_one<64, kEpiMerge, PART>(p, grid, stream);
+  return D == 128 ? launch_one<128, kEpiMerge, FORM>(p, grid, stream) : launch_one<64, kEpiMerge, FORM>(p, grid, stream);
 }
 
 template <int D, int EPI>
@@ -966,11 +995,16 @@ hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream
   if (p.xcd_map == 2) grid = dim3(8u * (unsigned)p.n_qtiles, (unsigned)(nbh / 8));
   if (p.n_parts > 0) {
     if ((int64_t)p.units * p.members == 0) return hipSuccess;
-    const hipError_t e = launch_typed<true>(p, D, epilogue, dim3((unsigned)((p.units + 7) / 8 * p.members * 8)), stream);
+    const hipError_t e = launch_typed<kPart>(p, D, epilogue, dim3((unsigned)((p.units + 7) / 8 * p.members * 8)), stream);
     if (e != hipSuccess || p.n_parts == 1) return e;
     return D == 128 ? launch_fold<128>(p, epilogue, stream) : launch_fold<64>(p, epilogue, stream);
   }
-  return launch_typed<false>(p, D, epilogue, grid, stream);
+  if (p.n_chunks > 0) {
+    grid = dim3((unsigned)nbh, (unsigned)((p.chunk_end - p.chunk_begin) * p.n_qtiles));
+    if (grid.y > 65535 || epilogue != kEpiMerge) return hipErrorInvalidValue;
+    return launch_typed<kChunks>(p, D, epilogue, grid, stream);
+  }
+  return launch_typed<kPlain>(p, D, epilogue, grid, stream);
 }
 
 int attn_rows_per_block() { return kBM; }

@@ -201,7 +201,7 @@ hipError_t launch_merge(const MergeParams& p, bool blk_bf16, hipStream_t stream)
   const int64_t n_threads = n_rows << tpr_log2;
   const int64_t nblocks = (n_threads + kMergeThreads - 1) / kMergeThreads;
   dim3 grid((unsigned)nblocks), block(kMergeThreads);
-  const bool stream_acc = p.stream_acc || n_rows * p.D * 4 > kStreamAccBytes;
+  const bool stream_acc = n_rows * p.D * 4 > kStreamAccBytes;
   if (blk_bf16) {
     if (stream_acc) return launch_kernel(merge_kernel<true, true>, grid, block, 0, stream, p, n_rows, tpr_log2);
     return launch_kernel(merge_kernel<true, false>, grid, block, 0, stream, p, n_rows, tpr_log2);

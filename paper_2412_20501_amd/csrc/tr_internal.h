@@ -30,6 +30,9 @@ struct AttnParams {
   int xcd_map;    // 1: place all query tiles of a K/V head on one XCD (grid x = batch*head, y = query tile); 2: the same with grid x = XCD + 8 * query tile, y = head within the XCD
   int gq;         // query heads per K/V head (Hq / Hkv)
   int gq_log2;    // log2(gq) if gq is a power of two, else -1
+  // Chunk form (n_chunks > 0): q, out, lse and k, v are chunk 0 of n_chunks chunks that lie one behind the other
+  // along S; the launch covers Query chunks chunk_begin .. chunk_end - 1.
+  int n_chunks, chunk_begin, chunk_end;
   // Partitioned form (n_parts > 0), see the kernel: n_qtiles then counts the tiles of the row space
   // (one head's Sq rows, or with pack the gq * Sq rows of a K/V head's group).
   int n_parts;    // parts of the keys, part_keys (a multiple of 128) each; 0: the plain form
@@ -54,7 +57,6 @@ struct MergeParams {
   int64_t bl_sb, bl_sh, bl_ss;
   int B, H, S, D;
   int contiguous;  // 1: all four tensors are dense [B*H*S, D] / [B*H*S]
-  int stream_acc;  // 1: the caller knows the accumulator is not touched again soon (access past the caches)
 };
 
 // Arguments of the n-ary merge kernel: up to kMergeNMax partial results with common strides.

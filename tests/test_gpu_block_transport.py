@@ -1,0 +1,48 @@
+"""tr_ring_attn_blocks with bf16 blocks against Algorithm 1 spelled out by the caller: tr_block_attn into a bf16
+block_out (the first block of a chunk straight into the accumulators), tr_merge after it, in the schedule's
+order.  The same bits.  Chunk lengths sit around tiles; up to 512 keys a block step is one pass over its keys."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import bits_to_dev, rand_bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("B,Hq,Hkv,chunk,n,D,token", [
+    (1, 2, 2, 1, 5, 64, False),        # chunks of one row
+    (2, 6, 2, 24, 7, 64, True),        # less than a wave, token-major
+    (1, 4, 2, 256, 4, 128, False),     # exactly one query tile
+    (1, 3, 3, 257, 3, 64, False),      # one row in the second tile
+    (1, 8, 8, 400, 3, 128, True),      # XCD-aware placement, ragged tiles
+    (1, 2, 1, 320, 1, 128, False),     # a single chunk: nothing is merged
+])
+def test_bf16_blocks_are_the_steps_one_by_one(lib, B, Hq, Hkv, chunk, n, D, token, causal):
+    S, scale = chunk * n, 1.0 / np.sqrt(D)
+
+    def tensor(H, seed):
+        x = rand_bits((B, H, S, D), seed)
+        return bits_to_dev(np.ascontiguousarray(x.transpose(0, 2, 1, 3))).permute(0, 2, 1, 3) if token else bits_to_dev(x)
+
+    q, k, v = tensor(Hq, 400), tensor(Hkv, 401), tensor(Hkv, 402)
+    new = lambda S: (torch.full((B, Hq, S, D), float("nan"), device="cuda"), torch.full((B, Hq, S), float("nan"), device="cuda"))
+    out, lse = new(S)
+    ws = torch.empty(lib.tr_ring_attn_blocks_workspace_bytes(q, n, lib.TR_BF16), dtype=torch.uint8, device="cuda")
+    lib.tr_ring_attn_blocks(q, k, v, n, causal, out, lse, lib.TR_BF16, ws, scale)
+
+    ref_o, ref_l = new(S)
+    blk_o, blk_l = torch.empty((B, Hq, chunk, D), dtype=torch.bfloat16, device="cuda"), torch.empty((B, Hq, chunk), device="cuda")
+    part = lambda t, c: t[:, :, c * chunk:(c + 1) * chunk]
+    seen = set()
+    for _, j, c in oracle.ring_schedule(n, causal):
+        mask = lib.TR_MASK_CAUSAL_DIAG if causal and j == c else lib.TR_MASK_NONE
+        o, l = (blk_o, blk_l) if c in seen else (part(ref_o, c), part(ref_l, c))
+        lib.tr_block_attn(part(q, c), part(k, j), part(v, j), mask, scale, o, l)
+        if c in seen:
+            lib.tr_merge(part(ref_o, c), part(ref_l, c), blk_o, blk_l)
+        seen.add(c)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref_o) and torch.equal(lse, ref_l)
