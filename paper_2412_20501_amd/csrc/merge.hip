@@ -32,6 +32,9 @@ constexpr int64_t kStreamAccBytes = (int64_t)128 << 20;
 // program order within one wave guarantees.  Neighbouring thread groups take neighbouring
 // rows, so a wave touches one contiguous span of each stream.  (Giving a group several rows,
 // near or far apart, measured slower; so did one or four chunks per thread.)
+// A wave whose rows all have an empty accumulator (the first Update of a fold) does not read it: the
+// block's loads go out first, the accumulator's once the two lse are there.  Eight Updates of
+// 512 MiB fp32 blocks, the first onto an empty accumulator, 2034 -> 1919 us; two of 32 MiB bf16 blocks 62.6 -> 53.2.
 template <bool BLK_BF16, bool STREAM_ACC>
 __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams p, int64_t n_rows, int tpr_log2) {
   const int64_t gtid = (int64_t)blockIdx.x * kMergeThreads + threadIdx.x;
@@ -69,12 +72,18 @@ __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams 
     if (STREAM_ACC) __builtin_nontemporal_store(val, dst);
     else *dst = val;
   };
+  const bool held = __any(plan.mode == 0 || plan.mode == 3);   // does some row of the wave use what the accumulator holds?
   for (int col = t * 4; col < p.D; col += tpr * 8) {
     const int col2 = col + tpr * 4;
     const bool two = col2 < p.D;
-    const f32x4 x0 = load_acc(col), y0 = load_blk(col);
-    f32x4 x1 = x0, y1 = y0;
-    if (two) { x1 = load_acc(col2); y1 = load_blk(col2); }
+    const f32x4 y0 = load_blk(col);
+    f32x4 y1 = y0;
+    if (two) y1 = load_blk(col2);
+    f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+    if (held) {
+      x0 = load_acc(col);
+      if (two) x1 = load_acc(col2);
+    }
     store_acc(col, apply_update(plan, x0, y0));
     if (two) store_acc(col2, apply_update(plan, x1, y1));
   }
