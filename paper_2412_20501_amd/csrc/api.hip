@@ -122,8 +122,8 @@ struct PartPlan {
 // 75 keys 18.2 against 17.6 us.)
 //
 // The keys are cut where an estimate of the call's time (us) says so, over rounds of one workgroup per compute
-// unit.  Measured: a tile of keys takes 0.65 while at most four waves of a workgroup have rows, else 1.0 on an
-// idle chip and 1.7 on a full one (the clock gives way); a workgroup's set-up and epilogue 8; the fold 5,
+// unit.  Measured: a tile of keys takes 0.7 (D 64, twice the keys: 1.0) while at most four waves of a workgroup
+// have rows, else 1.1 (1.6) on an idle chip and 1.75 (2.15) on a full one, where the clock gives way; a workgroup's set-up and epilogue 8; the fold 5,
 // 0.25 for each part in a row's chain, and its partials at 3.5 TB/s; nothing is faster than K and V at 5 TB/s.
 // Both sides of the line, us: 500 rows x 32 heads on 12500 keys 213 in one part, 106 in 4; 96 rows x 8
 // heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 1777 rows x 24
@@ -141,7 +141,7 @@ bool plan_parts(const tr::AttnParams& p, int D, PartPlan& best) {
   c.part_rows = space > bm ? bm : (int)((space + 31) / 32 * 32);
   c.part_keys = ((int64_t)p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
   best = c;
-  if (tiles * tr::kMaxParts >= ((int64_t)1 << 31)) return false;
+  if (tiles * tr::kMaxParts >= ((int64_t)1 << 30)) return false;
   if (tiles > 2 * kCUs) return c.pack;
   // keys that some row of row tile t sees
   auto seen = [&](int t) -> int64_t {
@@ -152,13 +152,14 @@ bool plan_parts(const tr::AttnParams& p, int D, PartPlan& best) {
   const double tile_keys = D == 64 ? 128.0 : 64.0, heads = (double)tiles / c.row_tiles;
   const int64_t all = seen(c.row_tiles - 1);
   const double stream = (double)kv * all * D * 4 / 5e6, fix = 8.0;
+  const double few = D == 64 ? 1.0 : 0.7, idle = D == 64 ? 1.6 : 1.1, busy = D == 64 ? 0.55 : 0.65;
   auto estimate = [&](int64_t part_keys) {
     double n = 0, keys = 0;
     for (int t = 0; t < c.row_tiles; t++) {
       n += heads * (double)std::max<int64_t>(1, (seen(t) + part_keys - 1) / part_keys);
       keys += heads * (double)seen(t);
     }
-    const double tile = c.part_rows <= 128 ? 0.65 : 1.0 + 0.7 * std::min(1.0, n / kCUs);
+    const double tile = c.part_rows <= 128 ? few : idle + busy * std::min(1.0, n / kCUs);
     const double longest = (double)std::min(all, part_keys) / tile_keys * tile + fix;
     double t = longest;
     if (n > kCUs) t = p.causal ? (keys / tile_keys * tile + n * fix) / kCUs + 0.5 * longest : (double)(((int64_t)n + kCUs - 1) / kCUs) * longest;

@@ -135,13 +135,16 @@ __device__ __forceinline__ const __bf16* uniform_ptr(const __bf16* ptr) {
 // ordered by explicit s_waitcnt vmcnt() on the direct-to-LDS loads instead.
 __device__ __forceinline__ void wg_barrier() { __builtin_amdgcn_s_barrier(); }
 
-// The same for the partitioned form (PART): a one-dimensional grid over units (K/V head of a batch
-// entry, part of the keys) and, inside a unit, the row tiles that read its keys.  Unit u goes to XCD
-// u mod 8, so whatever shares keys shares an L2.  Returns false for the ids that only fill the last eight up.
+// The same for the partitioned form: a one-dimensional grid over units (K/V head of a batch entry, part
+// of the keys) and, inside a unit, the row tiles that read its keys.  Every XCD takes one eighth of that
+// list, a contiguous piece, so what shares keys mostly shares an L2 and no XCD is left without work: whole units
+// dealt to XCDs in turn kept four XCDs idle with four units (3076 rows x 8 heads on 3898 keys 111 us against 77
+// uncut).  Returns false for the ids that only fill the last eight up.
 struct PartBlock { int tile, b, hk, hq0, part, group; };
 __device__ __forceinline__ bool decode_part(const AttnParams& p, PartBlock& w) {
-  const int x = (int)blockIdx.x & 7, rest = (int)blockIdx.x >> 3;
-  const int m = rest % p.members, u = rest / p.members * 8 + x;
+  const int per_xcd = (int)gridDim.x >> 3;
+  const int at = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+  const int u = at / p.members, m = at - u * p.members;
   if (u >= p.units) return false;
   const int kv = u / p.n_parts;
   w.part = u - kv * p.n_parts;
@@ -185,10 +188,9 @@ struct EpiLds {
 // one live part the tile is stored or merged as it is, otherwise tile and lse go to the scratch slot of
 // (row tile, part) for the fold kernel.
 template <int D, int EPI>
-__device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, int q0, int b, int hq0, int group, int part, int n_live,
-                                              float lse_blk) {
+__device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, int lane, int wave, int q0, int b, int hq0, int group, int part,
+                                              int n_live, float lse_blk) {
   constexpr int ROWB = 4 * D, CPRF = D / 4, RPI_OUT = 64 / CPRF, NIT = 32 / RPI_OUT;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ql = lane & 31, rr = lane / CPRF, cc = lane % CPRF;
   const int n_rows = part_rows_total(p), n_valid = n_rows - (q0 + wave * 32);   // rows of this wave (32 or more: all)
   if (n_valid <= 0) return;   // no barrier follows
@@ -810,6 +812,11 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   // chunk per lane, so that every global row is touched as one contiguous segment.
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();  // every wave is done with the K/V rings and none of its loads is still landing
+  {
+  // The lane is counted anew: held over the loop, it and what follows from it spill at D = 128, and a kernel with
+  // scratch starts about 1 us later.
+  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ql = lane & 31, hf = lane >> 5;
+  const int qrow = qw0 + ql;
   constexpr int ROWB = 4 * D;                 // bytes of one fp32 output row
   constexpr int CPRF = D / 4;                 // 16-byte chunks per fp32 row = lanes per row when reading back
   constexpr int RPI_OUT = 64 / CPRF;          // rows one wave-wide access covers
@@ -830,7 +837,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
       *reinterpret_cast<f32x4*>(my + ql * ROWB + ((c ^ (ql & 15)) << 4)) = o;
     }
   if constexpr (PART) {
-    part_epilogue<D, EPI>(p, lds, q0, b, hq, pb.group, pb.part, n_live, lse_blk);
+    part_epilogue<D, EPI>(p, lds, lane, wave, q0, b, hq, pb.group, pb.part, n_live, lse_blk);
     return;
   }
   if (EPI != kEpiMerge) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
@@ -933,6 +940,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
       dst += dst_step;
     }
   }
+  }
   if constexpr (CHUNKS) __syncthreads();  // the next block's loads land where other waves may still read their rows
   }
 }
@@ -995,7 +1003,7 @@ hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream
   if (p.xcd_map == 2) grid = dim3(8u * (unsigned)p.n_qtiles, (unsigned)(nbh / 8));
   if (p.n_parts > 0) {
     if ((int64_t)p.units * p.members == 0) return hipSuccess;
-    const hipError_t e = launch_typed<kPart>(p, D, epilogue, dim3((unsigned)((p.units + 7) / 8 * p.members * 8)), stream);
+    const hipError_t e = launch_typed<kPart>(p, D, epilogue, dim3((unsigned)(((int64_t)p.units * p.members + 7) / 8 * 8)), stream);
     if (e != hipSuccess || p.n_parts == 1) return e;
     return D == 128 ? launch_fold<128>(p, epilogue, stream) : launch_fold<64>(p, epilogue, stream);
   }
