@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import torch
 
@@ -84,6 +85,32 @@ def _load():
 
 _lib = _load()
 
+# The calls below hand descriptors over as packed bytes: a call of the smallest sizes is bound by its
+# marshalling (five ctypes structures and a stream object cost 8 us a call, more than the kernel's own 8 us;
+# packed and with the raw stream handle about half), and untyped pointer arguments take bytes as they are.
+_V, _I, _F = ctypes.c_void_p, ctypes.c_int, ctypes.c_float
+_DTYPES = {torch.bfloat16: TR_BF16, torch.float32: TR_F32}
+_DESC = struct.Struct("Pi4x8q")   # a tr_tensor and one word behind it (the stride of D)
+_DESC_PACK = _DESC.pack
+
+
+def _bind(name, *argtypes):
+    f = getattr(_calls, name)
+    f.argtypes, f.restype = list(argtypes), ctypes.c_int
+    return f
+
+
+_calls = ctypes.CDLL(LIB_PATH)   # function objects of their own: those of raw_lib() keep their typed arguments
+_block_attn = _bind("tr_block_attn", _V, _V, _V, _I, _F, _V, _V, _V)
+_block_attn_causal_at = _bind("tr_block_attn_causal_at", _V, _V, _V, ctypes.c_int64, ctypes.c_int64, _F, _V, _V, _V)
+_block_attn_merge = _bind("tr_block_attn_merge", _V, _V, _V, _I, _F, _V, _V, _V)
+_merge = _bind("tr_merge", _V, _V, _V, _V, _V)
+_merge_n = _bind("tr_merge_n", _V, _V, _V, _V, _I, _I, _V)
+_ring_attn = _bind("tr_ring_attn", _V, _V, _V, _I, _I, _V, _V, _F, _V, ctypes.c_size_t, _V)
+_ring_attn_noalloc = _bind("tr_ring_attn_noalloc", _V, _V, _V, _I, _I, _V, _V, _F, _V)
+_ring_attn_sched = _bind("tr_ring_attn_sched", _V, _V, _V, _I, _I, _I, _I, _V, _V, _F, _V)
+_ring_attn_blocks = _bind("tr_ring_attn_blocks", _V, _V, _V, _I, _I, _V, _V, _F, _I, _V, ctypes.c_size_t, _V)
+
 
 def raw_lib():
     """The loaded ctypes library (for tests that call the C ABI with hand-made descriptors)."""
@@ -117,9 +144,38 @@ def desc(t: torch.Tensor) -> TrTensor:
     return TrTensor(t.data_ptr() if t.numel() else None, dt, B, H, S, D, sb, sh, ss)
 
 
+def _pack(t: torch.Tensor) -> bytes:
+    """The descriptor of desc() as bytes, same checks."""
+    dt = _DTYPES.get(t.dtype)
+    if dt is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    stride = t.stride()
+    n = len(stride)
+    if n == 4:
+        if stride[3] != 1 and t.shape[3] > 1:
+            raise ValueError("innermost (D) stride must be 1")
+        return _DESC_PACK(t.data_ptr(), dt, *t.shape, *stride)
+    if n != 3:
+        raise ValueError("expected a [B,H,S,D] or [B,H,S] tensor")
+    return _DESC_PACK(t.data_ptr(), dt, *t.shape, 1, *stride, 1)
+
+
+def _pointers(descs):
+    """Host array of pointers to packed descriptors, and the buffer that keeps them."""
+    buf = ctypes.create_string_buffer(b"".join(descs), max(1, len(descs) * _DESC.size))
+    base = ctypes.addressof(buf)
+    return (_V * max(1, len(descs)))(*range(base, base + len(descs) * _DESC.size, _DESC.size)), buf
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def tr_version() -> str:
@@ -128,24 +184,24 @@ def tr_version() -> str:
 
 def tr_block_attn(q, k, v, mask_kind, scale, out, lse, stream=None):
     """block_out, block_lse <- Attention(Q, K, V) into `out`, `lse` (see tokenring.h)."""
-    _check(_lib.tr_block_attn(desc(q), desc(k), desc(v), int(mask_kind), float(scale), desc(out), desc(lse), _stream(stream)))
+    _check(_block_attn(_pack(q), _pack(k), _pack(v), int(mask_kind), float(scale), _pack(out), _pack(lse), _stream(stream)))
 
 
 def tr_block_attn_causal_at(q, k, v, q_pos0, k_pos0, scale, out, lse, stream=None):
     """Block step with the causal rule at chunk positions q_pos0 / k_pos0 (see tokenring.h)."""
-    _check(_lib.tr_block_attn_causal_at(desc(q), desc(k), desc(v), int(q_pos0), int(k_pos0), float(scale),
-                                        desc(out), desc(lse), _stream(stream)))
+    _check(_block_attn_causal_at(_pack(q), _pack(k), _pack(v), int(q_pos0), int(k_pos0), float(scale),
+                                        _pack(out), _pack(lse), _stream(stream)))
 
 
 def tr_block_attn_merge(q, k, v, mask_kind, scale, out_acc, lse_acc, stream=None):
     """Block step whose epilogue applies the Update to the fp32 accumulators (see tokenring.h)."""
-    _check(_lib.tr_block_attn_merge(desc(q), desc(k), desc(v), int(mask_kind), float(scale), desc(out_acc), desc(lse_acc),
+    _check(_block_attn_merge(_pack(q), _pack(k), _pack(v), int(mask_kind), float(scale), _pack(out_acc), _pack(lse_acc),
                                     _stream(stream)))
 
 
 def tr_merge(out_acc, lse_acc, block_out, block_lse, stream=None):
     """Out, Lse <- Update(block_out, block_lse), in place on out_acc / lse_acc."""
-    _check(_lib.tr_merge(desc(out_acc), desc(lse_acc), desc(block_out), desc(block_lse), _stream(stream)))
+    _check(_merge(_pack(out_acc), _pack(lse_acc), _pack(block_out), _pack(block_lse), _stream(stream)))
 
 
 def tr_merge_n(out, lse, block_outs, block_lses, accumulate=False, stream=None):
@@ -153,12 +209,9 @@ def tr_merge_n(out, lse, block_outs, block_lses, accumulate=False, stream=None):
     n = len(block_outs)
     if len(block_lses) != n:
         raise ValueError("block_outs and block_lses differ in length")
-    P = ctypes.POINTER(TrTensor)
-    bo = [desc(t) for t in block_outs]
-    bl = [desc(t) for t in block_lses]
-    bo_arr = (P * max(n, 1))(*[ctypes.pointer(d) for d in bo])
-    bl_arr = (P * max(n, 1))(*[ctypes.pointer(d) for d in bl])
-    _check(_lib.tr_merge_n(desc(out), desc(lse), bo_arr, bl_arr, n, int(bool(accumulate)), _stream(stream)))
+    bo_arr, _keep_o = _pointers([_pack(t) for t in block_outs])
+    bl_arr, _keep_l = _pointers([_pack(t) for t in block_lses])
+    _check(_merge_n(_pack(out), _pack(lse), bo_arr, bl_arr, n, int(bool(accumulate)), _stream(stream)))
 
 
 def tr_time_next_kernel(start_event, stop_event):
@@ -179,8 +232,8 @@ def tr_time_next_kernel(start_event, stop_event):
 
 def tr_ring_attn_sched(q, k, v, n_devices, causal, schedule, out, lse, scale=0.0, n_inner=1, stream=None):
     """tr_ring_attn with a selectable step order (TR_SCHED_*); Update fused into the attention epilogue."""
-    _check(_lib.tr_ring_attn_sched(desc(q), desc(k), desc(v), int(n_devices), int(bool(causal)), int(schedule), int(n_inner),
-                                   desc(out), desc(lse), float(scale), _stream(stream)))
+    _check(_ring_attn_sched(_pack(q), _pack(k), _pack(v), int(n_devices), int(bool(causal)), int(schedule), int(n_inner),
+                                   _pack(out), _pack(lse), float(scale), _stream(stream)))
 
 
 def tr_ring_attn_blocks_workspace_bytes(q, n_chunks, block_dtype) -> int:
@@ -189,7 +242,7 @@ def tr_ring_attn_blocks_workspace_bytes(q, n_chunks, block_dtype) -> int:
 
 def tr_ring_attn_blocks(q, k, v, n_chunks, causal, out, lse, block_dtype, workspace, scale=0.0, stream=None):
     """Algorithm 1 as tr_block_attn + tr_merge per step, the block result stored as block_dtype (TR_F32 / TR_BF16)."""
-    _check(_lib.tr_ring_attn_blocks(desc(q), desc(k), desc(v), int(n_chunks), int(bool(causal)), desc(out), desc(lse),
+    _check(_ring_attn_blocks(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
                                     float(scale), int(block_dtype), workspace.data_ptr(),
                                     workspace.numel() * workspace.element_size(), _stream(stream)))
 
@@ -218,11 +271,11 @@ def tr_ring_attn(q, k, v, n_chunks, causal, out, lse, scale=0.0, workspace=None,
     ws_ptr, ws_bytes = None, 0
     if workspace is not None:
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    _check(_lib.tr_ring_attn(desc(q), desc(k), desc(v), int(n_chunks), int(bool(causal)), desc(out), desc(lse),
+    _check(_ring_attn(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
                              float(scale), ws_ptr, ws_bytes, _stream(stream)))
 
 
 def tr_ring_attn_noalloc(q, k, v, n_chunks, causal, out, lse, scale=0.0, stream=None):
     """tr_ring_attn (two-kernel form) with the block workspace inside the library: nothing is allocated (see tokenring.h)."""
-    _check(_lib.tr_ring_attn_noalloc(desc(q), desc(k), desc(v), int(n_chunks), int(bool(causal)), desc(out), desc(lse),
+    _check(_ring_attn_noalloc(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
                                      float(scale), _stream(stream)))
