@@ -300,7 +300,7 @@ def bench_merge_only(tr, wl, steps, warmup):
 
 
 def bench_ring(tr, wl, name, steps, warmup, fused, schedule=None, n_inner=1, block_dtype=None):
-    """tr_ring_attn over a whole sequence; fused: Update in the attention epilogue (no workspace), else two kernels.
+    """tr_ring_attn over a whole sequence; fused: without a workspace, else with one (block_dtype bf16: blocks rounded one by one).
     schedule: None = tr_ring_attn (Algorithm 1), else a TR_SCHED_* value run through tr_ring_attn_sched."""
     import torch
     cfg = wl.CONFIGS[name]
@@ -312,7 +312,7 @@ def bench_ring(tr, wl, name, steps, warmup, fused, schedule=None, n_inner=1, blo
     ws = None if fused else torch.empty(tr.tr_ring_attn_workspace_bytes(q, cfg.n_chunks), dtype=torch.uint8, device="cuda")
 
     def run():
-        if block_dtype is not None:     # two-kernel form with a chosen transport format of block_out
+        if block_dtype is not None:     # a chosen transport format of block_out
             tr.tr_ring_attn_blocks(q, k, v, cfg.n_chunks, cfg.causal, out, lse, block_dtype, ws, cfg.scale)
         elif schedule is None:
             tr.tr_ring_attn(q, k, v, cfg.n_chunks, cfg.causal, out, lse, cfg.scale, ws)
@@ -336,8 +336,8 @@ def bench_ring(tr, wl, name, steps, warmup, fused, schedule=None, n_inner=1, blo
     sched_name = {None: "Algorithm 1", 0: "Algorithm 1", 1: "Ring Attention order", 2: "zigzag partition",
                   3: f"hybrid, {n_inner} devices per node"}[schedule]
     return {"workload": f"{name}: S={cfg.S} as {n} segments, Hq={cfg.Hq}, Hkv={cfg.Hkv}, causal={cfg.causal}, {sched_name}",
-            "form": ("Update fused into the attention epilogue" if fused else
-                     "tr_block_attn + tr_merge per step" + (", bf16 block_out" if block_dtype == tr.TR_BF16 else ", fp32 block_out")),
+            "form": ("one launch, each Query tile block by block, blocks rounded to bf16" if block_dtype == tr.TR_BF16 else
+                     "one launch over the whole key range" + ("" if fused else ", workspace given")),
             "block_steps": full_steps + diag_steps, "ms": ms, "tflops": flops / (ms * 1e-3) / 1e12,
             "frac_mfma_peak": flops / (ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS}
 
