@@ -260,10 +260,11 @@ hipError_t launch_parts(tr::AttnParams p, const PartPlan& plan, int D, int epilo
 }
 
 // fuse_update: out/lse are fp32 accumulators and the block is merged into them by the kernel's epilogue.
-// n_chunks > 0: all Query chunks against all K/V chunks with bf16 blocks in between; the tensors are views of chunk 0.
+// n_chunks > 0: all Query chunks against all K/V chunks block by block, rounded to bf16 if chunk_bf16; the tensors are
+// views of chunk 0.  renew: keys after which a row's exponent reference is taken anew (0: never).
 tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int causal, int64_t off64, float scale,
                       const tr_tensor* out, const tr_tensor* lse, void* stream, bool fuse_update = false,
-                      int n_chunks = 0) {
+                      int n_chunks = 0, bool chunk_bf16 = false, int renew = 0) {
   tr_status st;
   if ((st = check_tensor("q", q, true, false, 16)) != TR_OK) return st;
   if ((st = check_tensor("k", k, true, false, 16)) != TR_OK) return st;
@@ -300,6 +301,7 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   const int64_t lim = (int64_t)1 << 30;
   p.causal_off = (int)(off64 > lim ? lim : (off64 < -lim ? -lim : off64));
   p.scale = scale;
+  p.renew = renew;
   const int bm = tr::attn_rows_per_block();
   p.n_qtiles = (p.Sq + bm - 1) / bm;
   p.xcd_map = (p.B * p.Hkv) % 8 == 0 && (int64_t)p.n_qtiles * p.B * p.Hq >= 8;
@@ -317,6 +319,7 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   const int epilogue = fuse_update ? 2 : (out->dtype == TR_F32 ? 1 : 0);
   if (n_chunks > 0) {
     p.n_chunks = n_chunks;
+    p.chunk_bf16 = chunk_bf16 ? 1 : 0;
     const int step = std::max(1, 65535 / p.n_qtiles);   // chunks one grid holds; the later ones first, as inside a launch
     for (p.chunk_end = n_chunks; p.chunk_end > 0; p.chunk_end = p.chunk_begin) {
       p.chunk_begin = std::max(0, p.chunk_end - step);
@@ -436,14 +439,26 @@ std::vector<LaunchGroup> group_steps(const std::vector<RingStep>& steps, int n_s
 // S 256 in 4 chunks 29.5 -> 10.8, causal 8192 in 8 segments 615 -> 467, causal 32768 in 8 chunks 7603 -> 6959,
 // full 16384 at D 64 3555 -> 3160, GQA 131072 in 16 chunks 112.7 -> 108.0 ms: what goes are the set-up, the
 // epilogue and the idle tail of every launch but one.  Query rows beyond what a grid holds go out as further launches.
-tr_status attn_whole(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, bool causal, float scale,
+//
+// A block attended alone has an exponent reference of its own, hence one weight that bf16 holds exactly.  So that the
+// result is no further from the exact one than the blocks one by one, the reference is renewed once a segment; segments
+// shorter than a sub-tile (32 keys) are attended block by block, a Query tile running through them in one launch
+// (16 segments of 16 keys: 1.03e-3 by blocks, 1.17e-3 renewed at every sub-tile, 1.61e-3 with one reference).
+tr_status attn_whole(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int n_seg, bool causal, float scale,
                      const tr_tensor* out, const tr_tensor* lse, void* stream) {
+  const int64_t seg = q->S / n_seg;
+  if (n_seg > 1 && seg < 32) {
+    const tr_tensor q0 = rows_view(q, 0, seg), k0 = rows_view(k, 0, seg), v0 = rows_view(v, 0, seg);
+    const tr_tensor o0 = rows_view(out, 0, seg), l0 = rows_view(lse, 0, seg);
+    return attn_common(&q0, &k0, &v0, causal, 0, scale, &o0, &l0, stream, true, n_seg);
+  }
+  const int renew = n_seg > 1 ? (int)(seg / 32 * 32) : 0;
   const int64_t slab = (int64_t)65535 * tr::attn_rows_per_block();
   int64_t r0 = 0;
   do {
     const int64_t rows = std::min(slab, q->S - r0);
     const tr_tensor qs = rows_view(q, r0, rows), os = rows_view(out, r0, rows), ls = rows_view(lse, r0, rows);
-    const tr_status st = attn_common(&qs, k, v, causal, r0, scale, &os, &ls, stream);
+    const tr_status st = attn_common(&qs, k, v, causal, r0, scale, &os, &ls, stream, false, 0, false, renew);
     if (st != TR_OK) return st;
     r0 += rows;
   } while (r0 < q->S);
@@ -660,10 +675,10 @@ tr_status ring_attn_impl(const tr_tensor* q, const tr_tensor* k, const tr_tensor
 
   // fp32 blocks reach the Update unrounded, so folding them in registers is the same operation; bf16
   // blocks are rounded one by one on their way, as the caller asked.
-  if (block_dtype == TR_F32) return attn_whole(q, k, v, causal != 0, scale, out, lse, hip_stream);
+  if (block_dtype == TR_F32) return attn_whole(q, k, v, n_chunks, causal != 0, scale, out, lse, hip_stream);
   const tr_tensor q0 = chunk_view(q, 0, C), k0 = chunk_view(k, 0, C), v0 = chunk_view(v, 0, C);
   const tr_tensor o0 = chunk_view(out, 0, C), l0 = chunk_view(lse, 0, C);
-  return attn_common(&q0, &k0, &v0, causal != 0, 0, scale, &o0, &l0, hip_stream, true, n_chunks);
+  return attn_common(&q0, &k0, &v0, causal != 0, 0, scale, &o0, &l0, hip_stream, true, n_chunks, true);
 }
 
 }  // namespace
@@ -751,7 +766,7 @@ tr_status tr_ring_attn_sched(const tr_tensor* q, const tr_tensor* k, const tr_te
 
   if (overlaps(out, q) || overlaps(out, k) || overlaps(out, v) || overlaps(lse, q) || overlaps(lse, k) || overlaps(lse, v) || overlaps(out, lse))
     return fail(TR_ERR_ALIAS, "outputs overlap inputs or each other");
-  return attn_whole(q, k, v, causal != 0, scale, out, lse, hip_stream);
+  return attn_whole(q, k, v, n_seg, causal != 0, scale, out, lse, hip_stream);
 }
 
 }  // extern "C"

@@ -319,7 +319,8 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
 // over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 156 us, 500 Query rows x 32 heads
 // behind 12000 keys 216 -> 105 us against the plain form.
 //
-// FORM kChunks replays Algorithm 1 with block results that are rounded to bf16 on their way to the Update.
+// FORM kChunks replays Algorithm 1 block by block: with block results that are rounded to bf16 on their way to the
+// Update, or (chunks shorter than a sub-tile, which no reference of the running softmax can be kept for) in fp32.
 // A workgroup keeps its Query tile of chunk c and runs through the K/V chunks in the order the schedule
 // brings them, c, c + 1, ... mod n (causal: only those not after c); each block ends in the merging
 // epilogue, the first one unrounded onto an empty accumulator.  One launch instead of two per block: no
@@ -534,7 +535,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   float m_ref = -INFINITY;  // exponent reference of this query, in raw (unscaled) score units
   float mc = 0.f;           // m_ref * c2 (0 while m_ref is -inf), kept alongside m_ref
   float l_run = 0.f;        // this lane's share of the running sum of exp
-  float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite
+  float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite and where it is renewed
+  int renew_at = !CHUNKS && p.renew > 0 ? p.renew : 0x7fffffff;   // m_ref is renewed by the first step that starts at this key or later
   const float c2 = p.scale * 1.4426950408889634f;  // scale * log2(e)
 
   // ---- one step ---------------------------------------------------------------------
@@ -553,6 +555,11 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   // every P.  Only if some lane's sum exceeds the cap (or is NaN), or the reference is still
   // -inf, the slow path runs after the stream: row maximum, raise the reference, rescale l
   // and the O accumulators (which by then include P_{j-1}, consistently), redo the exponentials.
+  // With p.renew the slow path also runs once every p.renew keys and may lower the reference to its
+  // sub-tile's maximum: the weight of that maximum is then 1 and bf16 holds it exactly.  One
+  // reference for a whole sequence has one such weight a row where blocks attended one by one have one each,
+  // and the rounding of the largest weights is most of the error: 256 keys 1.42e-3 in blocks of 64, 1.60e-3 with one
+  // reference, 1.42e-3 renewed every 64 keys.
   // Row sums use the unrounded fp32 P: summing the bf16-rounded weights would cost up to
   // 2^-8 relative in l, more than the 1e-3 budget of lse for rows that see only a few keys.
   //
@@ -653,12 +660,16 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     for (int h = 0; h < 2; h++) p_out[h] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * h], pw[4 * h + 1], pw[4 * h + 2], pw[4 * h + 3]});
     float psum = ps0 + ps1;
 
-    if (__any(!(psum <= sum_cap))) {   // sum_cap < 0 while m_ref is -inf, so that case is included
+    if (__builtin_expect(__any(!(psum <= sum_cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
       float tmax = s_in[0];
 #pragma unroll
       for (int i = 1; i < 16; i++) tmax = fmaxf(tmax, s_in[i]);
       tmax = half_swap_max(tmax);
-      const float m_new = fmaxf(m_ref, tmax);
+      float m_new = fmaxf(m_ref, tmax);
+      // Renewed: down as well, while what the row has summed so far stays below 2^40 in the new units (else weights of
+      // this sub-tile do not count beside it).  Both halves of a row decide alike.
+      const float lowered = half_swap_max(l_run) * __builtin_amdgcn_exp2f((m_ref - tmax) * c2);
+      if (sum_cap < 0.f && tmax > -INFINITY && lowered <= 0x1p40f) m_new = tmax;
       const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * c2);  // m_ref = -inf -> 0; equal -> 1
       const float a = (m_new == -INFINITY) ? 0.f : alpha;                 // (-inf) - (-inf) would be NaN
       l_run *= a;
@@ -729,6 +740,10 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     constexpr unsigned k_imm = kt + 2 < NSUB ? su * TILE_BYTES + (kt + 2) * SUBB : sn * TILE_BYTES + (kt + 2 - NSUB) * SUBB;
     const int j = NSUB * u + kt;
     if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
+      if (!INNER && j * SUB >= renew_at) {
+        sum_cap = -1.f;
+        renew_at += p.renew;
+      }
       if (kt % 2 == 0) step(j * SUB, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sA, sB, pB, pA, inner_c);
       else step(j * SUB, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sB, sA, pA, pB, inner_c);
     }
@@ -785,17 +800,26 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
   const int j_inner = min(jw_in, kmask_from >= 0 ? kmask_from / SUB : -1) - (NSUB - 1);   // last step of the tile must pass both tests
   int u_inner = j_inner < 0 ? -1 : j_inner / NSUB;
   u_inner = __builtin_amdgcn_readfirstlane(min(u_inner, last_tile - 4));   // loads issued in tile u reach tile u + 3
+  if (p.renew > 0 && p.renew < NS * BN) u_inner = -1;   // inner tiles look at renew_at once a group: once a tile costs 1 - 3 % of a long ring
   // tiles 1 .. 3 (tile 0 was the prologue)
   if (1 <= n_tiles) tile_body(1, IC<1 % NS>{}, IC<0>{});
   if (2 <= n_tiles) tile_body(2, IC<2 % NS>{}, IC<0>{});
   if (3 <= n_tiles) tile_body(3, IC<3 % NS>{}, IC<0>{});
-  // Groups of NS tiles: first the groups of inner tiles, then general ones to the end.
+  // Groups of NS tiles: first the groups of inner tiles (up to where the reference is renewed, and on from there), then
+  // general ones to the end.
   int u0 = NS;
-  for (; u0 + NS - 1 <= u_inner; u0 += NS) {
-    tile_body(u0, IC<0>{}, IC<1>{});
-    tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{});
-    tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{});
-    tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{});
+  while (u0 + NS - 1 <= u_inner) {
+    if (u0 * BN >= renew_at) {
+      sum_cap = -1.f;
+      renew_at += p.renew;
+    }
+    const int stop = min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NS - 1);
+    for (; u0 + NS - 1 <= stop; u0 += NS) {
+      tile_body(u0, IC<0>{}, IC<1>{});
+      tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{});
+      tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{});
+      tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{});
+    }
   }
   for (; u0 <= n_tiles; u0 += NS) {
     tile_body(u0, IC<0>{}, IC<0>{});
@@ -883,7 +907,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     for (int it = 0; it < NIT; it++) {
       const int r = it * RPI_OUT + rr;
       ov[it] = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
-      if (CHUNKS && block > 0) {
+      if (CHUNKS && block > 0 && p.chunk_bf16) {
 #pragma unroll
         for (int e = 0; e < 4; e++) ov[it][e] = (float)(__bf16)ov[it][e];
       }

@@ -33,6 +33,8 @@ struct AttnParams {
   // Chunk form (n_chunks > 0): q, out, lse and k, v are chunk 0 of n_chunks chunks that lie one behind the other
   // along S; the launch covers Query chunks chunk_begin .. chunk_end - 1.
   int n_chunks, chunk_begin, chunk_end;
+  int chunk_bf16; // 1: every block after a Query chunk's first is rounded to bf16 before its Update
+  int renew;      // keys (a multiple of 32) after which a row's exponent reference is taken anew; 0: never
   // Partitioned form (n_parts > 0), see the kernel: n_qtiles then counts the tiles of the row space
   // (one head's Sq rows, or with pack the gq * Sq rows of a K/V head's group).
   int n_parts;    // parts of the keys, part_keys (a multiple of 128) each; 0: the plain form
