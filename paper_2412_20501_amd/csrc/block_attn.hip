@@ -891,7 +891,8 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     // on their way.  The same lane reads the row's old lse and writes the new one.
     {
       const int64_t l_at = l_bh + (int64_t)min(qrow, p.Sq - 1) * p.l_ss;
-      const UpdatePlan plq = plan_update(CHUNKS && block == 0 ? -INFINITY : p.lse[l_at], lse_blk);
+      UpdatePlan plq = plan_update(CHUNKS && block == 0 ? -INFINITY : p.lse[l_at], lse_blk);
+      if (CHUNKS && block == 0) plq.mode = 2;   // a first block is stored as it is, also where it is NaN (with lse -inf)
       if (hf == 0) {
         my_w[ql] = plq.w;
         my_mode[ql] = plq.mode;

@@ -46,3 +46,18 @@ def test_bf16_blocks_are_the_steps_one_by_one(lib, B, Hq, Hkv, chunk, n, D, toke
         seen.add(c)
     torch.cuda.synchronize()
     assert torch.equal(out, ref_o) and torch.equal(lse, ref_l)
+
+
+@pytest.mark.parametrize("causal,n", [(False, 1), (True, 3)])
+def test_a_first_block_is_stored_as_it_is(lib, causal, n):
+    chunk, D = 96, 64
+    q, k, v = (bits_to_dev(rand_bits((1, h, chunk * n, D), 530 + i)) for i, h in enumerate((2, 1, 1)))
+    q[0, 1, 7, 0] = float("nan")                         # a row that meets one block only (chunk 0)
+    out, lse = torch.zeros((1, 2, chunk * n, D), device="cuda"), torch.zeros((1, 2, chunk * n), device="cuda")
+    ws = torch.empty(lib.tr_ring_attn_blocks_workspace_bytes(q, n, lib.TR_BF16), dtype=torch.uint8, device="cuda")
+    lib.tr_ring_attn_blocks(q, k, v, n, causal, out, lse, lib.TR_BF16, ws, 0.1)
+    torch.cuda.synchronize()
+    assert torch.isnan(out[0, 1, 7]).all() and bool(torch.isneginf(lse[0, 1, 7]))
+    keep = torch.ones((2, chunk * n), dtype=torch.bool, device="cuda")
+    keep[1, 7] = False
+    assert torch.isfinite(out[0][keep]).all() and torch.isfinite(lse[0][keep]).all()
