@@ -19,9 +19,8 @@
  *     keys into parts; their partial results pass through device arrays inside the library (132 MiB,
  *     held by every GPU the library runs on until the process ends), one region for each of the
  *     first four streams of a GPU that make such a call.  Without a region - further streams, the per-thread
- *     default stream, graph capture - an fp32 result is folded part by part in the output instead,
- *     slower and bitwise the same; a bf16 block_out then takes all keys at once, which is the same
- *     result up to rounding.
+ *     default stream, graph capture - the call takes all keys at once in one launch, which is the same
+ *     result up to rounding.  The ring entry points never cut.
  *   - `hip_stream` is a hipStream_t (NULL = the default stream).  Calls enqueue work on
  *     it and return without synchronising.
  *   - A tensor a call writes (out, lse, out_acc, lse_acc) must not overlap itself: a stride of 0

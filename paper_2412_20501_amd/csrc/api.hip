@@ -112,9 +112,11 @@ constexpr int64_t kPartAlign = 128;   // parts begin on whole tiles of either he
 struct PartPlan {
   int pack = 0, parts = 1, members = 0, row_tiles = 0, part_rows = 0;
   int64_t part_keys = 0, out_elems = 0;   // out_elems: floats of block_out in the scratch
+  bool packs_uncut = false;               // heads are packed also where the keys are not cut
 };
 
-// Chooses the form of a launch; false: the plain one.
+// Chooses the form of a launch; false: the plain one.  may_cut false: the keys stay in one piece, which makes the
+// result independent of the stream and of capture, whatever scratch is there.
 //
 // Heads are packed when that leaves at most four fifths of the row tiles: the rows that fill a tile up cost
 // their share of the loads and of the time of its slowest wave all the same.  (Where the plain form fits the
@@ -128,7 +130,7 @@ struct PartPlan {
 // Both sides of the line, us: 500 rows x 32 heads on 12500 keys 213 in one part, 106 in 4; 96 rows x 8
 // heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 1777 rows x 24
 // heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 88 and 38 in 6.
-bool plan_parts(const tr::AttnParams& p, int D, PartPlan& best) {
+bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
   const int bm = tr::attn_rows_per_block();
   const int64_t rows = (int64_t)p.gq * p.Sq, kv = (int64_t)p.B * p.Hkv;
   if (p.Sk == 0 || p.Sq == 0 || kv == 0 || rows > ((int64_t)1 << 24)) return false;
@@ -139,10 +141,10 @@ bool plan_parts(const tr::AttnParams& p, int D, PartPlan& best) {
   c.members = (int)(c.pack ? packed : plain);
   const int64_t space = c.pack ? rows : p.Sq, tiles = kv * c.members;
   c.part_rows = space > bm ? bm : (int)((space + 31) / 32 * 32);
-  c.part_keys = ((int64_t)p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
+  c.packs_uncut = c.pack && kv * plain > kCUs;
   best = c;
   if (tiles * tr::kMaxParts >= ((int64_t)1 << 30)) return false;
-  if (tiles > 2 * kCUs) return c.pack;
+  if (tiles > 2 * kCUs || !may_cut) return c.packs_uncut;
   // keys that some row of row tile t sees
   auto seen = [&](int t) -> int64_t {
     if (!p.causal) return p.Sk;
@@ -177,7 +179,7 @@ bool plan_parts(const tr::AttnParams& p, int D, PartPlan& best) {
     best.part_keys = part_keys;
     best.out_elems = slot_rows * D;
   }
-  return best.parts > 1 || (c.pack && kv * plain > kCUs);
+  return best.parts > 1 || best.packs_uncut;
 }
 
 // Scratch of the partitioned launches: device arrays of the library itself (nothing is allocated), one
@@ -223,7 +225,8 @@ char* part_scratch_for(hipStream_t stream) {
   return d.bytes + (size_t)i * kPartBytes;
 }
 
-hipError_t launch_parts(tr::AttnParams p, const PartPlan& plan, int D, int epilogue, hipStream_t stream) {
+hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int D, int epilogue, hipStream_t stream) {
+  tr::AttnParams p = plain;
   p.pack = plan.pack;
   p.members = plan.members;
   p.n_qtiles = plan.row_tiles;
@@ -239,32 +242,23 @@ hipError_t launch_parts(tr::AttnParams p, const PartPlan& plan, int D, int epilo
       return tr::launch_block_attn(p, D, epilogue, stream);
     }
   }
+  // All keys at once, in one launch.  (The parts one after the other, folded in the output, give the bits of the cut
+  // form but pay a set-up and an epilogue for each: 1764 rows x 2 heads on 6491 keys 202 us replayed from a graph
+  // against 91 in one pass, a decode step of 4 sequences on 8192 keys 121 against 90.)
+  if (!plan.packs_uncut) return tr::launch_block_attn(plain, D, epilogue, stream);
   p.n_parts = 1;
+  p.part_keys = (p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
   p.units = p.B * p.Hkv;
-  // Without scratch: fp32 results are folded part by part in out / lse themselves, one launch after the
-  // other, which gives the same bits; a bf16 result has no room for that and takes all keys at once.
-  const int parts = epilogue == 0 ? 1 : plan.parts;
-  const __bf16 *k = p.k, *v = p.v;
-  const int sk = p.Sk, off = p.causal_off;
-  for (int i = 0; i < parts; i++) {
-    const int64_t k0 = i * plan.part_keys;
-    p.k = k + k0 * p.k_ss;
-    p.v = v + k0 * p.v_ss;
-    p.Sk = (int)(parts == 1 ? sk : std::min<int64_t>(sk - k0, plan.part_keys));
-    p.part_keys = (p.Sk + 127) / 128 * 128;
-    p.causal_off = off - (int)k0;
-    const hipError_t e = tr::launch_block_attn(p, D, i > 0 ? 2 : epilogue, stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return tr::launch_block_attn(p, D, epilogue, stream);
 }
 
 // fuse_update: out/lse are fp32 accumulators and the block is merged into them by the kernel's epilogue.
 // n_chunks > 0: all Query chunks against all K/V chunks block by block, rounded to bf16 if chunk_bf16; the tensors are
-// views of chunk 0.  renew: keys after which a row's exponent reference is taken anew (0: never).
+// views of chunk 0.  renew: keys after which a row's exponent reference is taken anew (0: never).  may_cut: the keys may
+// be cut into parts.
 tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int causal, int64_t off64, float scale,
                       const tr_tensor* out, const tr_tensor* lse, void* stream, bool fuse_update = false,
-                      int n_chunks = 0, bool chunk_bf16 = false, int renew = 0) {
+                      int n_chunks = 0, bool chunk_bf16 = false, int renew = 0, bool may_cut = true) {
   tr_status st;
   if ((st = check_tensor("q", q, true, false, 16)) != TR_OK) return st;
   if ((st = check_tensor("k", k, true, false, 16)) != TR_OK) return st;
@@ -329,8 +323,8 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
     return TR_OK;
   }
   PartPlan plan;
-  const hipError_t e = plan_parts(p, (int)q->D, plan) ? launch_parts(p, plan, (int)q->D, epilogue, (hipStream_t)stream)
-                                                      : tr::launch_block_attn(p, (int)q->D, epilogue, (hipStream_t)stream);
+  const hipError_t e = plan_parts(p, (int)q->D, may_cut, plan) ? launch_planned(p, plan, (int)q->D, epilogue, (hipStream_t)stream)
+                                                                 : tr::launch_block_attn(p, (int)q->D, epilogue, (hipStream_t)stream);
   if (e != hipSuccess) return fail(TR_ERR_HIP, "block attention launch failed: %s", hipGetErrorString(e));
   return TR_OK;
 }
@@ -439,6 +433,7 @@ std::vector<LaunchGroup> group_steps(const std::vector<RingStep>& steps, int n_s
 // S 256 in 4 chunks 29.5 -> 10.8, causal 8192 in 8 segments 615 -> 467, causal 32768 in 8 chunks 7603 -> 6959,
 // full 16384 at D 64 3555 -> 3160, GQA 131072 in 16 chunks 112.7 -> 108.0 ms: what goes are the set-up, the
 // epilogue and the idle tail of every launch but one.  Query rows beyond what a grid holds go out as further launches.
+// The keys are not cut (plan_parts): the result of a schedule is the same bits eagerly, in a graph and on any stream.
 //
 // A block attended alone has an exponent reference of its own, hence one weight that bf16 holds exactly.  So that the
 // result is no further from the exact one than the blocks one by one, the reference is renewed once a segment; segments
@@ -458,7 +453,7 @@ tr_status attn_whole(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v,
   do {
     const int64_t rows = std::min(slab, q->S - r0);
     const tr_tensor qs = rows_view(q, r0, rows), os = rows_view(out, r0, rows), ls = rows_view(lse, r0, rows);
-    const tr_status st = attn_common(&qs, k, v, causal, r0, scale, &os, &ls, stream, false, 0, false, renew);
+    const tr_status st = attn_common(&qs, k, v, causal, r0, scale, &os, &ls, stream, false, 0, false, renew, false);
     if (st != TR_OK) return st;
     r0 += rows;
   } while (r0 < q->S);

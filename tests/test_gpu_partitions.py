@@ -2,8 +2,7 @@
 
 Sizes sit where the form can go wrong: row counts around a wave and a tile, a last part of one key, parts
 that no row of a tile sees, heads that share a wave.  Reference: the fp64 oracle, tolerances as for every
-block step.  Without scratch (under graph capture, on a stream beyond those that have a region) fp32 results
-are folded part by part in the output and must be the same bits.
+block step.  Without scratch (under graph capture, on a stream beyond those that have a region) the keys are one piece.
 """
 import numpy as np
 import pytest
@@ -84,30 +83,51 @@ def test_parts_merge_into_accumulators(lib, case):
     assert max_abs(to_np(d_o), ref_o) <= OUT_TOL and max_abs(to_np(d_l), ref_l) <= LSE_TOL
 
 
+@pytest.mark.parametrize("form", ["bf16", "fp32", "merge"])
 @pytest.mark.parametrize("case", CASES, ids=str)
-def test_without_scratch_the_bits_are_the_same(lib, case):
+def test_without_scratch_the_result_is_the_same_up_to_rounding(lib, case, form):
+    """More streams at a time than have a scratch region, and a captured call: one pass over all keys, to the oracle's
+    tolerance; the replays of a graph agree bitwise."""
+    if form == "merge" and case[6] is not None:
+        pytest.skip("the merging step has no causal rule at arbitrary positions")
     B, Hq, Hkv, Sq, Sk, D, _ = case
-    q, k, v = (bits_to_dev(x) for x in _inputs(case, 360))
-    new = lambda: (torch.full((B, Hq, Sq, D), float("nan"), device="cuda"), torch.full((B, Hq, Sq), float("nan"), device="cuda"))
-    out, lse = new()
-    _attend(lib, case, q, k, v, 0.1, out, lse)
-    torch.cuda.synchronize()
-    # more streams than have a scratch region: each gives the same result
+    bits = _inputs(case, 360)
+    q, k, v = (bits_to_dev(x) for x in bits)
+    ref_o, ref_l = _reference(case, *bits, 0.1)
+    dtype = torch.bfloat16 if form == "bf16" else torch.float32
+    empty = float("-inf") if form == "merge" else float("nan")     # merge: onto an empty accumulator that holds garbage
+
+    def new():
+        return torch.full((B, Hq, Sq, D), float("nan"), dtype=dtype, device="cuda"), torch.full((B, Hq, Sq), empty, device="cuda")
+
+    def run(out, lse, stream=None):
+        if form == "merge":
+            lib.tr_block_attn_merge(q, k, v, lib.TR_MASK_NONE, 0.1, out, lse, stream)
+        else:
+            _attend(lib, case, q, k, v, 0.1, out, lse, stream)
+
+    def check(out, lse):
+        assert np.array_equal(np.isneginf(to_np(lse)), np.isneginf(ref_l))
+        assert max_abs(to_np(out), ref_o) <= OUT_TOL and max_abs(to_np(lse), ref_l) <= LSE_TOL
+
     streams = [torch.cuda.Stream() for _ in range(6)]
     results = [new() for _ in streams]
     torch.cuda.synchronize()
     for s, (o, l) in zip(streams, results):
-        _attend(lib, case, q, k, v, 0.1, o, l, s)
+        run(o, l, s)
     torch.cuda.synchronize()
     for o, l in results:
-        assert torch.equal(o, out) and torch.equal(l, lse)
+        check(o, l)
     graph_o, graph_l = new()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        _attend(lib, case, q, k, v, 0.1, graph_o, graph_l)
+        run(graph_o, graph_l)
+    first = None
     for _ in range(3):
-        graph_o.fill_(float("nan")); graph_l.fill_(float("nan"))
+        graph_o.fill_(float("nan")); graph_l.fill_(empty)
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
-        assert torch.equal(graph_o, out) and torch.equal(graph_l, lse)
+        check(graph_o, graph_l)
+        first = first or (graph_o.clone(), graph_l.clone())
+        assert torch.equal(graph_o, first[0]) and torch.equal(graph_l, first[1])
