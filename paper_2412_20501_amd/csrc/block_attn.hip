@@ -184,12 +184,12 @@ struct EpiLds {
 };
 
 // Epilogue of the partitioned form.  The wave's normalised 32 x D tile lies in LDS (chunk-swizzled, written
-// by this wave), lse_blk is the log-sum-exp of the lane's row over the workgroup's part of the keys.  With
-// one live part the tile is stored or merged as it is, otherwise tile and lse go to the scratch slot of
-// (row tile, part) for the fold kernel.
+// by this wave), lse_blk is the log-sum-exp of the lane's row over the workgroup's part of the keys (-inf also
+// for a row whose weights hold a NaN, which not_a_number says apart).  With one live part the tile is stored or
+// merged as it is, otherwise tile and lse go to the scratch slot of (row tile, part) for the fold kernel.
 template <int D, int EPI>
 __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, int lane, int wave, int q0, int b, int hq0, int group, int part,
-                                              int n_live, float lse_blk) {
+                                              int n_live, float lse_blk, bool not_a_number) {
   constexpr int ROWB = 4 * D, CPRF = D / 4, RPI_OUT = 64 / CPRF, NIT = 32 / RPI_OUT;
   const int ql = lane & 31, rr = lane / CPRF, cc = lane % CPRF;
   const int n_rows = part_rows_total(p), n_valid = n_rows - (q0 + wave * 32);   // rows of this wave (32 or more: all)
@@ -207,7 +207,7 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
       const f32x4 o = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
       if (r < n_valid) *reinterpret_cast<f32x4*>(dst + (int64_t)r * D) = o;
     }
-    if (own_row) p.part_lse[slot_row + ql] = lse_blk;
+    if (own_row) p.part_lse[slot_row + ql] = not_a_number ? __builtin_nanf("") : lse_blk;
     return;
   }
   float* const tab_w = reinterpret_cast<float*>(lds + EpiLds<D>::w) + wave * 32;
@@ -250,12 +250,14 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
   }
 }
 
-// Fold of a partitioned launch: out, lse <- the Update of Sec. 3.1 applied to the parts of a row in key order (with
-// kEpiMerge onto the accumulators).  A kernel of its own, because whoever finishes last would otherwise read all
+// Fold of a partitioned launch: the Update of Sec. 3.1 over the parts of a row at once, out = sum of exp(lse_i - lse)
+// out_i; with kEpiMerge that block then takes one Update onto the accumulators.  Weighted and not blended part by part,
+// so that an infinite value of V stays infinite (a blend would subtract it from itself), and a row with a NaN weight in
+// any part is the block that one pass over the keys gives: out = NaN, lse = -inf.  A kernel of its own, because whoever finishes last would otherwise read all
 // parts of a row tile through one compute unit and pay for cache write-backs between the XCDs first:
 // 16 rows x 4 heads in 16 parts of 1024 keys 50 -> 30 us, 500 rows x 32 heads in 4 parts 119 -> 106 us (whole call).
 // A thread owns 16 bytes of a row; lse values and pieces of all its parts (MAXP at most) are requested before
-// the chain of log-sum-exps starts.
+// the log-sum-exp starts.
 constexpr int kFoldThreads = 256;
 template <int D, int EPI, int MAXP>
 __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnParams p) {
@@ -283,18 +285,41 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
   for (int i = 0; i < MAXP; i++)
     y[i] = *reinterpret_cast<const f32x4*>(p.part_out + (slot_row + (int64_t)min(i, n_live - 1) * p.part_rows) * D + 4 * cc);
   float acc = -INFINITY;
-  f32x4 x = {0.f, 0.f, 0.f, 0.f};
+  f32x4 held = {0.f, 0.f, 0.f, 0.f};
   if (EPI == kEpiMerge) {
     acc = p.lse[l_at];
-    x = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.out) + o_at);
+    held = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.out) + o_at);
   }
+  float top = -INFINITY, total = 0.f;
+  bool not_a_number = false;
 #pragma unroll
   for (int i = 0; i < MAXP; i++)
     if (i < n_live) {
-      const UpdatePlan pl = plan_update(acc, ls[i]);
-      acc = pl.new_lse;
-      x = apply_update(pl, x, y[i]);
+      top = fmaxf(top, ls[i]);
+      not_a_number |= ls[i] != ls[i];
     }
+#pragma unroll
+  for (int i = 0; i < MAXP; i++)
+    if (i < n_live) {
+      ls[i] = ls[i] == -INFINITY ? -1.f : expf(ls[i] - top);   // -1: an empty part, whose values are not looked at
+      total += fmaxf(ls[i], 0.f);
+    }
+  const float inv = total > 0.f ? 1.f / total : 0.f;
+  f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < MAXP; i++)
+    if (i < n_live) {
+      const float w = ls[i] * inv;
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[e] = ls[i] >= 0.f ? __builtin_fmaf(w, y[i][e], x[e]) : x[e];
+    }
+  float lse = not_a_number || !(total > 0.f) ? -INFINITY : top + logf(total);
+  if (not_a_number) x = f32x4{1.f, 1.f, 1.f, 1.f} * __builtin_nanf("");
+  if (EPI == kEpiMerge) {
+    const UpdatePlan pl = plan_update(acc, lse);
+    lse = pl.new_lse;
+    x = apply_update(pl, held, x);
+  }
   if (EPI == kEpiBf16) {
     bf16x4 ob;
 #pragma unroll
@@ -303,7 +328,7 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
   } else {
     *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + o_at) = x;
   }
-  if (cc == 0) p.lse[l_at] = acc;   // a row lies within one wave, so every thread of it has read the old value
+  if (cc == 0) p.lse[l_at] = lse;   // a row lies within one wave, so every thread of it has read the old value
 }
 
 // EPI selects the epilogue: kEpiBf16 / kEpiF32 store block_out and block_lse; kEpiMerge folds
@@ -314,10 +339,10 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
 // row) pairs when that needs fewer workgroups: a decode step with grouped heads then reads every key
 // once instead of once per query head.  (2) The keys are cut into p.n_parts parts of p.part_keys
 // keys, each computed exactly as a launch over that part alone would; the block results go to a
-// scratch buffer in fp32 and fold_parts_kernel applies the Update of Sec. 3.1 to them in key order (a fixed
+// scratch buffer in fp32 and fold_parts_kernel adds them up in key order (a fixed
 // order: bitwise reproducible).  Bound: HBM for a decode step, MFMA otherwise, plus the fold.  Four decode steps
-// over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 156 us, 500 Query rows x 32 heads
-// behind 12000 keys 216 -> 105 us against the plain form.
+// over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 141 us, 500 Query rows x 32 heads
+// behind 12000 keys 216 -> 102 us against the plain form.
 //
 // FORM kChunks replays Algorithm 1 block by block: with block results that are rounded to bf16 on their way to the
 // Update, or (chunks shorter than a sub-tile, which no reference of the running softmax can be kept for) in fp32.
@@ -861,7 +886,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
       *reinterpret_cast<f32x4*>(my + ql * ROWB + ((c ^ (ql & 15)) << 4)) = o;
     }
   if constexpr (PART) {
-    part_epilogue<D, EPI>(p, lds, lane, wave, q0, b, hq, pb.group, pb.part, n_live, lse_blk);
+    part_epilogue<D, EPI>(p, lds, lane, wave, q0, b, hq, pb.group, pb.part, n_live, lse_blk, l_tot != l_tot);
     return;
   }
   if (EPI != kEpiMerge) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
