@@ -17,9 +17,9 @@
  *     layout can be passed through the strides.)
  *   - Attention calls whose grid would leave most of the GPU idle (few Query rows on many keys) cut the
  *     keys into parts; their partial results pass through device arrays inside the library (132 MiB,
- *     held by every GPU the library runs on until the process ends), one region for each of the
- *     first four streams of a GPU that make such a call.  Without a region - further streams, the per-thread
- *     default stream, graph capture - the call takes all keys at once in one launch, which is the same
+ *     held by every GPU the library runs on until the process ends): four regions a GPU, each in use by one
+ *     stream at a time and free for another once the work that used it is done.  Without a region - all four
+ *     busy on other streams, the per-thread default stream, graph capture - the call takes all keys at once in one launch, which is the same
  *     result up to rounding.  The ring entry points never cut.
  *   - `hip_stream` is a hipStream_t (NULL = the default stream).  Calls enqueue work on
  *     it and return without synchronising.

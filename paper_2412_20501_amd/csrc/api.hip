@@ -182,21 +182,31 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
   return best.parts > 1 || best.packs_uncut;
 }
 
-// Scratch of the partitioned launches: device arrays of the library itself (nothing is allocated), one
-// region per stream for up to kPartStreams streams of a device.  Launches on one stream run one after
-// the other, so a region is in use by one launch at a time; a region stays with its stream's
-// handle (hipStreamDestroy waits for the stream's work, measured with a 110 ms kernel, so the handle comes back idle).  No region: for a stream
-// beyond the first kPartStreams, for the per-thread default stream, whose handle stands for several, for
-// a stream of another device than the current one, and under capture, because a graph may be replayed
-// on any stream.
+// Scratch of the partitioned launches: device arrays of the library itself (nothing is allocated on the device), a pool
+// of kPartStreams regions per device.  Work on one stream runs in order, so a region is in use by one launch at a time if
+// every launch that takes it over waits for the one before: an event behind each use says when that one is done.  The
+// stream that used a region last waits for the event on the GPU (nothing to wait for while it lives, and in order
+// also where its handle has come back as another stream's); any other stream takes the region that has been idle
+// longest.  (The event rides on the fold's dispatch: recorded behind it, it costs 2.7 us a call.)  No region: while all are busy, for the per-thread default stream, whose handle stands for several, for a stream of
+// another device than the current one, and under capture, because a graph may be replayed on any stream.
 __device__ __align__(256) static unsigned char part_scratch[kPartStreams][kPartBytes];
-std::mutex g_part_lock;   // held from the choice of a region until the launches that use it are enqueued
+struct PartRegion {
+  char* bytes = nullptr;
+  hipStream_t owner = nullptr;
+  hipEvent_t done = nullptr;   // behind the last use
+  uint64_t used = 0;
+};
+struct PartPool {
+  std::mutex lock;             // held from the choice of a region until the launches that use it and its event are enqueued
+  PartRegion regions[kPartStreams];
+  int n = 0;                   // regions that have been used
+  uint64_t uses = 0;
+};
 
-// The region of a stream, or NULL.  Called with g_part_lock held.
-char* part_scratch_for(hipStream_t stream) {
+// The pool that serves launches on the stream, or NULL.
+PartPool* part_pool_for(hipStream_t stream) {
   constexpr int kDevices = 64;
-  struct Device { char* bytes = nullptr; int n = 0; hipStream_t owner[kPartStreams]; };
-  static Device devices[kDevices];
+  static PartPool pools[kDevices];
   if (stream == hipStreamPerThread || stream == (hipStream_t)1) return nullptr;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
@@ -206,23 +216,46 @@ char* part_scratch_for(hipStream_t stream) {
   if (capture != hipStreamCaptureStatusNone) return nullptr;
   int dev = -1, stream_dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return nullptr;
-  if (stream != nullptr && (hipStreamGetDevice(stream, &stream_dev) != hipSuccess || stream_dev != dev)) return nullptr;
-  Device& d = devices[dev];
-  if (!d.bytes) {
-    void* a = nullptr;
-    if (hipGetSymbolAddress(&a, HIP_SYMBOL(part_scratch)) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
+  if (stream != nullptr && (hipStreamGetDevice(stream, &stream_dev) != hipSuccess || stream_dev != dev)) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return &pools[dev];
+}
+
+// A region for the stream, or NULL.  Called with the pool's lock held and its device current.
+PartRegion* take_region(PartPool& pool, hipStream_t stream) {
+  // A query may disturb another stream's capture in global mode; this one is harmless to it.
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  PartRegion* r = nullptr;
+  for (int i = 0; i < pool.n; i++)
+    if (pool.regions[i].owner == stream) r = &pool.regions[i];
+  if (r) {
+    if (hipStreamWaitEvent(stream, r->done, 0) != hipSuccess) r = nullptr;
+  } else if (pool.n < kPartStreams) {
+    PartRegion& fresh = pool.regions[pool.n];
+    void* bytes = nullptr;
+    if (hipGetSymbolAddress(&bytes, HIP_SYMBOL(part_scratch)) == hipSuccess &&
+        hipEventCreateWithFlags(&fresh.done, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess) {
+      fresh.bytes = (char*)bytes + (size_t)pool.n * kPartBytes;
+      r = &fresh;
+      pool.n++;
     }
-    d.bytes = (char*)a;
+  } else {
+    for (PartRegion& c : pool.regions)
+      if ((!r || c.used < r->used) && hipEventQuery(c.done) == hipSuccess) r = &c;
   }
-  int i = 0;
-  while (i < d.n && d.owner[i] != stream) i++;
-  if (i == d.n) {
-    if (d.n == kPartStreams) return nullptr;
-    d.owner[d.n++] = stream;
+  (void)hipGetLastError();   // "not ready" and the like are no errors of this call
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (r) {
+    r->owner = stream;
+    r->used = ++pool.uses;
   }
-  return d.bytes + (size_t)i * kPartBytes;
+  return r;
 }
 
 hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int D, int epilogue, hipStream_t stream) {
@@ -233,13 +266,17 @@ hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int
   p.part_rows = plan.part_rows;
   p.part_keys = (int)plan.part_keys;
   if (plan.parts > 1) {
-    std::lock_guard<std::mutex> hold(g_part_lock);   // another thread on this stream must not enqueue between attention and fold
-    if (char* scratch = part_scratch_for(stream)) {
-      p.n_parts = plan.parts;
-      p.units = p.B * p.Hkv * p.n_parts;
-      p.part_out = (float*)scratch;
-      p.part_lse = p.part_out + plan.out_elems;
-      return tr::launch_block_attn(p, D, epilogue, stream);
+    if (PartPool* pool = part_pool_for(stream)) {
+      std::lock_guard<std::mutex> hold(pool->lock);   // another thread on this stream must not enqueue between attention and fold
+      if (PartRegion* r = take_region(*pool, stream)) {
+        p.n_parts = plan.parts;
+        p.units = p.B * p.Hkv * p.n_parts;
+        p.part_out = (float*)r->bytes;
+        p.part_lse = p.part_out + plan.out_elems;
+        const hipError_t e = tr::launch_block_attn(p, D, epilogue, stream, r->done);
+        if (e != hipSuccess) (void)hipEventRecord(r->done, stream);   // the fold did not go out, the attention may have
+        return e;
+      }
     }
   }
   // All keys at once, in one launch.  (The parts one after the other, folded in the output, give the bits of the cut

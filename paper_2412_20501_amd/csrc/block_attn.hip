@@ -1028,24 +1028,25 @@ hipError_t launch_typed(const AttnParams& p, int D, int epilogue, dim3 grid, hip
 }
 
 template <int D, int EPI>
-hipError_t launch_fold_typed(const AttnParams& p, dim3 grid, hipStream_t stream) {
-  if (p.n_parts <= 4) return launch_kernel(fold_parts_kernel<D, EPI, 4>, grid, dim3(kFoldThreads), 0, stream, p);
-  if (p.n_parts <= 8) return launch_kernel(fold_parts_kernel<D, EPI, 8>, grid, dim3(kFoldThreads), 0, stream, p);
-  return launch_kernel(fold_parts_kernel<D, EPI, kMaxParts>, grid, dim3(kFoldThreads), 0, stream, p);
+hipError_t launch_fold_typed(const AttnParams& p, dim3 grid, hipStream_t stream, hipEvent_t done) {
+  if (p.n_parts <= 4) hipExtLaunchKernelGGL((fold_parts_kernel<D, EPI, 4>), grid, dim3(kFoldThreads), 0, stream, nullptr, done, 0, p);
+  else if (p.n_parts <= 8) hipExtLaunchKernelGGL((fold_parts_kernel<D, EPI, 8>), grid, dim3(kFoldThreads), 0, stream, nullptr, done, 0, p);
+  else hipExtLaunchKernelGGL((fold_parts_kernel<D, EPI, kMaxParts>), grid, dim3(kFoldThreads), 0, stream, nullptr, done, 0, p);
+  return hipGetLastError();
 }
 template <int D>
-hipError_t launch_fold(const AttnParams& p, int epilogue, hipStream_t stream) {
+hipError_t launch_fold(const AttnParams& p, int epilogue, hipStream_t stream, hipEvent_t done) {
   constexpr int rows = kFoldThreads / (D / 4);   // rows one block folds
   const int tile_rows = p.part_rows < kBM ? p.part_rows : kBM;
   const dim3 grid((unsigned)(p.B * p.Hkv * p.members), (unsigned)((tile_rows + rows - 1) / rows));
-  if (epilogue == kEpiBf16) return launch_fold_typed<D, kEpiBf16>(p, grid, stream);
-  if (epilogue == kEpiF32) return launch_fold_typed<D, kEpiF32>(p, grid, stream);
-  return launch_fold_typed<D, kEpiMerge>(p, grid, stream);
+  if (epilogue == kEpiBf16) return launch_fold_typed<D, kEpiBf16>(p, grid, stream, done);
+  if (epilogue == kEpiF32) return launch_fold_typed<D, kEpiF32>(p, grid, stream, done);
+  return launch_fold_typed<D, kEpiMerge>(p, grid, stream, done);
 }
 
 }  // namespace
 
-hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream) {
+hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream, hipEvent_t fold_done) {
   const int64_t nbh = (int64_t)p.B * p.Hq;
   if (nbh * p.n_qtiles == 0) return hipSuccess;
   if (p.n_qtiles > 65535) return hipErrorInvalidValue;   // grid y limit
@@ -1055,7 +1056,7 @@ hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream
     if ((int64_t)p.units * p.members == 0) return hipSuccess;
     const hipError_t e = launch_typed<kPart>(p, D, epilogue, dim3((unsigned)(((int64_t)p.units * p.members + 7) / 8 * 8)), stream);
     if (e != hipSuccess || p.n_parts == 1) return e;
-    return D == 128 ? launch_fold<128>(p, epilogue, stream) : launch_fold<64>(p, epilogue, stream);
+    return D == 128 ? launch_fold<128>(p, epilogue, stream, fold_done) : launch_fold<64>(p, epilogue, stream, fold_done);
   }
   if (p.n_chunks > 0) {
     grid = dim3((unsigned)nbh, (unsigned)((p.chunk_end - p.chunk_begin) * p.n_qtiles));

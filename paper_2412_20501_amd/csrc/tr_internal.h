@@ -80,7 +80,8 @@ struct MergeNParams {
 
 // Launchers (defined next to their kernels). They only enqueue; errors come back as hipError_t.
 // epilogue: 0 = bf16 block_out, 1 = fp32 block_out, 2 = merge into the fp32 accumulators p.out / p.lse
-hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream);
+// fold_done: event that a launch in parts carries on its fold (may be NULL)
+hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream, hipEvent_t fold_done = nullptr);
 hipError_t launch_merge(const MergeParams& p, bool blk_bf16, hipStream_t stream);
 hipError_t launch_merge_n(const MergeNParams& p, bool blk_bf16, hipStream_t stream);
 int attn_rows_per_block();  // query rows one attention workgroup covers
