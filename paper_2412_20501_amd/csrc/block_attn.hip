@@ -693,8 +693,10 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
       float m_new = fmaxf(m_ref, tmax);
       // Renewed: down as well, while what the row has summed so far stays below 2^40 in the new units (else weights of
       // this sub-tile do not count beside it).  Both halves of a row decide alike.
-      const float lowered = half_swap_max(l_run) * __builtin_amdgcn_exp2f((m_ref - tmax) * c2);
-      if (sum_cap < 0.f && tmax > -INFINITY && lowered <= 0x1p40f) m_new = tmax;
+      if (__any(sum_cap < 0.f && m_ref > tmax)) {
+        const float lowered = half_swap_max(l_run) * __builtin_amdgcn_exp2f((m_ref - tmax) * c2);
+        if (sum_cap < 0.f && tmax > -INFINITY && lowered <= 0x1p40f) m_new = tmax;
+      }
       const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * c2);  // m_ref = -inf -> 0; equal -> 1
       const float a = (m_new == -INFINITY) ? 0.f : alpha;                 // (-inf) - (-inf) would be NaN
       l_run *= a;
@@ -765,7 +767,7 @@ __global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p
     constexpr unsigned k_imm = kt + 2 < NSUB ? su * TILE_BYTES + (kt + 2) * SUBB : sn * TILE_BYTES + (kt + 2 - NSUB) * SUBB;
     const int j = NSUB * u + kt;
     if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
-      if (!INNER && j * SUB >= renew_at) {
+      if (!INNER && __builtin_expect(j * SUB >= renew_at, 0)) {
         sum_cap = -1.f;
         renew_at += p.renew;
       }
