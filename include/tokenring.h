@@ -111,6 +111,14 @@ tr_status tr_block_attn_merge(const tr_tensor* q, const tr_tensor* k, const tr_t
                               const tr_tensor* out_acc, const tr_tensor* lse_acc, void* hip_stream);
 
 /*
+ * Host-only view of how a block step on these shapes is launched where a scratch region is there: returns the number of
+ * parts its keys are cut into (1: one pass), -1 on invalid arguments (tr_last_error() says why).  packed, if given, is set to 1
+ * if the rows of all query heads of a K/V head share row tiles, else 0.  causal and positions as in
+ * tr_block_attn_causal_at.  Touches no device.
+ */
+int tr_block_attn_plan(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int32_t* packed);
+
+/*
  * Out, Lse <- Update(block_out, block_lse), the two equations of Sec. 3.1, in place:
  *   out_acc <- out_acc - sigmoid(block_lse - lse_acc) * (out_acc - block_out)
  *   lse_acc <- lse_acc - ln(sigmoid(lse_acc - block_lse))

@@ -119,16 +119,18 @@ struct PartPlan {
 // result independent of the stream and of capture, whatever scratch is there.
 //
 // Heads are packed when that leaves at most four fifths of the row tiles: the rows that fill a tile up cost
-// their share of the loads and of the time of its slowest wave all the same.  (Where the plain form fits the
-// chip at once and the keys are too few to be cut, packing only idles compute units: 75 rows x 32 heads on
-// 75 keys 18.2 against 17.6 us.)
+// their share of the loads and of the time of its slowest wave all the same.  Without a cut they are packed only
+// where that takes fewer rounds of workgroups (one row x 32 heads on 8 K/V heads of 4096 keys, 32 sequences: 184 us
+// plain, 95 packed); as many rounds, or one, are better filled by the plain form (75 rows x 32 heads on 75 keys 17.6
+// plain, 18.2 packed; 538 rows x 128 heads on 16 K/V heads of 1070 keys at D 64 43.4 and 45.0).
 //
 // The keys are cut where an estimate of the call's time (us) says so, over rounds of one workgroup per compute
 // unit.  Measured: a tile of keys takes 0.7 (D 64, twice the keys: 1.0) while at most four waves of a workgroup
 // have rows, else 1.1 (1.6) on an idle chip and 1.75 (2.15) on a full one, where the clock gives way; a workgroup's set-up and epilogue 8; the fold 5,
 // 0.25 for each part in a row's chain, and its partials at 3.5 TB/s; nothing is faster than K and V at 5 TB/s.
 // Both sides of the line, us: 500 rows x 32 heads on 12500 keys 213 in one part, 106 in 4; 96 rows x 8
-// heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 1777 rows x 24
+// heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 100 rows x 256 heads on
+// 128 K/V heads of 2048 keys 40 uncut and 48 in 2; 1777 rows x 24
 // heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 88 and 38 in 6.
 bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
   const int bm = tr::attn_rows_per_block();
@@ -141,7 +143,8 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
   c.members = (int)(c.pack ? packed : plain);
   const int64_t space = c.pack ? rows : p.Sq, tiles = kv * c.members;
   c.part_rows = space > bm ? bm : (int)((space + 31) / 32 * 32);
-  c.packs_uncut = c.pack && kv * plain > kCUs;
+  auto rounds = [](int64_t workgroups) { return (workgroups + kCUs - 1) / kCUs; };
+  c.packs_uncut = c.pack && (tiles > 2 * kCUs || rounds(tiles) < rounds(kv * plain));
   best = c;
   if (tiles * tr::kMaxParts >= ((int64_t)1 << 30)) return false;
   if (tiles > 2 * kCUs || !may_cut) return c.packs_uncut;
@@ -167,7 +170,12 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     if (n > kCUs) t = p.causal ? (keys / tile_keys * tile + n * fix) / kCUs + 0.5 * longest : (double)(((int64_t)n + kCUs - 1) / kCUs) * longest;
     return std::max(t, stream + fix);
   };
-  double t_best = 0.95 * estimate(std::max<int64_t>(all, 1));
+  double uncut = estimate(std::max<int64_t>(all, 1));
+  if (c.pack && !c.packs_uncut) {   // a call that is not cut runs the plain form then
+    const double tile = p.Sq <= 128 ? few : idle + busy * std::min(1.0, (double)(kv * plain) / kCUs);
+    uncut = std::max((double)rounds(kv * plain) * ((double)all / tile_keys * tile + fix), stream + fix);
+  }
+  double t_best = 0.95 * uncut;
   for (int n = 2; n <= tr::kMaxParts; n++) {
     const int64_t part_keys = std::max<int64_t>(512, ((all + n - 1) / n + kPartAlign - 1) / kPartAlign * kPartAlign);
     const int64_t parts = (all + part_keys - 1) / part_keys, slot_rows = tiles * parts * c.part_rows;
@@ -289,6 +297,17 @@ hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int
   return tr::launch_block_attn(p, D, epilogue, stream);
 }
 
+// The part of a launch's parameters that plan_parts looks at.
+void set_shape(tr::AttnParams& p, const tr_tensor* q, const tr_tensor* k, int causal, int64_t off64) {
+  p.B = (int)q->B; p.Hq = (int)q->H; p.Hkv = (int)k->H; p.Sq = (int)q->S; p.Sk = (int)k->S;
+  p.causal = causal ? 1 : 0;
+  const int64_t lim = (int64_t)1 << 30;
+  p.causal_off = (int)(off64 > lim ? lim : (off64 < -lim ? -lim : off64));
+  const int bm = tr::attn_rows_per_block();
+  p.n_qtiles = (p.Sq + bm - 1) / bm;
+  p.gq = p.Hkv > 0 ? p.Hq / p.Hkv : 1;
+}
+
 // fuse_update: out/lse are fp32 accumulators and the block is merged into them by the kernel's epilogue.
 // n_chunks > 0: all Query chunks against all K/V chunks block by block, rounded to bf16 if chunk_bf16; the tensors are
 // views of chunk 0.  renew: keys after which a row's exponent reference is taken anew (0: never).  may_cut: the keys may
@@ -327,20 +346,14 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   p.v_sb = v->stride_b; p.v_sh = v->stride_h; p.v_ss = v->stride_s;
   p.o_sb = out->stride_b; p.o_sh = out->stride_h; p.o_ss = out->stride_s;
   p.l_sb = lse->stride_b; p.l_sh = lse->stride_h; p.l_ss = lse->stride_s;
-  p.B = (int)q->B; p.Hq = (int)q->H; p.Hkv = (int)k->H; p.Sq = (int)q->S; p.Sk = (int)k->S;
-  p.causal = causal ? 1 : 0;
-  const int64_t lim = (int64_t)1 << 30;
-  p.causal_off = (int)(off64 > lim ? lim : (off64 < -lim ? -lim : off64));
+  set_shape(p, q, k, causal, off64);
   p.scale = scale;
   p.renew = renew;
-  const int bm = tr::attn_rows_per_block();
-  p.n_qtiles = (p.Sq + bm - 1) / bm;
   p.xcd_map = (p.B * p.Hkv) % 8 == 0 && (int64_t)p.n_qtiles * p.B * p.Hq >= 8;
-  p.gq = p.Hkv > 0 ? p.Hq / p.Hkv : 1;
   p.gq_log2 = -1;
   for (int sh = 0; sh < 31; sh++)
     if (p.gq == (1 << sh)) p.gq_log2 = sh;
-  if (p.n_qtiles > 65535) return fail(TR_ERR_SHAPE, "Sq too long for one launch (at most 65535 query tiles of %d rows)", bm);
+  if (p.n_qtiles > 65535) return fail(TR_ERR_SHAPE, "Sq too long for one launch (at most 65535 query tiles of %d rows)", tr::attn_rows_per_block());
   if ((int64_t)p.n_qtiles * p.B * p.Hq >= ((int64_t)1 << 31)) return fail(TR_ERR_SHAPE, "too many workgroups for one launch");
   // Without the causal rule all query tiles cost the same, and an XCD may finish the
   // query tiles of one head before it starts the next: half as many heads' K/V are then live in
@@ -551,6 +564,22 @@ tr_status tr_block_attn_merge(const tr_tensor* q, const tr_tensor* k, const tr_t
   if (mask_kind == TR_MASK_CAUSAL_DIAG && q && k && q->S != k->S)
     return fail(TR_ERR_SHAPE, "the diagonal causal mask needs Sq == Sk (got %lld, %lld)", (long long)q->S, (long long)k->S);
   return attn_common(q, k, v, mask_kind == TR_MASK_CAUSAL_DIAG, 0, scale, out_acc, lse_acc, hip_stream, true);
+}
+
+int tr_block_attn_plan(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int32_t* packed) {
+  g_err[0] = 0;
+  if (check_tensor("q", q, true, false, 16) != TR_OK || check_tensor("k", k, true, false, 16) != TR_OK) return -1;
+  if ((q->D != 64 && q->D != 128) || k->D != q->D || k->B != q->B || (q->H > 0 && (k->H <= 0 || q->H % k->H))) {
+    fail(TR_ERR_SHAPE, "q and k do not fit together");
+    return -1;
+  }
+  tr::AttnParams p;
+  memset(&p, 0, sizeof(p));
+  set_shape(p, q, k, causal, q_pos0 - k_pos0);
+  PartPlan plan;
+  const bool planned = plan_parts(p, (int)q->D, true, plan);
+  if (packed) *packed = planned ? plan.pack : 0;
+  return planned ? plan.parts : 1;
 }
 
 tr_status tr_merge(const tr_tensor* out_acc, const tr_tensor* lse_acc, const tr_tensor* block_out, const tr_tensor* block_lse,

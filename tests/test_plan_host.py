@@ -1,0 +1,44 @@
+"""Which form an attention call takes (tr_block_attn_plan: host only, nothing is launched): parts of the keys, packed heads."""
+import ctypes
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def tr():
+    from paper_2412_20501_amd.build import ensure_built
+    ensure_built()
+    import paper_2412_20501_amd as m
+    return m
+
+
+def plan(tr, B, Hq, Hkv, Sq, Sk, D, offset=None):
+    """(parts, packed) of a call; offset of the causal rule, None: no mask."""
+    def t(H, S, ptr):
+        return tr.TrTensor(ptr, tr.TR_BF16, B, H, S, D, H * S * D, S * D, D)
+    packed = ctypes.c_int32(-1)
+    off = offset or 0
+    parts = tr.raw_lib().tr_block_attn_plan(ctypes.byref(t(Hq, Sq, 0x7F0000000000)), ctypes.byref(t(Hkv, Sk, 0x7F8000000000)),
+                                            int(offset is not None), max(off, 0), max(-off, 0), ctypes.byref(packed))
+    return parts, packed.value
+
+
+def test_calls_that_are_not_cut_are_packed_only_for_fewer_rounds(tr):
+    assert plan(tr, 8, 32, 16, 100, 2048, 128) == (1, 0)      # 256 plain workgroups are one round: 40 us, 48 in two parts
+    assert plan(tr, 16, 16, 2, 53, 1618, 128) == (1, 0)
+    assert plan(tr, 4, 24, 8, 87, 1823, 128) == (1, 0)
+    assert plan(tr, 2, 64, 8, 538, 1070, 64) == (1, 0)        # 384 plain, 272 packed: two rounds either way
+    assert plan(tr, 32, 32, 8, 1, 4096, 128) == (1, 1)        # 1024 plain, 256 packed
+    assert plan(tr, 64, 32, 8, 1, 2048, 128) == (1, 1)
+
+
+def test_few_rows_on_many_keys_are_cut(tr):
+    assert plan(tr, 4, 32, 8, 1, 8192, 128) == (4, 1)
+    assert plan(tr, 1, 32, 8, 500, 12500, 128, 12000) == (4, 0)
+    assert plan(tr, 1, 8, 1, 1, 256, 128) == (1, 0)
+    assert plan(tr, 1, 32, 32, 4096, 4096, 128) == (1, 0)
+
+
+def test_invalid_arguments(tr):
+    assert plan(tr, 1, 3, 2, 8, 8, 64)[0] == -1 and plan(tr, 1, 2, 2, 8, 8, 96)[0] == -1
+    assert tr.raw_lib().tr_block_attn_plan(None, None, 0, 0, 0, None) == -1
