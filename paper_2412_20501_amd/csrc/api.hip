@@ -146,7 +146,7 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
   auto rounds = [](int64_t workgroups) { return (workgroups + kCUs - 1) / kCUs; };
   c.packs_uncut = c.pack && (tiles > 2 * kCUs || rounds(tiles) < rounds(kv * plain));
   best = c;
-  if (tiles * tr::kMaxParts >= ((int64_t)1 << 30)) return false;
+  if (tiles >= ((int64_t)1 << 23) - 8) return false;   // a one-dimensional grid holds less than 2^32 threads, 512 a tile
   if (tiles > 2 * kCUs || !may_cut) return c.packs_uncut;
   // keys that some row of row tile t sees
   auto seen = [&](int t) -> int64_t {

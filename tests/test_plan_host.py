@@ -39,6 +39,12 @@ def test_few_rows_on_many_keys_are_cut(tr):
     assert plan(tr, 1, 32, 32, 4096, 4096, 128) == (1, 0)
 
 
+def test_a_packed_grid_stays_within_the_dispatch_limit(tr):
+    """2^32 threads in one dimension: the plain form's second grid dimension holds what a packed launch would not."""
+    assert plan(tr, 2_700_000, 2, 1, 257, 8, 64) == (1, 1)
+    assert plan(tr, 2_800_000, 2, 1, 257, 8, 64) == (1, 0)
+
+
 def test_invalid_arguments(tr):
     assert plan(tr, 1, 3, 2, 8, 8, 64)[0] == -1 and plan(tr, 1, 2, 2, 8, 8, 96)[0] == -1
     assert tr.raw_lib().tr_block_attn_plan(None, None, 0, 0, 0, None) == -1
