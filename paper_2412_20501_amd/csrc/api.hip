@@ -491,14 +491,15 @@ std::vector<LaunchGroup> group_steps(const std::vector<RingStep>& steps, int n_s
 // (16 segments of 16 keys: 1.03e-3 by blocks, 1.17e-3 renewed at every sub-tile, 1.61e-3 with one reference).
 tr_status attn_whole(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int n_seg, bool causal, float scale,
                      const tr_tensor* out, const tr_tensor* lse, void* stream) {
-  const int64_t seg = q->S / n_seg;
+  const int64_t seg = q->S / n_seg, bm = tr::attn_rows_per_block();
+  if (seg > 65535 * bm) return fail(TR_ERR_SHAPE, "segments of %lld rows are too long (at most 65535 query tiles of %d rows)", (long long)seg, (int)bm);
   if (n_seg > 1 && seg < 32) {
     const tr_tensor q0 = rows_view(q, 0, seg), k0 = rows_view(k, 0, seg), v0 = rows_view(v, 0, seg);
     const tr_tensor o0 = rows_view(out, 0, seg), l0 = rows_view(lse, 0, seg);
     return attn_common(&q0, &k0, &v0, causal, 0, scale, &o0, &l0, stream, true, n_seg);
   }
   const int renew = n_seg > 1 ? (int)(seg / 32 * 32) : 0;
-  const int64_t slab = (int64_t)65535 * tr::attn_rows_per_block();
+  const int64_t slab = 65535 * bm;
   int64_t r0 = 0;
   do {
     const int64_t rows = std::min(slab, q->S - r0);

@@ -143,6 +143,19 @@ def test_merge_n_and_sched_reject_bad_arguments(tr):
     assert sched(oo=_t(tr, tr.TR_BF16, 1, 4, 4096, 128, ptr=0x7F3000000000))[0] == 2
 
 
+def test_rings_refuse_segments_of_more_tiles_than_a_grid_holds(tr):
+    lib = tr.raw_lib()
+    B = ctypes.byref
+    S = 2 * 65536 * 256
+    q, k, v = (_t(tr, tr.TR_BF16, 1, 1, S, 64, ptr=0x100000000000 * i) for i in (1, 2, 3))
+    o, l = _t(tr, tr.TR_F32, 1, 1, S, 64, ptr=0x400000000000), _t(tr, tr.TR_F32, 1, 1, S, 1, ptr=0x500000000000)
+    for n in (1, 2):
+        st, msg = _status(tr, lib.tr_ring_attn, B(q), B(k), B(v), n, 0, B(o), B(l), 0.0, None, 0, None)
+        assert st == 3 and "65535 query tiles" in msg
+    for schedule, n in ((tr.TR_SCHED_TOKENRING, 2), (tr.TR_SCHED_ZIGZAG, 1), (tr.TR_SCHED_HYBRID, 2)):
+        assert lib.tr_ring_attn_sched(B(q), B(k), B(v), n, 1, schedule, 1, B(o), B(l), 0.0, None) == 3
+
+
 def test_written_tensors_must_not_overlap_themselves(tr):
     """A zero or too small stride on a written tensor would let two waves update one element."""
     lib = tr.raw_lib()
