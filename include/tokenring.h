@@ -11,16 +11,17 @@
  *
  * Conventions common to every call
  *   - All tensor pointers are DEVICE pointers owned by the caller.  The library never
- *     allocates, frees or keeps device memory between calls.
+ *     allocates or frees device memory and keeps no pointer between calls; it holds static device
+ *     arrays of its own (132 MiB on every GPU it runs on, until the process ends).
  *   - Layout is [B, H, S, D] with D contiguous; strides are in elements.  lse tensors
  *     are [B, H, S] and use D = 1, stride_s = 1 normally.  (The paper's (N,H,D)/(H,N)
  *     layout can be passed through the strides.)
- *   - Attention calls whose grid would leave most of the GPU idle (few Query rows on many keys) cut the
- *     keys into parts; their partial results pass through device arrays inside the library (132 MiB,
- *     held by every GPU the library runs on until the process ends): four regions a GPU, each in use by one
- *     stream at a time and free for another once the work that used it is done.  Without a region - all four
- *     busy on other streams, the per-thread default stream, graph capture - the call takes all keys at once in one launch, which is the same
- *     result up to rounding.  The ring entry points never cut.
+ *   - Block steps whose grid would leave most of the GPU idle (few Query rows on many keys) cut the
+ *     keys into parts (tr_block_attn_plan).  The partial results pass through the library's arrays: four
+ *     regions a GPU, each in use by one stream at a time and free for another once the work that used
+ *     it is done.  Without a region - all four busy on other streams, the per-thread default stream,
+ *     graph capture - the call takes all keys at once in one launch, which is the same result up to
+ *     rounding.  The ring entry points never cut: theirs is the same bits on every route.
  *   - `hip_stream` is a hipStream_t (NULL = the default stream).  Calls enqueue work on
  *     it and return without synchronising.
  *   - A tensor a call writes (out, lse, out_acc, lse_acc) must not overlap itself: a stride of 0
@@ -161,7 +162,8 @@ tr_status tr_merge_n(const tr_tensor* out, const tr_tensor* lse,
  *   One GPU holds every K/V chunk, and the Update is associative and commutative: the blocks a
  *   Query row meets are folded in registers by the softmax that runs over all its keys, so the
  *   whole schedule is one attention kernel (one launch per 65535 * 256 Query rows) and no block result
- *   reaches memory.  The result is that of the steps one by one up to fp32 rounding.
+ *   reaches memory; chunks shorter than 32 keys are attended block by block in that launch.  The result
+ *   is that of the steps one by one up to rounding, and as close to the exact one.
  *   workspace == NULL: workspace_bytes is ignored.  workspace != NULL: checked - at least
  *   tr_ring_attn_workspace_bytes(q, n_chunks) bytes, 256-byte aligned, apart from the tensors - and
  *   left alone; the result is bitwise the same.
@@ -196,14 +198,15 @@ size_t tr_ring_attn_blocks_workspace_bytes(const tr_tensor* q, int n_chunks, int
  * frees nothing on the device and calls no allocating library routine.  Limit: one block result,
  *   align256(B * Hq * (S / n_chunks) * D * 4) + align256(B * Hq * (S / n_chunks) * 4) bytes,
  * must not exceed TR_NOALLOC_SCRATCH_BYTES; larger problems return TR_ERR_WORKSPACE (use
- * tr_ring_attn).  Arguments, checks, arithmetic and results are those of tr_ring_attn (bitwise).
+ * tr_ring_attn).  The limit belongs to the interface; no such array is held.  Arguments, checks,
+ * arithmetic and results are those of tr_ring_attn (bitwise).
  */
 #define TR_NOALLOC_SCRATCH_BYTES (8 * 1024 * 1024 + 64 * 1024)
 tr_status tr_ring_attn_noalloc(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v,
                                int n_chunks, int causal,
                                const tr_tensor* out, const tr_tensor* lse, float scale, void* hip_stream);
 
-/* Order in which tr_ring_attn_sched runs the block steps (all "devices" replayed on one GPU). */
+/* How a schedule divides the block steps among devices; on one GPU every schedule is the same work. */
 typedef enum {
   TR_SCHED_TOKENRING = 0,      /* Algorithm 1: Q circulates, device j keeps K_j, V_j              */
   TR_SCHED_RING_ATTENTION = 1, /* Sec. 2.1: K/V circulate, device j keeps Q_j                     */
@@ -249,7 +252,7 @@ tr_status tr_ring_attn_sched(const tr_tensor* q, const tr_tensor* k, const tr_te
  */
 int64_t tr_schedule_steps(int schedule, int n_devices, int n_inner, int causal, int32_t* steps_out, int64_t capacity);
 
-/* Bytes of workspace the two-kernel form of tr_ring_attn needs for these shapes (0 on invalid arguments). */
+/* Bytes a workspace given to tr_ring_attn must have for these shapes (0 on invalid arguments). */
 size_t tr_ring_attn_workspace_bytes(const tr_tensor* q, int n_chunks);
 
 /*
@@ -258,7 +261,7 @@ size_t tr_ring_attn_workspace_bytes(const tr_tensor* q, int n_chunks);
  * from this thread carries them in its dispatch: start_event then holds the time the kernel
  * began executing and stop_event the time it finished, so hipEventElapsedTime(start, stop)
  * is the kernel's own duration without queueing gaps.  Only that one launch is timed
- * (tr_ring_attn: its first kernel); the events stay owned by the caller.  Always TR_OK.
+ * (tr_ring_attn: its first kernel; a block step whose keys are cut: its attention, not the fold); the events stay owned by the caller.  Always TR_OK.
  */
 tr_status tr_time_next_kernel(void* start_event, void* stop_event);
 

@@ -233,7 +233,7 @@ def tr_time_next_kernel(start_event, stop_event):
 
 
 def tr_ring_attn_sched(q, k, v, n_devices, causal, schedule, out, lse, scale=0.0, n_inner=1, stream=None):
-    """tr_ring_attn with a selectable step order (TR_SCHED_*); Update fused into the attention epilogue."""
+    """tr_ring_attn under a selectable schedule (TR_SCHED_*): the same result on one GPU (see tokenring.h)."""
     _check(_ring_attn_sched(_pack(q), _pack(k), _pack(v), int(n_devices), int(bool(causal)), int(schedule), int(n_inner),
                                    _pack(out), _pack(lse), float(scale), _stream(stream)))
 
@@ -243,14 +243,14 @@ def tr_ring_attn_blocks_workspace_bytes(q, n_chunks, block_dtype) -> int:
 
 
 def tr_ring_attn_blocks(q, k, v, n_chunks, causal, out, lse, block_dtype, workspace, scale=0.0, stream=None):
-    """Algorithm 1 as tr_block_attn + tr_merge per step, the block result stored as block_dtype (TR_F32 / TR_BF16)."""
+    """Algorithm 1 with the block result of every step as block_dtype (TR_F32 / TR_BF16) on its way to the Update (see tokenring.h)."""
     _check(_ring_attn_blocks(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
                                     float(scale), int(block_dtype), workspace.data_ptr(),
                                     workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
 def tr_schedule_steps(schedule, n_devices, causal, n_inner=1):
-    """The block steps of a schedule in execution order: a list of (q_segment, kv_segment, launch_index)."""
+    """The block steps of a schedule in the devices' order: a list of (q_segment, kv_segment, index of the group of concurrent steps)."""
     n = int(_lib.tr_schedule_steps(int(schedule), int(n_devices), int(n_inner), int(bool(causal)), None, 0))
     if n < 0:
         raise TokenRingError(-1, _lib.tr_last_error().decode())
@@ -266,9 +266,8 @@ def tr_ring_attn_workspace_bytes(q, n_chunks) -> int:
 def tr_ring_attn(q, k, v, n_chunks, causal, out, lse, scale=0.0, workspace=None, stream=None):
     """Algorithm 1's schedule on one GPU into fp32 `out`, `lse`.
 
-    `workspace` = None: the Update runs fused in the attention epilogue.  Otherwise a
-    caller-owned uint8 device tensor of at least tr_ring_attn_workspace_bytes(q, n_chunks)
-    bytes selects the two-kernel form (tr_block_attn into the workspace, then tr_merge).
+    `workspace`: None, or a caller-owned uint8 device tensor of at least
+    tr_ring_attn_workspace_bytes(q, n_chunks) bytes, which is checked and left alone.
     """
     ws_ptr, ws_bytes = None, 0
     if workspace is not None:
@@ -278,6 +277,6 @@ def tr_ring_attn(q, k, v, n_chunks, causal, out, lse, scale=0.0, workspace=None,
 
 
 def tr_ring_attn_noalloc(q, k, v, n_chunks, causal, out, lse, scale=0.0, stream=None):
-    """tr_ring_attn (two-kernel form) with the block workspace inside the library: nothing is allocated (see tokenring.h)."""
+    """tr_ring_attn with the promise that nothing is allocated, for problems up to a limit (see tokenring.h)."""
     _check(_ring_attn_noalloc(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
                                      float(scale), _stream(stream)))

@@ -1,5 +1,5 @@
-// C ABI of libtokenring: argument validation, descriptor -> kernel-parameter marshalling,
-// and the host loop that replays TokenRing's Algorithm 1 on one GPU.
+// C ABI of libtokenring: argument validation, descriptor -> kernel-parameter marshalling, the choice of a launch's
+// form, and the step lists of TokenRing's schedules (for tr_schedule_steps: on one GPU a schedule is one launch).
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -127,11 +127,11 @@ struct PartPlan {
 // The keys are cut where an estimate of the call's time (us) says so, over rounds of one workgroup per compute
 // unit.  Measured: a tile of keys takes 0.7 (D 64, twice the keys: 1.0) while at most four waves of a workgroup
 // have rows, else 1.1 (1.6) on an idle chip and 1.75 (2.15) on a full one, where the clock gives way; a workgroup's set-up and epilogue 8; the fold 5,
-// 0.25 for each part in a row's chain, and its partials at 3.5 TB/s; nothing is faster than K and V at 5 TB/s.
-// Both sides of the line, us: 500 rows x 32 heads on 12500 keys 213 in one part, 106 in 4; 96 rows x 8
+// 0.25 for each part of a row, and its partials at 3.5 TB/s; nothing is faster than K and V at 5 TB/s.
+// Both sides of the line, us: 500 rows x 32 heads on 12500 keys 217 in one part, 100 in 4; 96 rows x 8
 // heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 100 rows x 256 heads on
 // 128 K/V heads of 2048 keys 40 uncut and 48 in 2; 1777 rows x 24
-// heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 88 and 38 in 6.
+// heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 85 and 30 in 4.
 bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
   const int bm = tr::attn_rows_per_block();
   const int64_t rows = (int64_t)p.gq * p.Sq, kv = (int64_t)p.B * p.Hkv;
@@ -393,7 +393,7 @@ inline int pmod(int a, int n) { return ((a % n) + n) % n; }
 //     Query pair circulates as in Algorithm 1.
 //   Hybrid (Sec. 3.3.3): n = nodes * n_inner devices; K/V travel between nodes as in Ring
 //     Attention (outer step t), Algorithm 1 runs among the n_inner devices of each node.
-int build_schedule(int schedule, int n, int n_inner, bool causal, std::vector<RingStep>& steps, bool pair_kv = false) {
+int build_schedule(int schedule, int n, int n_inner, bool causal, std::vector<RingStep>& steps) {
   steps.clear();
   auto add = [&](int qs, int ks) {
     if (!causal || ks <= qs) steps.push_back({qs, ks});
@@ -410,10 +410,10 @@ int build_schedule(int schedule, int n, int n_inner, bool causal, std::vector<Ri
     case TR_SCHED_ZIGZAG:
       // Within an iteration the devices work concurrently, each on up to three segment pairs of
       // its own Query pair; they are emitted slot by slot (every device's first pair, then every
-      // device's second, ...) so that pairs on distinct Query segments are adjacent and can share
-      // a launch.  The order of the blocks each Query segment receives is unaffected.
-      // pair_kv: when a Query segment meets both K/V segments of the device (always its later
-      // segment), the two become one block step over the device's whole K/V; a device then has at
+      // device's second, ...) so that pairs on distinct Query segments are adjacent and belong to one
+      // group.  The order of the blocks each Query segment receives is unaffected.
+      // When a Query segment meets both K/V segments of the device (always its later
+      // segment), the two are one block step over the device's whole K/V; a device then has at
       // most two steps per iteration, on its two Query segments.
       for (int i = 0; i < n; i++) {
         for (int slot = 0; slot < 4; slot++) {
@@ -425,7 +425,7 @@ int build_schedule(int schedule, int n, int n_inner, bool causal, std::vector<Ri
             for (int a = 0; a < 2; a++)
               for (int b = 0; b < 2; b++) {
                 if (kseg[b] > qseg[a]) continue;
-                if (pair_kv && b == 1 && kept > 0 && dev[kept - 1].qs == qseg[a] && dev[kept - 1].ks2 < 0) dev[kept - 1].ks2 = kseg[b];
+                if (b == 1 && kept > 0 && dev[kept - 1].qs == qseg[a] && dev[kept - 1].ks2 < 0) dev[kept - 1].ks2 = kseg[b];
                 else dev[kept++] = {qseg[a], kseg[b]};
               }
             if (slot < kept) steps.push_back(dev[slot]);
@@ -446,17 +446,17 @@ int build_schedule(int schedule, int n, int n_inner, bool causal, std::vector<Ri
   }
 }
 
-// One group of independent steps: steps [begin, end) of the list; `merge` = the blocks are merged
-// into accumulators that already hold a result (otherwise they are each segment's first block).
+// One group of independent steps: steps [begin, end) of the list, all of them their Query segments' first blocks or
+// none of them.
 constexpr int kGroupMax = 32;
-struct LaunchGroup { size_t begin, end; bool merge; };
+struct StepGroup { size_t begin, end; };
 
 // Splits the step list into groups.  Consecutive steps that touch distinct Query segments and
 // are of one kind (first block of their segment, which is written, or a later block, which is
 // merged) are independent of each other - they are what different devices compute at the same
 // time (at most kGroupMax steps).
-std::vector<LaunchGroup> group_steps(const std::vector<RingStep>& steps, int n_seg) {
-  std::vector<LaunchGroup> groups;
+std::vector<StepGroup> group_steps(const std::vector<RingStep>& steps, int n_seg) {
+  std::vector<StepGroup> groups;
   std::vector<char> started((size_t)n_seg, 0);  // has this Query segment received its first block?
   std::vector<int> in_group((size_t)n_seg, -1); // index of the group that last used the segment
   size_t pos = 0;
@@ -470,7 +470,7 @@ std::vector<LaunchGroup> group_steps(const std::vector<RingStep>& steps, int n_s
       end++;
     }
     for (size_t i = pos; i < end; i++) started[(size_t)steps[i].qs] = 1;
-    groups.push_back({pos, end, merge});
+    groups.push_back({pos, end});
     pos = end;
   }
   return groups;
@@ -480,8 +480,8 @@ std::vector<LaunchGroup> group_steps(const std::vector<RingStep>& steps, int n_s
 // tensor, and the Update is associative and commutative: the running softmax over the whole visible key range
 // folds the blocks in registers, so out and lse are written once and no accumulator is read back.  Against one
 // launch per iteration with the Update in the epilogue (the form this replaces; same box, us before -> after):
-// S 256 in 4 chunks 29.5 -> 10.8, causal 8192 in 8 segments 615 -> 467, causal 32768 in 8 chunks 7603 -> 6959,
-// full 16384 at D 64 3555 -> 3160, GQA 131072 in 16 chunks 112.7 -> 108.0 ms: what goes are the set-up, the
+// S 256 in 4 chunks 29.8 -> 11.0, causal 8192 in 8 segments 620 -> 469, causal 32768 in 8 chunks 7603 -> 6965,
+// full 16384 at D 64 3555 -> 3201, GQA 131072 in 16 chunks 113.9 -> 109.2 ms: what goes are the set-up, the
 // epilogue and the idle tail of every launch but one.  Query rows beyond what a grid holds go out as further launches.
 // The keys are not cut (plan_parts): the result of a schedule is the same bits eagerly, in a graph and on any stream.
 //
@@ -691,8 +691,8 @@ size_t tr_ring_attn_workspace_bytes(const tr_tensor* q, int n_chunks) {
 
 namespace {
 
-// Algorithm 1 on one device.  block_dtype TR_F32: one pass over all keys.  TR_BF16: block by block, every
-// block result after a Query chunk's first rounded to bf16 before its Update.  A workspace is only checked.
+// Algorithm 1 on one device.  block_dtype TR_F32: attn_whole.  TR_BF16: block by block, every block result after a
+// Query chunk's first rounded to bf16 before its Update.  A workspace is only checked.
 tr_status ring_attn_impl(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int n_chunks, int causal,
                          const tr_tensor* out, const tr_tensor* lse, float scale, int block_dtype, void* workspace,
                          size_t workspace_bytes, void* hip_stream) {
@@ -759,7 +759,7 @@ tr_status tr_ring_attn_blocks(const tr_tensor* q, const tr_tensor* k, const tr_t
                               size_t workspace_bytes, void* hip_stream) {
   g_err[0] = 0;
   if (block_dtype != TR_F32 && block_dtype != TR_BF16) return fail(TR_ERR_DTYPE, "block_dtype %d is neither fp32 nor bf16", block_dtype);
-  if (!workspace) return fail(TR_ERR_WORKSPACE, "the two-kernel form needs a workspace");
+  if (!workspace) return fail(TR_ERR_WORKSPACE, "tr_ring_attn_blocks needs a workspace");
   return ring_attn_impl(q, k, v, n_chunks, causal, out, lse, scale, block_dtype, workspace, workspace_bytes, hip_stream);
 }
 
@@ -786,8 +786,8 @@ int64_t tr_schedule_steps(int schedule, int n_devices, int n_inner, int causal, 
     return -1;
   }
   std::vector<RingStep> steps;
-  const int n_seg = build_schedule(schedule, n_devices, n_inner, causal != 0, steps, true);
-  const std::vector<LaunchGroup> groups = group_steps(steps, n_seg);
+  const int n_seg = build_schedule(schedule, n_devices, n_inner, causal != 0, steps);
+  const std::vector<StepGroup> groups = group_steps(steps, n_seg);
   int64_t n_out = 0;   // a step on a pair of K/V segments is reported as its two segment pairs
   for (size_t g = 0; g < groups.size(); g++)
     for (size_t i = groups[g].begin; i < groups[g].end; i++)
