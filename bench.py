@@ -270,7 +270,8 @@ def bench_merge_only(tr, wl, steps, warmup):
             for _ in range(cfg.n_partials)]
     acc_o = torch.zeros(shape, dtype=torch.float32, device="cuda")
     acc_l = torch.full(shape[:3], float("-inf"), dtype=torch.float32, device="cuda")
-    per_call_bytes = 3 * (acc_o.numel() + acc_l.numel()) * 4
+    # block and accumulator read, accumulator written; the first of the eight does not read its empty accumulator
+    per_call_bytes = (3 * cfg.n_partials - 1) * (acc_o.numel() + acc_l.numel()) * 4 // cfg.n_partials
     for _ in range(warmup):
         tr.tr_merge(acc_o, acc_l, outs[0], lses[0])
     durations = []
@@ -299,9 +300,10 @@ def bench_merge_only(tr, wl, steps, warmup):
     return res
 
 
-def bench_ring(tr, wl, name, steps, warmup, fused, schedule=None, n_inner=1, block_dtype=None):
-    """tr_ring_attn over a whole sequence; fused: without a workspace, else with one (block_dtype bf16: blocks rounded one by one).
-    schedule: None = tr_ring_attn (Algorithm 1), else a TR_SCHED_* value run through tr_ring_attn_sched."""
+def bench_ring(tr, wl, name, steps, warmup, schedule=None, n_inner=1, form="ring"):
+    """A schedule over a whole sequence.  form "ring": tr_ring_attn, or with a TR_SCHED_* schedule tr_ring_attn_sched (one launch);
+    "bf16_blocks": tr_ring_attn_blocks, each block rounded to bf16 before its Update; "two_kernel": the caller's loop over the
+    schedule's steps, tr_block_attn into an fp32 block and tr_merge."""
     import torch
     cfg = wl.CONFIGS[name]
     g = torch.Generator(device="cuda").manual_seed(cfg.seed)
@@ -309,13 +311,30 @@ def bench_ring(tr, wl, name, steps, warmup, fused, schedule=None, n_inner=1, blo
     q, k, v = mk(cfg.Hq), mk(cfg.Hkv), mk(cfg.Hkv)
     out = torch.empty((cfg.B, cfg.Hq, cfg.S, cfg.D), dtype=torch.float32, device="cuda")
     lse = torch.empty((cfg.B, cfg.Hq, cfg.S), dtype=torch.float32, device="cuda")
-    ws = None if fused else torch.empty(tr.tr_ring_attn_workspace_bytes(q, cfg.n_chunks), dtype=torch.uint8, device="cuda")
+    ws = None
+    if form == "bf16_blocks":
+        ws = torch.empty(tr.tr_ring_attn_blocks_workspace_bytes(q, cfg.n_chunks, tr.TR_BF16), dtype=torch.uint8, device="cuda")
+    elif form == "two_kernel":
+        blk_o = torch.empty((cfg.B, cfg.Hq, cfg.chunk, cfg.D), dtype=torch.float32, device="cuda")
+        blk_l = torch.empty((cfg.B, cfg.Hq, cfg.chunk), dtype=torch.float32, device="cuda")
+        order = tr.tr_schedule_steps(tr.TR_SCHED_TOKENRING, cfg.n_chunks, cfg.causal)
+        part = lambda t, c: t[:, :, c * cfg.chunk:(c + 1) * cfg.chunk]
 
     def run():
-        if block_dtype is not None:     # a chosen transport format of block_out
-            tr.tr_ring_attn_blocks(q, k, v, cfg.n_chunks, cfg.causal, out, lse, block_dtype, ws, cfg.scale)
+        if form == "bf16_blocks":
+            tr.tr_ring_attn_blocks(q, k, v, cfg.n_chunks, cfg.causal, out, lse, tr.TR_BF16, ws, cfg.scale)
+        elif form == "two_kernel":
+            seen = set()
+            for c, j, _ in order:
+                first = c not in seen
+                seen.add(c)
+                o, l = (part(out, c), part(lse, c)) if first else (blk_o, blk_l)
+                mask = tr.TR_MASK_CAUSAL_DIAG if cfg.causal and j == c else tr.TR_MASK_NONE
+                tr.tr_block_attn(part(q, c), part(k, j), part(v, j), mask, cfg.scale, o, l)
+                if not first:
+                    tr.tr_merge(part(out, c), part(lse, c), blk_o, blk_l)
         elif schedule is None:
-            tr.tr_ring_attn(q, k, v, cfg.n_chunks, cfg.causal, out, lse, cfg.scale, ws)
+            tr.tr_ring_attn(q, k, v, cfg.n_chunks, cfg.causal, out, lse, cfg.scale)
         else:
             tr.tr_ring_attn_sched(q, k, v, cfg.n_chunks, cfg.causal, schedule, out, lse, cfg.scale, n_inner)
 
@@ -336,9 +355,10 @@ def bench_ring(tr, wl, name, steps, warmup, fused, schedule=None, n_inner=1, blo
     sched_name = {None: "Algorithm 1", 0: "Algorithm 1", 1: "Ring Attention order", 2: "zigzag partition",
                   3: f"hybrid, {n_inner} devices per node"}[schedule]
     return {"workload": f"{name}: S={cfg.S} as {n} segments, Hq={cfg.Hq}, Hkv={cfg.Hkv}, causal={cfg.causal}, {sched_name}",
-            "form": ("one launch, each Query tile block by block, blocks rounded to bf16" if block_dtype == tr.TR_BF16 else
-                     "one launch over the whole key range" + ("" if fused else ", workspace given")),
-            "block_steps": full_steps + diag_steps, "ms": ms, "tflops": flops / (ms * 1e-3) / 1e12,
+            "form": {"ring": "one launch over the whole key range",
+                     "bf16_blocks": "one launch, each Query tile block by block, blocks rounded to bf16",
+                     "two_kernel": "tr_block_attn (fp32 block) and tr_merge for every step of the schedule"}[form],
+            "steps_of_the_schedule": full_steps + diag_steps, "ms": ms, "tflops": flops / (ms * 1e-3) / 1e12,
             "frac_mfma_peak": flops / (ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS}
 
 
@@ -483,13 +503,13 @@ def main():
                                                      "cfg2 block step with scores rising 0.01 per key (+41 over the chunk)"),
             "merge_only": lambda: bench_merge_only(tr, wl, 3, 1),
             "ring_cfg1": lambda: bench_ring_small(tr, wl),
-            "ring_cfg3": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, fused=True),
-            "ring_cfg3_two_kernel": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, fused=False),
-            "ring_cfg3_two_kernel_bf16_blocks": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, fused=False, block_dtype=tr.TR_BF16),
-            "ring_cfg3_zigzag": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, fused=True, schedule=tr.TR_SCHED_ZIGZAG),
-            "ring_cfg3_hybrid_2x4": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, fused=True, schedule=tr.TR_SCHED_HYBRID, n_inner=4),
-            "ring_cfg5": lambda: bench_ring(tr, wl, "cfg5_gqa", 2, 1, fused=True),
-            "ring_dit": lambda: bench_ring(tr, wl, "dit_ring", ex_steps, 1, fused=True),
+            "ring_cfg3": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1),
+            "ring_cfg3_two_kernel": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, form="two_kernel"),
+            "ring_cfg3_bf16_blocks": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, form="bf16_blocks"),
+            "ring_cfg3_zigzag": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, schedule=tr.TR_SCHED_ZIGZAG),
+            "ring_cfg3_hybrid_2x4": lambda: bench_ring(tr, wl, "cfg3_ring", ex_steps, 1, schedule=tr.TR_SCHED_HYBRID, n_inner=4),
+            "ring_cfg5": lambda: bench_ring(tr, wl, "cfg5_gqa", 2, 1),
+            "ring_dit": lambda: bench_ring(tr, wl, "dit_ring", ex_steps, 1),
         }
         chosen = [n for n in args.extras.split(",") if n] or list(table)
         unknown = [n for n in chosen if n not in table]

@@ -770,7 +770,7 @@ tr_status tr_ring_attn_noalloc(const tr_tensor* q, const tr_tensor* k, const tr_
   const size_t need = tr_ring_attn_blocks_workspace_bytes(q, n_chunks, TR_F32);
   if (q && n_chunks >= 1 && q->S >= 0 && q->S % n_chunks == 0 && need > (size_t)TR_NOALLOC_SCRATCH_BYTES)
     return fail(TR_ERR_WORKSPACE, "tr_ring_attn_noalloc: one block result needs %zu bytes, the scratch limit is %zu "
-                "(B * Hq * (S / n_chunks) * (D + 1) * 4 bytes must fit); use tr_ring_attn with a workspace", need,
+                "(B * Hq * (S / n_chunks) * (D + 1) * 4 bytes must fit); use tr_ring_attn", need,
                 (size_t)TR_NOALLOC_SCRATCH_BYTES);
   if (!q || !k || !v || !out || !lse) return fail(TR_ERR_NULL, "a tensor descriptor is NULL");
   return ring_attn_impl(q, k, v, n_chunks, causal, out, lse, scale, TR_F32, nullptr, 0, hip_stream);

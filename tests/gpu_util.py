@@ -1,9 +1,22 @@
-"""Helpers shared by the GPU parity tests: host bits -> device tensors, oracle-side views."""
+"""Helpers shared by the GPU parity tests: host bits -> device tensors, oracle-side views; the plan of a block step."""
+import ctypes
+
 import numpy as np
 import torch
 
 import oracle
 import workloads as wl
+
+
+def attn_plan(lib, B, Hq, Hkv, Sq, Sk, D, offset=None):
+    """(parts of the keys, packed heads) of a block step on these shapes; offset of the causal rule, None: no mask.  Host only."""
+    def t(H, S, ptr):
+        return lib.TrTensor(ptr, lib.TR_BF16, B, H, S, D, H * S * D, S * D, D)
+    packed = ctypes.c_int32(-1)
+    off = offset or 0
+    parts = lib.raw_lib().tr_block_attn_plan(ctypes.byref(t(Hq, Sq, 0x7F0000000000)), ctypes.byref(t(Hkv, Sk, 0x7F8000000000)),
+                                             int(offset is not None), max(off, 0), max(-off, 0), ctypes.byref(packed))
+    return parts, packed.value
 
 
 def bits_to_dev(bits: np.ndarray) -> torch.Tensor:

@@ -109,7 +109,7 @@ def test_ring_attn_rejects_bad_arguments_and_workspace_size(tr):
     assert call(n=0)[0] == 3 and call(n=7)[0] == 3                                          # S % n_chunks
     assert call(o=_t(tr, tr.TR_BF16, 1, 32, 32768, 128, ptr=0x7F3000000000))[0] == 2         # out must be fp32
     assert call(k=_t(tr, tr.TR_BF16, 1, 32, 4096, 128, ptr=0x7F1000000000))[0] == 3
-    assert call(nb=need - 1)[0] == 7 and call(ws=ws + 16)[0] == 7 and call(nb=0)[0] == 7      # (ws = NULL selects the fused form)
+    assert call(nb=need - 1)[0] == 7 and call(ws=ws + 16)[0] == 7 and call(nb=0)[0] == 7      # (ws = NULL: no workspace to check)
     st, msg = call(ws=0x7F3000000000)
     assert st == 5 and "workspace" in msg
 

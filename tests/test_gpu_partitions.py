@@ -1,7 +1,7 @@
 """Attention on grids that leave the chip idle: keys cut into parts, grouped query heads packed into one row space.
 
 Sizes sit where the form can go wrong: row counts around a wave and a tile, a last part of one key, parts
-that no row of a tile sees, heads that share a wave.  Reference: the fp64 oracle, tolerances as for every
+that no row of a tile sees, heads that share a wave; the expected form stands beside each.  Reference: the fp64 oracle, tolerances as for every
 block step.  Without scratch (under graph capture, on a stream beyond those that have a region) the keys are one piece.
 """
 import numpy as np
@@ -9,23 +9,31 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import bits_to_dev, f64, max_abs, rand_bits, to_np
+from gpu_util import attn_plan, bits_to_dev, f64, max_abs, rand_bits, to_np
 
 pytestmark = pytest.mark.gpu
 OUT_TOL, LSE_TOL = 1e-2, 1e-3
 
-CASES = [
-    # B, Hq, Hkv, Sq, Sk, D, offset of the causal rule (None: no mask)
-    (1, 8, 1, 1, 4097, 128, None),        # decode: eight heads in one wave, last part of one key
-    (2, 6, 2, 11, 1500, 64, None),        # three heads, 33 rows: one row in the second wave
-    (1, 4, 1, 64, 3000, 128, None),       # 256 packed rows: exactly a tile
-    (1, 3, 1, 86, 2049, 64, None),        # 258 packed rows: two in the second tile
-    (1, 2, 2, 300, 8192, 128, None),      # no packing, two tiles, sixteen parts
-    (1, 4, 2, 40, 2600, 128, 2560),       # causal, packed heads that share waves
-    (1, 2, 2, 1030, 1030, 64, 0),         # diagonal: early tiles see one part only
-    (1, 2, 1, 20, 3000, 128, 1100),       # later parts that no row sees
-    (1, 2, 2, 600, 3000, 128, -300),      # rows without any key, and a tile with one part
-]
+FORMS = {
+    # B, Hq, Hkv, Sq, Sk, D, offset of the causal rule (None: no mask): parts of the keys, packed heads
+    (1, 8, 1, 1, 4097, 128, None): (9, 1),        # decode: eight heads in one wave, last part of one key
+    (2, 6, 2, 11, 1500, 64, None): (3, 1),        # three heads, 33 rows: one row in the second wave
+    (1, 4, 1, 64, 3000, 128, None): (6, 1),       # 256 packed rows: exactly a tile
+    (1, 3, 1, 86, 2049, 64, None): (5, 1),        # 258 packed rows: two in the second tile
+    (1, 2, 2, 300, 8192, 128, None): (16, 0),     # no packing, two tiles, sixteen parts
+    (1, 4, 2, 40, 2600, 128, 2560): (6, 1),       # causal, packed heads that share waves
+    (1, 4, 1, 300, 1100, 128, 744): (3, 1),       # causal, packed: a tile whose rows see two of three parts
+    (1, 8, 1, 600, 1600, 64, 1000): (4, 1),       # the same over several tiles of a head
+    (1, 2, 2, 2048, 2048, 64, 0): (4, 0),         # diagonal: early tiles see one part only
+    (1, 2, 1, 20, 4000, 128, 2100): (5, 1),       # later keys that no row sees
+    (1, 2, 2, 1600, 2500, 128, -300): (3, 0),     # rows without any key, and a tile with one part
+    (1, 2, 2, 2600, 2300, 64, -300): (5, 0),
+    (40, 8, 1, 1, 300, 64, None): (1, 1),         # one piece, packed for one round of workgroups instead of two
+    (30, 12, 4, 30, 500, 128, 480): (1, 1),       # the same, causal, three heads in 90 rows
+    (9, 32, 8, 300, 330, 64, 20): (1, 1),         # the same, a tile that ends one head and starts the next
+    (66, 32, 8, 2, 70, 64, None): (1, 1),         # more than two rounds of packed tiles
+}
+CASES = list(FORMS)
 
 
 def _inputs(case, seed):
@@ -48,6 +56,11 @@ def _reference(case, qb, kb, vb, scale):
     return oracle.attention_block(f64(qb), f64(kb), f64(vb), scale, causal_diag=True, q_offset=max(off, 0), k_offset=max(-off, 0))
 
 
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_the_cases_take_the_forms_they_stand_for(lib, case):
+    assert attn_plan(lib, *case) == FORMS[case]
+
+
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("case", CASES, ids=str)
 def test_parts_reach_the_oracle(lib, case, out_dtype):
@@ -65,9 +78,10 @@ def test_parts_reach_the_oracle(lib, case, out_dtype):
     assert max_abs(to_np(out), ref_o) <= OUT_TOL and max_abs(to_np(lse), ref_l) <= LSE_TOL
 
 
-@pytest.mark.parametrize("case", [c for c in CASES if c[6] is None], ids=str)
+@pytest.mark.parametrize("case", [c for c in CASES if c[6] is None or c[3] == c[4]], ids=str)
 def test_parts_merge_into_accumulators(lib, case):
-    B, Hq, Hkv, Sq, Sk, D, _ = case
+    B, Hq, Hkv, Sq, Sk, D, off = case
+    mask = lib.TR_MASK_NONE if off is None else lib.TR_MASK_CAUSAL_DIAG
     qb, kb, vb = _inputs(case, 330)
     rng = np.random.default_rng(333)
     acc_o = rng.standard_normal((B, Hq, Sq, D)).astype(np.float32)
@@ -77,9 +91,9 @@ def test_parts_merge_into_accumulators(lib, case):
     clean[:, 0, 0] = 0.0
     acc_o[:, 0, 0] = np.nan                                # an empty row may hold garbage
     d_o, d_l = torch.from_numpy(acc_o).cuda(), torch.from_numpy(acc_l).cuda()
-    lib.tr_block_attn_merge(bits_to_dev(qb), bits_to_dev(kb), bits_to_dev(vb), lib.TR_MASK_NONE, 0.1, d_o, d_l)
+    lib.tr_block_attn_merge(bits_to_dev(qb), bits_to_dev(kb), bits_to_dev(vb), mask, 0.1, d_o, d_l)
     torch.cuda.synchronize()
-    ref_o, ref_l = oracle.merge_pair(clean, acc_l, *oracle.attention_block(f64(qb), f64(kb), f64(vb), 0.1))
+    ref_o, ref_l = oracle.merge_pair(clean, acc_l, *_reference(case, qb, kb, vb, 0.1))
     assert max_abs(to_np(d_o), ref_o) <= OUT_TOL and max_abs(to_np(d_l), ref_l) <= LSE_TOL
 
 
@@ -88,7 +102,7 @@ def test_parts_merge_into_accumulators(lib, case):
 def test_without_scratch_the_result_is_the_same_up_to_rounding(lib, case, form):
     """More streams at a time than have a scratch region, and a captured call: one pass over all keys, to the oracle's
     tolerance; the replays of a graph agree bitwise."""
-    if form == "merge" and case[6] is not None:
+    if form == "merge" and case[6] is not None and case[3] != case[4]:
         pytest.skip("the merging step has no causal rule at arbitrary positions")
     B, Hq, Hkv, Sq, Sk, D, _ = case
     bits = _inputs(case, 360)
@@ -102,7 +116,8 @@ def test_without_scratch_the_result_is_the_same_up_to_rounding(lib, case, form):
 
     def run(out, lse, stream=None):
         if form == "merge":
-            lib.tr_block_attn_merge(q, k, v, lib.TR_MASK_NONE, 0.1, out, lse, stream)
+            mask = lib.TR_MASK_NONE if case[6] is None else lib.TR_MASK_CAUSAL_DIAG
+            lib.tr_block_attn_merge(q, k, v, mask, 0.1, out, lse, stream)
         else:
             _attend(lib, case, q, k, v, 0.1, out, lse, stream)
 

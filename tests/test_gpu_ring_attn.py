@@ -18,7 +18,7 @@ OUT_TOL, LSE_TOL = 1e-2, 1e-3
 
 
 def _ring(lib, q, k, v, n_chunks, causal, scale=0.0, poison=True, fused=True):
-    """fused=True: Update in the attention epilogue (no workspace); False: tr_block_attn + tr_merge."""
+    """fused=True: no workspace; False: with one, which is checked and changes nothing."""
     B, Hq, S, D = q.shape
     fill = float("nan") if poison else 0.0
     out = torch.full((B, Hq, S, D), fill, dtype=torch.float32, device="cuda")
@@ -62,8 +62,8 @@ def test_ring_n1_equals_single_block_step_bitwise(lib):
 
 
 def test_fused_and_two_kernel_forms_agree(lib):
-    """Same Update arithmetic in the same order: the fused epilogue and tr_block_attn + tr_merge
-    differ only in how the block reaches the Update (fp32 registers vs an fp32 workspace)."""
+    """With and without a workspace the ring is the same launch: the same bits.  (The steps spelled out by the caller,
+    tr_block_attn + tr_merge and tr_block_attn_merge, are compared with it in test_gpu_steps_one_by_one.py.)"""
     qb, kb, vb = rand_bits((1, 4, 1024, 128), 30), rand_bits((1, 2, 1024, 128), 31), rand_bits((1, 2, 1024, 128), 32)
     q, k, v = bits_to_dev(qb), bits_to_dev(kb), bits_to_dev(vb)
     a = _ring(lib, q, k, v, 4, True, fused=True)
@@ -136,6 +136,7 @@ def test_ring_config5_gqa_128k_16_chunks_sampled_rows(lib):
 
 
 def test_ring_blocks_fp32_is_the_two_kernel_form_bitwise(lib):
+    """fp32 blocks reach the Update unrounded, so tr_ring_attn_blocks with TR_F32 is tr_ring_attn, the same launch."""
     qb, kb, vb = rand_bits((1, 4, 768, 128), 50), rand_bits((1, 2, 768, 128), 51), rand_bits((1, 2, 768, 128), 52)
     q, k, v = bits_to_dev(qb), bits_to_dev(kb), bits_to_dev(vb)
     a = _ring(lib, q, k, v, 3, True, fused=False)
@@ -182,7 +183,7 @@ def test_ring_blocks_bf16_transport(lib, causal):
 
 
 def test_ring_config3_bf16_transport_sampled_rows(lib):
-    """cfg3 in the two-kernel form with bf16 block_out between Attention and Update (one bf16 rounding per merged block)."""
+    """cfg3 with bf16 block_out between Attention and Update (one bf16 rounding per merged block)."""
     cfg = wl.CONFIGS["cfg3_ring"]
     qb, kb, vb = wl.make_qkv_bits(cfg)
     q, k, v = bits_to_dev(qb), bits_to_dev(kb), bits_to_dev(vb)

@@ -65,7 +65,7 @@ def test_ring_schedule_captured_in_a_graph_replays_exactly(lib, fused):
 
 
 def test_zigzag_schedule_with_paired_segments_replays_from_a_graph(lib):
-    """The zigzag order on 128-key segments (block steps over a device's K/V pair, steps of a launch sorted by length)
+    """The zigzag order on 128-key segments
     captured once and replayed with eager work in between: every replay equals the eager result bitwise."""
     qb, kb, vb = rand_bits((1, 4, 1024, 128), 91), rand_bits((1, 2, 1024, 128), 92), rand_bits((1, 2, 1024, 128), 93)
     q, k, v = bits_to_dev(qb), bits_to_dev(kb), bits_to_dev(vb)

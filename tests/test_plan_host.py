@@ -1,7 +1,7 @@
 """Which form an attention call takes (tr_block_attn_plan: host only, nothing is launched): parts of the keys, packed heads."""
-import ctypes
-
 import pytest
+
+from gpu_util import attn_plan as plan
 
 
 @pytest.fixture(scope="module")
@@ -10,17 +10,6 @@ def tr():
     ensure_built()
     import paper_2412_20501_amd as m
     return m
-
-
-def plan(tr, B, Hq, Hkv, Sq, Sk, D, offset=None):
-    """(parts, packed) of a call; offset of the causal rule, None: no mask."""
-    def t(H, S, ptr):
-        return tr.TrTensor(ptr, tr.TR_BF16, B, H, S, D, H * S * D, S * D, D)
-    packed = ctypes.c_int32(-1)
-    off = offset or 0
-    parts = tr.raw_lib().tr_block_attn_plan(ctypes.byref(t(Hq, Sq, 0x7F0000000000)), ctypes.byref(t(Hkv, Sk, 0x7F8000000000)),
-                                            int(offset is not None), max(off, 0), max(-off, 0), ctypes.byref(packed))
-    return parts, packed.value
 
 
 def test_calls_that_are_not_cut_are_packed_only_for_fewer_rounds(tr):

@@ -1,6 +1,5 @@
-"""Host logic of the ring entry points, checked without a GPU: the step lists the library will run
-(tr_schedule_steps) against the oracle's enumerations of the same schedules, and the invariants of
-the grouping of steps into launches."""
+"""Host logic of the schedules, checked without a GPU: the step lists (tr_schedule_steps) against the oracle's
+enumerations of the same schedules, and the invariants of the grouping of concurrent steps."""
 import pytest
 
 import oracle

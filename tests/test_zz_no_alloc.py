@@ -1,7 +1,5 @@
-"""tr_ring_attn_noalloc (the two-kernel ring form with the block workspace inside the library)
-against tr_ring_attn with a caller workspace (bitwise: same kernels, same order) and against
-the fp64 oracle, on two calls in a row, the second with a smaller input: the library's
-scratch array keeps the first call's contents, which must not leak into the second."""
+"""tr_ring_attn_noalloc (tr_ring_attn for callers that must not allocate) against tr_ring_attn with a caller workspace
+(bitwise: the same launch) and against the fp64 oracle, on calls in a row of different sizes."""
 import numpy as np
 import pytest
 import torch
@@ -44,7 +42,7 @@ def test_noalloc_two_calls_second_smaller(lib):
 
 
 def test_noalloc_rejects_what_does_not_fit(lib):
-    # one block result of B1 H32 C4096 D128 is 64 MiB: far beyond the built-in scratch
+    # one block result of B1 H32 C4096 D128 is 64 MiB: far beyond the interface's limit
     q = torch.empty((1, 32, 8192, 128), dtype=torch.bfloat16, device="cuda")
     out = torch.empty((1, 32, 8192, 128), dtype=torch.float32, device="cuda"); lse = torch.empty((1, 32, 8192), dtype=torch.float32, device="cuda")
     with pytest.raises(lib.TokenRingError) as e:
