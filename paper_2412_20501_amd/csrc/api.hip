@@ -570,6 +570,10 @@ tr_status tr_block_attn_merge(const tr_tensor* q, const tr_tensor* k, const tr_t
 int tr_block_attn_plan(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int32_t* packed) {
   g_err[0] = 0;
   if (check_tensor("q", q, true, false, 16) != TR_OK || check_tensor("k", k, true, false, 16) != TR_OK) return -1;
+  if (q_pos0 < 0 || k_pos0 < 0) {
+    fail(TR_ERR_SHAPE, "chunk positions must be >= 0");
+    return -1;
+  }
   if ((q->D != 64 && q->D != 128) || k->D != q->D || k->B != q->B || (q->H > 0 && (k->H <= 0 || q->H % k->H))) {
     fail(TR_ERR_SHAPE, "q and k do not fit together");
     return -1;
@@ -770,7 +774,7 @@ tr_status tr_ring_attn_noalloc(const tr_tensor* q, const tr_tensor* k, const tr_
   const size_t need = tr_ring_attn_blocks_workspace_bytes(q, n_chunks, TR_F32);
   if (q && n_chunks >= 1 && q->S >= 0 && q->S % n_chunks == 0 && need > (size_t)TR_NOALLOC_SCRATCH_BYTES)
     return fail(TR_ERR_WORKSPACE, "tr_ring_attn_noalloc: one block result needs %zu bytes, the scratch limit is %zu "
-                "(B * Hq * (S / n_chunks) * (D + 1) * 4 bytes must fit); use tr_ring_attn", need,
+                "(B * Hq * (S / n_chunks) * (D + 1) * 4 bytes must fit); use tr_ring_attn (it needs no workspace)", need,
                 (size_t)TR_NOALLOC_SCRATCH_BYTES);
   if (!q || !k || !v || !out || !lse) return fail(TR_ERR_NULL, "a tensor descriptor is NULL");
   return ring_attn_impl(q, k, v, n_chunks, causal, out, lse, scale, TR_F32, nullptr, 0, hip_stream);

@@ -37,3 +37,5 @@ def test_a_packed_grid_stays_within_the_dispatch_limit(tr):
 def test_invalid_arguments(tr):
     assert plan(tr, 1, 3, 2, 8, 8, 64)[0] == -1 and plan(tr, 1, 2, 2, 8, 8, 96)[0] == -1
     assert tr.raw_lib().tr_block_attn_plan(None, None, 0, 0, 0, None) == -1
+    q = tr.TrTensor(0x7F0000000000, tr.TR_BF16, 1, 2, 8, 64, 1024, 512, 64)
+    assert tr.raw_lib().tr_block_attn_plan(q, q, 1, -1, 0, None) == -1 and "positions" in tr.raw_lib().tr_last_error().decode()
