@@ -126,12 +126,12 @@ struct PartPlan {
 //
 // The keys are cut where an estimate of the call's time (us) says so, over rounds of one workgroup per compute
 // unit.  Measured: a tile of keys takes 0.7 (D 64, twice the keys: 1.0) while at most four waves of a workgroup
-// have rows, else 1.1 (1.6) on an idle chip and 1.75 (2.15) on a full one, where the clock gives way; a workgroup's set-up and epilogue 8; the fold 5,
-// 0.25 for each part of a row, and its partials at 3.5 TB/s; nothing is faster than K and V at 5 TB/s.
+// have rows, else 1.1 (1.6) on an idle chip and 1.75 (2.15) on a full one, where the clock gives way; a workgroup's
+// set-up and epilogue 8; the fold 5, 0.25 for each part of a row, and its partials at 3.5 TB/s; nothing is faster than
+// K and V at 5 TB/s.
 // Both sides of the line, us: 500 rows x 32 heads on 12500 keys 217 in one part, 100 in 4; 96 rows x 8
 // heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 100 rows x 256 heads on
-// 128 K/V heads of 2048 keys 40 uncut and 48 in 2; 1777 rows x 24
-// heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 85 and 30 in 4.
+// 128 K/V heads of 2048 keys 40 uncut and 48 in 2; 1777 rows x 24 heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 85 and 30 in 4.
 bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
   const int bm = tr::attn_rows_per_block();
   const int64_t rows = (int64_t)p.gq * p.Sq, kv = (int64_t)p.B * p.Hkv;
@@ -195,8 +195,9 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
 // every launch that takes it over waits for the one before: an event behind each use says when that one is done.  The
 // stream that used a region last waits for the event on the GPU (nothing to wait for while it lives, and in order
 // also where its handle has come back as another stream's); any other stream takes the region that has been idle
-// longest.  (The event rides on the fold's dispatch: recorded behind it, it costs 2.7 us a call.)  No region: while all are busy, for the per-thread default stream, whose handle stands for several, for a stream of
-// another device than the current one, and under capture, because a graph may be replayed on any stream.
+// longest.  (The event rides on the fold's dispatch: recorded behind it, it costs 2.7 us a call.)  No region: while all
+// are busy, for the per-thread default stream, whose handle stands for several, for a stream of another device than the
+// current one, and under capture, because a graph may be replayed on any stream.
 __device__ __align__(256) static unsigned char part_scratch[kPartStreams][kPartBytes];
 struct PartRegion {
   char* bytes = nullptr;
