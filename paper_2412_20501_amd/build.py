@@ -12,16 +12,17 @@ import os
 import re
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(PKG_DIR, "libtokenring.so")
-SOURCES = ["api.hip", "block_attn.hip", "merge.hip"]
+SOURCES = ["api.hip", "merge.hip", "block_attn.hip"] + [f"block_attn_d{d}_{r}rows.hip" for d in (128, 64) for r in (256, 128, 64)]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed-fp32 VALU forms are kept out of the generated code on purpose
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
@@ -57,19 +58,29 @@ def build_library(verbose: bool = False) -> str:
     """Compile every kernel source into one shared library; returns its path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB_PATH + f".tmp{os.getpid()}"
-    cmd = [hipcc, *HIPCC_FLAGS, f'-DTR_SOURCE_HASH_STR="{source_hash()}"', "-I", INCLUDE, "-I", CSRC,
-           "-o", tmp, *[os.path.join(CSRC, s) for s in SOURCES]]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    noise = "is not a recognized feature for this target"
-    err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
-    if res.returncode != 0:
-        if os.path.exists(tmp):
-            os.remove(tmp)
-        raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
-    if verbose and err.strip():
-        print(err, file=sys.stderr)
+    objects = [f"{tmp}.{s}.o" for s in SOURCES]
+    compile_ = [hipcc, *HIPCC_FLAGS, f'-DTR_SOURCE_HASH_STR="{source_hash()}"', "-I", INCLUDE, "-I", CSRC, "-c"]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        noise = "is not a recognized feature for this target"
+        err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
+        if res.returncode != 0:
+            raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
+        if verbose and err.strip():
+            print(err, file=sys.stderr)
+
+    try:
+        with ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:   # one compiler per source
+            for done in [pool.submit(run, [*compile_, os.path.join(CSRC, s), "-o", o]) for s, o in zip(SOURCES, objects)]:
+                done.result()
+        run([hipcc, *HIPCC_FLAGS, "-shared", "-o", tmp, *objects])
+    finally:
+        for o in objects:
+            if os.path.exists(o):
+                os.remove(o)
     os.replace(tmp, LIB_PATH)      # atomic: a concurrent reader never sees a half-written library
     return LIB_PATH
 

@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <vector>
 
@@ -105,6 +106,7 @@ tr_tensor rows_view(const tr_tensor* t, int64_t r0, int64_t rows) {
 // ---- partitioned attention launches: which calls, how many parts, and where the partial results go.
 
 constexpr int kCUs = 256;
+constexpr int kMaxRows = 256;   // Query rows of the largest workgroup
 constexpr int kPartStreams = 4;
 constexpr int64_t kPartBytes = (int64_t)33 << 20;   // 256 workgroups' partials of 256 rows at D = 128
 constexpr int64_t kPartAlign = 128;   // parts begin on whole tiles of either head dim
@@ -133,7 +135,7 @@ struct PartPlan {
 // heads on 2048 keys 27.7 and 17.4 in 4; 8 rows x 16 heads on 700 keys 13.8 and 15.2 in 2; 100 rows x 256 heads on
 // 128 K/V heads of 2048 keys 40 uncut and 48 in 2; 1777 rows x 24 heads on as many 35 and 47 in 2; 4 sequences, 32 heads on 8 K/V heads of 8192 keys 85 and 30 in 4.
 bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
-  const int bm = tr::attn_rows_per_block();
+  const int bm = kMaxRows;
   const int64_t rows = (int64_t)p.gq * p.Sq, kv = (int64_t)p.B * p.Hkv;
   if (p.Sk == 0 || p.Sq == 0 || kv == 0 || rows > ((int64_t)1 << 24)) return false;
   const int64_t packed = (rows + bm - 1) / bm, plain = (int64_t)p.gq * p.n_qtiles;
@@ -267,21 +269,107 @@ PartRegion* take_region(PartPool& pool, hipStream_t stream) {
   return r;
 }
 
+// Query rows of a workgroup.  256 (eight row groups) is the best use of a full chip.  A launch that would leave compute
+// units idle runs workgroups of 128 or 64 rows whose waves also share the keys out among themselves: a tile
+// of keys then takes its workgroup about a half and a third of the time, and there are twice and four times as many workgroups.
+// Chosen by an estimate of the launch's time (us) from measured costs: set-up and epilogue of a workgroup, and a tile of keys
+// (64 at D 128, 128 at D 64) on an idle chip, on a full one, and with at most half of the waves at work.
+// Both sides of the line, us for 256 / 128 / 64 rows: 8 heads of 256 rows 12.5 / 10.9 / 8.6; 16 of 1024 27.7 / 21.8 / 18.1;
+// 8 of 4096 under the causal rule 76.8 / 52.4 / 47.9; 32 of 1024 29.6 / 25.2 / 30.4; 64 of 1024 40.1 / 48.7 / 58.7; one of 8192 at D 64 105 / 60 / 45;
+// 24 of 1777 at D 64 34.8 / 41.5 / 44.9, under the causal rule 30.9 / 22.6 / 29.2.
+// p holds the launch's parts and chunks; pack: the rows are those of a K/V head's whole group.
+int choose_rows(const tr::AttnParams& p, int D, bool pack) {
+  const int refs = p.renew > 0 ? (p.Sk - 1) / p.renew : 0;
+  const int64_t rows = pack ? (int64_t)p.gq * p.Sq : p.Sq, heads = (int64_t)p.B * (pack ? p.Hkv : p.Hq);
+  if (refs > tr::kMaxRefs || p.Sk == 0 || heads * ((rows + kMaxRows - 1) / kMaxRows) >= 4 * kCUs) return kMaxRows;
+  struct Shape { int rows; double fix, idle, busy, fix_few, few; };
+  static const Shape shapes[2][3] = {{{256, 7.5, 1.52, 2.15, 5.2, 1.0}, {128, 7.1, 0.83, 1.09, 6.0, 0.65}, {64, 5.8, 0.61, 0.72, 5.4, 0.6}},
+                                     {{256, 8.3, 1.1, 1.75, 6.2, 0.7}, {128, 9.0, 0.59, 0.93, 7.5, 0.5}, {64, 7.0, 0.47, 0.57, 6.5, 0.45}}};
+  const double tile_keys = D == 64 ? 128.0 : 64.0;
+  const int64_t part = p.n_parts > 1 ? p.part_keys : p.Sk;
+  const double later = p.n_chunks > 1 ? p.n_chunks - 1 : 0;   // blocks behind its first of the longest workgroup
+  int best = kMaxRows;
+  double t_best = 0;
+  for (const Shape& s : shapes[D == 128]) {
+    const int64_t tiles = (rows + s.rows - 1) / s.rows;
+    int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
+    if (p.causal && pack) {
+      least = most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, (int64_t)p.Sq + p.causal_off));
+      sum = most * tiles;
+    } else if (p.causal) {   // tile t sees the keys below (t + 1) * rows + causal_off
+      most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, rows + p.causal_off));
+      least = std::max<int64_t>(0, std::min<int64_t>(most, s.rows + (int64_t)p.causal_off));
+      const int64_t off = p.causal_off, all = std::min(tiles, std::max<int64_t>(0, (p.Sk - off + s.rows - 1) / s.rows - 1));
+      const int64_t none = std::min(all, off < 0 ? -off / s.rows : 0);   // tiles [none, all) see some, [all, tiles) every key
+      sum = (all * (all + 1) - none * (none + 1)) / 2 * s.rows + (all - none) * off + (tiles - all) * p.Sk;
+    }
+    const double blocks = p.causal ? later / 2 : later, chunks = later + 1;   // later blocks of the average workgroup
+    const double count = (double)(heads * tiles) * chunks;
+    double n = count, total = ((double)(heads * sum) + (double)(heads * tiles) * blocks * p.Sk) * chunks / tile_keys;
+    if (p.n_parts > 1) n *= std::max(1.0, p.causal ? (double)sum / (double)(tiles * part) + 0.5 : (double)p.n_parts);
+    const double longest = ((double)std::min(most, part) + later * p.Sk) / tile_keys;
+    const double shortest = p.n_parts > 1 ? 0.0 : (double)least / tile_keys;
+    const bool few = std::min<int64_t>(rows, s.rows) <= s.rows / 2;
+    const double fill = std::min(1.0, n / kCUs * std::min(1.0, total / (n * longest + 1e-9)));   // less than n / kCUs where some workgroups end early
+    const double tile = few ? s.few : s.idle + (s.busy - s.idle) * fill * fill;   // (a chip that is not full runs at a higher clock)
+    const double fix = (few ? s.fix_few : s.fix) + (s.rows < kMaxRows ? (0.7 + 0.6 * fill) * refs : 0.0);
+    double time = longest * tile + fix * (1 + 0.7 * later);
+    if (n > kCUs && !p.causal) time *= std::ceil(n / kCUs);
+    if (n > kCUs && p.causal)   // every round has its shortest workgroup's time, what is left evens out
+      time = std::max(time, (std::ceil(n / kCUs) * shortest + (total - n * shortest) / kCUs + 0.15 * (longest - shortest)) * tile +
+                                n * fix * (1 + 0.7 * blocks) / kCUs);
+    // (The causal parts of a launch are not dealt out longest first, so that a second round costs more than its share:
+    // 12 heads of 2306 rows on 2665 keys in 2 parts 43 us with 256 rows, 49 with 128.)
+    if (s.rows < kMaxRows && p.n_parts > 1 && p.causal && n > kCUs) continue;
+    if (s.rows == kMaxRows) {
+      t_best = time * (n > kCUs ? 0.9 : 0.97);   // a last round that is nearly empty runs faster than a full one
+    } else if (time * (n > kCUs ? 1.05 : 1.0) < t_best) {
+      t_best = time * (n > kCUs ? 1.05 : 1.0);
+      best = s.rows;
+    }
+  }
+  return best;
+}
+
+// Workgroups of bm rows each for a launch over (head, query tile) pairs; how they are placed on the XCDs.
+void set_rows(tr::AttnParams& p, int bm) {
+  p.bm = bm;
+  p.n_qtiles = (p.Sq + bm - 1) / bm;
+  p.xcd_map = (p.B * p.Hkv) % 8 == 0 && (int64_t)p.n_qtiles * p.B * p.Hq >= 8;
+  // Without the causal rule all query tiles cost the same, and an XCD may finish the
+  // query tiles of one head before it starts the next: half as many heads' K/V are then live in
+  // its L2 at a time.  (Under a causal mask that order would bunch the heavy tiles.)
+  if (p.xcd_map && !p.causal && p.n_chunks == 0 && (int64_t)p.B * p.Hq / 8 <= 65535) p.xcd_map = 2;
+}
+
+hipError_t launch_plain(const tr::AttnParams& plain, int D, int epilogue, hipStream_t stream) {
+  tr::AttnParams p = plain;
+  set_rows(p, choose_rows(p, D, false));
+  return tr::launch_block_attn(p, D, epilogue, stream);
+}
+
 hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int D, int epilogue, hipStream_t stream) {
   tr::AttnParams p = plain;
-  p.pack = plan.pack;
-  p.members = plan.members;
-  p.n_qtiles = plan.row_tiles;
-  p.part_rows = plan.part_rows;
-  p.part_keys = (int)plan.part_keys;
+  auto shape = [&](int bm) {   // the row space in tiles of bm rows
+    const int space = plan.pack ? p.gq * p.Sq : p.Sq;
+    p.bm = bm;
+    p.pack = plan.pack;
+    p.n_qtiles = (space + bm - 1) / bm;
+    p.members = plan.pack ? p.n_qtiles : p.gq * p.n_qtiles;
+    p.part_rows = space > bm ? bm : (space + 31) / 32 * 32;
+  };
   if (plan.parts > 1) {
     if (PartPool* pool = part_pool_for(stream)) {
       std::lock_guard<std::mutex> hold(pool->lock);   // another thread on this stream must not enqueue between attention and fold
       if (PartRegion* r = take_region(*pool, stream)) {
         p.n_parts = plan.parts;
+        p.part_keys = (int)plan.part_keys;
+        shape(choose_rows(p, D, plan.pack));
+        const auto slot_rows = [&]() { return (int64_t)p.B * p.Hkv * p.members * p.n_parts * p.part_rows; };
+        if (slot_rows() * (D + 1) * 4 > kPartBytes) shape(kMaxRows);   // the form the plan has counted for
         p.units = p.B * p.Hkv * p.n_parts;
         p.part_out = (float*)r->bytes;
-        p.part_lse = p.part_out + plan.out_elems;
+        p.part_lse = p.part_out + slot_rows() * D;
         const hipError_t e = tr::launch_block_attn(p, D, epilogue, stream, r->done);
         if (e != hipSuccess) (void)hipEventRecord(r->done, stream);   // the fold did not go out, the attention may have
         return e;
@@ -291,9 +379,10 @@ hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int
   // All keys at once, in one launch.  (The parts one after the other, folded in the output, give the bits of the cut
   // form but pay a set-up and an epilogue for each: 1764 rows x 2 heads on 6491 keys 202 us replayed from a graph
   // against 91 in one pass, a decode step of 4 sequences on 8192 keys 121 against 90.)
-  if (!plan.packs_uncut) return tr::launch_block_attn(plain, D, epilogue, stream);
+  if (!plan.packs_uncut) return launch_plain(plain, D, epilogue, stream);
   p.n_parts = 1;
   p.part_keys = (p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
+  shape(choose_rows(p, D, plan.pack));
   p.units = p.B * p.Hkv;
   return tr::launch_block_attn(p, D, epilogue, stream);
 }
@@ -304,8 +393,8 @@ void set_shape(tr::AttnParams& p, const tr_tensor* q, const tr_tensor* k, int ca
   p.causal = causal ? 1 : 0;
   const int64_t lim = (int64_t)1 << 30;
   p.causal_off = (int)(off64 > lim ? lim : (off64 < -lim ? -lim : off64));
-  const int bm = tr::attn_rows_per_block();
-  p.n_qtiles = (p.Sq + bm - 1) / bm;
+  p.bm = kMaxRows;
+  p.n_qtiles = (p.Sq + p.bm - 1) / p.bm;
   p.gq = p.Hkv > 0 ? p.Hq / p.Hkv : 1;
 }
 
@@ -350,21 +439,17 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   set_shape(p, q, k, causal, off64);
   p.scale = scale;
   p.renew = renew;
-  p.xcd_map = (p.B * p.Hkv) % 8 == 0 && (int64_t)p.n_qtiles * p.B * p.Hq >= 8;
   p.gq_log2 = -1;
   for (int sh = 0; sh < 31; sh++)
     if (p.gq == (1 << sh)) p.gq_log2 = sh;
-  if (p.n_qtiles > 65535) return fail(TR_ERR_SHAPE, "Sq too long for one launch (at most 65535 query tiles of %d rows)", tr::attn_rows_per_block());
+  if (p.n_qtiles > 65535) return fail(TR_ERR_SHAPE, "Sq too long for one launch (at most 65535 query tiles of %d rows)", kMaxRows);
   if ((int64_t)p.n_qtiles * p.B * p.Hq >= ((int64_t)1 << 31)) return fail(TR_ERR_SHAPE, "too many workgroups for one launch");
-  // Without the causal rule all query tiles cost the same, and an XCD may finish the
-  // query tiles of one head before it starts the next: half as many heads' K/V are then live in
-  // its L2 at a time.  (Under a causal mask that order would bunch the heavy tiles.)
-  if (p.xcd_map && !p.causal && n_chunks == 0 && (int64_t)p.B * p.Hq / 8 <= 65535) p.xcd_map = 2;
   if (p.B == 0 || p.Hq == 0 || p.Sq == 0) return TR_OK;
   const int epilogue = fuse_update ? 2 : (out->dtype == TR_F32 ? 1 : 0);
   if (n_chunks > 0) {
     p.n_chunks = n_chunks;
     p.chunk_bf16 = chunk_bf16 ? 1 : 0;
+    set_rows(p, choose_rows(p, (int)q->D, false));
     const int step = std::max(1, 65535 / p.n_qtiles);   // chunks one grid holds; the later ones first, as inside a launch
     for (p.chunk_end = n_chunks; p.chunk_end > 0; p.chunk_end = p.chunk_begin) {
       p.chunk_begin = std::max(0, p.chunk_end - step);
@@ -375,7 +460,7 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   }
   PartPlan plan;
   const hipError_t e = plan_parts(p, (int)q->D, may_cut, plan) ? launch_planned(p, plan, (int)q->D, epilogue, (hipStream_t)stream)
-                                                                 : tr::launch_block_attn(p, (int)q->D, epilogue, (hipStream_t)stream);
+                                                                 : launch_plain(p, (int)q->D, epilogue, (hipStream_t)stream);
   if (e != hipSuccess) return fail(TR_ERR_HIP, "block attention launch failed: %s", hipGetErrorString(e));
   return TR_OK;
 }
@@ -492,7 +577,7 @@ std::vector<StepGroup> group_steps(const std::vector<RingStep>& steps, int n_seg
 // (16 segments of 16 keys: 1.03e-3 by blocks, 1.17e-3 renewed at every sub-tile, 1.61e-3 with one reference).
 tr_status attn_whole(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v, int n_seg, bool causal, float scale,
                      const tr_tensor* out, const tr_tensor* lse, void* stream) {
-  const int64_t seg = q->S / n_seg, bm = tr::attn_rows_per_block();
+  const int64_t seg = q->S / n_seg, bm = kMaxRows;
   if (seg > 65535 * bm) return fail(TR_ERR_SHAPE, "segments of %lld rows are too long (at most 65535 query tiles of %d rows)", (long long)seg, (int)bm);
   if (n_seg > 1 && seg < 32) {
     const tr_tensor q0 = rows_view(q, 0, seg), k0 = rows_view(k, 0, seg), v0 = rows_view(v, 0, seg);

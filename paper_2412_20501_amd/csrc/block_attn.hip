@@ -1,254 +1,15 @@
-// Blockwise attention step for gfx950 (CDNA4): block_out, block_lse <- Attention(Q, K, V)
-// of TokenRing's Algorithm 1 (Sec. 3.2), one Query chunk against one K/V chunk.
-//
-// Formulation.  Scores are computed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16:
-// the A operand is a 32-key x 16-d slice of the K tile read from LDS, the B operand a
-// 16-d x 32-query slice of Q^T held in registers for the whole kernel.  In the MFMA
-// accumulator layout lane (q = lane%32, half = lane/32) then owns, for ONE query, the
-// 16 keys {8g + 4*half + r} of a 32-key sub-tile: the softmax is in-lane.  The
-// exponentiated sub-tile P^T, rounded to bf16, is already in the B-operand layout of the
-// second product O^T = V^T P^T; its A operand (32 d x 16 keys of V^T) comes from the
-// row-major V tile in LDS through the transposing read ds_read_b64_tr_b16, with the key
-// order inside each 16-key step permuted to match the accumulator layout of P^T (a
-// contraction index may be permuted freely as long as both operands agree).  The O^T
-// accumulator again has one query per lane, so rescaling and the final 1/l need no
-// cross-lane traffic.
-//
-// Pipeline.  A lone wave issues vector-ALU instructions far below the SIMD's rate and cannot
-// hide its softmax behind another wave's MFMAs, so MFMA and softmax work are interleaved
-// INSIDE every wave, one 32-key sub-tile apart: step j runs, as one instruction stream,
-//     MFMA : O += V_{j-1}^T P_{j-1}      and      S_{j+1} = K_{j+1} Q^T
-//     VALU : P_j = exp2((S_j - m_ref) * scale*log2e), row sums
-// with no dependency between the two halves.  Two such waves per SIMD fill each other's
-// gaps.  A workgroup has 8 waves of 32 query rows (256 rows); K/V tiles of 16 KiB (64 keys
-// = two sub-tiles at D = 128, 128 keys = four at D = 64) go straight from global memory into
-// 4-deep LDS rings (global_load_lds), the K tile with a 16-byte XOR swizzle and the V tile
-// with a 32-byte XOR swizzle that make the ds_read_b128 and the transposing reads
-// bank-conflict free.  One workgroup barrier per tile hands ring slots over.
-#include <type_traits>
-
-#include <atomic>
-
-#include "tr_internal.h"
+// Host side of the block attention kernel (block_attn_kernel.h): grids and shapes of the launches, and the fold of a
+// launch whose keys are cut into parts.
+#include "block_attn_kernel.h"
 
 namespace tr {
+
+#define TR_SHAPE(D, R, G) extern template hipError_t launch_attn_shape<D, R, G>(const AttnParams&, int, dim3, hipStream_t);
+TR_SHAPE(64, 8, 1) TR_SHAPE(64, 4, 2) TR_SHAPE(64, 2, 2)
+TR_SHAPE(128, 8, 1) TR_SHAPE(128, 4, 2) TR_SHAPE(128, 2, 2)
+#undef TR_SHAPE
+
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kWaves = 8;
-constexpr int kThreads = kWaves * 64;
-constexpr int kBM = kWaves * 32;  // query rows per workgroup
-// keys per LDS tile: 16 KiB of K (and of V) either way, so a tile is 2 sub-tiles of 32 keys at
-// D = 128 and 4 at D = 64, where a sub-tile carries half the MFMA work per barrier otherwise
-template <int D>
-constexpr int tile_keys() { return D == 64 ? 128 : 64; }
-constexpr int kRing = 4;          // LDS ring depth (tiles) of K and of V
-constexpr int kEpiBf16 = 0, kEpiF32 = 1, kEpiMerge = 2;
-constexpr int kPlain = 0, kPart = 1, kChunks = 2;   // forms of the kernel, see there
-
-// Exchange between the two 32-lane halves of a wave with v_permlane32_swap, which swaps the
-// upper half of its first operand with the lower half of its second: fed (x, x) it leaves
-// x[lane%32] in the first and x[32 + lane%32] in the second register, in every lane.
-// Written as inline asm: at -O3 the compiler folds the second result of the corresponding
-// builtin into the first, which silently drops the other half's contribution.  The s_nop
-// covers the VALU-write -> permlane-swap hazard the assembler does not see inside asm.
-__device__ __forceinline__ void half_pair(float x, float& lo, float& hi) {
-  float a = x, b = x;
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-  lo = a;
-  hi = b;
-}
-__device__ __forceinline__ float half_swap_max(float x) {
-  float lo, hi;
-  half_pair(x, lo, hi);
-  return fmaxf(lo, hi);
-}
-__device__ __forceinline__ float half_swap_sum(float x) {
-  float lo, hi;
-  half_pair(x, lo, hi);
-  return lo + hi;
-}
-
-// Byte offset of 16-byte chunk c of row `row` inside a K tile (row-major, D bf16 per row).
-template <int D>
-__device__ __forceinline__ int k_lds_off(int row, int c) {
-  constexpr int RB = 2 * D;             // row bytes
-  constexpr int R2 = 256 / RB;          // rows per 256-byte bank line
-  constexpr int NC = RB / 16;           // chunks per row
-  return row * RB + ((c ^ ((row / R2) % NC)) << 4);
-}
-// Byte offset of 16-byte chunk c of row `row` inside a V tile: 32-byte slots XOR-swizzled
-// by the row so that the four rows a transposing read touches fall on distinct banks.
-template <int D>
-__device__ __forceinline__ int v_lds_off(int row, int c) {
-  constexpr int RB = 2 * D;
-  int slot = c >> 1;
-  int swz = (D == 128) ? ((row & 3) << 1) : (row & 2);
-  return row * RB + ((slot ^ swz) << 5) + ((c & 1) << 4);
-}
-
-// Which (batch*head, query tile) a workgroup computes.  The grid is two-dimensional - x: batch*head,
-// y: query tile - so the indices come from the
-// hardware instead of integer divisions (a division costs ~40 dependent instructions and the
-// decoding sits in front of every workgroup's first load).  Workgroups are dealt round-robin to
-// the 8 XCDs in the order of their linear id, which is x-fastest, and the x extent is a multiple
-// of 8 whenever xcd_map is set: XCD = blockIdx.x mod 8.  XCD x gets the K/V heads x, x+8, ... and
-// all query heads and query tiles that read them, so a head's K/V stays in one L2.
-__device__ __forceinline__ void decode_block(const AttnParams& p, int& qt, int& b, int& hq, int& hk) {
-  const int gq = p.gq, sh = p.gq_log2;   // query heads per K/V head; its log2, or -1 if not a power of two
-  int bh = (int)blockIdx.x, qi = (int)blockIdx.y;
-  if (p.xcd_map) {
-    int x = bh & 7, hi = bh >> 3;
-    if (p.xcd_map == 2) {   // x = XCD + 8 * query tile, y = head within the XCD
-      qi = hi;
-      hi = (int)blockIdx.y;
-    }
-    const int kvi = sh >= 0 ? hi >> sh : hi / gq;
-    const int mem = sh >= 0 ? hi & (gq - 1) : hi % gq;
-    bh = (kvi * 8 + x) * gq + mem;
-  }
-  b = p.B == 1 ? 0 : bh / p.Hq;
-  hq = bh - b * p.Hq;
-  hk = sh >= 0 ? hq >> sh : hq / gq;
-  qt = p.n_qtiles - 1 - qi;  // late query tiles (most keys under a causal mask) first
-}
-
-typedef __attribute__((address_space(1))) const void* gptr_t;
-typedef __attribute__((address_space(3))) void* lptr_t;
-
-// A pointer the compiler must keep in an SGPR pair (it is wave-uniform by construction).
-__device__ __forceinline__ const __bf16* uniform_ptr(const __bf16* ptr) {
-  const unsigned long long v = (unsigned long long)ptr;
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-  return (const __bf16*)(((unsigned long long)hi << 32) | lo);
-}
-
-// Workgroup barrier without the memory fence of __syncthreads(): the tile hand-off is
-// ordered by explicit s_waitcnt vmcnt() on the direct-to-LDS loads instead.
-__device__ __forceinline__ void wg_barrier() { __builtin_amdgcn_s_barrier(); }
-
-// The same for the partitioned form: a one-dimensional grid over units (K/V head of a batch entry, part
-// of the keys) and, inside a unit, the row tiles that read its keys.  Every XCD takes one eighth of that
-// list, a contiguous piece, so what shares keys mostly shares an L2 and no XCD is left without work: whole units
-// dealt to XCDs in turn kept four XCDs idle with four units (3076 rows x 8 heads on 3898 keys 111 us against 77
-// uncut).  Returns false for the ids that only fill the last eight up.
-struct PartBlock { int tile, b, hk, hq0, part, group; };
-__device__ __forceinline__ bool decode_part(const AttnParams& p, PartBlock& w) {
-  const int per_xcd = (int)gridDim.x >> 3;
-  const int at = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
-  const int u = at / p.members, m = at - u * p.members;
-  if (u >= p.units) return false;
-  const int kv = u / p.n_parts;
-  w.part = u - kv * p.n_parts;
-  w.b = kv / p.Hkv;
-  w.hk = kv - w.b * p.Hkv;
-  w.group = kv * p.members + m;
-  const int head = p.pack ? 0 : m / p.n_qtiles;
-  w.hq0 = w.hk * p.gq + head;
-  w.tile = p.n_qtiles - 1 - (m - head * p.n_qtiles);
-  return true;
-}
-
-template <int N>
-using IC = std::integral_constant<int, N>;
-
-// The rows of a partitioned launch: row r of the row space of heads hq0, hq0 + 1, ... is Query row r mod Sq
-// of head hq0 + r / Sq.  pos_span: smallest and largest Query position among rows first .. first + n - 1.
-__device__ __forceinline__ int part_rows_total(const AttnParams& p) { return p.pack ? p.gq * p.Sq : p.Sq; }
-__device__ __forceinline__ void pos_span(const AttnParams& p, int first, int n, int& lo, int& hi) {
-  const int last = min(first + n, part_rows_total(p)) - 1;
-  const int ha = first / p.Sq, hb = last / p.Sq;
-  lo = ha == hb ? first - ha * p.Sq : 0;
-  hi = ha == hb ? last - hb * p.Sq : p.Sq - 1;
-}
-// Parts of the keys that any row of the tile sees, the first one always counted: parts 0 .. n - 1 are computed.
-__device__ __forceinline__ int live_parts(const AttnParams& p, int pos_last) {
-  const int seen = p.causal ? max(0, min(p.Sk, pos_last + p.causal_off + 1)) : p.Sk;
-  return max(1, (seen + p.part_keys - 1) / p.part_keys);
-}
-
-// LDS of the epilogue behind the waves' transposed 32 x D fp32 tiles (byte offsets from the start):
-// Update weight and case of each row, and for the partitioned form the rows' output offsets.
-template <int D>
-struct EpiLds {
-  static constexpr int w = kBM * 4 * D, mode = w + kBM * 4, off = mode + kBM * 4;
-  static constexpr int bytes = off, bytes_part = off + kBM * 8;
-};
-
-// Epilogue of the partitioned form.  The wave's normalised 32 x D tile lies in LDS (chunk-swizzled, written
-// by this wave), lse_blk is the log-sum-exp of the lane's row over the workgroup's part of the keys (-inf also
-// for a row whose weights hold a NaN, which not_a_number says apart).  With one live part the tile is stored or
-// merged as it is, otherwise tile and lse go to the scratch slot of (row tile, part) for the fold kernel.
-template <int D, int EPI>
-__device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, int lane, int wave, int q0, int b, int hq0, int group, int part,
-                                              int n_live, float lse_blk, bool not_a_number) {
-  constexpr int ROWB = 4 * D, CPRF = D / 4, RPI_OUT = 64 / CPRF, NIT = 32 / RPI_OUT;
-  const int ql = lane & 31, rr = lane / CPRF, cc = lane % CPRF;
-  const int n_rows = part_rows_total(p), n_valid = n_rows - (q0 + wave * 32);   // rows of this wave (32 or more: all)
-  if (n_valid <= 0) return;   // no barrier follows
-  const bool own_row = lane < 32 && ql < n_valid;
-  const char* const my = lds + wave * (32 * ROWB);
-
-  if (n_live > 1) {
-    const int64_t slot_row = ((int64_t)group * p.n_parts + part) * p.part_rows + wave * 32;
-    float* const dst = p.part_out + slot_row * D + 4 * cc;
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
-#pragma unroll
-    for (int it = 0; it < NIT; it++) {
-      const int r = it * RPI_OUT + rr;
-      const f32x4 o = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
-      if (r < n_valid) *reinterpret_cast<f32x4*>(dst + (int64_t)r * D) = o;
-    }
-    if (own_row) p.part_lse[slot_row + ql] = not_a_number ? __builtin_nanf("") : lse_blk;
-    return;
-  }
-  float* const tab_w = reinterpret_cast<float*>(lds + EpiLds<D>::w) + wave * 32;
-  int* const tab_mode = reinterpret_cast<int*>(lds + EpiLds<D>::mode) + wave * 32;
-  int64_t* const off = reinterpret_cast<int64_t*>(lds + EpiLds<D>::off) + wave * 32;
-  {
-    const int row = min(q0 + wave * 32 + ql, n_rows - 1), head = row / p.Sq, pos = row - head * p.Sq;
-    const int64_t l_at = (int64_t)b * p.l_sb + (int64_t)(hq0 + head) * p.l_sh + (int64_t)pos * p.l_ss;
-    const UpdatePlan pl = plan_update(EPI == kEpiMerge ? p.lse[l_at] : -INFINITY, lse_blk);
-    if (lane < 32) {
-      off[ql] = (int64_t)b * p.o_sb + (int64_t)(hq0 + head) * p.o_sh + (int64_t)pos * p.o_ss;
-      tab_w[ql] = pl.w;
-      tab_mode[ql] = pl.mode;
-    }
-    if (own_row) p.lse[l_at] = pl.new_lse;
-  }
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), as above
-#pragma unroll
-  for (int it = 0; it < NIT; it++) {
-    const int r = it * RPI_OUT + rr;
-    if (r >= n_valid) continue;
-    f32x4 o = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
-    const int64_t at = off[r] + 4 * cc;
-    if (EPI == kEpiBf16) {
-      bf16x4 ob;
-#pragma unroll
-      for (int e = 0; e < 4; e++) ob[e] = (__bf16)o[e];
-      *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + at) = ob;
-    } else {
-      f32x4* const dst = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + at);
-      if (EPI == kEpiMerge) {
-        UpdatePlan pl;
-        pl.w = tab_w[r];
-        pl.mode = tab_mode[r];
-        pl.new_lse = 0.f;
-        o = apply_update(pl, *dst, o);
-      }
-      *dst = o;
-    }
-  }
-}
 
 // Fold of a partitioned launch: the Update of Sec. 3.1 over the parts of a row at once, out = sum of exp(lse_i - lse)
 // out_i; with kEpiMerge that block then takes one Update onto the accumulators.  Weighted and not blended part by part,
@@ -265,11 +26,11 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
   const int group = (int)blockIdx.x, kv = group / p.members, m = group - kv * p.members;
   const int b = kv / p.Hkv, hk = kv - b * p.Hkv;
   const int head0 = p.pack ? 0 : m / p.n_qtiles;
-  const int q0 = (p.n_qtiles - 1 - (m - head0 * p.n_qtiles)) * kBM, n_tile = min(kBM, part_rows_total(p) - q0);
+  const int q0 = (p.n_qtiles - 1 - (m - head0 * p.n_qtiles)) * p.bm, n_tile = min(p.bm, part_rows_total(p) - q0);
   const int r = (int)blockIdx.y * (kFoldThreads / CPRF) + (int)threadIdx.x / CPRF, cc = (int)threadIdx.x % CPRF;
   if (r >= n_tile) return;
   int lo, hi;
-  pos_span(p, q0, kBM, lo, hi);
+  pos_span(p, q0, p.bm, lo, hi);
   const int n_live = live_parts(p, hi);
   if (n_live == 1) return;   // written by the attention kernel
 
@@ -331,704 +92,6 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
   if (cc == 0) p.lse[l_at] = lse;   // a row lies within one wave, so every thread of it has read the old value
 }
 
-// EPI selects the epilogue: kEpiBf16 / kEpiF32 store block_out and block_lse; kEpiMerge folds
-// the block straight into fp32 accumulators with the Update of Sec. 3.1 (no block_out round trip).
-//
-// PART is the form for grids that would leave most of the chip idle (a decode step, a short prompt
-// behind a long cache).  (1) The rows of a workgroup are (query head of one K/V head's group, Query
-// row) pairs when that needs fewer workgroups: a decode step with grouped heads then reads every key
-// once instead of once per query head.  (2) The keys are cut into p.n_parts parts of p.part_keys
-// keys, each computed exactly as a launch over that part alone would; the block results go to a
-// scratch buffer in fp32 and fold_parts_kernel adds them up in key order (a fixed
-// order: bitwise reproducible).  Bound: HBM for a decode step, MFMA otherwise, plus the fold.  Four decode steps
-// over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 141 us, 500 Query rows x 32 heads
-// behind 12000 keys 216 -> 102 us against the plain form.
-//
-// FORM kChunks replays Algorithm 1 block by block: with block results that are rounded to bf16 on their way to the
-// Update, or (chunks shorter than a sub-tile, which no reference of the running softmax can be kept for) in fp32.
-// A workgroup keeps its Query tile of chunk c and runs through the K/V chunks in the order the schedule
-// brings them, c, c + 1, ... mod n (causal: only those not after c); each block ends in the merging
-// epilogue, the first one unrounded onto an empty accumulator.  One launch instead of two per block: no
-// block result in memory, no idle tail between the blocks (chunks of 1502 rows x 16 heads fill 96 of 256
-// compute units), the longest chunks first.  Bound: as the plain form, plus an epilogue for each block.
-// Causal 6008 rows in 4 chunks, 16 heads: 401 -> 193 us, the same bits.
-template <int D, int EPI, int FORM>
-__global__ void __launch_bounds__(kThreads) block_attn_kernel(const AttnParams p) {
-  constexpr bool PART = FORM == kPart, CHUNKS = FORM == kChunks;
-  static_assert(!CHUNKS || EPI == kEpiMerge, "blocks of the chunk form are merged");
-  constexpr int RB = 2 * D;
-  constexpr int KS = D / 16;               // MFMA k-steps over the head dim
-  constexpr int DB = D / 32;               // 32-wide d blocks of the output
-  constexpr int CPR = D / 8;               // 16-byte chunks per row
-  constexpr int BN = tile_keys<D>();       // keys per LDS tile
-  constexpr int TILE_BYTES = BN * RB;
-  constexpr int RPI = 1024 / RB;           // tile rows one wave-wide 16-byte load instruction covers
-  constexpr int IPW = BN / RPI / kWaves;   // load instructions per wave, tile and tensor
-  constexpr int NS = kRing;                // ring depth of the K and of the V tiles
-  constexpr int SUB = 32;                  // keys per sub-tile (one MFMA row block)
-  constexpr int NSUB = BN / SUB;           // sub-tiles (= steps) per tile
-  static_assert(NSUB % 2 == 0, "the S / P register sets alternate with the step parity");
-  static_assert(IPW >= 1, "tile too small for the workgroup");
-
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // K ring | V ring
-
-  // which batch, head and query tile this workgroup computes (wave-uniform)
-  int qt, b, hq, hk;
-  PartBlock pb = {0, 0, 0, 0, 0, 0};
-  if constexpr (PART) {
-    if (!decode_part(p, pb)) return;
-    qt = pb.tile; b = pb.b; hq = pb.hq0; hk = pb.hk;
-  } else {
-    decode_block(p, qt, b, hq, hk);
-  }
-  int chunk = 0;
-  if constexpr (CHUNKS) {   // grid y runs over (chunk, query tile), both from the last on
-    const int y = (int)blockIdx.y / p.n_qtiles;
-    chunk = p.chunk_end - 1 - y;
-    qt += y * p.n_qtiles;
-  }
-  const int64_t chunk_row = (int64_t)chunk * p.Sq;
-  for (int block = 0; block < (CHUNKS ? p.n_chunks : 1); block++) {
-  const int kv_chunk = CHUNKS ? (chunk + block < p.n_chunks ? chunk + block : chunk + block - p.n_chunks) : 0;
-  if (CHUNKS && p.causal && kv_chunk > chunk) continue;
-  int tid = threadIdx.x;
-  if constexpr (CHUNKS) asm volatile("" : "+v"(tid));   // nothing derived from it is held in registers from block to block (179 spills otherwise)
-  const int lane = tid & 63, ql = lane & 31, hf = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in an SGPR
-  const bool causal = CHUNKS ? p.causal && block == 0 : p.causal != 0;
-  int Sk = p.Sk, causal_off = p.causal_off;
-  const int q0 = qt * kBM, qw0 = q0 + wave * 32;
-  const int qrow = qw0 + ql;
-  // rows of this workgroup's row space: the Query rows of one head, or of a whole group of heads
-  const int n_rows = PART ? part_rows_total(p) : p.Sq;
-  const int qrow_ld = min(qrow, n_rows - 1);
-  // Query position of this lane's row (its head is hq + lane_head), the smallest and largest position
-  // of the wave's rows, the largest of the workgroup's: what the causal rule needs
-  int lane_head = 0, lane_pos = qrow, pos_first = qw0, pos_last = min(qw0 + 31, p.Sq - 1), pos_last_wg = min(q0 + kBM, p.Sq) - 1;
-  int n_live = 1;   // parts of the keys that any row of this workgroup sees
-  if constexpr (PART) {
-    lane_head = qrow_ld / p.Sq;
-    lane_pos = qrow_ld - lane_head * p.Sq;
-    int unused;
-    pos_span(p, min(qw0, n_rows - 1), 32, pos_first, pos_last);
-    pos_span(p, q0, kBM, unused, pos_last_wg);
-    n_live = live_parts(p, pos_last_wg);
-    if (pb.part >= n_live) return;
-    const int k0 = pb.part * p.part_keys;
-    Sk = min(Sk - k0, p.part_keys);
-    causal_off -= k0;
-  }
-
-  // Key range of this workgroup in tiles (needed to start the loads; the wave's own range follows below)
-  int kv_end = Sk;
-  if (causal) kv_end = max(0, min(Sk, pos_last_wg + causal_off + 1));
-  const int n_tiles = (kv_end + BN - 1) / BN;
-
-  const __bf16* kg = p.k + (int64_t)b * p.k_sb + (int64_t)hk * p.k_sh;
-  const __bf16* vg = p.v + (int64_t)b * p.v_sb + (int64_t)hk * p.v_sh;
-  if constexpr (CHUNKS) {
-    kg += (int64_t)kv_chunk * p.Sk * p.k_ss;
-    vg += (int64_t)kv_chunk * p.Sk * p.v_ss;
-  }
-  if constexpr (PART) {
-    kg += (int64_t)pb.part * p.part_keys * p.k_ss;
-    vg += (int64_t)pb.part * p.part_keys * p.v_ss;
-  }
-
-  // Direct global -> LDS staging (no VGPRs, no ds_write): one wave-wide instruction deposits
-  // lane l's 16 bytes at lds_base + 16*l, i.e. RPI consecutive tile rows.  The swizzle is
-  // applied on the global side: the lane that fills LDS position (row, pc) fetches the chunk
-  // the swizzle maps there.  Addresses are a wave-uniform 64-bit tile base (SGPR pair) plus a
-  // per-lane 32-bit byte offset that never changes, so issuing a tile costs no vector
-  // arithmetic.  Rows past the end of the keys re-read the last key (they are masked later):
-  // the last, possibly partial, tile has its own clamped offsets, and tiles beyond it (the
-  // ring runs ahead of the loop) re-read the last tile.
-  const int last_tile = (Sk - 1) / BN;
-  unsigned k_off[IPW], v_off[IPW], k_off_last[IPW], v_off_last[IPW];
-#pragma unroll
-  for (int i = 0; i < IPW; i++) {
-    const int row = (wave * IPW + i) * RPI + lane / CPR, pc = lane % CPR;
-    const int kc = (pc ^ ((row / (256 / RB)) % CPR)) * 8;
-    const int vswz = (D == 128) ? ((row & 3) << 1) : (row & 2);
-    const int vc = ((((pc >> 1) ^ vswz) << 1) | (pc & 1)) * 8;
-    const int row_last = max(0, min(row, Sk - 1 - last_tile * BN));
-    k_off[i] = (unsigned)(((int64_t)row * p.k_ss + kc) * 2);
-    v_off[i] = (unsigned)(((int64_t)row * p.v_ss + vc) * 2);
-    k_off_last[i] = (unsigned)(((int64_t)row_last * p.k_ss + kc) * 2);
-    v_off_last[i] = (unsigned)(((int64_t)row_last * p.v_ss + vc) * 2);
-  }
-  // Issued as inline asm: the compiler would otherwise treat every later LDS read as possibly
-  // aliasing the in-flight load and drain vmcnt to 0 in front of it, serialising the pipeline;
-  // here completion is waited for explicitly, one tile ahead of the first use.
-  // The statement overwrites m0.  The compiler reserves m0 and sets it itself right before each of
-  // its own uses (dynamic register indexing, LDS-direct forms), none of which this kernel
-  // contains: every register-array index is a compile-time constant.  (m0 cannot be named in
-  // the clobber list: it is a reserved register and the compiler rejects the promise.)
-  const unsigned lds_base = (unsigned)(unsigned long)(lptr_t)lds;
-  auto dma16 = [&](const __bf16* base, unsigned off, unsigned lds_off) __attribute__((always_inline)) {
-    const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base + lds_off);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(off), "s"(base) : "memory");
-  };
-  // Tiles are issued strictly in order, so the tile base is a running wave-uniform pointer that
-  // stops advancing at the last tile (later issues re-read it with the clamped offsets).
-  const __bf16* k_next = uniform_ptr(kg);
-  const __bf16* v_next = uniform_ptr(vg);
-  const int64_t k_tile_stride = (int64_t)BN * p.k_ss, v_tile_stride = (int64_t)BN * p.v_ss;
-  int k_left = last_tile, v_left = last_tile;  // tiles still ahead of the pointer
-  auto issue_k = [&](int slot) __attribute__((always_inline)) {
-    const bool last = k_left <= 0;
-#pragma unroll
-    for (int i = 0; i < IPW; i++)
-      dma16(k_next, last ? k_off_last[i] : k_off[i], slot * TILE_BYTES + (wave * IPW + i) * 1024);
-    k_next = uniform_ptr(k_next + (last ? 0 : k_tile_stride));
-    k_left--;
-  };
-  auto issue_v = [&](int slot) __attribute__((always_inline)) {
-    const bool last = v_left <= 0;
-#pragma unroll
-    for (int i = 0; i < IPW; i++)
-      dma16(v_next, last ? v_off_last[i] : v_off[i], (NS + slot) * TILE_BYTES + (wave * IPW + i) * 1024);
-    v_next = uniform_ptr(v_next + (last ? 0 : v_tile_stride));
-    v_left--;
-  };
-
-  // ---- prologue: K_0..K_2, V_0, V_1 into the rings, then the Query fragments.  The loads go out
-  // before the rest of the set-up (this wave's key range, LDS read addresses, cleared accumulators)
-  // so that their latency, the longest wait of a workgroup's life, runs under that arithmetic.
-  if (n_tiles > 0) {
-    issue_k(0);
-    issue_v(0);
-    issue_k(1);
-    issue_v(1);
-    issue_k(2);
-  }
-  // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step.
-  bf16x8 qf[KS];
-  {
-    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)(PART ? hq + lane_head : hq) * p.q_sh + (PART ? lane_pos : chunk_row + qrow_ld) * p.q_ss;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * hf);
-  }
-
-
-  // Key range of this wave (in 32-key sub-tiles).
-  int wave_kv_end = 0;
-  if (qw0 < n_rows) {
-    wave_kv_end = Sk;
-    if (causal) wave_kv_end = max(0, min(Sk, pos_last + causal_off + 1));
-  }
-  const int jw = (wave_kv_end + SUB - 1) / SUB;  // sub-tiles this wave has visible keys in
-  // wave-uniform loop bounds, forced into scalar registers so that every per-step test is one compare
-  const int jw_first = __builtin_amdgcn_readfirstlane(jw);                            // last allowed step that opens a tile
-  const int jw_in = __builtin_amdgcn_readfirstlane(min(jw, NSUB * n_tiles - 1));      // last allowed step inside a tile
-  // a sub-tile starting at kstart needs masking iff kstart > kmask_from
-  int kmask_from_v = Sk - SUB;
-  if (causal) kmask_from_v = min(kmask_from_v, pos_first + causal_off - SUB + 1);
-  const int kmask_from = __builtin_amdgcn_readfirstlane(kmask_from_v);
-
-  // Per-lane LDS read offsets.
-  // K operand: lane (key = ql, hf) reads chunk 2*ks + hf of row 32*kt + ql.
-  // (All read addresses are LDS byte addresses with the ring base folded in, so that ring
-  // slot and sub-tile offsets are instruction immediates.)
-  unsigned k_rd[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) k_rd[ks] = lds_base + k_lds_off<D>(ql, 2 * ks + hf);
-  // V^T operand through the transposing read: within each group of 16 lanes, lane i supplies
-  // the address of row (i/4) of the 4-key group, 8-byte segment (i%4) of the 16 d's the
-  // group covers, and receives the 4 keys of d = i.  (The V ring base is folded in.)
-  unsigned v_rd[DB];
-  {
-    const int i16 = lane & 15, gq = (lane >> 4) & 1;
-    const int row = 4 * hf + (i16 >> 2);
-#pragma unroll
-    for (int db = 0; db < DB; db++)
-      v_rd[db] = lds_base + NS * TILE_BYTES + v_lds_off<D>(row, 4 * db + 2 * gq) + (i16 & 3) * 8;
-  }
-
-  f32x16 o_acc[DB];
-#pragma unroll
-  for (int db = 0; db < DB; db++)
-#pragma unroll
-    for (int i = 0; i < 16; i++) o_acc[db][i] = 0.f;
-  // Largest sub-tile sum (16 weights of one row) the fast path accepts: 2^80.  The weights, their
-  // bf16 roundings and the fp32 accumulators all carry an 8-bit exponent, so precision does not
-  // depend on the magnitude; the cap only has to keep sums over all keys (up to 2^30, i.e. 2^25
-  // sub-tiles, |v| up to 2^7) below 2^127.  A score must therefore exceed the reference by 55 (in natural
-  // units) before the reference is moved: on all but pathological inputs that happens once, at
-  // the row's first keys.
-  constexpr float kSumCap = 0x1p80f;
-  float m_ref = -INFINITY;  // exponent reference of this query, in raw (unscaled) score units
-  float mc = 0.f;           // m_ref * c2 (0 while m_ref is -inf), kept alongside m_ref
-  float l_run = 0.f;        // this lane's share of the running sum of exp
-  float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite and where it is renewed
-  int renew_at = !CHUNKS && p.renew > 0 ? p.renew : 0x7fffffff;   // m_ref is renewed by the first step that starts at this key or later
-  const float c2 = p.scale * 1.4426950408889634f;  // scale * log2(e)
-
-  // ---- one step ---------------------------------------------------------------------
-  // Step j (sub-tile j starts at key kstart) runs, as ONE interleaved instruction stream,
-  //   MFMA : S_{j+1} = K_{j+1} Q^T   (NQK MFMAs, operands read from LDS by the PREVIOUS step)
-  //          O += V_{j-1}^T P_{j-1}^T (NPV MFMAs, operands read from LDS during the QK half)
-  //   LDS  : while the PV half runs, the K operands of step j+1 are read (into `pre`), so the
-  //          read stream never stops at a step boundary or at a barrier (the tile they come
-  //          from became visible a whole tile earlier)
-  //   VALU : P_j = exp2((S_j - m_ref) * c2) and its row sums
-  // QK goes first so that S_{j+1} is complete long before the next step's softmax reads it.
-  //
-  // P = exp2((s - m_ref) * scale*log2e) with an exponent reference m_ref that is NOT the
-  // running maximum: any reference gives the same out = O/l and lse = m_ref*scale + ln l, so
-  // the common path takes no row maximum.  Since P >= 0, a sub-tile sum <= kSumCap bounds
-  // every P.  Only if some lane's sum exceeds the cap (or is NaN), or the reference is still
-  // -inf, the slow path runs after the stream: row maximum, raise the reference, rescale l
-  // and the O accumulators (which by then include P_{j-1}, consistently), redo the exponentials.
-  // With p.renew the slow path also runs once every p.renew keys and may lower the reference to its
-  // sub-tile's maximum: the weight of that maximum is then 1 and bf16 holds it exactly.  One
-  // reference for a whole sequence has one such weight a row where blocks attended one by one have one each,
-  // and the rounding of the largest weights is most of the error: 256 keys 1.42e-3 in blocks of 64, 1.60e-3 with one
-  // reference, 1.42e-3 renewed every 64 keys.
-  // Row sums use the unrounded fp32 P: summing the bf16-rounded weights would cost up to
-  // 2^-8 relative in l, more than the 1e-3 budget of lse for rows that see only a few keys.
-  //
-  // The stream is written out in the order it should issue - per MFMA: one operand's LDS
-  // reads, the MFMA, and a slice of the softmax whose three dependent stages (fma, exp2,
-  // add/convert) are staggered across consecutive slices - and pinned with sched_barrier.
-  constexpr int NPV = 2 * DB, NQK = KS;
-  static_assert(NPV == NQK, "the two halves of a step carry the same number of MFMAs");
-  typedef const s16x4 __attribute__((address_space(3)))* lds_tr_ptr;
-  typedef const bf16x8 __attribute__((address_space(3)))* lds_b128_ptr;
-  auto load_k = [&](int ks, unsigned k_imm) __attribute__((always_inline)) -> bf16x8 {
-    return *(lds_b128_ptr)(unsigned long)(k_rd[ks] + k_imm);
-  };
-  auto load_v = [&](int i, unsigned v_imm) __attribute__((always_inline)) -> bf16x8 {
-    const int t = i / DB, db = i % DB;
-    const unsigned a = v_rd[db] + v_imm + 16 * t * RB;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(lds_tr_ptr)(unsigned long)a);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(lds_tr_ptr)(unsigned long)(a + 8 * RB));
-    const bf16x4 lo_b = __builtin_bit_cast(bf16x4, lo), hi_b = __builtin_bit_cast(bf16x4, hi);
-    return __builtin_shufflevector(lo_b, hi_b, 0, 1, 2, 3, 4, 5, 6, 7);
-  };
-  bf16x8 pre[NQK];  // K operands of the next step's QK half, read one step ahead
-
-  auto step = [&](int kstart, auto first_c, auto v_imm_c, auto k_imm_next_c, f32x16& s_in, f32x16& s_out,
-                  bf16x8 (&p_in)[2], bf16x8 (&p_out)[2], auto inner_c) __attribute__((always_inline)) {
-    constexpr bool FIRST = decltype(first_c)::value != 0;   // no previous sub-tile: QK half only
-    constexpr bool INNER = decltype(inner_c)::value != 0;   // every key of the sub-tile is visible to every row: no mask test
-    constexpr int n_mfma = FIRST ? NQK : NQK + NPV;
-    constexpr int EPM = 16 / n_mfma;  // softmax elements handled per MFMA slice
-    static_assert(16 % n_mfma == 0, "softmax elements must divide evenly over the MFMAs");
-    constexpr unsigned v_imm = decltype(v_imm_c)::value, k_imm_next = decltype(k_imm_next_c)::value;
-
-    if (!INNER && kstart > kmask_from) {  // some key of the sub-tile is past Sk or above this wave's first diagonal
-      int limit = Sk - 1;
-      if (causal) limit = min(limit, lane_pos + causal_off);
-#pragma unroll
-      for (int i = 0; i < 16; i++) {
-        const int key = kstart + 8 * (i >> 2) + 4 * hf + (i & 3);
-        if (key > limit) s_in[i] = -INFINITY;
-      }
-    }
-
-    f32x16 acc;
-#pragma unroll
-    for (int i = 0; i < 16; i++) acc[i] = 0.f;
-    bf16x8 pv_ops[NPV], nxt[NQK];
-    float tq[16], ex[16];
-    unsigned pw[8];
-    float ps0 = 0.f, ps1 = 0.f;
-    // Softmax element group g (EPM elements) passes stage A (fma) in slice g-2, stage B (exp2) in
-    // slice g-1 and stage C (sum, convert) in slice g, so the stream ends with the last MFMA
-    // and nothing but the sum check is left behind it.  The convert is opaque to the compiler,
-    // which would otherwise sink all of them behind the slow-path branch.
-    auto stage_a = [&](int g) __attribute__((always_inline)) {
-#pragma unroll
-      for (int k = 0; k < EPM; k++) tq[g * EPM + k] = __builtin_fmaf(s_in[g * EPM + k], c2, -mc);
-    };
-    auto stage_b = [&](int g) __attribute__((always_inline)) {
-#pragma unroll
-      for (int k = 0; k < EPM; k++) ex[g * EPM + k] = __builtin_amdgcn_exp2f(tq[g * EPM + k]);
-    };
-    auto stage_c = [&](int g) __attribute__((always_inline)) {
-#pragma unroll
-      for (int k = 0; k < EPM; k++) {
-        const int e = g * EPM + k;
-        if (e & 1) {
-          ps1 += ex[e];
-          asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(pw[e >> 1]) : "v"(ex[e - 1]), "v"(ex[e]));
-        } else {
-          ps0 += ex[e];
-        }
-      }
-    };
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < n_mfma; i++) {
-      if (i < NQK) {
-        if (FIRST) nxt[i] = load_k(i, k_imm_next);
-        else pv_ops[i] = load_v(i, v_imm);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pre[i], qf[i], acc, 0, 0, 0);
-      } else {
-        const int j = i - NQK;
-        nxt[j] = load_k(j, k_imm_next);
-        o_acc[j % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pv_ops[j], p_in[j / DB], o_acc[j % DB], 0, 0, 0);
-      }
-      if (i == 0) {
-        __builtin_amdgcn_sched_barrier(0);  // the first MFMA issues before any softmax work
-        stage_a(0);
-        stage_b(0);
-        stage_a(1);
-      }
-      if (i + 1 < n_mfma) stage_b(i + 1);
-      if (i + 2 < n_mfma) stage_a(i + 2);
-      stage_c(i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int h = 0; h < 2; h++) p_out[h] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * h], pw[4 * h + 1], pw[4 * h + 2], pw[4 * h + 3]});
-    float psum = ps0 + ps1;
-
-    if (__builtin_expect(__any(!(psum <= sum_cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
-      float tmax = s_in[0];
-#pragma unroll
-      for (int i = 1; i < 16; i++) tmax = fmaxf(tmax, s_in[i]);
-      tmax = half_swap_max(tmax);
-      float m_new = fmaxf(m_ref, tmax);
-      // Renewed: down as well, while what the row has summed so far stays below 2^40 in the new units (else weights of
-      // this sub-tile do not count beside it).  Both halves of a row decide alike.
-      if (__any(sum_cap < 0.f && m_ref > tmax)) {
-        const float lowered = half_swap_max(l_run) * __builtin_amdgcn_exp2f((m_ref - tmax) * c2);
-        if (sum_cap < 0.f && tmax > -INFINITY && lowered <= 0x1p40f) m_new = tmax;
-      }
-      const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * c2);  // m_ref = -inf -> 0; equal -> 1
-      const float a = (m_new == -INFINITY) ? 0.f : alpha;                 // (-inf) - (-inf) would be NaN
-      l_run *= a;
-#pragma unroll
-      for (int db = 0; db < DB; db++)
-#pragma unroll
-        for (int i = 0; i < 16; i++) o_acc[db][i] *= a;
-      m_ref = m_new;
-      mc = (m_ref == -INFINITY) ? 0.f : m_ref * c2;
-      sum_cap = (m_ref == -INFINITY) ? -1.f : kSumCap;
-      const float mc2 = mc;
-      float q0s = 0.f, q1s = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_in[i], c2, -mc2));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_in[i + 1], c2, -mc2));
-        p_out[i >> 3][i & 7] = (__bf16)p0;
-        p_out[i >> 3][(i & 7) + 1] = (__bf16)p1;
-        q0s += p0;
-        q1s += p1;
-      }
-      psum = q0s + q1s;
-    }
-    l_run += psum;
-    s_out = acc;
-#pragma unroll
-    for (int i = 0; i < NQK; i++) pre[i] = nxt[i];
-  };
-
-  // Tiles that are certain to lie before the last tile of the keys need neither the choice between
-  // the two offset sets nor the end-of-stream test.
-  auto issue_k_inner = [&](int slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < IPW; i++) dma16(k_next, k_off[i], slot * TILE_BYTES + (wave * IPW + i) * 1024);
-    k_next = uniform_ptr(k_next + k_tile_stride);
-    k_left--;
-  };
-  auto issue_v_inner = [&](int slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < IPW; i++) dma16(v_next, v_off[i], (NS + slot) * TILE_BYTES + (wave * IPW + i) * 1024);
-    v_next = uniform_ptr(v_next + v_tile_stride);
-    v_left--;
-  };
-
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(qf[ks]));  // Q is in registers before the loop
-  __builtin_amdgcn_s_waitcnt(0);
-  wg_barrier();  // B_0
-
-  // Ring protocol.  Sub-tile j = NSUB*u + kt lives in tile u.  Step j reads the V operands of
-  // sub-tile j-1 and the K operands of sub-tile j+2, so K_u is read in steps NSUB*u-2 ..
-  // NSUB*(u+1)-3 and V_u in steps NSUB*u+1 .. NSUB*(u+1).  Barrier B_u sits in front of step
-  // NSUB*u.  Right after B_w every wave issues the loads of K_{w+3} and V_{w+2} into the slots
-  // K_{w-1} and V_{w-2} vacated (all waves are past step NSUB*w-1); they are first read two
-  // tiles later, so each wave waits for its share (all but the newest 2*IPW loads, in order)
-  // right before B_{w+2}.
-  // S and P alternate between two register sets: even steps read sA / pB and write sB / pA,
-  // odd steps the other way round, so no step has to copy its results.
-  f32x16 sA, sB;
-  bf16x8 pA[2], pB[2];
-  constexpr unsigned SUBB = SUB * RB;  // bytes of one sub-tile inside a tile
-  // Step NSUB*u + kt of the tile in ring slot `su` (previous tile in sp, next in sn).
-  auto tile_step = [&](int u, auto su_c, auto kt_c, auto inner_c) __attribute__((always_inline)) {
-    constexpr int su = decltype(su_c)::value, kt = decltype(kt_c)::value;
-    constexpr bool INNER = decltype(inner_c)::value != 0;   // the step certainly runs and needs no mask
-    constexpr int sp = (su + NS - 1) % NS, sn = (su + 1) % NS;
-    constexpr unsigned v_imm = kt == 0 ? sp * TILE_BYTES + (NSUB - 1) * SUBB : su * TILE_BYTES + (kt - 1) * SUBB;
-    constexpr unsigned k_imm = kt + 2 < NSUB ? su * TILE_BYTES + (kt + 2) * SUBB : sn * TILE_BYTES + (kt + 2 - NSUB) * SUBB;
-    const int j = NSUB * u + kt;
-    if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
-      if (!INNER && __builtin_expect(j * SUB >= renew_at, 0)) {
-        sum_cap = -1.f;
-        renew_at += p.renew;
-      }
-      if (kt % 2 == 0) step(j * SUB, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sA, sB, pB, pA, inner_c);
-      else step(j * SUB, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sB, sA, pA, pB, inner_c);
-    }
-  };
-  if (n_tiles > 0) {
-    issue_k(3 % NS);
-    issue_v(2 % NS);
-    if (jw > 0) {
-      // S_0 = K_0[0:32] Q^T, plain (nothing to overlap with yet); operands of step 0 (sub-tile 1)
-#pragma unroll
-      for (int i = 0; i < 16; i++) sA[i] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_k(ks, 0), qf[ks], sA, 0, 0, 0);
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) pre[ks] = load_k(ks, SUBB);
-      // step 0: S_1 alongside the softmax of sub-tile 0 (no PV yet); prefetch the K operands of sub-tile 2
-      constexpr unsigned k_imm0 = 2 < NSUB ? 2 * SUBB : 1 * TILE_BYTES;
-      step(0, IC<1>{}, IC<0>{}, IC<(int)k_imm0>{}, sA, sB, pB, pA, IC<0>{});
-      // the other steps of tile 0 (tiles 0 and 1 sit in ring slots 0 and 1)
-      tile_step(0, IC<0>{}, IC<1>{}, IC<0>{});
-      if constexpr (NSUB > 2) {
-        tile_step(0, IC<0>{}, IC<2>{}, IC<0>{});
-        tile_step(0, IC<0>{}, IC<3>{}, IC<0>{});
-      }
-    }
-  }
-  // tiles u = 1 .. n_tiles: steps NSUB*u .. NSUB*u + NSUB-1 (the last tile index only has its first
-  // step, which folds in the PV product of the final sub-tile; its softmax sees only masked keys)
-  auto tile_body = [&](int u, auto slot_c, auto inner_c) __attribute__((always_inline)) {   // slot_c = u % NS
-    constexpr int su = decltype(slot_c)::value;
-    constexpr bool INNER = decltype(inner_c)::value != 0;
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * IPW));  // vmcnt only
-    wg_barrier();                                    // B_u
-    if (INNER) {
-      issue_k_inner((su + 3) % NS);   // K_{u+3}
-      issue_v_inner((su + 2) % NS);   // V_{u+2}
-    } else {
-      issue_k((su + 3) % NS);
-      issue_v((su + 2) % NS);
-    }
-    tile_step(u, slot_c, IC<0>{}, inner_c);
-    tile_step(u, slot_c, IC<1>{}, inner_c);
-    if constexpr (NSUB > 2) {
-      tile_step(u, slot_c, IC<2>{}, inner_c);
-      tile_step(u, slot_c, IC<3>{}, inner_c);
-    }
-  };
-  static_assert(NSUB == 2 || NSUB == 4, "tile_body spells out 2 or 4 steps");
-  // Inner tiles: every step of the tile runs in this wave without masking (all its keys are visible
-  // to all of the wave's rows and lie inside the K/V segment) and the tiles it puts on their way
-  // lie before the segment's last tile.  They take a tile body without the per-step tests; the
-  // remaining tiles take the general one.  Both bodies hold the same barrier and the same number
-  // of loads, so the waves of a workgroup may disagree about where the inner tiles end.
-  const int j_inner = min(jw_in, kmask_from >= 0 ? kmask_from / SUB : -1) - (NSUB - 1);   // last step of the tile must pass both tests
-  int u_inner = j_inner < 0 ? -1 : j_inner / NSUB;
-  u_inner = __builtin_amdgcn_readfirstlane(min(u_inner, last_tile - 4));   // loads issued in tile u reach tile u + 3
-  if (p.renew > 0 && p.renew < NS * BN) u_inner = -1;   // inner tiles look at renew_at once a group: once a tile costs 1 - 3 % of a long ring
-  // tiles 1 .. 3 (tile 0 was the prologue)
-  if (1 <= n_tiles) tile_body(1, IC<1 % NS>{}, IC<0>{});
-  if (2 <= n_tiles) tile_body(2, IC<2 % NS>{}, IC<0>{});
-  if (3 <= n_tiles) tile_body(3, IC<3 % NS>{}, IC<0>{});
-  // Groups of NS tiles: first the groups of inner tiles (up to where the reference is renewed, and on from there), then
-  // general ones to the end.
-  int u0 = NS;
-  while (u0 + NS - 1 <= u_inner) {
-    if (u0 * BN >= renew_at) {
-      sum_cap = -1.f;
-      renew_at += p.renew;
-    }
-    const int stop = min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NS - 1);
-    for (; u0 + NS - 1 <= stop; u0 += NS) {
-      tile_body(u0, IC<0>{}, IC<1>{});
-      tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{});
-      tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{});
-      tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{});
-    }
-  }
-  for (; u0 <= n_tiles; u0 += NS) {
-    tile_body(u0, IC<0>{}, IC<0>{});
-    if (u0 + 1 <= n_tiles) tile_body(u0 + 1, IC<1 % NS>{}, IC<0>{});
-    if (u0 + 2 <= n_tiles) tile_body(u0 + 2, IC<2 % NS>{}, IC<0>{});
-    if (u0 + 3 <= n_tiles) tile_body(u0 + 3, IC<3 % NS>{}, IC<0>{});
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // no LDS write of this workgroup may still be in flight at exit
-
-  // ---- epilogue: normalise, then store (or merge) with fully coalesced global accesses.
-  // In the accumulator layout a lane holds 4-float pieces of ONE row, 32 bytes apart from its
-  // neighbour's; each wave therefore transposes its 32 x D tile through a private, chunk-
-  // swizzled LDS region (the rings are dead by now) and reads it back row-major, one 16-byte
-  // chunk per lane, so that every global row is touched as one contiguous segment.
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();  // every wave is done with the K/V rings and none of its loads is still landing
-  {
-  // The lane is counted anew: held over the loop, it and what follows from it spill at D = 128, and a kernel with
-  // scratch starts about 1 us later.
-  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ql = lane & 31, hf = lane >> 5;
-  const int qrow = qw0 + ql;
-  constexpr int ROWB = 4 * D;                 // bytes of one fp32 output row
-  constexpr int CPRF = D / 4;                 // 16-byte chunks per fp32 row = lanes per row when reading back
-  constexpr int RPI_OUT = 64 / CPRF;          // rows one wave-wide access covers
-  char* const my = lds + wave * (32 * ROWB);
-  float* const my_w = reinterpret_cast<float*>(lds + EpiLds<D>::w) + wave * 32;     // Update weight of each of the wave's rows
-  int* const my_mode = reinterpret_cast<int*>(lds + EpiLds<D>::mode) + wave * 32;   // and its case
-  const float l_tot = half_swap_sum(l_run);
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const float lse_blk = l_tot > 0.f ? m_ref * p.scale + logf(l_tot) : -INFINITY;
-#pragma unroll
-  for (int db = 0; db < DB; db++)
-#pragma unroll
-    for (int g = 0; g < 4; g++) {
-      const int c = 8 * db + 2 * g + hf;  // 16-byte chunk of d = 32*db + 8*g + 4*hf
-      f32x4 o;
-#pragma unroll
-      for (int r = 0; r < 4; r++) o[r] = o_acc[db][4 * g + r] * inv;
-      *reinterpret_cast<f32x4*>(my + ql * ROWB + ((c ^ (ql & 15)) << 4)) = o;
-    }
-  if constexpr (PART) {
-    part_epilogue<D, EPI>(p, lds, lane, wave, q0, b, hq, pb.group, pb.part, n_live, lse_blk, l_tot != l_tot);
-    return;
-  }
-  if (EPI != kEpiMerge) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
-  if (EPI != kEpiMerge && hf == 0 && qrow < p.Sq)
-    p.lse[(int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (int64_t)qrow * p.l_ss] = lse_blk;
-  const int rr = lane / CPRF, cc = lane % CPRF;
-  constexpr int NIT = 32 / RPI_OUT;
-  const int64_t o_bh = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + chunk_row * p.o_ss + 4 * cc;
-  const int64_t l_bh = (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + chunk_row * p.l_ss;
-  if (EPI == kEpiMerge) {
-    // Out, Lse <- Update(block_out, block_lse) on the accumulators p.out / p.lse.  All of the
-    // wave's accumulator rows are fetched first (the O registers are free by now), so their
-    // latencies overlap instead of each load waiting behind the previous row's store.  Rows
-    // past Sq fetch the last valid row and are never stored.  The accumulator is touched once
-    // per launch, so it is read and written past the caches (non-temporal).
-    float* const acc_out = reinterpret_cast<float*>(p.out);
-    f32x4 x[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; it++) {
-      const int grow = min(qw0 + it * RPI_OUT + rr, p.Sq - 1);
-      if (CHUNKS && block == 0) x[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-      else x[it] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(acc_out + o_bh + (int64_t)grow * p.o_ss));
-    }
-    // The Update of a row is planned once, by the lanes that own the row in the accumulator layout
-    // (its two exponentials and its logarithm would otherwise be evaluated in every lane that
-    // blends a chunk of the row, 16 times per wave at D = 128), while the accumulator pieces are
-    // on their way.  The same lane reads the row's old lse and writes the new one.
-    {
-      const int64_t l_at = l_bh + (int64_t)min(qrow, p.Sq - 1) * p.l_ss;
-      UpdatePlan plq = plan_update(CHUNKS && block == 0 ? -INFINITY : p.lse[l_at], lse_blk);
-      if (CHUNKS && block == 0) plq.mode = 2;   // a first block is stored as it is, also where it is NaN (with lse -inf)
-      if (hf == 0) {
-        my_w[ql] = plq.w;
-        my_mode[ql] = plq.mode;
-        if (qrow < p.Sq) p.lse[l_at] = plq.new_lse;
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
-    // All LDS reads of the wave's rows go out first (block piece, weight and case of its row), then
-    // the pieces are blended and stored; the row address advances by a fixed step.
-    f32x4 ov[NIT];
-    UpdatePlan pl[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; it++) {
-      const int r = it * RPI_OUT + rr;
-      ov[it] = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
-      if (CHUNKS && block > 0 && p.chunk_bf16) {
-#pragma unroll
-        for (int e = 0; e < 4; e++) ov[it][e] = (float)(__bf16)ov[it][e];
-      }
-      pl[it].w = my_w[r];
-      pl[it].mode = my_mode[r];
-      pl[it].new_lse = 0.f;
-    }
-    float* dst = acc_out + o_bh + (int64_t)(qw0 + rr) * p.o_ss;
-    const int64_t dst_step = (int64_t)RPI_OUT * p.o_ss;
-#pragma unroll
-    for (int it = 0; it < NIT; it++) {
-      if (qw0 + it * RPI_OUT + rr < p.Sq) __builtin_nontemporal_store(apply_update(pl[it], x[it], ov[it]), reinterpret_cast<f32x4*>(dst));
-      dst += dst_step;
-    }
-  } else if (EPI == kEpiF32) {
-    f32x4 ov[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; it++) {
-      const int r = it * RPI_OUT + rr;
-      ov[it] = *reinterpret_cast<const f32x4*>(my + r * ROWB + ((cc ^ (r & 15)) << 4));
-    }
-    float* dst = reinterpret_cast<float*>(p.out) + o_bh + (int64_t)(qw0 + rr) * p.o_ss;
-    const int64_t dst_step = (int64_t)RPI_OUT * p.o_ss;
-#pragma unroll
-    for (int it = 0; it < NIT; it++) {
-      if (qw0 + it * RPI_OUT + rr < p.Sq) *reinterpret_cast<f32x4*>(dst) = ov[it];
-      dst += dst_step;
-    }
-  } else {
-    // bf16 rows are half as long: a lane converts two neighbouring chunks and stores 16 bytes
-    constexpr int LPR = D / 8;          // lanes per bf16 row
-    constexpr int RPI_B = 64 / LPR;     // rows one wave-wide store covers
-    constexpr int NIT_B = 32 / RPI_B;
-    const int rb = lane / LPR, cb = lane % LPR;
-    const int64_t ob_bh = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + 8 * cb;
-    f32x4 o0[NIT_B], o1[NIT_B];
-#pragma unroll
-    for (int it = 0; it < NIT_B; it++) {
-      const int r = it * RPI_B + rb;
-      o0[it] = *reinterpret_cast<const f32x4*>(my + r * ROWB + (((2 * cb) ^ (r & 15)) << 4));
-      o1[it] = *reinterpret_cast<const f32x4*>(my + r * ROWB + (((2 * cb + 1) ^ (r & 15)) << 4));
-    }
-    __bf16* dst = reinterpret_cast<__bf16*>(p.out) + ob_bh + (int64_t)(qw0 + rb) * p.o_ss;
-    const int64_t dst_step = (int64_t)RPI_B * p.o_ss;
-#pragma unroll
-    for (int it = 0; it < NIT_B; it++) {
-      bf16x8 ob;
-#pragma unroll
-      for (int k = 0; k < 4; k++) {
-        ob[k] = (__bf16)o0[it][k];
-        ob[4 + k] = (__bf16)o1[it][k];
-      }
-      if (qw0 + it * RPI_B + rb < p.Sq) *reinterpret_cast<bf16x8*>(dst) = ob;
-      dst += dst_step;
-    }
-  }
-  }
-  if constexpr (CHUNKS) __syncthreads();  // the next block's loads land where other waves may still read their rows
-  }
-}
-
-template <int D, int EPI, int FORM>
-hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
-  // K/V rings; the epilogue reuses them for kWaves private 32 x D fp32 tiles and its row tables
-  constexpr int ring_bytes = 2 * kRing * tile_keys<D>() * 2 * D;
-  constexpr int epi_bytes = FORM == kPart ? EpiLds<D>::bytes_part : EpiLds<D>::bytes;
-  constexpr int lds_bytes = ring_bytes > epi_bytes ? ring_bytes : epi_bytes;
-  static_assert(lds_bytes <= 160 * 1024, "LDS budget of one CU exceeded");
-  // Raising the dynamic-LDS limit is a per-function, per-device setting: done once for each
-  // device this process launches on (the flags are atomics, a repeated set is harmless).
-  constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices];
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&block_attn_kernel<D, EPI, FORM>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-    if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
-  }
-  return launch_kernel(block_attn_kernel<D, EPI, FORM>, grid, dim3(kThreads), lds_bytes, stream, p);
-}
-
-template <int FORM>
-hipError_t launch_typed(const AttnParams& p, int D, int epilogue, dim3 grid, hipStream_t stream) {
-  if constexpr (FORM != kChunks) {
-    if (epilogue == kEpiBf16) return D == 128 ? launch_one<128, kEpiBf16, FORM>(p, grid, stream) : launch_one<64, kEpiBf16, FORM>(p, grid, stream);
-    if (epilogue == kEpiF32) return D == 128 ? launch_one<128, kEpiF32, FORM>(p, grid, stream) : launch_one<64, kEpiF32, FORM>(p, grid, stream);
-  }
-  return D == 128 ? launch_one<128, kEpiMerge, FORM>(p, grid, stream) : launch_one<64, kEpiMerge, FORM>(p, grid, stream);
-}
-
 template <int D, int EPI>
 hipError_t launch_fold_typed(const AttnParams& p, dim3 grid, hipStream_t stream, hipEvent_t done) {
   if (p.n_parts <= 4) hipExtLaunchKernelGGL((fold_parts_kernel<D, EPI, 4>), grid, dim3(kFoldThreads), 0, stream, nullptr, done, 0, p);
@@ -1039,11 +102,18 @@ hipError_t launch_fold_typed(const AttnParams& p, dim3 grid, hipStream_t stream,
 template <int D>
 hipError_t launch_fold(const AttnParams& p, int epilogue, hipStream_t stream, hipEvent_t done) {
   constexpr int rows = kFoldThreads / (D / 4);   // rows one block folds
-  const int tile_rows = p.part_rows < kBM ? p.part_rows : kBM;
+  const int tile_rows = p.part_rows < p.bm ? p.part_rows : p.bm;
   const dim3 grid((unsigned)(p.B * p.Hkv * p.members), (unsigned)((tile_rows + rows - 1) / rows));
   if (epilogue == kEpiBf16) return launch_fold_typed<D, kEpiBf16>(p, grid, stream, done);
   if (epilogue == kEpiF32) return launch_fold_typed<D, kEpiF32>(p, grid, stream, done);
   return launch_fold_typed<D, kEpiMerge>(p, grid, stream, done);
+}
+
+template <int D>
+hipError_t launch_attn(const AttnParams& p, int epilogue, dim3 grid, hipStream_t stream) {
+  if (p.bm == 64) return launch_attn_shape<D, 2, 2>(p, epilogue, grid, stream);
+  if (p.bm == 128) return launch_attn_shape<D, 4, 2>(p, epilogue, grid, stream);
+  return launch_attn_shape<D, 8, 1>(p, epilogue, grid, stream);
 }
 
 }  // namespace
@@ -1051,23 +121,19 @@ hipError_t launch_fold(const AttnParams& p, int epilogue, hipStream_t stream, hi
 hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream, hipEvent_t fold_done) {
   const int64_t nbh = (int64_t)p.B * p.Hq;
   if (nbh * p.n_qtiles == 0) return hipSuccess;
-  if (p.n_qtiles > 65535) return hipErrorInvalidValue;   // grid y limit
+  if (p.n_qtiles > 65535 || (p.bm != 64 && p.bm != 128 && p.bm != 256)) return hipErrorInvalidValue;   // grid y limit
   dim3 grid((unsigned)nbh, (unsigned)p.n_qtiles);
   if (p.xcd_map == 2) grid = dim3(8u * (unsigned)p.n_qtiles, (unsigned)(nbh / 8));
   if (p.n_parts > 0) {
     if ((int64_t)p.units * p.members == 0) return hipSuccess;
-    const hipError_t e = launch_typed<kPart>(p, D, epilogue, dim3((unsigned)(((int64_t)p.units * p.members + 7) / 8 * 8)), stream);
-    if (e != hipSuccess || p.n_parts == 1) return e;
-    return D == 128 ? launch_fold<128>(p, epilogue, stream, fold_done) : launch_fold<64>(p, epilogue, stream, fold_done);
-  }
-  if (p.n_chunks > 0) {
+    grid = dim3((unsigned)(((int64_t)p.units * p.members + 7) / 8 * 8));
+  } else if (p.n_chunks > 0) {
     grid = dim3((unsigned)nbh, (unsigned)((p.chunk_end - p.chunk_begin) * p.n_qtiles));
     if (grid.y > 65535 || epilogue != kEpiMerge) return hipErrorInvalidValue;
-    return launch_typed<kChunks>(p, D, epilogue, grid, stream);
   }
-  return launch_typed<kPlain>(p, D, epilogue, grid, stream);
+  const hipError_t e = D == 128 ? launch_attn<128>(p, epilogue, grid, stream) : launch_attn<64>(p, epilogue, grid, stream);
+  if (e != hipSuccess || p.n_parts <= 1) return e;
+  return D == 128 ? launch_fold<128>(p, epilogue, stream, fold_done) : launch_fold<64>(p, epilogue, stream, fold_done);
 }
-
-int attn_rows_per_block() { return kBM; }
 
 }  // namespace tr

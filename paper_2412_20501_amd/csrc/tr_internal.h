@@ -8,6 +8,7 @@
 
 namespace tr {
 
+constexpr int kMaxRefs = 32;   // references of later segments that workgroups of fewer than 256 rows keep in LDS
 constexpr int kMaxParts = 16;  // parts the keys of one partitioned attention launch are cut into at most
 
 // Arguments of the block-attention kernel: raw pointers, element strides, sizes.
@@ -26,7 +27,8 @@ struct AttnParams {
   int causal;     // 0: every key visible; 1: key c visible to query r iff c <= r + causal_off
   int causal_off; // q_pos0 - k_pos0, clamped so that r + causal_off cannot overflow
   float scale;    // softmax scale (natural units)
-  int n_qtiles;   // ceil(Sq / rows per workgroup)
+  int bm;         // Query rows of a workgroup: 256, 128 or 64
+  int n_qtiles;   // ceil(Sq / bm)
   int xcd_map;    // 1: place all query tiles of a K/V head on one XCD (grid x = batch*head, y = query tile); 2: the same with grid x = XCD + 8 * query tile, y = head within the XCD
   int gq;         // query heads per K/V head (Hq / Hkv)
   int gq_log2;    // log2(gq) if gq is a power of two, else -1
@@ -84,7 +86,6 @@ struct MergeNParams {
 hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream, hipEvent_t fold_done = nullptr);
 hipError_t launch_merge(const MergeParams& p, bool blk_bf16, hipStream_t stream);
 hipError_t launch_merge_n(const MergeNParams& p, bool blk_bf16, hipStream_t stream);
-int attn_rows_per_block();  // query rows one attention workgroup covers
 
 // Events armed by tr_time_next_kernel for the calling thread; the next launch consumes them.
 struct TimingEvents { hipEvent_t start, stop; };

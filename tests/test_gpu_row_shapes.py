@@ -1,0 +1,126 @@
+"""Workgroups of 64 and 128 Query rows, whose waves share the keys out among themselves, against workgroups of 256 rows:
+the same inputs as one entry of a batch so large that the launch takes the latter.  Both round the same weights (one
+exponent reference for a row and segment, whatever the shape), so only fp32 sums differ: a few 2^-23 of values of size 1
+(out) and 10 (lse).  Sizes sit at the edges of row groups, workgroups, sub-tiles and tiles of keys, and where a segment's
+reference is renewed; the oracle stands beside the smallest."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import bits_to_dev, f64, max_abs, rand_bits, to_np
+
+pytestmark = pytest.mark.gpu
+MANY = 2048      # (batch, head, row tile) triples of 256 rows from which on every launch takes 256 rows
+
+
+def _qkv(Hq, Hkv, Sq, Sk, D, seed, token=False):
+    def tensor(H, S, s):
+        x = rand_bits((1, H, S, D), s)
+        return bits_to_dev(np.ascontiguousarray(x.transpose(0, 2, 1, 3))).permute(0, 2, 1, 3) if token else bits_to_dev(x)
+    return tensor(Hq, Sq, seed), tensor(Hkv, Sk, seed + 1), tensor(Hkv, Sk, seed + 2)
+
+
+def _new(B, H, S, D, dtype=torch.float32, lse=float("nan")):
+    return torch.full((B, H, S, D), float("nan"), device="cuda", dtype=dtype), torch.full((B, H, S), lse, device="cuda")
+
+
+def _agree(few, many, tol=1e-5):
+    (o, l), (bo, bl) = few, many
+    assert torch.equal(torch.isneginf(l[0]), torch.isneginf(bl[-1]))
+    seen = ~torch.isneginf(l[0])
+    worst = float((o[0].float() - bo[-1].float()).abs().max()), float((l[0] - bl[-1])[seen].abs().max()) if bool(seen.any()) else 0.0
+    print("out, lse:", worst)
+    assert max(worst) <= tol
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,seg,n,D,token", [
+    (1, 1, 1, 1, 64, False),
+    (2, 1, 33, 2, 128, True),          # a reference every sub-tile
+    (1, 1, 96, 4, 128, False),         # segments of three sub-tiles: their first one belongs to either key group
+    (3, 1, 65, 1, 64, True),           # one row in the second workgroup
+    (2, 2, 129, 1, 128, False),
+    (2, 1, 191, 3, 64, False),
+    (1, 1, 128, 33, 128, False),       # as many later references as are kept
+    (8, 2, 1024, 2, 128, False),       # renewed between groups of inner tiles
+    (4, 4, 1536, 2, 64, False),
+    (24, 8, 1000, 1, 64, True),        # 128 rows
+    (20, 20, 768, 1, 128, False),
+])
+def test_rings(lib, Hq, Hkv, seg, n, D, token, causal):
+    S = seg * n
+    q, k, v = _qkv(Hq, Hkv, S, S, D, 700, token)
+    few = _new(1, Hq, S, D)
+    lib.tr_ring_attn(q, k, v, n, causal, *few)
+    B = -(-MANY // (Hq * -(-S // 256)))
+    many = _new(B, Hq, S, D)
+    lib.tr_ring_attn(q.expand(B, -1, -1, -1), k.expand(B, -1, -1, -1), v.expand(B, -1, -1, -1), n, causal, *many)
+    torch.cuda.synchronize()
+    _agree(few, many)
+
+
+@pytest.mark.parametrize("Hq,Hkv,seg,n", [(1, 1, 501, 3), (2, 1, 700, 4), (2, 2, 32, 34)])
+def test_rings_renewed_elsewhere(lib, Hq, Hkv, seg, n):
+    """Segments that end between groups of inner tiles, or of which there are too many: the references differ, so the
+    weights' bf16 roundings do, by 2^-8 of a value at the worst and a few 1e-4 of its norm."""
+    S, D = seg * n, 128
+    q, k, v = _qkv(Hq, Hkv, S, S, D, 710)
+    ref = oracle.attention_full(f64(q.cpu().view(torch.int16).numpy().view(np.uint16)), f64(k.cpu().view(torch.int16).numpy().view(np.uint16)),
+                                f64(v.cpu().view(torch.int16).numpy().view(np.uint16)), D ** -0.5, True)
+    out, lse = _new(1, Hq, S, D)
+    lib.tr_ring_attn(q, k, v, n, True, out, lse)
+    torch.cuda.synchronize()
+    assert max_abs(to_np(out), ref[0]) <= 1e-2 and max_abs(to_np(lse), ref[1]) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, None])   # None: merged into accumulators
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk,D,off", [
+    (1, 1, 1, 1, 64, None),
+    (2, 1, 31, 33, 128, None),         # one sub-tile and one key, the second key group's
+    (2, 2, 64, 64, 64, 0),
+    (1, 1, 130, 500, 128, 370),        # causal, the last row sees the last key
+    (3, 3, 70, 129, 64, 20),           # keys that no row sees
+    (2, 1, 200, 450, 128, -90),        # rows that see none
+    (12, 4, 500, 512, 64, 12),         # 128 rows
+    (16, 8, 700, 300, 128, None),
+])
+def test_steps(lib, Hq, Hkv, Sq, Sk, D, off, dtype):
+    if dtype is None and off is not None:
+        pytest.skip("the merging step has no causal rule at arbitrary positions")
+    q, k, v = _qkv(Hq, Hkv, Sq, Sk, D, 720, True)
+    B = -(-MANY // (Hq * -(-Sq // 256)))
+
+    def run(B, q, k, v):
+        out, lse = _new(B, Hq, Sq, D, dtype or torch.float32)
+        if dtype is None:
+            gen = torch.Generator(device="cuda").manual_seed(5)
+            out.copy_(torch.randn((1, Hq, Sq, D), device="cuda", generator=gen))
+            lse.copy_(torch.randn((1, Hq, Sq), device="cuda", generator=gen) * 4)
+            lse[:, 0, 0] = float("-inf")
+            out[:, 0, 0] = float("nan")
+            lib.tr_block_attn_merge(q, k, v, lib.TR_MASK_NONE, 0.1, out, lse)
+        elif off is None:
+            lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, 0.1, out, lse)
+        else:
+            lib.tr_block_attn_causal_at(q, k, v, max(off, 0), max(-off, 0), 0.1, out, lse)
+        return out, lse
+
+    few, many = run(1, q, k, v), run(B, *(x.expand(B, -1, -1, -1) for x in (q, k, v)))
+    torch.cuda.synchronize()
+    _agree(few, many, 2 ** -8 * 4 if dtype is torch.bfloat16 else 1e-5)   # a bf16 ulp of values below 4, where a sum lies at a tie
+
+
+def test_scores_beyond_the_fast_path(lib):
+    """Scores 40 wide: references are raised per key group and the groups' sums meet at different ones."""
+    S, D = 320, 64
+    q, k, v = _qkv(2, 2, S, S, D, 730)
+    q, k = (q.float() * 6).bfloat16(), (k.float() * 6).bfloat16()
+    out, lse = _new(1, 2, S, D)
+    lib.tr_ring_attn(q, k, v, 1, False, out, lse)
+    torch.cuda.synchronize()
+    s = (q.double() * D ** -0.5) @ k.double().transpose(-1, -2).contiguous()
+    want = torch.softmax(s, -1) @ v.double()
+    # all weight on a few keys: 2^-8 of the largest value
+    assert float((out - want).abs().max()) <= 2 ** -8 * float(v.abs().max()) * 1.02 + 1e-4
+    assert float((lse - torch.logsumexp(s, -1)).abs().max()) <= 1e-3
