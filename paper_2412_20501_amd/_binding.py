@@ -1,4 +1,4 @@
-"""ctypes binding of libtokenring.so: argument marshalling only.
+"""Python names of libtokenring.so: argument marshalling only.
 
 Every step of the path runs in the HIP kernels behind the C ABI declared in
 include/tokenring.h; torch tensors are used here for device memory and streams alone.
@@ -87,31 +87,11 @@ def _load():
 
 _lib = _load()
 
-# The calls below hand descriptors over as packed bytes: a call of the smallest sizes is bound by its
-# marshalling (five ctypes structures and a stream object cost 8 us a call, more than the kernel's own 8 us;
-# packed and with the raw stream handle about half), and untyped pointer arguments take bytes as they are.
-_V, _I, _F = ctypes.c_void_p, ctypes.c_int, ctypes.c_float
+# The calls below go through the extension module (csrc/binding.cpp), which makes the descriptors itself.
+from . import _native  # noqa: E402  (behind _load(): the module needs the library)
+
 _DTYPES = {torch.bfloat16: TR_BF16, torch.float32: TR_F32}
-_DESC = struct.Struct("Pi4x8q")   # a tr_tensor and one word behind it (the stride of D)
-_DESC_PACK = _DESC.pack
-
-
-def _bind(name, *argtypes):
-    f = getattr(_calls, name)
-    f.argtypes, f.restype = list(argtypes), ctypes.c_int
-    return f
-
-
-_calls = ctypes.CDLL(LIB_PATH)   # function objects of their own: those of raw_lib() keep their typed arguments
-_block_attn = _bind("tr_block_attn", _V, _V, _V, _I, _F, _V, _V, _V)
-_block_attn_causal_at = _bind("tr_block_attn_causal_at", _V, _V, _V, ctypes.c_int64, ctypes.c_int64, _F, _V, _V, _V)
-_block_attn_merge = _bind("tr_block_attn_merge", _V, _V, _V, _I, _F, _V, _V, _V)
-_merge = _bind("tr_merge", _V, _V, _V, _V, _V)
-_merge_n = _bind("tr_merge_n", _V, _V, _V, _V, _I, _I, _V)
-_ring_attn = _bind("tr_ring_attn", _V, _V, _V, _I, _I, _V, _V, _F, _V, ctypes.c_size_t, _V)
-_ring_attn_noalloc = _bind("tr_ring_attn_noalloc", _V, _V, _V, _I, _I, _V, _V, _F, _V)
-_ring_attn_sched = _bind("tr_ring_attn_sched", _V, _V, _V, _I, _I, _I, _I, _V, _V, _F, _V)
-_ring_attn_blocks = _bind("tr_ring_attn_blocks", _V, _V, _V, _I, _I, _V, _V, _F, _I, _V, ctypes.c_size_t, _V)
+_DESC_PACK = struct.Struct("Pi4x8q").pack   # a tr_tensor and one word behind it (the stride of D)
 
 
 def raw_lib():
@@ -147,7 +127,7 @@ def desc(t: torch.Tensor) -> TrTensor:
 
 
 def _pack(t: torch.Tensor) -> bytes:
-    """The descriptor of desc() as bytes, same checks."""
+    """The descriptor of desc() as bytes, same checks: for what the extension module leaves to Python."""
     dt = _DTYPES.get(t.dtype)
     if dt is None:
         raise TypeError(f"unsupported dtype {t.dtype}")
@@ -162,13 +142,6 @@ def _pack(t: torch.Tensor) -> bytes:
     return _DESC_PACK(t.data_ptr(), dt, *t.shape, 1, *stride, 1)
 
 
-def _pointers(descs):
-    """Host array of pointers to packed descriptors, and the buffer that keeps them."""
-    buf = ctypes.create_string_buffer(b"".join(descs), max(1, len(descs) * _DESC.size))
-    base = ctypes.addressof(buf)
-    return (_V * max(1, len(descs)))(*range(base, base + len(descs) * _DESC.size, _DESC.size)), buf
-
-
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
@@ -180,30 +153,31 @@ def _stream(stream) -> int:
     return torch.cuda.current_stream().cuda_stream
 
 
+_native.bind(_pack, torch.cuda.is_initialized, getattr(torch._C, "_cuda_getDevice", None), _raw_stream, _stream)
+
+
 def tr_version() -> str:
     return _lib.tr_version().decode()
 
 
 def tr_block_attn(q, k, v, mask_kind, scale, out, lse, stream=None):
     """block_out, block_lse <- Attention(Q, K, V) into `out`, `lse` (see tokenring.h)."""
-    _check(_block_attn(_pack(q), _pack(k), _pack(v), int(mask_kind), float(scale), _pack(out), _pack(lse), _stream(stream)))
+    _check(_native.block_attn(q, k, v, mask_kind, scale, out, lse, stream))
 
 
 def tr_block_attn_causal_at(q, k, v, q_pos0, k_pos0, scale, out, lse, stream=None):
     """Block step with the causal rule at chunk positions q_pos0 / k_pos0 (see tokenring.h)."""
-    _check(_block_attn_causal_at(_pack(q), _pack(k), _pack(v), int(q_pos0), int(k_pos0), float(scale),
-                                        _pack(out), _pack(lse), _stream(stream)))
+    _check(_native.block_attn_causal_at(q, k, v, q_pos0, k_pos0, scale, out, lse, stream))
 
 
 def tr_block_attn_merge(q, k, v, mask_kind, scale, out_acc, lse_acc, stream=None):
     """Block step whose epilogue applies the Update to the fp32 accumulators (see tokenring.h)."""
-    _check(_block_attn_merge(_pack(q), _pack(k), _pack(v), int(mask_kind), float(scale), _pack(out_acc), _pack(lse_acc),
-                                    _stream(stream)))
+    _check(_native.block_attn_merge(q, k, v, mask_kind, scale, out_acc, lse_acc, stream))
 
 
 def tr_merge(out_acc, lse_acc, block_out, block_lse, stream=None):
     """Out, Lse <- Update(block_out, block_lse), in place on out_acc / lse_acc."""
-    _check(_merge(_pack(out_acc), _pack(lse_acc), _pack(block_out), _pack(block_lse), _stream(stream)))
+    _check(_native.merge(out_acc, lse_acc, block_out, block_lse, stream))
 
 
 def tr_merge_n(out, lse, block_outs, block_lses, accumulate=False, stream=None):
@@ -211,9 +185,7 @@ def tr_merge_n(out, lse, block_outs, block_lses, accumulate=False, stream=None):
     n = len(block_outs)
     if len(block_lses) != n:
         raise ValueError("block_outs and block_lses differ in length")
-    bo_arr, _keep_o = _pointers([_pack(t) for t in block_outs])
-    bl_arr, _keep_l = _pointers([_pack(t) for t in block_lses])
-    _check(_merge_n(_pack(out), _pack(lse), bo_arr, bl_arr, n, int(bool(accumulate)), _stream(stream)))
+    _check(_native.merge_n(out, lse, block_outs, block_lses, accumulate, stream))
 
 
 def tr_time_next_kernel(start_event, stop_event):
@@ -234,8 +206,7 @@ def tr_time_next_kernel(start_event, stop_event):
 
 def tr_ring_attn_sched(q, k, v, n_devices, causal, schedule, out, lse, scale=0.0, n_inner=1, stream=None):
     """tr_ring_attn under a selectable schedule (TR_SCHED_*): the same result on one GPU (see tokenring.h)."""
-    _check(_ring_attn_sched(_pack(q), _pack(k), _pack(v), int(n_devices), int(bool(causal)), int(schedule), int(n_inner),
-                                   _pack(out), _pack(lse), float(scale), _stream(stream)))
+    _check(_native.ring_attn_sched(q, k, v, n_devices, causal, schedule, n_inner, out, lse, scale, stream))
 
 
 def tr_ring_attn_blocks_workspace_bytes(q, n_chunks, block_dtype) -> int:
@@ -244,9 +215,7 @@ def tr_ring_attn_blocks_workspace_bytes(q, n_chunks, block_dtype) -> int:
 
 def tr_ring_attn_blocks(q, k, v, n_chunks, causal, out, lse, block_dtype, workspace, scale=0.0, stream=None):
     """Algorithm 1 with the block result of every step as block_dtype (TR_F32 / TR_BF16) on its way to the Update (see tokenring.h)."""
-    _check(_ring_attn_blocks(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
-                                    float(scale), int(block_dtype), workspace.data_ptr(),
-                                    workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(_native.ring_attn_blocks(q, k, v, n_chunks, causal, out, lse, scale, block_dtype, workspace.data_ptr(), workspace.numel() * workspace.element_size(), stream))
 
 
 def tr_schedule_steps(schedule, n_devices, causal, n_inner=1):
@@ -269,14 +238,12 @@ def tr_ring_attn(q, k, v, n_chunks, causal, out, lse, scale=0.0, workspace=None,
     `workspace`: None, or a caller-owned uint8 device tensor of at least
     tr_ring_attn_workspace_bytes(q, n_chunks) bytes, which is checked and left alone.
     """
-    ws_ptr, ws_bytes = None, 0
+    ws_ptr = ws_bytes = 0
     if workspace is not None:
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    _check(_ring_attn(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
-                             float(scale), ws_ptr, ws_bytes, _stream(stream)))
+    _check(_native.ring_attn(q, k, v, n_chunks, causal, out, lse, scale, ws_ptr, ws_bytes, stream))
 
 
 def tr_ring_attn_noalloc(q, k, v, n_chunks, causal, out, lse, scale=0.0, stream=None):
     """tr_ring_attn with the promise that nothing is allocated, for problems up to a limit (see tokenring.h)."""
-    _check(_ring_attn_noalloc(_pack(q), _pack(k), _pack(v), int(n_chunks), int(bool(causal)), _pack(out), _pack(lse),
-                                     float(scale), _stream(stream)))
+    _check(_native.ring_attn_noalloc(q, k, v, n_chunks, causal, out, lse, scale, stream))

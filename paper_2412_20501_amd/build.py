@@ -12,6 +12,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +20,7 @@ ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(PKG_DIR, "libtokenring.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_native.so")   # Python module over it
 SOURCES = ["api.hip", "merge.hip", "block_attn.hip"] + [f"block_attn_d{d}_{r}rows.hip" for d in (128, 64) for r in (256, 128, 64)]
 
 HIPCC_FLAGS = [
@@ -37,7 +39,7 @@ def source_hash() -> str:
     for folder in (CSRC, INCLUDE):
         for name in sorted(os.listdir(folder)):
             path = os.path.join(folder, name)
-            if os.path.isfile(path) and name.endswith((".hip", ".h", ".hpp", ".inc")):
+            if os.path.isfile(path) and name.endswith((".hip", ".cpp", ".h", ".hpp", ".inc")):
                 h.update(name.encode() + b"\0")
                 with open(path, "rb") as f:
                     h.update(f.read())
@@ -55,9 +57,9 @@ def library_hash(path: str = LIB_PATH):
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile every kernel source into one shared library; returns its path."""
+    """Compile every kernel source into one shared library, and the Python module over it; returns the library's path."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    tmp = LIB_PATH + f".tmp{os.getpid()}"
+    tmp, tmp_binding = LIB_PATH + f".tmp{os.getpid()}", BINDING_PATH + f".tmp{os.getpid()}"
     objects = [f"{tmp}.{s}.o" for s in SOURCES]
     compile_ = [hipcc, *HIPCC_FLAGS, f'-DTR_SOURCE_HASH_STR="{source_hash()}"', "-I", INCLUDE, "-I", CSRC, "-c"]
 
@@ -68,26 +70,36 @@ def build_library(verbose: bool = False) -> str:
         noise = "is not a recognized feature for this target"
         err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
         if res.returncode != 0:
-            raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
+            raise RuntimeError(f"{os.path.basename(cmd[0])} failed ({res.returncode}):\n{err}")
         if verbose and err.strip():
             print(err, file=sys.stderr)
 
+    import torch   # its headers and libraries
+    torch_root = os.path.dirname(torch.__file__)
+    cxx, binding = os.environ.get("CXX", "g++"), tmp_binding + ".o"
+    compile_binding = [cxx, "-O2", "-std=c++17", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                       f'-DTR_SOURCE_HASH_STR="{source_hash()}"', "-I", INCLUDE, "-isystem", sysconfig.get_paths()["include"],
+                       "-isystem", os.path.join(torch_root, "include"), "-c", os.path.join(CSRC, "binding.cpp"), "-o", binding]
+    commands = [[*compile_, os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objects)] + [compile_binding]
     try:
-        with ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:   # one compiler per source
-            for done in [pool.submit(run, [*compile_, os.path.join(CSRC, s), "-o", o]) for s, o in zip(SOURCES, objects)]:
+        with ThreadPoolExecutor(min(len(commands), os.cpu_count() or 1, 8)) as pool:   # one compiler per source
+            for done in [pool.submit(run, cmd) for cmd in commands]:
                 done.result()
         run([hipcc, *HIPCC_FLAGS, "-shared", "-o", tmp, *objects])
+        os.replace(tmp, LIB_PATH)      # atomic: a concurrent reader never sees a half-written library
+        run([cxx, "-shared", "-o", tmp_binding, binding, "-L", os.path.join(torch_root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+             "-L", PKG_DIR, "-l:" + os.path.basename(LIB_PATH), "-Wl,-rpath,$ORIGIN"])
+        os.replace(tmp_binding, BINDING_PATH)
     finally:
-        for o in objects:
+        for o in (*objects, binding, tmp, tmp_binding):
             if os.path.exists(o):
                 os.remove(o)
-    os.replace(tmp, LIB_PATH)      # atomic: a concurrent reader never sees a half-written library
     return LIB_PATH
 
 
 def ensure_built() -> str:
     """Build unless a library compiled from exactly the sources on disk is already there."""
-    if library_hash() == source_hash():
+    if library_hash() == source_hash() == library_hash(BINDING_PATH):
         return LIB_PATH
     return build_library()
 
