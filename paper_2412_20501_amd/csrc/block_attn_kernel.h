@@ -392,9 +392,10 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   // the swizzle maps there.  Addresses are a wave-uniform 64-bit tile base (SGPR pair) plus a
   // per-lane 32-bit byte offset that never changes, so issuing a tile costs no vector
   // arithmetic.  Rows past the end of the keys re-read the last key (they are masked later):
-  // the last, possibly partial, tile has its own clamped offsets, and tiles beyond it (the
-  // ring runs ahead of the loop) re-read the last tile.
-  const int last_tile = (Sk - 1) / BN;
+  // the last, possibly partial, tile has its own clamped offsets.  Nothing is loaded beyond the last tile the workgroup
+  // sees: what the ring holds there takes part in scores that are masked and in no product with V.  (A ring that ran ahead of its end
+  // re-read the last tile five times, and the workgroup waited for that before it ended: 64 rows on 64 keys 6.47 -> 5.88 us.)
+  const int last_tile = n_tiles - 1;
   unsigned k_off[IPW], v_off[IPW], k_off_last[IPW], v_off_last[IPW];
 #pragma unroll
   for (int i = 0; i < IPW; i++) {
@@ -420,26 +421,27 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
     const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base + lds_off);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(off), "s"(base) : "memory");
   };
-  // Tiles are issued strictly in order, so the tile base is a running wave-uniform pointer that
-  // stops advancing at the last tile (later issues re-read it with the clamped offsets).
+  // Tiles are issued strictly in order, so the tile base is a running wave-uniform pointer.
   const __bf16* k_next = uniform_ptr(kg);
   const __bf16* v_next = uniform_ptr(vg);
   const int64_t k_tile_stride = (int64_t)BN * p.k_ss, v_tile_stride = (int64_t)BN * p.v_ss;
   int k_left = last_tile, v_left = last_tile;  // tiles still ahead of the pointer
   auto issue_k = [&](int slot) __attribute__((always_inline)) {
-    const bool last = k_left <= 0;
+    if (k_left < 0) return;
+    const bool last = k_left == 0;
 #pragma unroll
     for (int i = 0; i < IPW; i++)
       dma16(k_next, last ? k_off_last[i] : k_off[i], slot * TILE_BYTES + (wave * IPW + i) * 1024);
-    k_next = uniform_ptr(k_next + (last ? 0 : k_tile_stride));
+    k_next = uniform_ptr(k_next + k_tile_stride);
     k_left--;
   };
   auto issue_v = [&](int slot) __attribute__((always_inline)) {
-    const bool last = v_left <= 0;
+    if (v_left < 0) return;
+    const bool last = v_left == 0;
 #pragma unroll
     for (int i = 0; i < IPW; i++)
       dma16(v_next, last ? v_off_last[i] : v_off[i], (NS + slot) * TILE_BYTES + (wave * IPW + i) * 1024);
-    v_next = uniform_ptr(v_next + (last ? 0 : v_tile_stride));
+    v_next = uniform_ptr(v_next + v_tile_stride);
     v_left--;
   };
 
@@ -753,7 +755,7 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   // Right after B_w every wave issues the loads of K_{w+3} and V_{w+2} into the slots
   // K_{w-1} and V_{w-2} vacated (all waves are past step NSW*w-1); they are first read two
   // tiles later, so each wave waits for its share (all but the newest 2*IPW loads, in order)
-  // right before B_{w+2}.  NSW = 1: K_u is read in step u-2, so K_{w+4} goes into the slot of K_w, which
+  // right before B_{w+2} (towards the end, where nothing more is issued, all of it).  NSW = 1: K_u is read in step u-2, so K_{w+4} goes into the slot of K_w, which
   // all waves have left behind B_w from w = 2 on; K_0 and K_1 are read before step 0, so the
   // slot of K_0 is free at B_1, where K_4 is issued in front of K_5.  K_{w+2} and V_{w-1}, read first in step w, were issued
   // before the newest 2*IPW loads at B_w.
@@ -831,7 +833,8 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   auto tile_body = [&](int u, auto slot_c, auto inner_c, auto second_c) __attribute__((always_inline)) {   // slot_c = u % NS; second_c: u = 1
     constexpr int su = decltype(slot_c)::value;
     constexpr bool INNER = decltype(inner_c)::value != 0;
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * IPW));  // vmcnt only
+    if (INNER || u + KA - 1 <= last_tile) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * IPW));  // vmcnt only
+    else __builtin_amdgcn_s_waitcnt(0x0F70);         // the tile before issued no K: everything that is on its way
     wg_barrier();                                    // B_u
     if (KA == 4 && decltype(second_c)::value) issue_k(0);   // K_4
     if (INNER) {
