@@ -269,70 +269,92 @@ PartRegion* take_region(PartPool& pool, hipStream_t stream) {
   return r;
 }
 
-// Query rows of a workgroup.  256 (eight row groups) is the best use of a full chip.  A launch that would leave compute
-// units idle runs workgroups of 128 or 64 rows whose waves also share the keys out among themselves: a tile
-// of keys then takes its workgroup about a half and a third of the time, and there are twice and four times as many workgroups.
+// Shape of a launch's workgroups.  8 x 1 (256 rows) has the least traffic for its products and is the best use of a full chip
+// over long key ranges.  4 x 1, several to a compute unit, hides set-up and epilogue and ends more evenly.  A launch that would leave
+// compute units idle runs 4 x 2 or 2 x 2, whose waves also share the keys out among themselves.
 // Chosen by an estimate of the launch's time (us) from measured costs: set-up and epilogue of a workgroup, and a tile of keys
-// (64 at D 128, 128 at D 64) on an idle chip, on a full one, and with at most half of the waves at work.
-// Both sides of the line, us for 256 / 128 / 64 rows: 8 heads of 256 rows 12.5 / 10.9 / 8.6; 16 of 1024 27.7 / 21.8 / 18.1;
-// 8 of 4096 under the causal rule 76.8 / 52.4 / 47.9; 32 of 1024 29.6 / 25.2 / 30.4; 64 of 1024 40.1 / 48.7 / 58.7; one of 8192 at D 64 105 / 60 / 45;
-// 24 of 1777 at D 64 34.8 / 41.5 / 44.9, under the causal rule 30.9 / 22.6 / 29.2.
-// p holds the launch's parts and chunks; pack: the rows are those of a K/V head's whole group.
-int choose_rows(const tr::AttnParams& p, int D, bool pack) {
+// (64 at D 128, 128 at D 64) on an idle and on a full chip, on a compute unit with one, two, three workgroups, and with at most half of
+// the waves at work.  Both sides of the lines, us for 8 x 1 / 4 x 1 / 4 x 2 / 2 x 2 at D 128: 8 heads of 256 rows 12.5 / - / 10.9 / 8.6; 16 of
+// 1024 27.7 / 21.6 / 21.8 / 18.1; 32 of 1024 29.2 / 24.5 / 25.2 / 30.4; 64 of 1024 39.1 / 39.2 / 48.7 / 58.7, under the causal rule 30.8 / 28.0 / 34.7 / 43.9;
+// 8 of 4096 84 / 71 / 69 / 85; 24 of 1777 51.2 / 51.5 / 59.7 / 64.9, under the causal rule 42.4 / 35.5 / 33.2 / 40.9; 16 of 8192 438 / 460.
+// p holds the launch's parts and chunks; pack: the rows are those of a K/V head's whole group; out_bytes: of an output element.
+int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes) {
   const int refs = p.renew > 0 ? (p.Sk - 1) / p.renew : 0;
   const int64_t rows = pack ? (int64_t)p.gq * p.Sq : p.Sq, heads = (int64_t)p.B * (pack ? p.Hkv : p.Hq);
-  if (refs > tr::kMaxRefs || p.Sk == 0 || heads * ((rows + kMaxRows - 1) / kMaxRows) >= 4 * kCUs) return kMaxRows;
-  struct Shape { int rows; double fix, idle, busy, fix_few, few; };
-  static const Shape shapes[2][3] = {{{256, 7.5, 1.52, 2.15, 5.2, 1.0}, {128, 7.1, 0.83, 1.09, 6.0, 0.65}, {64, 5.8, 0.61, 0.72, 5.4, 0.6}},
-                                     {{256, 8.3, 1.1, 1.75, 6.2, 0.7}, {128, 9.0, 0.59, 0.93, 7.5, 0.5}, {64, 7.0, 0.47, 0.57, 6.5, 0.45}}};
+  if (p.Sk == 0) return tr::kShape8x1;
+  struct Cost { double fix, idle, busy, two, three, fix_few, few, block; };   // block: of a later block of the chunk form, in units of fix
+  static const Cost costs[2][4] = {{{7.5, 1.52, 2.03, 0, 0, 5.2, 1.0, 1.7}, {6.5, 1.0, 1.12, 2.03, 2.96, 5.6, 0.95, 1.3},
+                                    {7.1, 0.83, 1.09, 0, 0, 6.0, 0.65, 0.75}, {5.8, 0.61, 0.72, 0, 0, 5.4, 0.6, 0.75}},
+                                   {{8.3, 1.1, 1.67, 0, 0, 6.2, 0.7, 1.7}, {8.5, 0.7, 0.95, 1.78, 0, 6.8, 0.65, 1.3},
+                                    {9.0, 0.59, 0.93, 0, 0, 7.5, 0.5, 0.75}, {7.0, 0.47, 0.57, 0, 0, 6.5, 0.45, 0.75}}};
   const double tile_keys = D == 64 ? 128.0 : 64.0;
   const int64_t part = p.n_parts > 1 ? p.part_keys : p.Sk;
   const double later = p.n_chunks > 1 ? p.n_chunks - 1 : 0;   // blocks behind its first of the longest workgroup
-  int best = kMaxRows;
+  const double blocks = p.causal ? later / 2 : later, chunks = later + 1;   // later blocks of the average workgroup
+  const double memory = (double)(heads * rows) * chunks * D * (2 + (p.n_parts > 1 ? 4 : out_bytes)) / 5.2e6;   // Query rows in, result out
+  int best = tr::kShape8x1;
   double t_best = 0;
-  for (const Shape& s : shapes[D == 128]) {
-    const int64_t tiles = (rows + s.rows - 1) / s.rows;
+  for (int shape = 0; shape < 4; shape++) {
+    const Cost& c = costs[D == 128][shape];
+    const int bm = tr::shape_rows(shape), per_cu = shape != tr::kShape4x1 ? 1 : D == 64 ? 3 : 2;
+    const bool groups = shape >= tr::kShape4x2;
+    const int64_t tiles = (rows + bm - 1) / bm;
+    if (groups && (refs > tr::kMaxRefs || heads * tiles >= 8 * kCUs)) continue;
     int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
     if (p.causal && pack) {
       least = most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, (int64_t)p.Sq + p.causal_off));
       sum = most * tiles;
     } else if (p.causal) {   // tile t sees the keys below (t + 1) * rows + causal_off
       most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, rows + p.causal_off));
-      least = std::max<int64_t>(0, std::min<int64_t>(most, s.rows + (int64_t)p.causal_off));
-      const int64_t off = p.causal_off, all = std::min(tiles, std::max<int64_t>(0, (p.Sk - off + s.rows - 1) / s.rows - 1));
-      const int64_t none = std::min(all, off < 0 ? -off / s.rows : 0);   // tiles [none, all) see some, [all, tiles) every key
-      sum = (all * (all + 1) - none * (none + 1)) / 2 * s.rows + (all - none) * off + (tiles - all) * p.Sk;
+      least = std::max<int64_t>(0, std::min<int64_t>(most, bm + (int64_t)p.causal_off));
+      const int64_t off = p.causal_off, all = std::min(tiles, std::max<int64_t>(0, (p.Sk - off + bm - 1) / bm - 1));
+      const int64_t none = std::min(all, off < 0 ? -off / bm : 0);   // tiles [none, all) see some, [all, tiles) every key
+      sum = (all * (all + 1) - none * (none + 1)) / 2 * bm + (all - none) * off + (tiles - all) * p.Sk;
     }
-    const double blocks = p.causal ? later / 2 : later, chunks = later + 1;   // later blocks of the average workgroup
-    const double count = (double)(heads * tiles) * chunks;
-    double n = count, total = ((double)(heads * sum) + (double)(heads * tiles) * blocks * p.Sk) * chunks / tile_keys;
+    double n = (double)(heads * tiles) * chunks, total = ((double)(heads * sum) + (double)(heads * tiles) * blocks * p.Sk) * chunks / tile_keys;
     if (p.n_parts > 1) n *= std::max(1.0, p.causal ? (double)sum / (double)(tiles * part) + 0.5 : (double)p.n_parts);
     const double longest = ((double)std::min(most, part) + later * p.Sk) / tile_keys;
     const double shortest = p.n_parts > 1 ? 0.0 : (double)least / tile_keys;
-    const bool few = std::min<int64_t>(rows, s.rows) <= s.rows / 2;
+    const bool few = std::min<int64_t>(rows, bm) <= bm / 2;
     const double fill = std::min(1.0, n / kCUs * std::min(1.0, total / (n * longest + 1e-9)));   // less than n / kCUs where some workgroups end early
-    const double tile = few ? s.few : s.idle + (s.busy - s.idle) * fill * fill;   // (a chip that is not full runs at a higher clock)
-    const double fix = (few ? s.fix_few : s.fix) + (s.rows < kMaxRows ? (0.7 + 0.6 * fill) * refs : 0.0);
-    double time = longest * tile + fix * (1 + 0.7 * later);
-    if (n > kCUs && !p.causal) time *= std::ceil(n / kCUs);
-    if (n > kCUs && p.causal)   // every round has its shortest workgroup's time, what is left evens out
-      time = std::max(time, (std::ceil(n / kCUs) * shortest + (total - n * shortest) / kCUs + 0.15 * (longest - shortest)) * tile +
-                                n * fix * (1 + 0.7 * blocks) / kCUs);
+    const double alone = few ? c.few : c.idle + (c.busy - c.idle) * fill * fill;   // (a chip that is not full runs at a higher clock)
+    const double fix = (few ? c.fix_few : c.fix) + (groups ? (0.7 + 0.6 * fill) * refs : 0.0);
+    const double rounds = std::ceil(n / kCUs);
+    double time;
+    if (per_cu > 1 && n > kCUs) {   // workgroups of one compute unit fill each other's gaps
+      const double at_once = std::min<double>(per_cu, rounds), tile = at_once == 3 ? c.three : c.two;
+      time = total * tile / (kCUs * at_once);
+      if (!p.causal && rounds <= per_cu) time = longest * tile * (0.85 + 0.15 * n / (kCUs * rounds));   // all at once: as slow as the fullest compute unit
+      if (p.causal || later > 0) time += 0.15 * longest * tile;
+      time = std::max(time, memory) + fix + 0.35 * blocks * fix * n / (kCUs * at_once);
+      time = std::max(time, longest * alone + fix * (1 + c.block * later));
+    } else {
+      const double each = fix * (1 + c.block * later), average = fix * (1 + c.block * blocks);
+      time = longest * alone + std::max(each, std::min(memory, 2 * each));
+      if (n > kCUs && !p.causal) time = rounds * longest * alone + std::max(rounds * each, memory + 3 * rounds);
+      if (n > kCUs && p.causal)   // every round has its shortest workgroup's time, what is left evens out
+        time = std::max(time, (rounds * shortest + (total - n * shortest) / kCUs + 0.15 * (longest - shortest)) * alone + std::max(n * average / kCUs, memory));
+    }
     // (The causal parts of a launch are not dealt out longest first, so that a second round costs more than its share:
     // 12 heads of 2306 rows on 2665 keys in 2 parts 43 us with 256 rows, 49 with 128.)
-    if (s.rows < kMaxRows && p.n_parts > 1 && p.causal && n > kCUs) continue;
-    if (s.rows == kMaxRows) {
-      t_best = time * (n > kCUs ? 0.9 : 0.97);   // a last round that is nearly empty runs faster than a full one
-    } else if (time * (n > kCUs ? 1.05 : 1.0) < t_best) {
-      t_best = time * (n > kCUs ? 1.05 : 1.0);
-      best = s.rows;
+    if (shape != tr::kShape8x1 && p.n_parts > 1 && p.causal && n > kCUs * per_cu) continue;
+    if (shape == tr::kShape8x1) {
+      t_best = time * (n > kCUs ? 0.95 : 0.97);   // a last round that is nearly empty runs faster than a full one
+    } else {   // over several rounds the estimates lie closer together than their errors, unless there are many
+      time *= n > 8 * kCUs ? 0.97 : n > kCUs * per_cu ? 1.03 : 1.0;
+      if (time < t_best) {
+        t_best = time;
+        best = shape;
+      }
     }
   }
   return best;
 }
 
-// Workgroups of bm rows each for a launch over (head, query tile) pairs; how they are placed on the XCDs.
-void set_rows(tr::AttnParams& p, int bm) {
+// The shape of a launch over (head, query tile) pairs; how its workgroups are placed on the XCDs.
+void use_shape(tr::AttnParams& p, int shape) {
+  const int bm = tr::shape_rows(shape);
+  p.shape = shape;
   p.bm = bm;
   p.n_qtiles = (p.Sq + bm - 1) / bm;
   p.xcd_map = (p.B * p.Hkv) % 8 == 0 && (int64_t)p.n_qtiles * p.B * p.Hq >= 8;
@@ -344,13 +366,15 @@ void set_rows(tr::AttnParams& p, int bm) {
 
 hipError_t launch_plain(const tr::AttnParams& plain, int D, int epilogue, hipStream_t stream) {
   tr::AttnParams p = plain;
-  set_rows(p, choose_rows(p, D, false));
+  use_shape(p, choose_shape(p, D, false, epilogue == 0 ? 2 : epilogue == 1 ? 4 : 8));
   return tr::launch_block_attn(p, D, epilogue, stream);
 }
 
 hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int D, int epilogue, hipStream_t stream) {
   tr::AttnParams p = plain;
-  auto shape = [&](int bm) {   // the row space in tiles of bm rows
+  auto use = [&](int shape) {   // the row space in tiles of the shape's rows
+    const int bm = tr::shape_rows(shape);
+    p.shape = shape;
     const int space = plan.pack ? p.gq * p.Sq : p.Sq;
     p.bm = bm;
     p.pack = plan.pack;
@@ -364,9 +388,9 @@ hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int
       if (PartRegion* r = take_region(*pool, stream)) {
         p.n_parts = plan.parts;
         p.part_keys = (int)plan.part_keys;
-        shape(choose_rows(p, D, plan.pack));
+        use(choose_shape(p, D, plan.pack, 4));
         const auto slot_rows = [&]() { return (int64_t)p.B * p.Hkv * p.members * p.n_parts * p.part_rows; };
-        if (slot_rows() * (D + 1) * 4 > kPartBytes) shape(kMaxRows);   // the form the plan has counted for
+        if (slot_rows() * (D + 1) * 4 > kPartBytes) use(tr::kShape8x1);   // the form the plan has counted for
         p.units = p.B * p.Hkv * p.n_parts;
         p.part_out = (float*)r->bytes;
         p.part_lse = p.part_out + slot_rows() * D;
@@ -382,7 +406,7 @@ hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int
   if (!plan.packs_uncut) return launch_plain(plain, D, epilogue, stream);
   p.n_parts = 1;
   p.part_keys = (p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
-  shape(choose_rows(p, D, plan.pack));
+  use(choose_shape(p, D, plan.pack, epilogue == 0 ? 2 : epilogue == 1 ? 4 : 8));
   p.units = p.B * p.Hkv;
   return tr::launch_block_attn(p, D, epilogue, stream);
 }
@@ -393,6 +417,7 @@ void set_shape(tr::AttnParams& p, const tr_tensor* q, const tr_tensor* k, int ca
   p.causal = causal ? 1 : 0;
   const int64_t lim = (int64_t)1 << 30;
   p.causal_off = (int)(off64 > lim ? lim : (off64 < -lim ? -lim : off64));
+  p.shape = tr::kShape8x1;
   p.bm = kMaxRows;
   p.n_qtiles = (p.Sq + p.bm - 1) / p.bm;
   p.gq = p.Hkv > 0 ? p.Hq / p.Hkv : 1;
@@ -449,7 +474,7 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   if (n_chunks > 0) {
     p.n_chunks = n_chunks;
     p.chunk_bf16 = chunk_bf16 ? 1 : 0;
-    set_rows(p, choose_rows(p, (int)q->D, false));
+    use_shape(p, choose_shape(p, (int)q->D, false, 8));
     const int step = std::max(1, 65535 / p.n_qtiles);   // chunks one grid holds; the later ones first, as inside a launch
     for (p.chunk_end = n_chunks; p.chunk_end > 0; p.chunk_end = p.chunk_begin) {
       p.chunk_begin = std::max(0, p.chunk_end - step);

@@ -5,8 +5,8 @@
 namespace tr {
 
 #define TR_SHAPE(D, R, G) extern template hipError_t launch_attn_shape<D, R, G>(const AttnParams&, int, dim3, hipStream_t);
-TR_SHAPE(64, 8, 1) TR_SHAPE(64, 4, 2) TR_SHAPE(64, 2, 2)
-TR_SHAPE(128, 8, 1) TR_SHAPE(128, 4, 2) TR_SHAPE(128, 2, 2)
+TR_SHAPE(64, 8, 1) TR_SHAPE(64, 4, 2) TR_SHAPE(64, 2, 2) TR_SHAPE(64, 4, 1)
+TR_SHAPE(128, 8, 1) TR_SHAPE(128, 4, 2) TR_SHAPE(128, 2, 2) TR_SHAPE(128, 4, 1)
 #undef TR_SHAPE
 
 namespace {
@@ -111,9 +111,12 @@ hipError_t launch_fold(const AttnParams& p, int epilogue, hipStream_t stream, hi
 
 template <int D>
 hipError_t launch_attn(const AttnParams& p, int epilogue, dim3 grid, hipStream_t stream) {
-  if (p.bm == 64) return launch_attn_shape<D, 2, 2>(p, epilogue, grid, stream);
-  if (p.bm == 128) return launch_attn_shape<D, 4, 2>(p, epilogue, grid, stream);
-  return launch_attn_shape<D, 8, 1>(p, epilogue, grid, stream);
+  switch (p.shape) {
+    case kShape2x2: return launch_attn_shape<D, 2, 2>(p, epilogue, grid, stream);
+    case kShape4x2: return launch_attn_shape<D, 4, 2>(p, epilogue, grid, stream);
+    case kShape4x1: return launch_attn_shape<D, 4, 1>(p, epilogue, grid, stream);
+    default: return launch_attn_shape<D, 8, 1>(p, epilogue, grid, stream);
+  }
 }
 
 }  // namespace
@@ -121,7 +124,7 @@ hipError_t launch_attn(const AttnParams& p, int epilogue, dim3 grid, hipStream_t
 hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream, hipEvent_t fold_done) {
   const int64_t nbh = (int64_t)p.B * p.Hq;
   if (nbh * p.n_qtiles == 0) return hipSuccess;
-  if (p.n_qtiles > 65535 || (p.bm != 64 && p.bm != 128 && p.bm != 256)) return hipErrorInvalidValue;   // grid y limit
+  if (p.n_qtiles > 65535 || p.bm != shape_rows(p.shape)) return hipErrorInvalidValue;   // grid y limit
   dim3 grid((unsigned)nbh, (unsigned)p.n_qtiles);
   if (p.xcd_map == 2) grid = dim3(8u * (unsigned)p.n_qtiles, (unsigned)(nbh / 8));
   if (p.n_parts > 0) {

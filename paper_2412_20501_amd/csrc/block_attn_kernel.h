@@ -33,6 +33,12 @@
 // 1.1 us with R x G = 8 x 1, 0.59 with 4 x 2, 0.47 with 2 x 2 (four waves; alone on its SIMD a wave takes 1.6 times
 // a shared SIMD's time).  4 x 1024 rows on 1024 keys 25.6 -> 15.0 us, 1 x 8192 rows 144 -> 67, at D = 64 105 -> 45.
 // 2 x 4 measured 5 - 14 % less than 2 x 2 from 4096 keys on and 1 us more below (D = 64); at D = 128 its tiles leave room for two.
+//
+// Small workgroups.  Shape 4 x 1 is the 256-row workgroup's work in halves, two to a compute unit at D = 128 and three at
+// D = 64 (166 VGPRs): one's loads, epilogue and waits at barriers run beside another's products, and a launch ends more evenly.
+// What it costs is twice the K/V traffic from L2 into LDS for the same rows.  us, 8 x 1 -> 4 x 1: 512 heads of 256 rows on as many keys
+// 41.8 -> 35.4, at D 64 26.2 -> 19.6; 48 heads of 3000 225 -> 207, at D 64 145 -> 121; 64 of 2048 125.3 -> 126.7, at D 64 77.0 -> 73.8; 32 of
+// 24576 7720 -> 8015, at D 64 4847 -> 4721; bf16 blocks of 6008 rows in 4 chunks, 16 heads 190 -> 169.
 #pragma once
 #include <type_traits>
 
@@ -52,11 +58,13 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Shapes of a workgroup: R row groups of 32 Query rows, G key groups; one wave for each pair.
-// keys per LDS tile: 16 KiB of K (and of V) either way, so a tile is 2 sub-tiles of 32 keys at
-// D = 128 and 4 at D = 64, where a sub-tile carries half the MFMA work per barrier otherwise
-template <int D>
-constexpr int tile_keys() { return D == 64 ? 128 : 64; }
-constexpr int kRing = 4;          // LDS ring depth (tiles) of K and of V
+// Keys per LDS tile: 16 KiB of K (and of V) either way, so a tile is 2 sub-tiles of 32 keys at
+// D = 128 and 4 at D = 64, where a sub-tile carries half the MFMA work per barrier otherwise.  Shape 4 x 1: half of that, so
+// that two (D = 64, with rings of three: three) workgroups share a compute unit.
+template <int D, int R, int G>
+constexpr int tile_keys() { return (D == 64 ? 128 : 64) / (R == 4 && G == 1 ? 2 : 1); }
+template <int D, int R, int G>
+constexpr int ring_depth() { return D == 64 && R == 4 && G == 1 ? 3 : 4; }   // LDS ring depth (tiles) of K and of V
 constexpr int kEpiBf16 = 0, kEpiF32 = 1, kEpiMerge = 2;
 constexpr int kPlain = 0, kPart = 1, kChunks = 2;   // forms of the kernel, see there
 
@@ -187,7 +195,7 @@ __device__ __forceinline__ int live_parts(const AttnParams& p, int pos_last) {
 // and sum of each wave's rows and the references of later segments (more than one key group).
 template <int D, int R, int G>
 struct Lds {
-  static constexpr int rings = 2 * kRing * tile_keys<D>() * 2 * D, tiles = R * G * 32 * 4 * D, rows = R * 32;
+  static constexpr int rings = 2 * ring_depth<D, R, G>() * tile_keys<D, R, G>() * 2 * D, tiles = R * G * 32 * 4 * D, rows = R * 32;
   static constexpr int w = rings > tiles ? rings : tiles, mode = w + rows * 4, off = mode + rows * 4;
   static constexpr int sums = off + rows * 8, refs = sums + (G > 1 ? G * rows * 8 : 0);
   static constexpr int bytes(int form) {
@@ -300,7 +308,7 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // compute units), the longest chunks first.  Bound: as the plain form, plus an epilogue for each block.
 // Causal 6008 rows in 4 chunks, 16 heads: 401 -> 193 us, the same bits.
 template <int D, int EPI, int FORM, int R, int G>
-__global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnParams p) {
+__global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 2) block_attn_kernel(const AttnParams p) {
   constexpr bool PART = FORM == kPart, CHUNKS = FORM == kChunks;
   constexpr int W = R * G, BM = 32 * R;    // waves, Query rows of a workgroup
   static_assert(!CHUNKS || EPI == kEpiMerge, "blocks of the chunk form are merged");
@@ -308,15 +316,15 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   constexpr int KS = D / 16;               // MFMA k-steps over the head dim
   constexpr int DB = D / 32;               // 32-wide d blocks of the output
   constexpr int CPR = D / 8;               // 16-byte chunks per row
-  constexpr int BN = tile_keys<D>();       // keys per LDS tile
+  constexpr int BN = tile_keys<D, R, G>();       // keys per LDS tile
   constexpr int TILE_BYTES = BN * RB;
   constexpr int RPI = 1024 / RB;           // tile rows one wave-wide 16-byte load instruction covers
   constexpr int IPW = BN / RPI / W;        // load instructions per wave, tile and tensor
-  constexpr int NS = kRing;                // ring depth of the K and of the V tiles
+  constexpr int NS = ring_depth<D, R, G>();                // ring depth of the K and of the V tiles
   constexpr int SUB = 32;                  // keys per sub-tile (one MFMA row block)
   constexpr int NSUB = BN / SUB;           // sub-tiles per tile
   constexpr int NSW = NSUB / G;            // sub-tiles of one key group (= steps of a wave) per tile
-  constexpr int KA = NSW == 1 ? 4 : 3;     // K tile issued in tile u: u + KA
+  constexpr int KA = NSW == 1 ? 4 : 3, VA = NS - 2;   // K and V tile issued in tile u: u + KA, u + VA
   static_assert(NSUB % G == 0 && (NSW * NS) % 2 == 0, "the S / P register sets alternate with the step parity");
   static_assert(IPW >= 1, "tile too small for the workgroup");
 
@@ -452,7 +460,7 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
     issue_k(0);
     issue_v(0);
     issue_k(1);
-    issue_v(1);
+    if (VA == 2) issue_v(1);
     issue_k(2);
     if (KA == 4) issue_k(3);
   }
@@ -519,7 +527,7 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   constexpr bool RENEW = !CHUNKS;           // (the chunk form ends every segment in a block of its own)
   int renew_at = RENEW && p.renew > 0 ? p.renew : 0x7fffffff;   // m_ref is renewed by the first step that starts at this key or later
   int segment = -1;         // later segment the wave is in, -1: the first one
-  int at_start = 0;         // 1: its reference was due at a sub-tile where the wave renews it, not on the way to one
+  int at_start = 0;         // 1: the wave renews at the first sub-tile of its own that the segment holds, not later
   const float c2 = p.scale * 1.4426950408889634f;  // scale * log2(e)
 
   // ---- one step ---------------------------------------------------------------------
@@ -648,7 +656,7 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
 #pragma unroll
       for (int i = 1; i < 16; i++) tmax = fmaxf(tmax, s_in[i]);
       tmax = half_swap_max(tmax);
-      // The segment's reference, unless this sub-tile lies beyond the fast path's range.  (Renewed late, between groups of
+      // The segment's reference, unless this sub-tile lies beyond the fast path's range.  (Renewed late, behind a group of
       // inner tiles, each key group takes its own sub-tile's: the weight of the segment's first maximum is already summed.)
       if (G > 1 && RENEW && segment >= 0 && at_start && sum_cap < 0.f) {
         const float seg_ref = *reinterpret_cast<const float*>(lds + Lds<D, R, G>::refs + (min(segment, kMaxRefs - 1) * BM + rg * 32 + ql) * 4);
@@ -717,7 +725,7 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
     return half_swap_max(t);
   };
   if constexpr (G > 1 && RENEW) {
-    if (p.renew > 0) {   // at most kMaxRefs of them, see choose_rows
+    if (p.renew > 0) {   // at most kMaxRefs of them, see choose_shape
       auto load = [&](int s, bf16x8 (&kf)[KS]) __attribute__((always_inline)) {
         const __bf16* kp = kg + (int64_t)min((s + 1) * p.renew + ql, Sk - 1) * p.k_ss + 8 * hf;
 #pragma unroll
@@ -758,7 +766,8 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   // right before B_{w+2} (towards the end, where nothing more is issued, all of it).  NSW = 1: K_u is read in step u-2, so K_{w+4} goes into the slot of K_w, which
   // all waves have left behind B_w from w = 2 on; K_0 and K_1 are read before step 0, so the
   // slot of K_0 is free at B_1, where K_4 is issued in front of K_5.  K_{w+2} and V_{w-1}, read first in step w, were issued
-  // before the newest 2*IPW loads at B_w.
+  // before the newest 2*IPW loads at B_w.  Rings of three tiles (NSW = 2): K_{w+3} goes into the slot of K_w and V_{w+1}, issued in
+  // front of it, into the one of V_{w-2}; all but the newest IPW loads have landed at B_{w+1}, and K_3 is issued at B_1, like K_4 above.
   // S and P alternate between two register sets: even steps read sA / pB and write sB / pA,
   // odd steps the other way round, so no step has to copy its results.
   f32x16 sA, sB;
@@ -781,15 +790,15 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
           renew_at += p.renew;
           segment++;
         } while (G > 1 && kstart >= renew_at);
-        at_start = 1;
+        at_start = kstart - (renew_at - p.renew) < G * SUB;
       }
       if (even) step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sA, sB, pB, pA, inner_c);
       else step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sB, sA, pA, pB, inner_c);
     }
   };
   if (n_tiles > 0) {
-    if (KA == 3) issue_k(3 % NS);
-    issue_v(2 % NS);
+    if (KA == 3 && NS == 4) issue_k(3 % NS);
+    issue_v(VA % NS);
     if (jw > 0) {
       // S_0 = K_0[0:32] Q^T, plain (nothing to overlap with yet); operands of step 0 (the wave's sub-tile 1)
 #pragma unroll
@@ -833,16 +842,20 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   auto tile_body = [&](int u, auto slot_c, auto inner_c, auto second_c) __attribute__((always_inline)) {   // slot_c = u % NS; second_c: u = 1
     constexpr int su = decltype(slot_c)::value;
     constexpr bool INNER = decltype(inner_c)::value != 0;
-    if (INNER || u + KA - 1 <= last_tile) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * IPW));  // vmcnt only
-    else __builtin_amdgcn_s_waitcnt(0x0F70);         // the tile before issued no K: everything that is on its way
+    // vmcnt; of a ring of three also lgkmcnt(0): the slot that is filled behind the barrier was read in the step before it
+    constexpr int none = NS == 3 ? 0x0070 : 0x0F70;
+    if (INNER || (u + KA - 1 <= last_tile && !(NS == 3 && decltype(second_c)::value))) __builtin_amdgcn_s_waitcnt(none | (NS == 3 ? IPW : 2 * IPW));
+    else __builtin_amdgcn_s_waitcnt(none);           // the tile before issued no K: everything that is on its way
     wg_barrier();                                    // B_u
-    if (KA == 4 && decltype(second_c)::value) issue_k(0);   // K_4
-    if (INNER) {
-      issue_k_inner((su + KA) % NS);  // K_{u+KA}
-      issue_v_inner((su + 2) % NS);   // V_{u+2}
+    if ((KA == 4 || NS == 3) && decltype(second_c)::value) issue_k(0);   // K_4 of a ring of four, K_3 of a ring of three
+    if (INNER) {   // K_{u+KA}, V_{u+VA}; first what is needed first
+      if (NS == 3) issue_v_inner((su + VA) % NS);
+      issue_k_inner((su + KA) % NS);
+      if (NS == 4) issue_v_inner((su + VA) % NS);
     } else {
+      if (NS == 3) issue_v((su + VA) % NS);
       issue_k((su + KA) % NS);
-      issue_v((su + 2) % NS);
+      if (NS == 4) issue_v((su + VA) % NS);
     }
     tile_step(u, slot_c, IC<0>{}, inner_c);
     if constexpr (NSW > 1) tile_step(u, slot_c, IC<1>{}, inner_c);
@@ -864,7 +877,7 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
   // tiles 1 .. 3 (tile 0 was the prologue)
   if (1 <= n_tiles) tile_body(1, IC<1 % NS>{}, IC<0>{}, IC<1>{});
   if (2 <= n_tiles) tile_body(2, IC<2 % NS>{}, IC<0>{}, IC<0>{});
-  if (3 <= n_tiles) tile_body(3, IC<3 % NS>{}, IC<0>{}, IC<0>{});
+  if (NS > 3 && 3 <= n_tiles) tile_body(3, IC<3 % NS>{}, IC<0>{}, IC<0>{});
   // Groups of NS tiles: first the groups of inner tiles (up to where the reference is renewed, and on from there), then
   // general ones to the end.
   int u0 = NS;
@@ -880,14 +893,14 @@ __global__ void __launch_bounds__(64 * R * G, 2) block_attn_kernel(const AttnPar
       tile_body(u0, IC<0>{}, IC<1>{}, IC<0>{});
       tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{}, IC<0>{});
       tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{}, IC<0>{});
-      tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{}, IC<0>{});
+      if constexpr (NS > 3) tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{}, IC<0>{});
     }
   }
   for (; u0 <= n_tiles; u0 += NS) {
     tile_body(u0, IC<0>{}, IC<0>{}, IC<0>{});
     if (u0 + 1 <= n_tiles) tile_body(u0 + 1, IC<1 % NS>{}, IC<0>{}, IC<0>{});
     if (u0 + 2 <= n_tiles) tile_body(u0 + 2, IC<2 % NS>{}, IC<0>{}, IC<0>{});
-    if (u0 + 3 <= n_tiles) tile_body(u0 + 3, IC<3 % NS>{}, IC<0>{}, IC<0>{});
+    if (NS > 3 && u0 + 3 <= n_tiles) tile_body(u0 + 3, IC<3 % NS>{}, IC<0>{}, IC<0>{});
   }
   __builtin_amdgcn_s_waitcnt(0);  // no LDS write of this workgroup may still be in flight at exit
 

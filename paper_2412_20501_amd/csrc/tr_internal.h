@@ -11,6 +11,10 @@ namespace tr {
 constexpr int kMaxRefs = 32;   // references of later segments that workgroups of fewer than 256 rows keep in LDS
 constexpr int kMaxParts = 16;  // parts the keys of one partitioned attention launch are cut into at most
 
+// Shapes of an attention workgroup: row groups of 32 Query rows x key groups.
+constexpr int kShape8x1 = 0, kShape4x1 = 1, kShape4x2 = 2, kShape2x2 = 3;
+constexpr int shape_rows(int shape) { return shape == kShape8x1 ? 256 : shape == kShape2x2 ? 64 : 128; }
+
 // Arguments of the block-attention kernel: raw pointers, element strides, sizes.
 struct AttnParams {
   const __bf16* q;
@@ -27,7 +31,8 @@ struct AttnParams {
   int causal;     // 0: every key visible; 1: key c visible to query r iff c <= r + causal_off
   int causal_off; // q_pos0 - k_pos0, clamped so that r + causal_off cannot overflow
   float scale;    // softmax scale (natural units)
-  int bm;         // Query rows of a workgroup: 256, 128 or 64
+  int shape;      // of a workgroup, kShape8x1 ...
+  int bm;         // its Query rows
   int n_qtiles;   // ceil(Sq / bm)
   int xcd_map;    // 1: place all query tiles of a K/V head on one XCD (grid x = batch*head, y = query tile); 2: the same with grid x = XCD + 8 * query tile, y = head within the XCD
   int gq;         // query heads per K/V head (Hq / Hkv)

@@ -1,8 +1,9 @@
-"""Workgroups of 64 and 128 Query rows, whose waves share the keys out among themselves, against workgroups of 256 rows:
-the same inputs as one entry of a batch so large that the launch takes the latter.  Both round the same weights (one
+"""Shapes of an attention workgroup: 128 Query rows (two or three workgroups to a compute unit), and 128 or 64 rows whose waves
+share the keys out among themselves, against workgroups of 256 rows or others of a full chip: the same inputs as one entry of a batch so large
+that the launch takes those.  All round the same weights (one
 exponent reference for a row and segment, whatever the shape), so only fp32 sums differ: a few 2^-23 of values of size 1
 (out) and 10 (lse).  Sizes sit at the edges of row groups, workgroups, sub-tiles and tiles of keys, and where a segment's
-reference is renewed; the oracle stands beside the smallest."""
+reference is renewed."""
 import numpy as np
 import pytest
 import torch
@@ -72,6 +73,58 @@ def test_rings_renewed_elsewhere(lib, Hq, Hkv, seg, n):
     lib.tr_ring_attn(q, k, v, n, True, out, lse)
     torch.cuda.synchronize()
     assert max_abs(to_np(out), ref[0]) <= 1e-2 and max_abs(to_np(lse), ref[1]) <= 1e-5
+
+
+def _exact(q, k, v, off):
+    g = q.shape[1] // k.shape[1]
+    s = (q.double() * q.shape[-1] ** -0.5) @ k.double().repeat_interleave(g, 1).transpose(-1, -2).contiguous()
+    if off is not None:
+        rows, keys = torch.arange(q.shape[2], device="cuda"), torch.arange(k.shape[2], device="cuda")
+        s = s.masked_fill(keys[None, :] > rows[:, None] + off, float("-inf"))
+    lse = torch.logsumexp(s, -1)
+    return torch.exp(s - lse.masked_fill(torch.isinf(lse), 0.0)[..., None]) @ v.double().repeat_interleave(g, 1), lse
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,off", [
+    (2, 24, 8, 300, 300, 128, None),   # two workgroups to a compute unit; a ragged last one
+    (2, 24, 8, 300, 300, 64, None),    # three
+    (3, 32, 32, 129, 31, 64, None),    # one row in the second workgroup, less than a sub-tile
+    (3, 32, 32, 129, 65, 64, None),    # one key in the second tile
+    (3, 32, 32, 129, 193, 64, 64),     # a ring of three tiles once round, and one key more
+    (3, 32, 32, 140, 257, 64, 117),
+    (3, 32, 32, 140, 161, 128, 21),    # a ring of four tiles of 32 keys once round, and one more
+    (3, 32, 32, 250, 700, 128, 500),   # inner tiles, keys that no row sees
+    (3, 32, 32, 250, 700, 64, -100),   # rows without any key
+    (1, 64, 16, 1024, 1024, 64, 0),
+    (1, 64, 16, 1024, 1024, 128, 0),
+])
+def test_small_workgroups(lib, B, Hq, Hkv, Sq, Sk, D, off):
+    q, k, v = (bits_to_dev(rand_bits((B, h, S, D), 740 + i)) for i, (h, S) in enumerate(((Hq, Sq), (Hkv, Sk), (Hkv, Sk))))
+    out, lse = _new(B, Hq, Sq, D)
+    if off is None:
+        lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, D ** -0.5, out, lse)
+    else:
+        lib.tr_block_attn_causal_at(q, k, v, max(off, 0), max(-off, 0), D ** -0.5, out, lse)
+    torch.cuda.synchronize()
+    want_o, want_l = _exact(q, k, v, off)
+    assert torch.equal(torch.isneginf(lse), torch.isneginf(want_l))
+    seen = ~torch.isneginf(want_l)
+    assert float((out - want_o).abs().max()) <= 1e-2 and float((lse - want_l)[seen].abs().max()) <= 1e-5   # as for every block step
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_bf16_blocks_of_small_workgroups(lib, D, causal):
+    """96 heads of 3 chunks of 300 rows: the chunk form and its steps spelled out, which take other shapes."""
+    B, H, chunk, n = 4, 24, 300, 3
+    q, k, v = (bits_to_dev(rand_bits((B, H, chunk * n, D), 760 + i)) for i in range(3))
+    out, lse = _new(B, H, chunk * n, D)
+    ws = torch.empty(lib.tr_ring_attn_blocks_workspace_bytes(q, n, lib.TR_BF16), dtype=torch.uint8, device="cuda")
+    lib.tr_ring_attn_blocks(q, k, v, n, causal, out, lse, lib.TR_BF16, ws, D ** -0.5)
+    torch.cuda.synchronize()
+    want_o, want_l = _exact(q, k, v, 0 if causal else None)
+    # a bf16 rounding of each later block on top of a block step's distance
+    assert float((out - want_o).abs().max()) <= 1e-2 + 2 ** -8 * float(v.abs().max()) and float((lse - want_l).abs().max()) <= 1e-5
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, None])   # None: merged into accumulators
