@@ -299,6 +299,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes) {
     const int bm = tr::shape_rows(shape), per_cu = shape != tr::kShape4x1 ? 1 : D == 64 ? 3 : 2;
     const bool groups = shape >= tr::kShape4x2;
     const int64_t tiles = (rows + bm - 1) / bm;
+    if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
     if (groups && (refs > tr::kMaxRefs || heads * tiles >= 8 * kCUs)) continue;
     int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
     if (p.causal && pack) {

@@ -164,6 +164,20 @@ def test_steps(lib, Hq, Hkv, Sq, Sk, D, off, dtype):
     _agree(few, many, 2 ** -8 * 4 if dtype is torch.bfloat16 else 1e-5)   # a bf16 ulp of values below 4, where a sum lies at a tie
 
 
+def test_more_rows_than_a_grid_of_small_workgroups_holds(lib):
+    """65536 workgroups of 128 rows are one too many for a grid's second dimension; 32769 of 256 rows are not."""
+    S, D = 65536 * 128 + 5, 64
+    q = torch.randn((1, 1, S, D), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3)).bfloat16()
+    k, v = (bits_to_dev(rand_bits((1, 1, 3, D), 770 + i)) for i in range(2))
+    out, lse = torch.full((1, 1, S, D), float("nan"), dtype=torch.bfloat16, device="cuda"), torch.full((1, 1, S), float("nan"), device="cuda")
+    lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, D ** -0.5, out, lse)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(lse).all())
+    for r in (slice(0, 300), slice(S // 2 - 200, S // 2 + 200), slice(S - 300, S)):
+        want_o, want_l = _exact(q[:, :, r], k, v, None)
+        assert float((out[:, :, r] - want_o).abs().max()) <= 1e-2 * 2 and float((lse[:, :, r] - want_l).abs().max()) <= 1e-5   # (and bf16's rounding of values to 4)
+
+
 def test_scores_beyond_the_fast_path(lib):
     """Scores 40 wide: references are raised per key group and the groups' sums meet at different ones."""
     S, D = 320, 64
