@@ -117,6 +117,90 @@ struct PartPlan {
   bool packs_uncut = false;               // heads are packed also where the keys are not cut
 };
 
+// Shape of a launch's workgroups.  8 x 1 (256 rows) has the least traffic for its products and is the best use of a full chip
+// over long key ranges.  4 x 1, several to a compute unit, hides set-up and epilogue and ends more evenly.  A launch that would leave
+// compute units idle runs 4 x 2 or 2 x 2, whose waves also share the keys out among themselves.
+// Chosen by an estimate of the launch's time (us) from measured costs: set-up and epilogue of a workgroup, and a tile of keys
+// (64 at D 128, 128 at D 64) on an idle and on a full chip, on a compute unit with one, two, three workgroups, and with at most half of
+// the waves at work.  Both sides of the lines, us for 8 x 1 / 4 x 1 / 4 x 2 / 2 x 2 at D 128: 8 heads of 256 rows 12.5 / - / 10.9 / 8.6; 16 of
+// 1024 27.7 / 21.6 / 21.8 / 18.1; 32 of 1024 29.2 / 24.5 / 25.2 / 30.4; 64 of 1024 39.1 / 39.2 / 48.7 / 58.7, under the causal rule 30.8 / 28.0 / 34.7 / 43.9;
+// 8 of 4096 84 / 71 / 69 / 85; 24 of 1777 51.2 / 51.5 / 59.7 / 64.9, under the causal rule 42.4 / 35.5 / 33.2 / 40.9; 16 of 8192 438 / 460.
+// p holds the launch's parts and chunks; pack: the rows are those of a K/V head's whole group; out_bytes: of an output element; estimate: of the time, if asked for.
+int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, double* estimate = nullptr) {
+  const int refs = p.renew > 0 ? (p.Sk - 1) / p.renew : 0;
+  const int64_t rows = pack ? (int64_t)p.gq * p.Sq : p.Sq, heads = (int64_t)p.B * (pack ? p.Hkv : p.Hq);
+  if (p.Sk == 0) return tr::kShape8x1;
+  struct Cost { double fix, idle, busy, two, three, fix_few, few, block; };   // block: of a later block of the chunk form, in units of fix
+  static const Cost costs[2][4] = {{{7.5, 1.52, 2.03, 0, 0, 5.2, 1.0, 1.7}, {6.5, 1.0, 1.12, 2.03, 2.96, 5.6, 0.95, 1.3},
+                                    {7.1, 0.83, 1.09, 0, 0, 6.0, 0.65, 0.75}, {5.8, 0.61, 0.72, 0, 0, 5.4, 0.6, 0.75}},
+                                   {{8.3, 1.1, 1.67, 0, 0, 6.2, 0.7, 1.7}, {8.5, 0.7, 0.95, 1.78, 0, 6.8, 0.65, 1.3},
+                                    {9.0, 0.59, 0.93, 0, 0, 7.5, 0.5, 0.75}, {7.0, 0.47, 0.57, 0, 0, 6.5, 0.45, 0.75}}};
+  const double tile_keys = D == 64 ? 128.0 : 64.0;
+  const int64_t part = p.n_parts > 1 ? p.part_keys : p.Sk;
+  const double later = p.n_chunks > 1 ? p.n_chunks - 1 : 0;   // blocks behind its first of the longest workgroup
+  const double blocks = p.causal ? later / 2 : later, chunks = later + 1;   // later blocks of the average workgroup
+  const double memory = (double)(heads * rows) * chunks * D * (2 + (p.n_parts > 1 ? 4 : out_bytes)) / 5.2e6;   // Query rows in, result out
+  int best = tr::kShape8x1;
+  double t_best = 0;
+  for (int shape = 0; shape < 4; shape++) {
+    const Cost& c = costs[D == 128][shape];
+    const int bm = tr::shape_rows(shape), per_cu = shape != tr::kShape4x1 ? 1 : D == 64 ? 3 : 2;
+    const bool groups = shape >= tr::kShape4x2;
+    const int64_t tiles = (rows + bm - 1) / bm;
+    if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
+    if (groups && (refs > tr::kMaxRefs || heads * tiles >= 8 * kCUs)) continue;
+    int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
+    if (p.causal && pack) {
+      least = most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, (int64_t)p.Sq + p.causal_off));
+      sum = most * tiles;
+    } else if (p.causal) {   // tile t sees the keys below (t + 1) * rows + causal_off
+      most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, rows + p.causal_off));
+      least = std::max<int64_t>(0, std::min<int64_t>(most, bm + (int64_t)p.causal_off));
+      const int64_t off = p.causal_off, all = std::min(tiles, std::max<int64_t>(0, (p.Sk - off + bm - 1) / bm - 1));
+      const int64_t none = std::min(all, off < 0 ? -off / bm : 0);   // tiles [none, all) see some, [all, tiles) every key
+      sum = (all * (all + 1) - none * (none + 1)) / 2 * bm + (all - none) * off + (tiles - all) * p.Sk;
+    }
+    double n = (double)(heads * tiles) * chunks, total = ((double)(heads * sum) + (double)(heads * tiles) * blocks * p.Sk) * chunks / tile_keys;
+    if (p.n_parts > 1) n *= std::max(1.0, p.causal ? (double)sum / (double)(tiles * part) + 0.5 : (double)p.n_parts);
+    const double longest = ((double)std::min(most, part) + later * p.Sk) / tile_keys;
+    const double shortest = p.n_parts > 1 ? 0.0 : (double)least / tile_keys;
+    const bool few = std::min<int64_t>(rows, bm) <= bm / 2;
+    const double fill = std::min(1.0, n / kCUs * std::min(1.0, total / (n * longest + 1e-9)));   // less than n / kCUs where some workgroups end early
+    const double alone = few ? c.few : c.idle + (c.busy - c.idle) * fill * fill;   // (a chip that is not full runs at a higher clock)
+    const double fix = (few ? c.fix_few : c.fix) + (groups ? (0.7 + 0.6 * fill) * refs : 0.0);
+    const double rounds = std::ceil(n / kCUs);
+    double time;
+    if (per_cu > 1 && n > kCUs) {   // workgroups of one compute unit fill each other's gaps
+      const double at_once = std::min<double>(per_cu, rounds), tile = at_once == 3 ? c.three : c.two;
+      time = total * tile / (kCUs * at_once);
+      if (!p.causal && rounds <= per_cu) time = longest * tile * (0.85 + 0.15 * n / (kCUs * rounds));   // all at once: as slow as the fullest compute unit
+      if (p.causal || later > 0) time += 0.15 * longest * tile;
+      time = std::max(time, memory) + fix + 0.35 * blocks * fix * n / (kCUs * at_once);
+      time = std::max(time, longest * alone + fix * (1 + c.block * later));
+    } else {
+      const double each = fix * (1 + c.block * later), average = fix * (1 + c.block * blocks);
+      time = longest * alone + std::max(each, std::min(memory, 2 * each));
+      if (n > kCUs && !p.causal) time = rounds * longest * alone + std::max(rounds * each, memory + 3 * rounds);
+      if (n > kCUs && p.causal)   // every round has its shortest workgroup's time, what is left evens out
+        time = std::max(time, (rounds * shortest + (total - n * shortest) / kCUs + 0.15 * (longest - shortest)) * alone + std::max(n * average / kCUs, memory));
+    }
+    // (The causal parts of a launch are not dealt out longest first, so that a second round costs more than its share:
+    // 12 heads of 2306 rows on 2665 keys in 2 parts 43 us with 256 rows, 49 with 128.)
+    if (shape != tr::kShape8x1 && p.n_parts > 1 && p.causal && n > kCUs * per_cu) continue;
+    if (shape == tr::kShape8x1) {
+      t_best = time * (n > kCUs ? 0.95 : 0.97);   // a last round that is nearly empty runs faster than a full one
+    } else {   // over several rounds the estimates lie closer together than their errors, unless there are many
+      time *= n > 8 * kCUs ? 0.97 : n > kCUs * per_cu ? 1.03 : 1.0;
+      if (time < t_best) {
+        t_best = time;
+        best = shape;
+      }
+    }
+  }
+  if (estimate) *estimate = t_best;
+  return best;
+}
+
 // Chooses the form of a launch; false: the plain one.  may_cut false: the keys stay in one piece, which makes the
 // result independent of the stream and of capture, whatever scratch is there.
 //
@@ -188,6 +272,22 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     best.parts = (int)parts;
     best.part_keys = part_keys;
     best.out_elems = slot_rows * D;
+  }
+  // Workgroups of fewer rows take some of the calls back that 256-row ones would have to cut: 4 x 3 heads of 935 rows on 1385 keys 31 us
+  // in 3 parts, 19 uncut; 12 heads of 1611 under the causal rule 30.5 and 20.4; 4 heads of 295 rows on 1041 keys 14.3 and 14.7.  (Not
+  // where heads are packed: uncut they would not be, and every key would be read once for each of them.)
+  if (best.parts > 1 && !c.pack) {
+    double whole = 0, cut = 0;
+    choose_shape(p, D, false, 4, &whole);
+    tr::AttnParams q = p;
+    q.n_parts = best.parts;
+    q.part_keys = (int)best.part_keys;
+    choose_shape(q, D, false, 4, &cut);
+    cut += 5.0 + 0.25 * best.parts + (double)best.out_elems * 4 / 3.5e6;
+    if (1.1 * std::max(whole, stream + fix) < cut) {
+      best = c;
+      return false;
+    }
   }
   return best.parts > 1 || best.packs_uncut;
 }
@@ -267,89 +367,6 @@ PartRegion* take_region(PartPool& pool, hipStream_t stream) {
     r->used = ++pool.uses;
   }
   return r;
-}
-
-// Shape of a launch's workgroups.  8 x 1 (256 rows) has the least traffic for its products and is the best use of a full chip
-// over long key ranges.  4 x 1, several to a compute unit, hides set-up and epilogue and ends more evenly.  A launch that would leave
-// compute units idle runs 4 x 2 or 2 x 2, whose waves also share the keys out among themselves.
-// Chosen by an estimate of the launch's time (us) from measured costs: set-up and epilogue of a workgroup, and a tile of keys
-// (64 at D 128, 128 at D 64) on an idle and on a full chip, on a compute unit with one, two, three workgroups, and with at most half of
-// the waves at work.  Both sides of the lines, us for 8 x 1 / 4 x 1 / 4 x 2 / 2 x 2 at D 128: 8 heads of 256 rows 12.5 / - / 10.9 / 8.6; 16 of
-// 1024 27.7 / 21.6 / 21.8 / 18.1; 32 of 1024 29.2 / 24.5 / 25.2 / 30.4; 64 of 1024 39.1 / 39.2 / 48.7 / 58.7, under the causal rule 30.8 / 28.0 / 34.7 / 43.9;
-// 8 of 4096 84 / 71 / 69 / 85; 24 of 1777 51.2 / 51.5 / 59.7 / 64.9, under the causal rule 42.4 / 35.5 / 33.2 / 40.9; 16 of 8192 438 / 460.
-// p holds the launch's parts and chunks; pack: the rows are those of a K/V head's whole group; out_bytes: of an output element.
-int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes) {
-  const int refs = p.renew > 0 ? (p.Sk - 1) / p.renew : 0;
-  const int64_t rows = pack ? (int64_t)p.gq * p.Sq : p.Sq, heads = (int64_t)p.B * (pack ? p.Hkv : p.Hq);
-  if (p.Sk == 0) return tr::kShape8x1;
-  struct Cost { double fix, idle, busy, two, three, fix_few, few, block; };   // block: of a later block of the chunk form, in units of fix
-  static const Cost costs[2][4] = {{{7.5, 1.52, 2.03, 0, 0, 5.2, 1.0, 1.7}, {6.5, 1.0, 1.12, 2.03, 2.96, 5.6, 0.95, 1.3},
-                                    {7.1, 0.83, 1.09, 0, 0, 6.0, 0.65, 0.75}, {5.8, 0.61, 0.72, 0, 0, 5.4, 0.6, 0.75}},
-                                   {{8.3, 1.1, 1.67, 0, 0, 6.2, 0.7, 1.7}, {8.5, 0.7, 0.95, 1.78, 0, 6.8, 0.65, 1.3},
-                                    {9.0, 0.59, 0.93, 0, 0, 7.5, 0.5, 0.75}, {7.0, 0.47, 0.57, 0, 0, 6.5, 0.45, 0.75}}};
-  const double tile_keys = D == 64 ? 128.0 : 64.0;
-  const int64_t part = p.n_parts > 1 ? p.part_keys : p.Sk;
-  const double later = p.n_chunks > 1 ? p.n_chunks - 1 : 0;   // blocks behind its first of the longest workgroup
-  const double blocks = p.causal ? later / 2 : later, chunks = later + 1;   // later blocks of the average workgroup
-  const double memory = (double)(heads * rows) * chunks * D * (2 + (p.n_parts > 1 ? 4 : out_bytes)) / 5.2e6;   // Query rows in, result out
-  int best = tr::kShape8x1;
-  double t_best = 0;
-  for (int shape = 0; shape < 4; shape++) {
-    const Cost& c = costs[D == 128][shape];
-    const int bm = tr::shape_rows(shape), per_cu = shape != tr::kShape4x1 ? 1 : D == 64 ? 3 : 2;
-    const bool groups = shape >= tr::kShape4x2;
-    const int64_t tiles = (rows + bm - 1) / bm;
-    if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
-    if (groups && (refs > tr::kMaxRefs || heads * tiles >= 8 * kCUs)) continue;
-    int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
-    if (p.causal && pack) {
-      least = most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, (int64_t)p.Sq + p.causal_off));
-      sum = most * tiles;
-    } else if (p.causal) {   // tile t sees the keys below (t + 1) * rows + causal_off
-      most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, rows + p.causal_off));
-      least = std::max<int64_t>(0, std::min<int64_t>(most, bm + (int64_t)p.causal_off));
-      const int64_t off = p.causal_off, all = std::min(tiles, std::max<int64_t>(0, (p.Sk - off + bm - 1) / bm - 1));
-      const int64_t none = std::min(all, off < 0 ? -off / bm : 0);   // tiles [none, all) see some, [all, tiles) every key
-      sum = (all * (all + 1) - none * (none + 1)) / 2 * bm + (all - none) * off + (tiles - all) * p.Sk;
-    }
-    double n = (double)(heads * tiles) * chunks, total = ((double)(heads * sum) + (double)(heads * tiles) * blocks * p.Sk) * chunks / tile_keys;
-    if (p.n_parts > 1) n *= std::max(1.0, p.causal ? (double)sum / (double)(tiles * part) + 0.5 : (double)p.n_parts);
-    const double longest = ((double)std::min(most, part) + later * p.Sk) / tile_keys;
-    const double shortest = p.n_parts > 1 ? 0.0 : (double)least / tile_keys;
-    const bool few = std::min<int64_t>(rows, bm) <= bm / 2;
-    const double fill = std::min(1.0, n / kCUs * std::min(1.0, total / (n * longest + 1e-9)));   // less than n / kCUs where some workgroups end early
-    const double alone = few ? c.few : c.idle + (c.busy - c.idle) * fill * fill;   // (a chip that is not full runs at a higher clock)
-    const double fix = (few ? c.fix_few : c.fix) + (groups ? (0.7 + 0.6 * fill) * refs : 0.0);
-    const double rounds = std::ceil(n / kCUs);
-    double time;
-    if (per_cu > 1 && n > kCUs) {   // workgroups of one compute unit fill each other's gaps
-      const double at_once = std::min<double>(per_cu, rounds), tile = at_once == 3 ? c.three : c.two;
-      time = total * tile / (kCUs * at_once);
-      if (!p.causal && rounds <= per_cu) time = longest * tile * (0.85 + 0.15 * n / (kCUs * rounds));   // all at once: as slow as the fullest compute unit
-      if (p.causal || later > 0) time += 0.15 * longest * tile;
-      time = std::max(time, memory) + fix + 0.35 * blocks * fix * n / (kCUs * at_once);
-      time = std::max(time, longest * alone + fix * (1 + c.block * later));
-    } else {
-      const double each = fix * (1 + c.block * later), average = fix * (1 + c.block * blocks);
-      time = longest * alone + std::max(each, std::min(memory, 2 * each));
-      if (n > kCUs && !p.causal) time = rounds * longest * alone + std::max(rounds * each, memory + 3 * rounds);
-      if (n > kCUs && p.causal)   // every round has its shortest workgroup's time, what is left evens out
-        time = std::max(time, (rounds * shortest + (total - n * shortest) / kCUs + 0.15 * (longest - shortest)) * alone + std::max(n * average / kCUs, memory));
-    }
-    // (The causal parts of a launch are not dealt out longest first, so that a second round costs more than its share:
-    // 12 heads of 2306 rows on 2665 keys in 2 parts 43 us with 256 rows, 49 with 128.)
-    if (shape != tr::kShape8x1 && p.n_parts > 1 && p.causal && n > kCUs * per_cu) continue;
-    if (shape == tr::kShape8x1) {
-      t_best = time * (n > kCUs ? 0.95 : 0.97);   // a last round that is nearly empty runs faster than a full one
-    } else {   // over several rounds the estimates lie closer together than their errors, unless there are many
-      time *= n > 8 * kCUs ? 0.97 : n > kCUs * per_cu ? 1.03 : 1.0;
-      if (time < t_best) {
-        t_best = time;
-        best = shape;
-      }
-    }
-  }
-  return best;
 }
 
 // The shape of a launch over (head, query tile) pairs; how its workgroups are placed on the XCDs.

@@ -28,6 +28,15 @@ def test_few_rows_on_many_keys_are_cut(tr):
     assert plan(tr, 1, 32, 32, 4096, 4096, 128) == (1, 0)
 
 
+def test_workgroups_of_fewer_rows_make_a_cut_needless(tr):
+    """us, cut and uncut: 31.2 and 19.0, 30.5 and 20.4, 33.5 and 25.4; still cut: 17.1 and 40.6, 47.7 and 137."""
+    assert plan(tr, 4, 3, 1, 935, 1385, 128) == (1, 0)
+    assert plan(tr, 1, 12, 4, 1611, 1611, 128, 0) == (1, 0)
+    assert plan(tr, 1, 16, 16, 1594, 2428, 64, 834) == (1, 0)
+    assert plan(tr, 1, 3, 3, 234, 4714, 128, 4480)[0] > 1
+    assert plan(tr, 1, 3, 3, 1307, 27907, 64, 26600)[0] > 1
+
+
 def test_a_packed_grid_stays_within_the_dispatch_limit(tr):
     """2^32 threads in one dimension: the plain form's second grid dimension holds what a packed launch would not."""
     assert plan(tr, 2_700_000, 2, 1, 257, 8, 64) == (1, 1)
