@@ -609,7 +609,7 @@ std::vector<StepGroup> group_steps(const std::vector<RingStep>& steps, int n_seg
 // tensor, and the Update is associative and commutative: the running softmax over the whole visible key range
 // folds the blocks in registers, so out and lse are written once and no accumulator is read back.  Against one
 // launch per iteration with the Update in the epilogue (the form this replaces; same box, us before -> after):
-// S 256 in 4 chunks 29.8 -> 11.0, causal 8192 in 8 segments 620 -> 469, causal 32768 in 8 chunks 7603 -> 6965,
+// S 256 in 4 chunks 29.8 -> 7.9, causal 8192 in 8 segments 620 -> 460, causal 32768 in 8 chunks 7603 -> 6965,
 // full 16384 at D 64 3555 -> 3201, GQA 131072 in 16 chunks 113.9 -> 109.2 ms: what goes are the set-up, the
 // epilogue and the idle tail of every launch but one.  Query rows beyond what a grid holds go out as further launches.
 // The keys are not cut (plan_parts): the result of a schedule is the same bits eagerly, in a graph and on any stream.

@@ -296,7 +296,7 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // keys, each computed exactly as a launch over that part alone would; the block results go to a
 // scratch buffer in fp32 and fold_parts_kernel adds them up in key order (a fixed
 // order: bitwise reproducible).  Bound: HBM for a decode step, MFMA otherwise, plus the fold.  Four decode steps
-// over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 141 us, 500 Query rows x 32 heads
+// over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 136 us, 500 Query rows x 32 heads
 // behind 12000 keys 216 -> 102 us against the plain form.
 //
 // FORM kChunks replays Algorithm 1 block by block: with block results that are rounded to bf16 on their way to the
@@ -306,7 +306,8 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // epilogue, the first one unrounded onto an empty accumulator.  One launch instead of two per block: no
 // block result in memory, no idle tail between the blocks (chunks of 1502 rows x 16 heads fill 96 of 256
 // compute units), the longest chunks first.  Bound: as the plain form, plus an epilogue for each block.
-// Causal 6008 rows in 4 chunks, 16 heads: 401 -> 193 us, the same bits.
+// Causal 6008 rows in 4 chunks, 16 heads: 401 -> 193 us in 256-row workgroups, 165 in shape 4 x 1; the same bits as the steps where both take
+// the same shape.
 template <int D, int EPI, int FORM, int R, int G>
 __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 2) block_attn_kernel(const AttnParams p) {
   constexpr bool PART = FORM == kPart, CHUNKS = FORM == kChunks;
