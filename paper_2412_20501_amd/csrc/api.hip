@@ -149,6 +149,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
     const int64_t tiles = (rows + bm - 1) / bm;
     if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
     if (groups && (refs > tr::kMaxRefs || heads * tiles >= 8 * kCUs)) continue;
+    if (groups && p.renew > 0 && p.renew < 64) continue;   // both groups start in the first segment
     int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
     if (p.causal && pack) {
       least = most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, (int64_t)p.Sq + p.causal_off));
@@ -482,6 +483,7 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
   set_shape(p, q, k, causal, off64);
   p.scale = scale;
   p.renew = renew;
+  p.renew_log2 = q->D == 64 ? 9 : 8;   // four tiles of a 256-row workgroup
   p.gq_log2 = -1;
   for (int sh = 0; sh < 31; sh++)
     if (p.gq == (1 << sh)) p.gq_log2 = sh;

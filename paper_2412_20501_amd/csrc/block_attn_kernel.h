@@ -526,9 +526,33 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   float l_run = 0.f;        // this lane's share of the running sum of exp
   float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite and where it is renewed
   constexpr bool RENEW = !CHUNKS;           // (the chunk form ends every segment in a block of its own)
-  int renew_at = RENEW && p.renew > 0 ? p.renew : 0x7fffffff;   // m_ref is renewed by the first step that starts at this key or later
+  // Shape 4 x 1 looks at renew_at in inner steps too: a group of its tiles (192 keys at D 64) may hold a key at which the reference is
+  // renewed.  Without a branch: the cap of that step is lowered and the slow path does the rest (DiT shape 3157 -> 3170 us, 24 heads
+  // of 1024 in 8 segments 22.9 -> 23.3; renewed by the general body alone 24.5, 4 heads of 2048 in 8 at D 64 28.2 for 24.7).
+  constexpr bool RENEW_INNER = RENEW && R == 4 && G == 1;
+  // Where the reference is renewed for a segment that starts at key r: at r, or at the next multiple of 2^renew_log2 keys while that
+  // lies in the stretch (up to renew_end) that no row of the wave needs a mask for, four quarters and more before the keys end.  A
+  // multiple is a group of inner tiles of 256-row workgroups; a function of the wave's rows and the keys alone, so every shape of the
+  // workgroup renews at the same keys and rounds the same weights.
+  const int renew_log2 = p.renew_log2;
+  int renew_end = 0;
+  if (RENEW && p.renew >= 1 << renew_log2) {
+    const int j = min(jw, kmask_from >= 0 ? kmask_from / SUB : -1) - (1 << (renew_log2 - 7)) + 1;   // a quarter's last sub-tile must pass both tests
+    const int quarters = j < 0 ? 0 : min(j >> (renew_log2 - 7), ((Sk - 1) >> (renew_log2 - 2)) - 4) + 1;
+    renew_end = __builtin_amdgcn_readfirstlane(max(0, quarters) >> 2 << renew_log2);
+  }
+  auto renew_key = [&](int r) __attribute__((always_inline)) -> int {
+    return max(r, min((r + (1 << renew_log2) - 1) >> renew_log2 << renew_log2, renew_end));
+  };
+  int segment_at = RENEW ? p.renew : 0;                                      // key at which the next segment starts
+  int renew_at = RENEW && p.renew > 0 ? renew_key(segment_at) : 0x7fffffff;  // the first step that starts here or later renews m_ref
   int segment = -1;         // later segment the wave is in, -1: the first one
-  int at_start = 0;         // 1: the wave renews at the first sub-tile of its own that the segment holds, not later
+  auto next_segment = [&]() __attribute__((always_inline)) {
+    sum_cap = -1.f;
+    segment_at += p.renew;
+    renew_at = renew_key(segment_at);
+    segment++;
+  };
   const float c2 = p.scale * 1.4426950408889634f;  // scale * log2(e)
 
   // ---- one step ---------------------------------------------------------------------
@@ -651,15 +675,17 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
 #pragma unroll
     for (int h = 0; h < 2; h++) p_out[h] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * h], pw[4 * h + 1], pw[4 * h + 2], pw[4 * h + 3]});
     float psum = ps0 + ps1;
+    float cap = sum_cap;
+    if (RENEW_INNER && INNER) cap = kstart == renew_at ? -1.f : sum_cap;
 
-    if (__builtin_expect(__any(!(psum <= sum_cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
+    if (__builtin_expect(__any(!(psum <= cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
+      if (RENEW_INNER && INNER && kstart == renew_at) next_segment();
       float tmax = s_in[0];
 #pragma unroll
       for (int i = 1; i < 16; i++) tmax = fmaxf(tmax, s_in[i]);
       tmax = half_swap_max(tmax);
-      // The segment's reference, unless this sub-tile lies beyond the fast path's range.  (Renewed late, behind a group of
-      // inner tiles, each key group takes its own sub-tile's: the weight of the segment's first maximum is already summed.)
-      if (G > 1 && RENEW && segment >= 0 && at_start && sum_cap < 0.f) {
+      // The segment's reference, unless this sub-tile lies beyond the fast path's range.
+      if (G > 1 && RENEW && segment >= 0 && sum_cap < 0.f) {
         const float seg_ref = *reinterpret_cast<const float*>(lds + Lds<D, R, G>::refs + (min(segment, kMaxRefs - 1) * BM + rg * 32 + ql) * 4);
         if (tmax > -INFINITY && seg_ref > -INFINITY && (tmax - seg_ref) * c2 <= 64.f) tmax = seg_ref;   // (no key visible: perhaps never written)
       }
@@ -714,8 +740,9 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     v_left--;
   };
 
-  // One exponent reference for a row and segment, whatever the number of key groups: the weights are then rounded
-  // alike in every shape of the workgroup.  Those of later segments are found here, each by one key group, from K rows
+  // One exponent reference for a row and segment, whatever the number of key groups, and renewed at the same keys (renew_key): the
+  // weights are then rounded alike in every shape of the workgroup (but where a row's scores leave the fast path's range: each key
+  // group raises its own).  Those of later segments are found here, each by one key group, from K rows
   // that go straight into registers (K is the A operand as it lies in memory).
   auto masked_max = [&](const f32x16& s, int kstart) __attribute__((always_inline)) -> float {
     int limit = Sk - 1;
@@ -728,7 +755,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   if constexpr (G > 1 && RENEW) {
     if (p.renew > 0) {   // at most kMaxRefs of them, see choose_shape
       auto load = [&](int s, bf16x8 (&kf)[KS]) __attribute__((always_inline)) {
-        const __bf16* kp = kg + (int64_t)min((s + 1) * p.renew + ql, Sk - 1) * p.k_ss + 8 * hf;
+        const __bf16* kp = kg + (int64_t)min(renew_key((s + 1) * p.renew) + ql, Sk - 1) * p.k_ss + 8 * hf;
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) kf[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks);
       };
@@ -738,7 +765,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
         for (int i = 0; i < 16; i++) sr[i] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) sr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sr, 0, 0, 0);
-        const float t = masked_max(sr, (s + 1) * p.renew);
+        const float t = masked_max(sr, renew_key((s + 1) * p.renew));
         if (hf == 0) *reinterpret_cast<float*>(lds + Lds<D, R, G>::refs + (s * BM + rg * 32 + ql) * 4) = t;
       };
       // two at a time: a wait for rows of K costs more than the rest
@@ -785,13 +812,9 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     const int j = NSW * u + kt;
     const int kstart = G == 1 ? j * SUB : (j * G + kgrp) * SUB;
     if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
-      if (!INNER && __builtin_expect(kstart >= renew_at, 0)) {
-        sum_cap = -1.f;
-        do {   // (once with one key group: a segment holds a sub-tile)
-          renew_at += p.renew;
-          segment++;
-        } while (G > 1 && kstart >= renew_at);
-        at_start = kstart - (renew_at - p.renew) < G * SUB;
+      if (RENEW && !INNER && __builtin_expect(kstart >= renew_at, 0)) {
+        do next_segment();   // (once with one key group: the keys lie a sub-tile apart)
+        while (G > 1 && kstart >= renew_at);
       }
       if (even) step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sA, sB, pB, pA, inner_c);
       else step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sB, sA, pA, pB, inner_c);
@@ -817,12 +840,6 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
         if (m_ref > -INFINITY) {
           mc = m_ref * c2;
           sum_cap = kSumCap;
-        }
-        while (kgrp * SUB >= renew_at) {   // segments of one sub-tile: this group starts in a later one
-          sum_cap = -1.f;
-          renew_at += p.renew;
-          segment++;
-          at_start = 1;
         }
       }
 #pragma unroll
@@ -874,7 +891,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   const int j_inner = min(min(jw, NSUB * n_tiles - 1), kmask_from >= 0 ? kmask_from / SUB : -1) - (NSUB - 1);   // last sub-tile of the tile must pass both tests
   int u_inner = j_inner < 0 ? -1 : j_inner / NSUB;
   u_inner = __builtin_amdgcn_readfirstlane(min(u_inner, last_tile - KA - 1));   // loads issued in tile u reach tile u + KA
-  if (p.renew > 0 && p.renew < NS * BN) u_inner = -1;   // inner tiles look at renew_at once a group: once a tile costs 1 - 3 % of a long ring
+  if (RENEW && !RENEW_INNER && p.renew > 0) u_inner = min(u_inner, renew_end / BN - 1);   // up to there the reference is renewed where a group starts
   // tiles 1 .. 3 (tile 0 was the prologue)
   if (1 <= n_tiles) tile_body(1, IC<1 % NS>{}, IC<0>{}, IC<1>{});
   if (2 <= n_tiles) tile_body(2, IC<2 % NS>{}, IC<0>{}, IC<0>{});
@@ -883,13 +900,8 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // general ones to the end.
   int u0 = NS;
   while (u0 + NS - 1 <= u_inner) {
-    if (u0 * BN >= renew_at) {
-      sum_cap = -1.f;
-      at_start = u0 * BN == renew_at;
-      renew_at += p.renew;
-      segment++;
-    }
-    const int stop = min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NS - 1);
+    if (!RENEW_INNER && u0 * BN >= renew_at) next_segment();
+    const int stop = !RENEW_INNER ? min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NS - 1) : u_inner;
     for (; u0 + NS - 1 <= stop; u0 += NS) {
       tile_body(u0, IC<0>{}, IC<1>{}, IC<0>{});
       tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{}, IC<0>{});

@@ -42,6 +42,7 @@ struct AttnParams {
   int n_chunks, chunk_begin, chunk_end;
   int chunk_bf16; // 1: every block after a Query chunk's first is rounded to bf16 before its Update
   int renew;      // keys (a multiple of 32) after which a row's exponent reference is taken anew; 0: never
+  int renew_log2; // log2 of the keys (at least 128) to whose next multiple that may wait
   // Partitioned form (n_parts > 0), see the kernel: n_qtiles then counts the tiles of the row space
   // (one head's Sq rows, or with pack the gq * Sq rows of a K/V head's group).
   int n_parts;    // parts of the keys, part_keys (a multiple of 128) each; 0: the plain form

@@ -1,7 +1,7 @@
 """Shapes of an attention workgroup: 128 Query rows (two or three workgroups to a compute unit), and 128 or 64 rows whose waves
 share the keys out among themselves, against workgroups of 256 rows or others of a full chip: the same inputs as one entry of a batch so large
 that the launch takes those.  All round the same weights (one
-exponent reference for a row and segment, whatever the shape), so only fp32 sums differ: a few 2^-23 of values of size 1
+exponent reference for a row and segment, renewed at the same keys whatever the shape), so only fp32 sums differ: a few 2^-23 of values of size 1
 (out) and 10 (lse).  Sizes sit at the edges of row groups, workgroups, sub-tiles and tiles of keys, and where a segment's
 reference is renewed."""
 import numpy as np
@@ -61,10 +61,24 @@ def test_rings(lib, Hq, Hkv, seg, n, D, token, causal):
     _agree(few, many)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("seg,n,D", [(1024, 2, 64), (1000, 3, 64), (545, 4, 64), (4096, 2, 64), (478, 4, 128), (700, 3, 128), (2000, 2, 128)])
+def test_rings_renew_at_the_same_keys(lib, seg, n, D, causal):
+    """One head alone and as one of 12, 16, 24 and 96, which take workgroups of other shapes: segments that start between the
+    tiles and groups of tiles of any of them round the same weights, so that fp32 sums are all that differs."""
+    q, k, v = _qkv(1, 1, seg * n, seg * n, D, 780)
+    few = _new(1, 1, seg * n, D)
+    lib.tr_ring_attn(q, k, v, n, causal, *few)
+    for heads in (12, 16, 24, 96):
+        many = _new(1, heads, seg * n, D)
+        lib.tr_ring_attn(*(x.expand(-1, heads, -1, -1) for x in (q, k, v)), n, causal, *many)
+        torch.cuda.synchronize()
+        _agree(few, [x.transpose(0, 1) for x in many])
+
+
 @pytest.mark.parametrize("Hq,Hkv,seg,n", [(1, 1, 501, 3), (2, 1, 700, 4), (2, 2, 32, 34)])
-def test_rings_renewed_elsewhere(lib, Hq, Hkv, seg, n):
-    """Segments that end between groups of inner tiles, or of which there are too many: the references differ, so the
-    weights' bf16 roundings do, by 2^-8 of a value at the worst and a few 1e-4 of its norm."""
+def test_rings_against_the_oracle(lib, Hq, Hkv, seg, n):
+    """Segments that start between groups of inner tiles, or that are as short or as many as key groups don't take."""
     S, D = seg * n, 128
     q, k, v = _qkv(Hq, Hkv, S, S, D, 710)
     ref = oracle.attention_full(f64(q.cpu().view(torch.int16).numpy().view(np.uint16)), f64(k.cpu().view(torch.int16).numpy().view(np.uint16)),
