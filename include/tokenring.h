@@ -120,6 +120,18 @@ tr_status tr_block_attn_merge(const tr_tensor* q, const tr_tensor* k, const tr_t
 int tr_block_attn_plan(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int32_t* packed);
 
 /*
+ * Host-only view of the workgroups a call on these shapes is launched in, where a scratch region is there: returns their Query
+ * rows (256, 128 or 64), -1 on invalid arguments (tr_last_error() says why).  key_groups, if given, is set to the number of
+ * groups of waves among which a row's keys are shared out (1 or 2).  form says which call; n_chunks is that of the rings (zigzag:
+ * twice its devices), 1 for block steps, and positions are those of block steps.  Touches no device.
+ */
+enum { TR_FORM_STEP_BF16 = 0, TR_FORM_STEP_F32 = 1, TR_FORM_STEP_MERGE = 2,   /* block step: type of out, or tr_block_attn_merge */
+       TR_FORM_RING = 3,                                                       /* every ring with fp32 blocks */
+       TR_FORM_RING_BF16 = 4 };                                                /* tr_ring_attn_blocks with TR_BF16 */
+int tr_attn_workgroup(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int form, int n_chunks,
+                      int32_t* key_groups);
+
+/*
  * Out, Lse <- Update(block_out, block_lse), the two equations of Sec. 3.1, in place:
  *   out_acc <- out_acc - sigmoid(block_lse - lse_acc) * (out_acc - block_out)
  *   lse_acc <- lse_acc - ln(sigmoid(lse_acc - block_lse))

@@ -383,50 +383,53 @@ void use_shape(tr::AttnParams& p, int shape) {
   if (p.xcd_map && !p.causal && p.n_chunks == 0 && (int64_t)p.B * p.Hq / 8 <= 65535) p.xcd_map = 2;
 }
 
-hipError_t launch_plain(const tr::AttnParams& plain, int D, int epilogue, hipStream_t stream) {
-  tr::AttnParams p = plain;
-  use_shape(p, choose_shape(p, D, false, epilogue == 0 ? 2 : epilogue == 1 ? 4 : 8));
-  return tr::launch_block_attn(p, D, epilogue, stream);
+// The shape of a launch over the row tiles of K/V heads (of each query head, or with plan.pack of a K/V head's whole group).
+void use_packed_shape(tr::AttnParams& p, const PartPlan& plan, int shape) {
+  const int bm = tr::shape_rows(shape), space = plan.pack ? p.gq * p.Sq : p.Sq;
+  p.shape = shape;
+  p.bm = bm;
+  p.pack = plan.pack;
+  p.n_qtiles = (space + bm - 1) / bm;
+  p.members = plan.pack ? p.n_qtiles : p.gq * p.n_qtiles;
+  p.part_rows = space > bm ? bm : (space + 31) / 32 * 32;
+}
+int64_t scratch_rows(const tr::AttnParams& p) { return (int64_t)p.B * p.Hkv * p.members * p.n_parts * p.part_rows; }
+
+// Settles form and shape of a call that plan_parts has looked at (planned: its answer); scratch: a region is there.
+void settle_launch(tr::AttnParams& p, const PartPlan& plan, bool planned, int D, int epilogue, bool scratch) {
+  const int out_bytes = epilogue == 0 ? 2 : epilogue == 1 ? 4 : 8;
+  if (planned && plan.parts > 1 && scratch) {
+    p.n_parts = plan.parts;
+    p.part_keys = (int)plan.part_keys;
+    use_packed_shape(p, plan, choose_shape(p, D, plan.pack, 4));
+    if (scratch_rows(p) * (D + 1) * 4 > kPartBytes) use_packed_shape(p, plan, tr::kShape8x1);   // the form the plan has counted for
+    p.units = p.B * p.Hkv * p.n_parts;
+  } else if (planned && plan.packs_uncut) {
+    // (Without scratch, all keys at once, here and below.  The parts one after the other, folded in the output, give the bits of the cut
+    // form but pay a set-up and an epilogue for each: 1764 rows x 2 heads on 6491 keys 202 us replayed from a graph
+    // against 91 in one pass, a decode step of 4 sequences on 8192 keys 121 against 90.)
+    p.n_parts = 1;
+    p.part_keys = (p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
+    use_packed_shape(p, plan, choose_shape(p, D, plan.pack, out_bytes));
+    p.units = p.B * p.Hkv;
+  } else {
+    use_shape(p, choose_shape(p, D, false, out_bytes));
+  }
 }
 
-hipError_t launch_planned(const tr::AttnParams& plain, const PartPlan& plan, int D, int epilogue, hipStream_t stream) {
-  tr::AttnParams p = plain;
-  auto use = [&](int shape) {   // the row space in tiles of the shape's rows
-    const int bm = tr::shape_rows(shape);
-    p.shape = shape;
-    const int space = plan.pack ? p.gq * p.Sq : p.Sq;
-    p.bm = bm;
-    p.pack = plan.pack;
-    p.n_qtiles = (space + bm - 1) / bm;
-    p.members = plan.pack ? p.n_qtiles : p.gq * p.n_qtiles;
-    p.part_rows = space > bm ? bm : (space + 31) / 32 * 32;
-  };
-  if (plan.parts > 1) {
-    if (PartPool* pool = part_pool_for(stream)) {
-      std::lock_guard<std::mutex> hold(pool->lock);   // another thread on this stream must not enqueue between attention and fold
-      if (PartRegion* r = take_region(*pool, stream)) {
-        p.n_parts = plan.parts;
-        p.part_keys = (int)plan.part_keys;
-        use(choose_shape(p, D, plan.pack, 4));
-        const auto slot_rows = [&]() { return (int64_t)p.B * p.Hkv * p.members * p.n_parts * p.part_rows; };
-        if (slot_rows() * (D + 1) * 4 > kPartBytes) use(tr::kShape8x1);   // the form the plan has counted for
-        p.units = p.B * p.Hkv * p.n_parts;
-        p.part_out = (float*)r->bytes;
-        p.part_lse = p.part_out + slot_rows() * D;
-        const hipError_t e = tr::launch_block_attn(p, D, epilogue, stream, r->done);
-        if (e != hipSuccess) (void)hipEventRecord(r->done, stream);   // the fold did not go out, the attention may have
-        return e;
-      }
+hipError_t launch_planned(tr::AttnParams& p, const PartPlan& plan, bool planned, int D, int epilogue, hipStream_t stream) {
+  if (PartPool* pool = planned && plan.parts > 1 ? part_pool_for(stream) : nullptr) {
+    std::lock_guard<std::mutex> hold(pool->lock);   // another thread on this stream must not enqueue between attention and fold
+    if (PartRegion* r = take_region(*pool, stream)) {
+      settle_launch(p, plan, planned, D, epilogue, true);
+      p.part_out = (float*)r->bytes;
+      p.part_lse = p.part_out + scratch_rows(p) * D;
+      const hipError_t e = tr::launch_block_attn(p, D, epilogue, stream, r->done);
+      if (e != hipSuccess) (void)hipEventRecord(r->done, stream);   // the fold did not go out, the attention may have
+      return e;
     }
   }
-  // All keys at once, in one launch.  (The parts one after the other, folded in the output, give the bits of the cut
-  // form but pay a set-up and an epilogue for each: 1764 rows x 2 heads on 6491 keys 202 us replayed from a graph
-  // against 91 in one pass, a decode step of 4 sequences on 8192 keys 121 against 90.)
-  if (!plan.packs_uncut) return launch_plain(plain, D, epilogue, stream);
-  p.n_parts = 1;
-  p.part_keys = (p.Sk + kPartAlign - 1) / kPartAlign * kPartAlign;
-  use(choose_shape(p, D, plan.pack, epilogue == 0 ? 2 : epilogue == 1 ? 4 : 8));
-  p.units = p.B * p.Hkv;
+  settle_launch(p, plan, planned, D, epilogue, false);
   return tr::launch_block_attn(p, D, epilogue, stream);
 }
 
@@ -504,8 +507,8 @@ tr_status attn_common(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v
     return TR_OK;
   }
   PartPlan plan;
-  const hipError_t e = plan_parts(p, (int)q->D, may_cut, plan) ? launch_planned(p, plan, (int)q->D, epilogue, (hipStream_t)stream)
-                                                                 : launch_plain(p, (int)q->D, epilogue, (hipStream_t)stream);
+  const bool planned = plan_parts(p, (int)q->D, may_cut, plan);
+  const hipError_t e = launch_planned(p, plan, planned, (int)q->D, epilogue, (hipStream_t)stream);
   if (e != hipSuccess) return fail(TR_ERR_HIP, "block attention launch failed: %s", hipGetErrorString(e));
   return TR_OK;
 }
@@ -607,6 +610,9 @@ std::vector<StepGroup> group_steps(const std::vector<RingStep>& steps, int n_seg
   return groups;
 }
 
+// Keys after which a ring of n_seg segments renews the exponent reference of a row: a segment in whole sub-tiles.
+int ring_renewal(int64_t seg, int n_seg) { return n_seg > 1 ? (int)(seg / 32 * 32) : 0; }
+
 // Every block step of a schedule on one GPU.  The K/V segments a Query segment meets lie side by side in one
 // tensor, and the Update is associative and commutative: the running softmax over the whole visible key range
 // folds the blocks in registers, so out and lse are written once and no accumulator is read back.  Against one
@@ -629,7 +635,7 @@ tr_status attn_whole(const tr_tensor* q, const tr_tensor* k, const tr_tensor* v,
     const tr_tensor o0 = rows_view(out, 0, seg), l0 = rows_view(lse, 0, seg);
     return attn_common(&q0, &k0, &v0, causal, 0, scale, &o0, &l0, stream, true, n_seg);
   }
-  const int renew = n_seg > 1 ? (int)(seg / 32 * 32) : 0;
+  const int renew = ring_renewal(seg, n_seg);
   const int64_t slab = 65535 * bm;
   int64_t r0 = 0;
   do {
@@ -698,24 +704,53 @@ tr_status tr_block_attn_merge(const tr_tensor* q, const tr_tensor* k, const tr_t
   return attn_common(q, k, v, mask_kind == TR_MASK_CAUSAL_DIAG, 0, scale, out_acc, lse_acc, hip_stream, true);
 }
 
-int tr_block_attn_plan(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int32_t* packed) {
+// Checks of the host-only views; true: the sizes are in p.
+static bool view_sizes(tr::AttnParams& p, const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0) {
   g_err[0] = 0;
-  if (check_tensor("q", q, true, false, 16) != TR_OK || check_tensor("k", k, true, false, 16) != TR_OK) return -1;
+  if (check_tensor("q", q, true, false, 16) != TR_OK || check_tensor("k", k, true, false, 16) != TR_OK) return false;
   if (q_pos0 < 0 || k_pos0 < 0) {
     fail(TR_ERR_SHAPE, "chunk positions must be >= 0");
-    return -1;
+    return false;
   }
   if ((q->D != 64 && q->D != 128) || k->D != q->D || k->B != q->B || (q->H > 0 && (k->H <= 0 || q->H % k->H))) {
     fail(TR_ERR_SHAPE, "q and k do not fit together");
-    return -1;
+    return false;
   }
-  tr::AttnParams p;
   memset(&p, 0, sizeof(p));
   set_shape(p, q, k, causal, q_pos0 - k_pos0);
+  return true;
+}
+
+int tr_block_attn_plan(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int32_t* packed) {
+  tr::AttnParams p;
+  if (!view_sizes(p, q, k, causal, q_pos0, k_pos0)) return -1;
   PartPlan plan;
   const bool planned = plan_parts(p, (int)q->D, true, plan);
   if (packed) *packed = planned ? plan.pack : 0;
   return planned ? plan.parts : 1;
+}
+
+int tr_attn_workgroup(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int form, int n_chunks, int32_t* key_groups) {
+  tr::AttnParams p;
+  if (!view_sizes(p, q, k, causal, q_pos0, k_pos0)) return -1;
+  const int D = (int)q->D;
+  if (form < TR_FORM_STEP_BF16 || form > TR_FORM_RING_BF16 || n_chunks < 1 || (form >= TR_FORM_RING && (q->S % n_chunks || k->S != q->S))) {
+    fail(TR_ERR_SHAPE, "unknown form %d, or a sequence that is no multiple of %d chunks", form, n_chunks);
+    return -1;
+  }
+  const int64_t seg = q->S / n_chunks;
+  if (form == TR_FORM_RING_BF16 || (form == TR_FORM_RING && n_chunks > 1 && seg < 32)) {
+    p.Sq = p.Sk = (int)seg;
+    p.n_chunks = n_chunks;
+    use_shape(p, choose_shape(p, D, false, 8));
+  } else {
+    p.renew = form == TR_FORM_RING ? ring_renewal(seg, n_chunks) : 0;
+    PartPlan plan;
+    const bool planned = plan_parts(p, D, form != TR_FORM_RING, plan);
+    settle_launch(p, plan, planned, D, form == TR_FORM_RING ? 1 : form, true);
+  }
+  if (key_groups) *key_groups = tr::shape_key_groups(p.shape);
+  return p.bm;
 }
 
 tr_status tr_merge(const tr_tensor* out_acc, const tr_tensor* lse_acc, const tr_tensor* block_out, const tr_tensor* block_lse,

@@ -14,6 +14,7 @@ constexpr int kMaxParts = 16;  // parts the keys of one partitioned attention la
 // Shapes of an attention workgroup: row groups of 32 Query rows x key groups.
 constexpr int kShape8x1 = 0, kShape4x1 = 1, kShape4x2 = 2, kShape2x2 = 3;
 constexpr int shape_rows(int shape) { return shape == kShape8x1 ? 256 : shape == kShape2x2 ? 64 : 128; }
+constexpr int shape_key_groups(int shape) { return shape >= kShape4x2 ? 2 : 1; }
 
 // Arguments of the block-attention kernel: raw pointers, element strides, sizes.
 struct AttnParams {

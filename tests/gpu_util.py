@@ -19,6 +19,20 @@ def attn_plan(lib, B, Hq, Hkv, Sq, Sk, D, offset=None):
     return parts, packed.value
 
 
+STEP_BF16, STEP_F32, STEP_MERGE, RING, RING_BF16 = range(5)
+
+
+def attn_shape(lib, form, B, Hq, Hkv, Sq, Sk, D, offset=None, n=1):
+    """(Query rows of a workgroup, key groups) of a call on these shapes; offset as above, n chunks of a ring.  Host only."""
+    def t(H, S, ptr):
+        return lib.TrTensor(ptr, lib.TR_BF16, B, H, S, D, H * S * D, S * D, D)
+    groups = ctypes.c_int32(-1)
+    off = offset or 0
+    rows = lib.raw_lib().tr_attn_workgroup(ctypes.byref(t(Hq, Sq, 0x7F0000000000)), ctypes.byref(t(Hkv, Sk, 0x7F8000000000)),
+                                           int(offset is not None), max(off, 0), max(-off, 0), form, n, ctypes.byref(groups))
+    return rows, groups.value
+
+
 def bits_to_dev(bits: np.ndarray) -> torch.Tensor:
     """bf16 bit patterns (uint16 numpy) -> bf16 torch tensor on cuda:0 with the same bits."""
     return torch.from_numpy(bits.view(np.int16)).to("cuda").view(torch.bfloat16)

@@ -1,12 +1,13 @@
 """tr_ring_attn_blocks with bf16 blocks against Algorithm 1 spelled out by the caller: tr_block_attn into a bf16
 block_out (the first block of a chunk straight into the accumulators), tr_merge after it, in the schedule's
-order.  The same bits.  Chunk lengths sit around tiles; up to 512 keys a block step is one pass over its keys."""
+order.  The same bits where both share the keys out alike (the number of key groups, asserted; with another one fp32 sums differ,
+and so does what is rounded to bf16).  Chunk lengths sit around tiles; up to 512 keys a block step is one pass over its keys."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from gpu_util import bits_to_dev, rand_bits
+from gpu_util import RING_BF16, STEP_BF16, STEP_F32, attn_shape, bits_to_dev, rand_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -22,6 +23,10 @@ pytestmark = pytest.mark.gpu
 ])
 def test_bf16_blocks_are_the_steps_one_by_one(lib, B, Hq, Hkv, chunk, n, D, token, causal):
     S, scale = chunk * n, 1.0 / np.sqrt(D)
+    off = 0 if causal else None
+    groups = {attn_shape(lib, RING_BF16, B, Hq, Hkv, S, S, D, off, n)[1], attn_shape(lib, STEP_F32, B, Hq, Hkv, chunk, chunk, D, off)[1]}
+    groups |= {attn_shape(lib, STEP_BF16, B, Hq, Hkv, chunk, chunk, D)[1]} if n > 1 else set()
+    assert len(groups) == 1 or chunk <= 32               # (a sub-tile belongs to one group)
 
     def tensor(H, seed):
         x = rand_bits((B, H, S, D), seed)

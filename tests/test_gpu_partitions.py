@@ -1,7 +1,7 @@
 """Attention on grids that leave the chip idle: keys cut into parts, grouped query heads packed into one row space.
 
 Sizes sit where the form can go wrong: row counts around a wave and a tile, a last part of one key, parts
-that no row of a tile sees, heads that share a wave; the expected form stands beside each.  Reference: the fp64 oracle, tolerances as for every
+that no row of a tile sees, heads that share a wave; the expected form, and the shape of the workgroups, stand beside each.  Reference: the fp64 oracle, tolerances as for every
 block step.  Without scratch (under graph capture, on a stream beyond those that have a region) the keys are one piece.
 """
 import numpy as np
@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import attn_plan, bits_to_dev, f64, max_abs, rand_bits, to_np
+from gpu_util import STEP_BF16, STEP_F32, STEP_MERGE, attn_plan, attn_shape, bits_to_dev, f64, max_abs, rand_bits, to_np
 
 pytestmark = pytest.mark.gpu
 OUT_TOL, LSE_TOL = 1e-2, 1e-3
@@ -32,8 +32,34 @@ FORMS = {
     (30, 12, 4, 30, 500, 128, 480): (1, 1),       # the same, causal, three heads in 90 rows
     (9, 32, 8, 300, 330, 64, 20): (1, 1),         # the same, a tile that ends one head and starts the next
     (66, 32, 8, 2, 70, 64, None): (1, 1),         # more than two rounds of packed tiles
+    (1, 32, 8, 73, 5186, 64, None): (11, 1),      # 256-row workgroups, packed: 292 rows
+    (2, 12, 4, 135, 4095, 128, 3960): (8, 1),     # the same, causal: 405 rows of three heads
+    (2, 4, 4, 299, 5172, 64, None): (11, 0),      # not packed: 43 rows in the second tile
+    (1, 8, 8, 388, 4460, 128, 4072): (9, 0),      # the same, causal
+    (3, 6, 3, 129, 2825, 128, None): (6, 0),      # 128-row workgroups: one row in the second
+    (4, 6, 2, 45, 6006, 128, None): (12, 1),      # the same, packed: 135 rows
+    (1, 16, 16, 133, 2797, 128, 2664): (6, 0),    # 128 rows and two key groups, causal
+    (4, 12, 4, 43, 2730, 128, None): (6, 1),      # the same, packed: 129 rows
+    (1, 32, 16, 68, 2637, 128, 2569): (6, 1),     # the same, causal: 136 rows of two heads
 }
 CASES = list(FORMS)
+ROWS_256, ROWS_128, ROWS_128_GROUPS, ROWS_64_GROUPS = (256, 1), (128, 1), (128, 2), (64, 2)    # Query rows of a workgroup, key groups
+SHAPES = dict.fromkeys(CASES, ROWS_64_GROUPS)
+SHAPES.update({
+    (1, 8, 1, 600, 1600, 64, 1000): ROWS_128,
+    (30, 12, 4, 30, 500, 128, 480): ROWS_256,
+    (9, 32, 8, 300, 330, 64, 20): ROWS_128,
+    (66, 32, 8, 2, 70, 64, None): ROWS_128,
+    (1, 32, 8, 73, 5186, 64, None): ROWS_256,
+    (2, 12, 4, 135, 4095, 128, 3960): ROWS_256,
+    (2, 4, 4, 299, 5172, 64, None): ROWS_256,
+    (1, 8, 8, 388, 4460, 128, 4072): ROWS_256,
+    (3, 6, 3, 129, 2825, 128, None): ROWS_128,
+    (4, 6, 2, 45, 6006, 128, None): ROWS_128,
+    (1, 16, 16, 133, 2797, 128, 2664): ROWS_128_GROUPS,
+    (4, 12, 4, 43, 2730, 128, None): ROWS_128_GROUPS,
+    (1, 32, 16, 68, 2637, 128, 2569): ROWS_128_GROUPS,
+})
 
 
 def _inputs(case, seed):
@@ -59,6 +85,26 @@ def _reference(case, qb, kb, vb, scale):
 @pytest.mark.parametrize("case", CASES, ids=str)
 def test_the_cases_take_the_forms_they_stand_for(lib, case):
     assert attn_plan(lib, *case) == FORMS[case]
+    assert {attn_shape(lib, form, *case) for form in (STEP_BF16, STEP_F32, STEP_MERGE)} == {SHAPES[case]}
+
+
+def test_parts_of_small_workgroups_that_scratch_does_not_hold(lib):
+    """136 rows are 160 of a 256-row workgroup's slot and 256 of two 128-row ones: 144 heads in 5 parts fit the 33 MiB of a region
+    only in the first form, which the call goes back to (96 heads take 128 rows)."""
+    B, H, Sq, Sk, D = 6, 24, 136, 29362, 64
+    assert attn_plan(lib, 4, H, H, Sq, Sk, D) == (5, 0) and attn_shape(lib, STEP_F32, 4, H, H, Sq, Sk, D) == ROWS_128
+    assert attn_plan(lib, B, H, H, Sq, Sk, D) == (5, 0) and attn_shape(lib, STEP_F32, B, H, H, Sq, Sk, D) == ROWS_256
+    assert B * H * 5 * 160 * (D + 1) * 4 <= 33 << 20 < B * H * 5 * 256 * (D + 1) * 4
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (torch.randn((B, H, S, D), device="cuda", generator=gen).bfloat16() for S in (Sq, Sk, Sk))
+    out, lse = torch.full((B, H, Sq, D), float("nan"), device="cuda"), torch.full((B, H, Sq), float("nan"), device="cuda")
+    lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, D ** -0.5, out, lse)
+    torch.cuda.synchronize()
+    for b in range(B):
+        s = (q[b].double() * D ** -0.5) @ k[b].double().transpose(-1, -2).contiguous()
+        want_l = torch.logsumexp(s, -1)
+        want_o = torch.exp(s - want_l[..., None]) @ v[b].double()
+        assert float((out[b] - want_o).abs().max()) <= OUT_TOL and float((lse[b] - want_l).abs().max()) <= LSE_TOL
 
 
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])

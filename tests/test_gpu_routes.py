@@ -83,7 +83,8 @@ def test_an_eager_call_beside_a_capture_leaves_the_capture_alone(lib):
     lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, 0.1, out, lse)
     graph_o, graph_l = new()
     beside = [new() for _ in range(6)]
-    streams = [torch.cuda.Stream() for _ in beside]
+    # torch deals its streams out in turn, and the one that captures is one of them
+    streams = [s for s in (torch.cuda.Stream() for _ in range(len(beside) + 1)) if s != torch.cuda.graph.default_capture_stream]
     torch.cuda.synchronize()
 
     def run():

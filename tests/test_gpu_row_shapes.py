@@ -1,6 +1,6 @@
 """Shapes of an attention workgroup: 128 Query rows (two or three workgroups to a compute unit), and 128 or 64 rows whose waves
-share the keys out among themselves, against workgroups of 256 rows or others of a full chip: the same inputs as one entry of a batch so large
-that the launch takes those.  All round the same weights (one
+share the keys out among themselves, against what a full chip takes, workgroups of 128 or 256 rows with one key group: the same inputs as one
+entry of a batch so large that the launch takes those.  The shape a case stands for is beside it.  All round the same weights (one
 exponent reference for a row and segment, renewed at the same keys whatever the shape), so only fp32 sums differ: a few 2^-23 of values of size 1
 (out) and 10 (lse).  Sizes sit at the edges of row groups, workgroups, sub-tiles and tiles of keys, and where a segment's
 reference is renewed."""
@@ -9,10 +9,11 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import bits_to_dev, f64, max_abs, rand_bits, to_np
+from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, STEP_MERGE, attn_shape, bits_to_dev, f64, max_abs, rand_bits, to_np
 
 pytestmark = pytest.mark.gpu
-MANY = 2048      # (batch, head, row tile) triples of 256 rows from which on every launch takes 256 rows
+MANY = 2048      # (batch, head, row tile) triples of 256 rows from which on the launches here take 128 rows and one key group
+ROWS_256, ROWS_128, ROWS_128_GROUPS, ROWS_64_GROUPS = (256, 1), (128, 1), (128, 2), (64, 2)    # Query rows of a workgroup, key groups
 
 
 def _qkv(Hq, Hkv, Sq, Sk, D, seed, token=False):
@@ -36,25 +37,28 @@ def _agree(few, many, tol=1e-5):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("Hq,Hkv,seg,n,D,token", [
-    (1, 1, 1, 1, 64, False),
-    (2, 1, 33, 2, 128, True),          # a reference every sub-tile
-    (1, 1, 96, 4, 128, False),         # segments of three sub-tiles: their first one belongs to either key group
-    (3, 1, 65, 1, 64, True),           # one row in the second workgroup
-    (2, 2, 129, 1, 128, False),
-    (2, 1, 191, 3, 64, False),
-    (1, 1, 128, 33, 128, False),       # as many later references as are kept
-    (8, 2, 1024, 2, 128, False),       # renewed between groups of inner tiles
-    (4, 4, 1536, 2, 64, False),
-    (24, 8, 1000, 1, 64, True),        # 128 rows
-    (20, 20, 768, 1, 128, False),
+@pytest.mark.parametrize("Hq,Hkv,seg,n,D,token,shape", [
+    (1, 1, 1, 1, 64, False, ROWS_256),
+    (2, 1, 33, 2, 128, True, ROWS_256),            # a reference every sub-tile, which key groups don't take
+    (1, 1, 96, 4, 128, False, ROWS_64_GROUPS),     # segments of three sub-tiles: their first one belongs to either key group
+    (3, 1, 65, 1, 64, True, ROWS_256),
+    (2, 2, 129, 1, 128, False, ROWS_64_GROUPS),    # one row in the third workgroup
+    (2, 1, 191, 3, 64, False, ROWS_64_GROUPS),
+    (1, 1, 128, 33, 128, False, ROWS_128),         # 32 later references, by 128-row workgroups on either side
+    (1, 1, 288, 33, 128, False, ROWS_64_GROUPS),   # as many later references as key groups keep
+    (8, 2, 1024, 2, 128, False, ROWS_64_GROUPS),   # renewed between groups of inner tiles
+    (4, 4, 1536, 2, 64, False, ROWS_64_GROUPS),
+    (24, 8, 1000, 1, 64, True, ROWS_128_GROUPS),
+    (20, 20, 768, 1, 128, False, ROWS_64_GROUPS),
 ])
-def test_rings(lib, Hq, Hkv, seg, n, D, token, causal):
+def test_rings(lib, Hq, Hkv, seg, n, D, token, shape, causal):
     S = seg * n
     q, k, v = _qkv(Hq, Hkv, S, S, D, 700, token)
     few = _new(1, Hq, S, D)
     lib.tr_ring_attn(q, k, v, n, causal, *few)
     B = -(-MANY // (Hq * -(-S // 256)))
+    assert attn_shape(lib, RING, 1, Hq, Hkv, S, S, D, 0 if causal else None, n) == shape
+    assert attn_shape(lib, RING, B, Hq, Hkv, S, S, D, 0 if causal else None, n) == ROWS_128
     many = _new(B, Hq, S, D)
     lib.tr_ring_attn(q.expand(B, -1, -1, -1), k.expand(B, -1, -1, -1), v.expand(B, -1, -1, -1), n, causal, *many)
     torch.cuda.synchronize()
@@ -64,16 +68,23 @@ def test_rings(lib, Hq, Hkv, seg, n, D, token, causal):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("seg,n,D", [(1024, 2, 64), (1000, 3, 64), (545, 4, 64), (4096, 2, 64), (478, 4, 128), (700, 3, 128), (2000, 2, 128)])
 def test_rings_renew_at_the_same_keys(lib, seg, n, D, causal):
-    """One head alone and as one of 12, 16, 24 and 96, which take workgroups of other shapes: segments that start between the
+    """One head alone and as one of several, which take workgroups of other shapes: segments that start between the
     tiles and groups of tiles of any of them round the same weights, so that fp32 sums are all that differs."""
     q, k, v = _qkv(1, 1, seg * n, seg * n, D, 780)
     few = _new(1, 1, seg * n, D)
     lib.tr_ring_attn(q, k, v, n, causal, *few)
-    for heads in (12, 16, 24, 96):
+    shapes = [attn_shape(lib, RING, 1, 1, 1, seg * n, seg * n, D, 0 if causal else None, n)]
+    for heads in (2, 4, 8, 12, 16, 24, 32, 96):
+        shapes.append(attn_shape(lib, RING, 1, heads, heads, seg * n, seg * n, D, 0 if causal else None, n))
+        if shapes[-1] in shapes[:-1]:
+            continue
         many = _new(1, heads, seg * n, D)
         lib.tr_ring_attn(*(x.expand(-1, heads, -1, -1) for x in (q, k, v)), n, causal, *many)
         torch.cuda.synchronize()
         _agree(few, [x.transpose(0, 1) for x in many])
+    assert shapes[0] == ROWS_64_GROUPS and ROWS_128 in shapes
+    assert ROWS_256 in shapes or (causal and (seg, n) in ((1024, 2), (545, 4), (478, 4)))
+    assert ROWS_128_GROUPS in shapes or (seg, n) not in ((4096, 2), (2000, 2)) or (seg, causal) == (2000, False)
 
 
 @pytest.mark.parametrize("Hq,Hkv,seg,n", [(1, 1, 501, 3), (2, 1, 700, 4), (2, 2, 32, 34)])
@@ -99,20 +110,26 @@ def _exact(q, k, v, off):
     return torch.exp(s - lse.masked_fill(torch.isinf(lse), 0.0)[..., None]) @ v.double().repeat_interleave(g, 1), lse
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,off", [
-    (2, 24, 8, 300, 300, 128, None),   # two workgroups to a compute unit; a ragged last one
-    (2, 24, 8, 300, 300, 64, None),    # three
-    (3, 32, 32, 129, 31, 64, None),    # one row in the second workgroup, less than a sub-tile
-    (3, 32, 32, 129, 65, 64, None),    # one key in the second tile
-    (3, 32, 32, 129, 193, 64, 64),     # a ring of three tiles once round, and one key more
-    (3, 32, 32, 140, 257, 64, 117),
-    (3, 32, 32, 140, 161, 128, 21),    # a ring of four tiles of 32 keys once round, and one more
-    (3, 32, 32, 250, 700, 128, 500),   # inner tiles, keys that no row sees
-    (3, 32, 32, 250, 700, 64, -100),   # rows without any key
-    (1, 64, 16, 1024, 1024, 64, 0),
-    (1, 64, 16, 1024, 1024, 128, 0),
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,off,shape", [
+    (2, 24, 8, 300, 300, 128, None, ROWS_64_GROUPS),    # a ragged last workgroup
+    (2, 24, 8, 300, 300, 64, None, ROWS_64_GROUPS),
+    (9, 24, 8, 300, 300, 128, None, ROWS_128),          # two workgroups to a compute unit
+    (4, 24, 8, 300, 300, 64, None, ROWS_128),           # three
+    (3, 32, 32, 129, 31, 64, None, ROWS_128),           # one row in the second workgroup, less than a sub-tile
+    (3, 32, 32, 129, 65, 64, None, ROWS_128),           # one key in the second tile
+    (3, 32, 32, 129, 193, 64, 64, ROWS_128),            # a ring of three tiles once round, and one key more
+    (3, 32, 32, 140, 257, 64, 117, ROWS_128),
+    (3, 32, 32, 140, 161, 128, 21, ROWS_64_GROUPS),
+    (4, 32, 32, 140, 161, 128, 21, ROWS_128),           # a ring of four tiles of 32 keys once round, and one more
+    (4, 32, 32, 140, 129, 128, None, ROWS_128),         # one key in the fifth tile
+    (3, 32, 32, 250, 700, 128, 500, ROWS_128_GROUPS),   # inner tiles, keys that no row sees
+    (4, 32, 32, 250, 700, 128, 500, ROWS_128),
+    (3, 32, 32, 250, 700, 64, -100, ROWS_128),          # rows without any key
+    (1, 64, 16, 1024, 1024, 64, 0, ROWS_128),
+    (1, 64, 16, 1024, 1024, 128, 0, ROWS_128),
 ])
-def test_small_workgroups(lib, B, Hq, Hkv, Sq, Sk, D, off):
+def test_small_workgroups(lib, B, Hq, Hkv, Sq, Sk, D, off, shape):
+    assert attn_shape(lib, STEP_F32, B, Hq, Hkv, Sq, Sk, D, off) == shape
     q, k, v = (bits_to_dev(rand_bits((B, h, S, D), 740 + i)) for i, (h, S) in enumerate(((Hq, Sq), (Hkv, Sk), (Hkv, Sk))))
     out, lse = _new(B, Hq, Sq, D)
     if off is None:
@@ -129,8 +146,9 @@ def test_small_workgroups(lib, B, Hq, Hkv, Sq, Sk, D, off):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("causal", [False, True])
 def test_bf16_blocks_of_small_workgroups(lib, D, causal):
-    """96 heads of 3 chunks of 300 rows: the chunk form and its steps spelled out, which take other shapes."""
+    """96 heads of 3 chunks of 300 rows in the chunk form."""
     B, H, chunk, n = 4, 24, 300, 3
+    assert attn_shape(lib, RING_BF16, B, H, H, chunk * n, chunk * n, D, 0 if causal else None, n) == ROWS_128
     q, k, v = (bits_to_dev(rand_bits((B, H, chunk * n, D), 760 + i)) for i in range(3))
     out, lse = _new(B, H, chunk * n, D)
     ws = torch.empty(lib.tr_ring_attn_blocks_workspace_bytes(q, n, lib.TR_BF16), dtype=torch.uint8, device="cuda")
@@ -142,21 +160,26 @@ def test_bf16_blocks_of_small_workgroups(lib, D, causal):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, None])   # None: merged into accumulators
-@pytest.mark.parametrize("Hq,Hkv,Sq,Sk,D,off", [
-    (1, 1, 1, 1, 64, None),
-    (2, 1, 31, 33, 128, None),         # one sub-tile and one key, the second key group's
-    (2, 2, 64, 64, 64, 0),
-    (1, 1, 130, 500, 128, 370),        # causal, the last row sees the last key
-    (3, 3, 70, 129, 64, 20),           # keys that no row sees
-    (2, 1, 200, 450, 128, -90),        # rows that see none
-    (12, 4, 500, 512, 64, 12),         # 128 rows
-    (16, 8, 700, 300, 128, None),
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk,D,off,shape", [
+    (1, 1, 1, 1, 64, None, ROWS_256),
+    (2, 1, 31, 33, 128, None, ROWS_256),           # one sub-tile and one key
+    (2, 2, 64, 64, 64, 0, ROWS_256),
+    (2, 2, 129, 97, 128, None, ROWS_64_GROUPS),    # an odd sub-tile of one key, the second key group's
+    (1, 1, 130, 500, 128, 370, ROWS_64_GROUPS),    # causal, the last row sees the last key
+    (3, 3, 70, 129, 64, 20, ROWS_256),             # keys that no row sees
+    (2, 1, 200, 450, 128, -90, ROWS_64_GROUPS),    # rows that see none
+    (12, 4, 500, 512, 64, 12, ROWS_64_GROUPS),
+    (16, 8, 700, 300, 128, None, ROWS_64_GROUPS),
+    (32, 32, 624, 738, 64, None, ROWS_128_GROUPS),
+    (32, 32, 612, 964, 128, 352, ROWS_128_GROUPS),
 ])
-def test_steps(lib, Hq, Hkv, Sq, Sk, D, off, dtype):
+def test_steps(lib, Hq, Hkv, Sq, Sk, D, off, shape, dtype):
     if dtype is None and off is not None:
         pytest.skip("the merging step has no causal rule at arbitrary positions")
     q, k, v = _qkv(Hq, Hkv, Sq, Sk, D, 720, True)
     B = -(-MANY // (Hq * -(-Sq // 256)))
+    form = {None: STEP_MERGE, torch.float32: STEP_F32, torch.bfloat16: STEP_BF16}[dtype]
+    assert attn_shape(lib, form, 1, Hq, Hkv, Sq, Sk, D, off) == shape and attn_shape(lib, form, B, Hq, Hkv, Sq, Sk, D, off) == ROWS_128
 
     def run(B, q, k, v):
         out, lse = _new(B, Hq, Sq, D, dtype or torch.float32)

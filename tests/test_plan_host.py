@@ -1,7 +1,8 @@
-"""Which form an attention call takes (tr_block_attn_plan: host only, nothing is launched): parts of the keys, packed heads."""
+"""Which form an attention call takes (tr_block_attn_plan, tr_attn_workgroup: host only, nothing is launched): parts of the keys,
+packed heads, shape of the workgroups."""
 import pytest
 
-from gpu_util import attn_plan as plan
+from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, attn_plan as plan, attn_shape as shape
 
 
 @pytest.fixture(scope="module")
@@ -43,7 +44,22 @@ def test_a_packed_grid_stays_within_the_dispatch_limit(tr):
     assert plan(tr, 2_800_000, 2, 1, 257, 8, 64) == (1, 0)
 
 
+def test_shapes_of_a_workgroup(tr):
+    assert shape(tr, RING, 1, 32, 32, 32768, 32768, 128, 0, 8) == (256, 1)      # a full chip
+    assert shape(tr, RING, 2, 24, 24, 16384, 16384, 64, None, 4) == (128, 1)
+    assert shape(tr, RING, 1, 1, 1, 8192, 8192, 128) == (64, 2)                 # an idle one
+    assert shape(tr, RING_BF16, 1, 16, 4, 6008, 6008, 128, 0, 4) == (128, 1)
+    assert shape(tr, RING, 1, 1, 1, 34 * 288, 34 * 288, 128, 0, 34)[1] == 1     # more references than key groups keep
+    for H in (1, 2, 4, 8, 16):
+        for n in (2, 3, 33):                                                    # segments of one sub-tile: key groups would both start in the first
+            assert shape(tr, RING, 1, H, H, 33 * n, 33 * n, 64, None, n)[1] == 1
+    assert shape(tr, STEP_BF16, 4, 32, 8, 1, 8192, 128) == (64, 2)
+
+
 def test_invalid_arguments(tr):
+    assert shape(tr, 5, 1, 2, 2, 8, 8, 64)[0] == -1 and shape(tr, STEP_F32, 1, 3, 2, 8, 8, 64)[0] == -1
+    assert shape(tr, RING, 1, 2, 2, 8, 8, 64, None, 3)[0] == -1 and shape(tr, RING_BF16, 1, 2, 2, 8, 16, 64)[0] == -1
+    assert tr.raw_lib().tr_attn_workgroup(None, None, 0, 0, 0, 0, 1, None) == -1
     assert plan(tr, 1, 3, 2, 8, 8, 64)[0] == -1 and plan(tr, 1, 2, 2, 8, 8, 96)[0] == -1
     assert tr.raw_lib().tr_block_attn_plan(None, None, 0, 0, 0, None) == -1
     q = tr.TrTensor(0x7F0000000000, tr.TR_BF16, 1, 2, 8, 64, 1024, 512, 64)
