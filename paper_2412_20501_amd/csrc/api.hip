@@ -115,6 +115,7 @@ struct PartPlan {
   int pack = 0, parts = 1, members = 0, row_tiles = 0, part_rows = 0;
   int64_t part_keys = 0, out_elems = 0;   // out_elems: floats of block_out in the scratch
   bool packs_uncut = false;               // heads are packed also where the keys are not cut
+  int renew = 0;                          // of an uncut call: keys after which a row's exponent reference is taken anew
 };
 
 // Shape of a launch's workgroups.  8 x 1 (256 rows) has the least traffic for its products and is the best use of a full chip
@@ -274,12 +275,17 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     best.part_keys = part_keys;
     best.out_elems = slot_rows * D;
   }
-  // Workgroups of fewer rows take some of the calls back that 256-row ones would have to cut: 4 x 3 heads of 935 rows on 1385 keys 31 us
-  // in 3 parts, 19 uncut; 12 heads of 1611 under the causal rule 30.5 and 20.4; 4 heads of 295 rows on 1041 keys 14.3 and 14.7.  (Not
+  // Workgroups of fewer rows take some of the calls back that 256-row ones would have to cut.  (Not
   // where heads are packed: uncut they would not be, and every key would be read once for each of them.)
+  // The reference is renewed where the parts would have begun: the weights are those of the cut call.  (With one reference for all
+  // keys, 66 such calls were 0.2 - 2 % further from 64 bits, and took 10 % less time.)  us cut and uncut, in shapes of fewer rows both:
+  // 8 heads of 2041 under the causal rule 32.2 and 25.4; 16 of 446 rows on 1657 keys 23.1 and 22.0; 12 of 968 on 1316 33.1 and 18.6;
+  // 8 of 860 on 2645 26.5 and 30.7; 32 of 290 on 6291 at D 64 33.3 and 39.8.
   if (best.parts > 1 && !c.pack) {
     double whole = 0, cut = 0;
-    choose_shape(p, D, false, 4, &whole);
+    tr::AttnParams w = p;
+    w.renew = (int)best.part_keys;
+    choose_shape(w, D, false, 4, &whole);
     tr::AttnParams q = p;
     q.n_parts = best.parts;
     q.part_keys = (int)best.part_keys;
@@ -287,6 +293,7 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     cut += 5.0 + 0.25 * best.parts + (double)best.out_elems * 4 / 3.5e6;
     if (1.1 * std::max(whole, stream + fix) < cut) {
       best = c;
+      best.renew = w.renew;
       return false;
     }
   }
@@ -413,6 +420,10 @@ void settle_launch(tr::AttnParams& p, const PartPlan& plan, bool planned, int D,
     use_packed_shape(p, plan, choose_shape(p, D, plan.pack, out_bytes));
     p.units = p.B * p.Hkv;
   } else {
+    if (plan.renew > 0) {
+      p.renew = plan.renew;
+      p.renew_log2 = 29;   // at the parts' first keys, never later
+    }
     use_shape(p, choose_shape(p, D, false, out_bytes));
   }
 }

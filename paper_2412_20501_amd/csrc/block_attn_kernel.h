@@ -526,10 +526,11 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   float l_run = 0.f;        // this lane's share of the running sum of exp
   float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite and where it is renewed
   constexpr bool RENEW = !CHUNKS;           // (the chunk form ends every segment in a block of its own)
-  // Shape 4 x 1 looks at renew_at in inner steps too: a group of its tiles (192 keys at D 64) may hold a key at which the reference is
-  // renewed.  Without a branch: the cap of that step is lowered and the slow path does the rest (DiT shape 3157 -> 3170 us, 24 heads
-  // of 1024 in 8 segments 22.9 -> 23.3; renewed by the general body alone 24.5, 4 heads of 2048 in 8 at D 64 28.2 for 24.7).
-  constexpr bool RENEW_INNER = RENEW && R == 4 && G == 1;
+  // Shapes of fewer than 256 rows look at renew_at in inner steps too: a group of 4 x 1's tiles (192 keys at D 64) may hold a key at which
+  // the reference is renewed, and block steps renew at any multiple of 128 keys.  Without a branch: the cap of that step is lowered
+  // and the slow path does the rest (DiT shape 3157 -> 3170 us, 24 heads of 1024 in 8 segments 22.9 -> 23.3; renewed by the general body
+  // alone 24.5, 4 heads of 2048 in 8 at D 64 28.2 for 24.7, 2 x 16 heads of 499 rows on 3201 keys 39.4 for 36.0).
+  constexpr bool RENEW_INNER = RENEW && R < 8;
   // Where the reference is renewed for a segment that starts at key r: at r, or at the next multiple of 2^renew_log2 keys while that
   // lies in the stretch (up to renew_end) that no row of the wave needs a mask for, four quarters and more before the keys end.  A
   // multiple is a group of inner tiles of 256-row workgroups; a function of the wave's rows and the keys alone, so every shape of the
@@ -676,10 +677,11 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     for (int h = 0; h < 2; h++) p_out[h] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * h], pw[4 * h + 1], pw[4 * h + 2], pw[4 * h + 3]});
     float psum = ps0 + ps1;
     float cap = sum_cap;
-    if (RENEW_INNER && INNER) cap = kstart == renew_at ? -1.f : sum_cap;
+    if (RENEW_INNER && INNER) cap = kstart >= renew_at ? -1.f : sum_cap;
 
     if (__builtin_expect(__any(!(psum <= cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
-      if (RENEW_INNER && INNER && kstart == renew_at) next_segment();
+      if (RENEW_INNER && INNER)
+        while (kstart >= renew_at) next_segment();   // (once with one key group: the keys lie a sub-tile apart)
       float tmax = s_in[0];
 #pragma unroll
       for (int i = 1; i < 16; i++) tmax = fmaxf(tmax, s_in[i]);
@@ -813,7 +815,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     const int kstart = G == 1 ? j * SUB : (j * G + kgrp) * SUB;
     if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
       if (RENEW && !INNER && __builtin_expect(kstart >= renew_at, 0)) {
-        do next_segment();   // (once with one key group: the keys lie a sub-tile apart)
+        do next_segment();   // (as above)
         while (G > 1 && kstart >= renew_at);
       }
       if (even) step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sA, sB, pB, pA, inner_c);

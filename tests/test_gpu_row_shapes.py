@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, STEP_MERGE, attn_shape, bits_to_dev, f64, max_abs, rand_bits, to_np
+from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, STEP_MERGE, attn_plan, attn_shape, bits_to_dev, f64, max_abs, rand_bits, to_np
 
 pytestmark = pytest.mark.gpu
 MANY = 2048      # (batch, head, row tile) triples of 256 rows from which on the launches here take 128 rows and one key group
@@ -199,6 +199,47 @@ def test_steps(lib, Hq, Hkv, Sq, Sk, D, off, shape, dtype):
     few, many = run(1, q, k, v), run(B, *(x.expand(B, -1, -1, -1) for x in (q, k, v)))
     torch.cuda.synchronize()
     _agree(few, many, 2 ** -8 * 4 if dtype is torch.bfloat16 else 1e-5)   # a bf16 ulp of values below 4, where a sum lies at a tie
+
+
+@pytest.mark.parametrize("merge", [False, True])
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,off,parts", [
+    (4, 3, 1, 935, 1385, 128, None, 3),
+    (1, 12, 4, 1611, 1611, 128, 0, 3),
+    (1, 16, 16, 1594, 2428, 64, 834, 2),
+    (2, 4, 2, 2272, 2339, 128, 67, 3),
+    (1, 8, 8, 2900, 2900, 128, 0, 2),
+])
+def test_uncut_calls_round_as_their_parts(lib, B, Hq, Hkv, Sq, Sk, D, off, parts, merge):
+    """Block steps that workgroups of fewer rows run in one piece: the weights are those of the parts that 256-row ones would cut
+    the keys into, attended one by one here (none of them as large as to be cut again), so that fp32 sums are all that differs."""
+    assert attn_plan(lib, B, Hq, Hkv, Sq, Sk, D, off) == (1, 0)
+    if merge and off is not None:
+        pytest.skip("the merging step has no causal rule at arbitrary positions")
+    q, k, v = (bits_to_dev(rand_bits((B, h, S, D), 790 + i)) for i, (h, S) in enumerate(((Hq, Sq), (Hkv, Sk), (Hkv, Sk))))
+
+    def step(k, v, k0, out, lse):
+        if merge:
+            out.fill_(float("nan"))
+            lse.fill_(float("-inf"))
+            lib.tr_block_attn_merge(q, k, v, lib.TR_MASK_NONE, D ** -0.5, out, lse)
+        elif off is None:
+            lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, D ** -0.5, out, lse)
+        else:
+            lib.tr_block_attn_causal_at(q, k, v, off, k0, D ** -0.5, out, lse)
+
+    whole = _new(B, Hq, Sq, D)
+    step(k, v, 0, *whole)
+    keys = max(512, -(-Sk // parts) + 127 & -128)
+    outs, lses = zip(*(_new(B, Hq, Sq, D) for _ in range(parts)))
+    for i in range(parts):
+        part = slice(i * keys, (i + 1) * keys)
+        assert attn_plan(lib, B, Hq, Hkv, Sq, k[:, :, part].shape[2], D, off if off is None else off - i * keys) == (1, 0)
+        step(k[:, :, part], v[:, :, part], i * keys, outs[i], lses[i])
+    folded = _new(B, Hq, Sq, D)
+    lib.tr_merge_n(*folded, list(outs), list(lses))
+    torch.cuda.synchronize()
+    for b in range(B):
+        _agree([x[b:b + 1] for x in whole], [x[b:b + 1] for x in folded])
 
 
 def test_more_rows_than_a_grid_of_small_workgroups_holds(lib):
