@@ -526,10 +526,11 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   float l_run = 0.f;        // this lane's share of the running sum of exp
   float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite and where it is renewed
   constexpr bool RENEW = !CHUNKS;           // (the chunk form ends every segment in a block of its own)
-  // Shapes of fewer than 256 rows look at renew_at in inner steps too: a group of 4 x 1's tiles (192 keys at D 64) may hold a key at which
-  // the reference is renewed, and block steps renew at any multiple of 128 keys.  Without a branch: the cap of that step is lowered
-  // and the slow path does the rest (DiT shape 3157 -> 3170 us, 24 heads of 1024 in 8 segments 22.9 -> 23.3; renewed by the general body
-  // alone 24.5, 4 heads of 2048 in 8 at D 64 28.2 for 24.7, 2 x 16 heads of 499 rows on 3201 keys 39.4 for 36.0).
+  // Shapes of fewer than 256 rows renew inside a group of inner tiles too: a group of 4 x 1's (192 keys at D 64) may hold a key at which
+  // the reference is renewed, and block steps renew at any multiple of 128 keys.  Such a group has a body of its own, whose steps look at
+  // renew_at without a branch: the cap is lowered and the slow path does the rest.  (In every inner step the look costs
+  // the DiT shape 0.6 % and 1 head of 9984 rows in 2 segments 4 %; renewed by the general body alone 4 heads of 2048 in 8 at D 64 take 28.2
+  // us for 24.8, 2 x 16 heads of 499 rows on 3201 keys 39.4 for 36.0.)
   constexpr bool RENEW_INNER = RENEW && R < 8;
   // Where the reference is renewed for a segment that starts at key r: at r, or at the next multiple of 2^renew_log2 keys while that
   // lies in the stretch (up to renew_end) that no row of the wave needs a mask for, four quarters and more before the keys end.  A
@@ -604,6 +605,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
                   bf16x8 (&p_in)[2], bf16x8 (&p_out)[2], auto inner_c) __attribute__((always_inline)) {
     constexpr bool FIRST = decltype(first_c)::value != 0;   // no previous sub-tile: QK half only
     constexpr bool INNER = decltype(inner_c)::value != 0;   // every key of the sub-tile is visible to every row: no mask test
+    constexpr bool CHECKED = decltype(inner_c)::value == 2; // and the reference may be renewed here
     constexpr int n_mfma = FIRST ? NQK : NQK + NPV;
     constexpr int EPM = 16 / n_mfma;  // softmax elements handled per MFMA slice
     static_assert(16 % n_mfma == 0, "softmax elements must divide evenly over the MFMAs");
@@ -677,10 +679,10 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     for (int h = 0; h < 2; h++) p_out[h] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * h], pw[4 * h + 1], pw[4 * h + 2], pw[4 * h + 3]});
     float psum = ps0 + ps1;
     float cap = sum_cap;
-    if (RENEW_INNER && INNER) cap = kstart >= renew_at ? -1.f : sum_cap;
+    if (CHECKED) cap = kstart >= renew_at ? -1.f : sum_cap;
 
     if (__builtin_expect(__any(!(psum <= cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
-      if (RENEW_INNER && INNER)
+      if (CHECKED)
         while (kstart >= renew_at) next_segment();   // (once with one key group: the keys lie a sub-tile apart)
       float tmax = s_in[0];
 #pragma unroll
@@ -898,17 +900,24 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   if (1 <= n_tiles) tile_body(1, IC<1 % NS>{}, IC<0>{}, IC<1>{});
   if (2 <= n_tiles) tile_body(2, IC<2 % NS>{}, IC<0>{}, IC<0>{});
   if (NS > 3 && 3 <= n_tiles) tile_body(3, IC<3 % NS>{}, IC<0>{}, IC<0>{});
-  // Groups of NS tiles: first the groups of inner tiles (up to where the reference is renewed, and on from there), then
+  // Groups of NS tiles: first the groups of inner tiles (up to where the reference is renewed, and on from there; see RENEW_INNER), then
   // general ones to the end.
   int u0 = NS;
   while (u0 + NS - 1 <= u_inner) {
     if (!RENEW_INNER && u0 * BN >= renew_at) next_segment();
-    const int stop = !RENEW_INNER ? min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NS - 1) : u_inner;
+    const int stop = RENEW_INNER ? min(u_inner, (int)((unsigned)renew_at / BN) - 1) : min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NS - 1);
     for (; u0 + NS - 1 <= stop; u0 += NS) {
       tile_body(u0, IC<0>{}, IC<1>{}, IC<0>{});
       tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{}, IC<0>{});
       tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{}, IC<0>{});
       if constexpr (NS > 3) tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{}, IC<0>{});
+    }
+    if (RENEW_INNER && u0 + NS - 1 <= u_inner) {
+      tile_body(u0, IC<0>{}, IC<2>{}, IC<0>{});
+      tile_body(u0 + 1, IC<1 % NS>{}, IC<2>{}, IC<0>{});
+      tile_body(u0 + 2, IC<2 % NS>{}, IC<2>{}, IC<0>{});
+      if constexpr (NS > 3) tile_body(u0 + 3, IC<3 % NS>{}, IC<2>{}, IC<0>{});
+      u0 += NS;
     }
   }
   for (; u0 <= n_tiles; u0 += NS) {
