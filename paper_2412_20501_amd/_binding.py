@@ -40,11 +40,12 @@ class TokenRingError(RuntimeError):
         self.status = status
 
 
+_HOW_TO_BUILD = "Build it with `python -m paper_2412_20501_amd.build` (or __graft_entry__.build()); there is no CPU or PyTorch fallback."
+
+
 def _load():
     if not os.path.exists(LIB_PATH):
-        raise ImportError(
-            f"{LIB_PATH} is not built. Build it with `python -m paper_2412_20501_amd.build` "
-            "(or __graft_entry__.build()); there is no CPU or PyTorch fallback.")
+        raise ImportError(f"{LIB_PATH} is not built. {_HOW_TO_BUILD}")
     lib = ctypes.CDLL(LIB_PATH)
     P = ctypes.POINTER(TrTensor)
     lib.tr_block_attn.argtypes = [P, P, P, ctypes.c_int, ctypes.c_float, P, P, ctypes.c_void_p]
@@ -90,7 +91,10 @@ def _load():
 _lib = _load()
 
 # The calls below go through the extension module (csrc/binding.cpp), which makes the descriptors itself.
-from . import _native  # noqa: E402  (behind _load(): the module needs the library)
+try:
+    from . import _native  # noqa: E402  (behind _load(): the module needs the library)
+except ImportError as e:
+    raise ImportError(f"the module _native.so beside {LIB_PATH} is not built, or not for this torch and Python ({e}). {_HOW_TO_BUILD}") from e
 
 _DTYPES = {torch.bfloat16: TR_BF16, torch.float32: TR_F32}
 _DESC_PACK = struct.Struct("Pi4x8q").pack   # a tr_tensor and one word behind it (the stride of D)

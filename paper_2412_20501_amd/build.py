@@ -3,7 +3,8 @@
 The library carries a hash of everything it was compiled from (kernel sources, internal and
 public headers, compiler flags): tr_version() reports it, and ensure_built() recompiles when
 the hash found inside an existing library differs from the hash of the sources on disk, so a
-test or benchmark run can never silently exercise a stale binary.
+test or benchmark run can never silently exercise a stale binary.  The hash in the Python module over it
+covers torch's version and C++ ABI and Python's, which it is compiled against, as well.
 """
 from __future__ import annotations
 
@@ -29,6 +30,7 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+CXX_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall"]
 _HASH_TAG = b"TR_SOURCE_HASH="
 
 
@@ -45,6 +47,13 @@ def source_hash() -> str:
                     h.update(f.read())
                 h.update(b"\0")
     return h.hexdigest()[:16]
+
+
+def binding_hash() -> str:
+    """The same for the Python module: the sources, its compiler's flags, and the torch and Python it is compiled against."""
+    import torch
+    what = [source_hash(), *CXX_FLAGS, torch.__version__, str(torch._C._GLIBCXX_USE_CXX11_ABI), sysconfig.get_config_var("SOABI") or sys.version]
+    return hashlib.sha256("\0".join(what).encode()).hexdigest()[:16]
 
 
 def library_hash(path: str = LIB_PATH):
@@ -77,8 +86,8 @@ def build_library(verbose: bool = False) -> str:
     import torch   # its headers and libraries
     torch_root = os.path.dirname(torch.__file__)
     cxx, binding = os.environ.get("CXX", "g++"), tmp_binding + ".o"
-    compile_binding = [cxx, "-O2", "-std=c++17", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-                       f'-DTR_SOURCE_HASH_STR="{source_hash()}"', "-I", INCLUDE, "-isystem", sysconfig.get_paths()["include"],
+    compile_binding = [cxx, *CXX_FLAGS, f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                       f'-DTR_SOURCE_HASH_STR="{binding_hash()}"', "-I", INCLUDE, "-isystem", sysconfig.get_paths()["include"],
                        "-isystem", os.path.join(torch_root, "include"), "-c", os.path.join(CSRC, "binding.cpp"), "-o", binding]
     commands = [[*compile_, os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objects)] + [compile_binding]
     try:
@@ -98,8 +107,8 @@ def build_library(verbose: bool = False) -> str:
 
 
 def ensure_built() -> str:
-    """Build unless a library compiled from exactly the sources on disk is already there."""
-    if library_hash() == source_hash() == library_hash(BINDING_PATH):
+    """Build unless a library compiled from exactly the sources on disk is already there, and a module that fits this torch and Python."""
+    if library_hash() == source_hash() and library_hash(BINDING_PATH) == binding_hash():
         return LIB_PATH
     return build_library()
 

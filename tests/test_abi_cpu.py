@@ -217,6 +217,37 @@ def test_library_is_rebuilt_when_a_source_changes(tr, tmp_path, monkeypatch):
     assert calls == [1]
 
 
+def test_module_is_rebuilt_for_another_torch_or_python(tr, monkeypatch):
+    """_native.so is compiled against torch's C++ ABI and Python's: its hash covers both, and the flags."""
+    import sysconfig
+    import torch
+    from paper_2412_20501_amd import build
+    assert build.library_hash(build.BINDING_PATH) == build.binding_hash()
+    calls = []
+    monkeypatch.setattr(build, "build_library", lambda verbose=False: calls.append(1) or build.LIB_PATH)
+    build.ensure_built()
+    assert calls == []
+    soabi = sysconfig.get_config_var("SOABI")
+    for target, name, value in ((torch, "__version__", "2.0.0"), (torch._C, "_GLIBCXX_USE_CXX11_ABI", not torch._C._GLIBCXX_USE_CXX11_ABI),
+                                (sysconfig, "get_config_var", lambda key: "other-" + soabi), (build, "CXX_FLAGS", ["-O0"])):
+        with monkeypatch.context() as m:
+            m.setattr(target, name, value)
+            build.ensure_built()
+    assert calls == [1] * 4
+
+
+def test_a_missing_module_is_named_with_the_build_command(tr, tmp_path):
+    import shutil
+    import subprocess
+    import sys
+    pkg = tmp_path / "paper_2412_20501_amd"
+    shutil.copytree(os.path.dirname(tr.LIB_PATH), pkg, ignore=shutil.ignore_patterns("_native.so", "csrc", "__pycache__"))
+    res = subprocess.run([sys.executable, "-c", "import paper_2412_20501_amd as tr; tr.raw_lib()"], cwd=tmp_path, capture_output=True, text=True,
+                         timeout=120, env={**os.environ, "PYTHONPATH": str(tmp_path)})
+    assert res.returncode != 0 and "ImportError" in res.stderr
+    assert "_native.so" in res.stderr and "python -m paper_2412_20501_amd.build" in res.stderr
+
+
 def test_noalloc_ring_rejects_oversize_before_touching_a_device(tr):
     lib = tr.raw_lib()
     B = ctypes.byref
