@@ -33,7 +33,8 @@ FORMS = {
     (9, 32, 8, 300, 330, 64, 20): (1, 1),         # the same, a tile that ends one head and starts the next
     (66, 32, 8, 2, 70, 64, None): (1, 1),         # more than two rounds of packed tiles
     (1, 32, 8, 73, 5186, 64, None): (11, 1),      # 256-row workgroups, packed: 292 rows
-    (2, 12, 4, 135, 4095, 128, 3960): (8, 1),     # the same, causal: 405 rows of three heads
+    (8, 8, 1, 53, 4110, 128, 4057): (9, 1),       # the same, causal: 424 rows of eight heads
+    (2, 12, 4, 135, 4095, 128, 3960): (8, 1),     # 128-row workgroups, packed, causal: 405 rows of three heads
     (2, 4, 4, 299, 5172, 64, None): (11, 0),      # not packed: 43 rows in the second tile
     (1, 8, 8, 388, 4460, 128, 4072): (9, 0),      # the same, causal
     (3, 6, 3, 129, 2825, 128, None): (6, 0),      # 128-row workgroups: one row in the second
@@ -51,7 +52,8 @@ SHAPES.update({
     (9, 32, 8, 300, 330, 64, 20): ROWS_128,
     (66, 32, 8, 2, 70, 64, None): ROWS_128,
     (1, 32, 8, 73, 5186, 64, None): ROWS_256,
-    (2, 12, 4, 135, 4095, 128, 3960): ROWS_256,
+    (8, 8, 1, 53, 4110, 128, 4057): ROWS_256,
+    (2, 12, 4, 135, 4095, 128, 3960): ROWS_128,
     (2, 4, 4, 299, 5172, 64, None): ROWS_256,
     (1, 8, 8, 388, 4460, 128, 4072): ROWS_256,
     (3, 6, 3, 129, 2825, 128, None): ROWS_128,

@@ -30,7 +30,7 @@ def test_few_rows_on_many_keys_are_cut(tr):
 
 
 def test_workgroups_of_fewer_rows_make_a_cut_needless(tr):
-    """us, cut and uncut: 31.2 and 19.0, 30.5 and 20.4, 33.5 and 25.4; still cut: 17.1 and 40.6, 47.7 and 137."""
+    """us, cut and uncut: 29.5 and 19.2, 29.7 and 20.5, 31.4 and 24.4; still cut: 17.1 and 40.6, 47.7 and 137."""
     assert plan(tr, 4, 3, 1, 935, 1385, 128) == (1, 0)
     assert plan(tr, 1, 12, 4, 1611, 1611, 128, 0) == (1, 0)
     assert plan(tr, 1, 16, 16, 1594, 2428, 64, 834) == (1, 0)
@@ -42,6 +42,13 @@ def test_a_packed_grid_stays_within_the_dispatch_limit(tr):
     """2^32 threads in one dimension: the plain form's second grid dimension holds what a packed launch would not."""
     assert plan(tr, 2_700_000, 2, 1, 257, 8, 64) == (1, 1)
     assert plan(tr, 2_800_000, 2, 1, 257, 8, 64) == (1, 0)
+
+
+def test_workgroups_of_a_causal_cut_are_counted_as_they_are(tr):
+    """A row tile has as many workgroups as parts that its rows see, one at least and never more than there are parts; us in 256 rows and in
+    the shape chosen: 31.6 and 27.7, 27.0 and 23.8, 23.9 and 20.7, 20.0 and 17.3."""
+    for case in ((1, 32, 32, 120, 6905, 128, 6785), (2, 32, 32, 122, 2508, 128, 2386), (1, 32, 4, 26, 26034, 64, 26008), (1, 12, 3, 206, 2534, 128, 2328)):
+        assert plan(tr, *case)[0] > 1 and shape(tr, STEP_F32, *case) == (64, 2)
 
 
 def test_shapes_of_a_workgroup(tr):
