@@ -150,7 +150,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
     const int64_t tiles = (rows + bm - 1) / bm;
     if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
     if (groups && (refs > tr::kMaxRefs || heads * tiles >= 8 * kCUs)) continue;
-    if (groups && p.renew > 0 && p.renew < 64) continue;   // both groups start in the first segment
+    if (groups && p.renew > 0 && p.renew < 64) continue;   // renewals lie as far apart as a group's sub-tiles
     int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
     if (p.causal && pack) {
       least = most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, (int64_t)p.Sq + p.causal_off));

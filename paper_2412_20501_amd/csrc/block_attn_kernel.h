@@ -682,8 +682,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     if (CHECKED) cap = kstart >= renew_at ? -1.f : sum_cap;
 
     if (__builtin_expect(__any(!(psum <= cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
-      if (CHECKED)
-        while (kstart >= renew_at) next_segment();   // (once with one key group: the keys lie a sub-tile apart)
+      while (CHECKED && kstart >= renew_at) next_segment();   // (once, the keys lie as far apart as a wave's sub-tiles; as an if it spills 31 SGPRs in shape 2 x 2 at D 64)
       float tmax = s_in[0];
 #pragma unroll
       for (int i = 1; i < 16; i++) tmax = fmaxf(tmax, s_in[i]);
@@ -816,10 +815,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     const int j = NSW * u + kt;
     const int kstart = G == 1 ? j * SUB : (j * G + kgrp) * SUB;
     if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
-      if (RENEW && !INNER && __builtin_expect(kstart >= renew_at, 0)) {
-        do next_segment();   // (as above)
-        while (G > 1 && kstart >= renew_at);
-      }
+      if (RENEW && !INNER && __builtin_expect(kstart >= renew_at, 0)) next_segment();
       if (even) step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sA, sB, pB, pA, inner_c);
       else step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sB, sA, pA, pB, inner_c);
     }
