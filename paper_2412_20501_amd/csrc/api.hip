@@ -118,6 +118,30 @@ struct PartPlan {
   int renew = 0;                          // of an uncut call: keys after which a row's exponent reference is taken anew
 };
 
+// Workgroups of a cut launch under the causal rule: those of the fullest XCD, for all eight.  A row tile has one for each part that some
+// row of it sees, one at least; the kernel deals the tiles of all parts out in eight contiguous pieces (decode_part), and
+// pieces of the first parts hold the most: 255 workgroups of 3 heads of 3929 rows in 5 parts are 58 on one XCD of 32 compute units.
+int64_t causal_workgroups(const tr::AttnParams& p, int64_t heads, int64_t rows, int bm) {
+  const int64_t tiles = (rows + bm - 1) / bm, gq = p.gq, per_xcd = (heads * p.n_parts * tiles + 7) / 8;
+  int64_t live[tr::kMaxParts], least = tiles;   // row tiles of a head that have a part
+  for (int i = 0; i < p.n_parts; i++) {
+    // (tile t sees keys of part i from row i * part_keys - causal_off on)
+    const int64_t first = std::max<int64_t>(0, (int64_t)i * p.part_keys - p.causal_off);
+    live[i] = i == 0 ? tiles : std::max<int64_t>(0, tiles - first / bm) * (first < rows && (int64_t)i * p.part_keys < p.Sk);
+    least = std::min(least, live[i]);
+  }
+  if (least == tiles) return heads * p.n_parts * tiles;
+  int64_t on[8] = {};
+  for (int64_t unit = 0, at = 0; unit < heads / gq * p.n_parts; unit++)
+    for (int64_t h = 0; h < gq; h++, at += tiles)   // its live tiles lie in front
+      for (int64_t a = at, end = at + live[unit % p.n_parts]; a < end;) {
+        const int64_t x = a / per_xcd, stop = std::min(end, (x + 1) * per_xcd);
+        on[x] += stop - a;
+        a = stop;
+      }
+  return 8 * *std::max_element(on, on + 8);
+}
+
 // Shape of a launch's workgroups.  8 x 1 (256 rows) has the least traffic for its products and is the best use of a full chip
 // over long key ranges.  4 x 1, several to a compute unit, hides set-up and epilogue and ends more evenly.  A launch that would leave
 // compute units idle runs 4 x 2 or 2 x 2, whose waves also share the keys out among themselves.
@@ -163,16 +187,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
       sum = (all * (all + 1) - none * (none + 1)) / 2 * bm + (all - none) * off + (tiles - all) * p.Sk;
     }
     double n = (double)(heads * tiles) * chunks, total = ((double)(heads * sum) + (double)(heads * tiles) * blocks * p.Sk) * chunks / tile_keys;
-    if (p.n_parts > 1 && p.causal && !pack) {   // the parts that some row of a tile sees, one at least
-      int64_t live = 0;
-      for (int64_t t = 0; t < tiles; t++) {
-        const int64_t seen = std::max<int64_t>(0, std::min<int64_t>(p.Sk, std::min(rows, (t + 1) * bm) + p.causal_off));
-        live += std::max<int64_t>(1, (seen + part - 1) / part);
-      }
-      n = (double)(heads * live);
-    } else if (p.n_parts > 1) {
-      n *= std::max(1.0, std::ceil((double)most / (double)part));
-    }
+    if (p.n_parts > 1) n = p.causal && !pack ? (double)causal_workgroups(p, heads, rows, bm) : n * std::max(1.0, std::ceil((double)most / (double)part));
     const double longest = ((double)std::min(most, part) + later * p.Sk) / tile_keys;
     const double shortest = p.n_parts > 1 ? 0.0 : (double)least / tile_keys;
     const bool few = std::min<int64_t>(rows, bm) <= bm / 2;
@@ -300,9 +315,9 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     q.part_keys = (int)best.part_keys;
     choose_shape(q, D, false, 4, &cut);
     cut += 5.0 + 0.25 * best.parts + (double)best.out_elems * 4 / 3.5e6;
-    // Behind the estimate: 1.5 where a reference is renewed at all and 0.4 each time.  With the factor, of those tried the line with the least
-    // regret on 371 calls near it (0.9 % above the faster side on average, 14 calls by more than a tenth; the estimates as they are 1.6 % and 28).
-    if (0.95 * std::max(whole + 1.5 + 0.4 * (best.parts - 1), stream + fix) < cut) {
+    // Behind the estimate: 2 where a reference is renewed at all and 0.8 each time.  With the factor, of those tried the line with the least
+    // regret on 371 calls near it (0.5 % above the faster side on average, 4 calls by more than a tenth; the estimates as they are 1.7 % and 30).
+    if (0.9 * std::max(whole + 2.0 + 0.8 * (best.parts - 1), stream + fix) < cut) {
       best = c;
       best.renew = w.renew;
       return false;

@@ -48,6 +48,7 @@ ROWS_256, ROWS_128, ROWS_128_GROUPS, ROWS_64_GROUPS = (256, 1), (128, 1), (128, 
 SHAPES = dict.fromkeys(CASES, ROWS_64_GROUPS)
 SHAPES.update({
     (1, 8, 1, 600, 1600, 64, 1000): ROWS_128,
+    (1, 2, 2, 2600, 2300, 64, -300): ROWS_128_GROUPS,
     (30, 12, 4, 30, 500, 128, 480): ROWS_256,
     (9, 32, 8, 300, 330, 64, 20): ROWS_128,
     (66, 32, 8, 2, 70, 64, None): ROWS_128,

@@ -49,6 +49,9 @@ def test_workgroups_of_a_causal_cut_are_counted_as_they_are(tr):
     the shape chosen: 31.6 and 27.7, 27.0 and 23.8, 23.9 and 20.7, 20.0 and 17.3."""
     for case in ((1, 32, 32, 120, 6905, 128, 6785), (2, 32, 32, 122, 2508, 128, 2386), (1, 32, 4, 26, 26034, 64, 26008), (1, 12, 3, 206, 2534, 128, 2328)):
         assert plan(tr, *case)[0] > 1 and shape(tr, STEP_F32, *case) == (64, 2)
+    # 255 workgroups of 128 rows, but 58 of them on the first XCD's 32 compute units: 41.8 in (128, 2)
+    assert plan(tr, 1, 3, 3, 3929, 3929, 128, 0) == (5, 0) and shape(tr, STEP_F32, 1, 3, 3, 3929, 3929, 128, 0) == (128, 1)
+    assert plan(tr, 1, 3, 3, 2646, 2646, 128, 0)[0] > 1 and shape(tr, STEP_F32, 1, 3, 3, 2646, 2646, 128, 0) == (128, 1)     # 33.3 -> 25.7
 
 
 def test_shapes_of_a_workgroup(tr):
