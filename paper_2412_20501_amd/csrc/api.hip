@@ -315,9 +315,10 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     q.part_keys = (int)best.part_keys;
     choose_shape(q, D, false, 4, &cut);
     cut += 5.0 + 0.25 * best.parts + (double)best.out_elems * 4 / 3.5e6;
-    // Behind the estimate: 2 where a reference is renewed at all and 0.8 each time.  With the factor, of those tried the line with the least
-    // regret on 371 calls near it (0.5 % above the faster side on average, 4 calls by more than a tenth; the estimates as they are 1.7 % and 30).
-    if (0.9 * std::max(whole + 2.0 + 0.8 * (best.parts - 1), stream + fix) < cut) {
+    // The line with the least regret of those tried, on 371 calls near it and 125 long ones: 0.3 % and 0.8 % above the faster side on average,
+    // 2 and 4 calls by more than a tenth; the estimates as they are 1.7 % and 30, 1.2 % and 6.  (What it adds is the renewals of short calls.)
+    whole = std::max(whole, stream + fix);
+    if (std::max(0.85 * whole + 3.0 + 0.6 * (best.parts - 1), 0.95 * whole) < cut) {
       best = c;
       best.renew = w.renew;
       return false;
