@@ -35,7 +35,7 @@
 // 2 x 4 measured 5 - 14 % less than 2 x 2 from 4096 keys on and 1 us more below (D = 64); at D = 128 its tiles leave room for two.
 //
 // Small workgroups.  Shape 4 x 1 is the 256-row workgroup's work in halves, two to a compute unit at D = 128 and three at
-// D = 64 (166 VGPRs): one's loads, epilogue and waits at barriers run beside another's products, and a launch ends more evenly.
+// D = 64 (158 VGPRs): one's loads, epilogue and waits at barriers run beside another's products, and a launch ends more evenly.
 // What it costs is twice the K/V traffic from L2 into LDS for the same rows.  us, 8 x 1 -> 4 x 1: 512 heads of 256 rows on as many keys
 // 41.8 -> 35.4, at D 64 26.2 -> 19.6; 48 heads of 3000 225 -> 207, at D 64 145 -> 121; 64 of 2048 125.3 -> 126.7, at D 64 77.0 -> 73.8; 32 of
 // 24576 7720 -> 8015, at D 64 4847 -> 4721; bf16 blocks of 6008 rows in 4 chunks, 16 heads 190 -> 169.
@@ -306,8 +306,8 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // epilogue, the first one unrounded onto an empty accumulator.  One launch instead of two per block: no
 // block result in memory, no idle tail between the blocks (chunks of 1502 rows x 16 heads fill 96 of 256
 // compute units), the longest chunks first.  Bound: as the plain form, plus an epilogue for each block.
-// Causal 6008 rows in 4 chunks, 16 heads: 401 -> 193 us in 256-row workgroups, 165 in shape 4 x 1; the same bits as the steps where both take
-// the same shape.
+// Causal 6008 rows in 4 chunks, 16 heads: 401 -> 193 us in 256-row workgroups, 170 in shape 4 x 1; the same bits as the steps where both have
+// as many key groups.
 template <int D, int EPI, int FORM, int R, int G>
 __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 2) block_attn_kernel(const AttnParams p) {
   constexpr bool PART = FORM == kPart, CHUNKS = FORM == kChunks;
@@ -1044,8 +1044,8 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     }
   } else if (EPI == kEpiF32) {
     // Results are stored past the L2 (non-temporal), here and below: dirty lines would be written back when the kernel ends, with
-    // nothing beside it.  256 heads of 256 rows 22.1 -> 20.6 us, 32 of 1024 24.6 -> 23.7, causal 8192 466 -> 463; bf16 blocks
-    // that a merge reads next 489.5 -> 488.  (Partials of a cut call and their fold: no change either way.)
+    // nothing beside it.  256 heads of 256 rows 22.1 -> 20.6 us, 32 of 1024 24.6 -> 23.7, causal 8192 466 -> 463; bf16 results of causal
+    // steps 1 - 5 % less, 4096 rows x 32 heads and the merge that reads them next 254.3 -> 256.3.  (Partials of a cut call and their fold: no change either way.)
     f32x4 ov[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; it++) {
