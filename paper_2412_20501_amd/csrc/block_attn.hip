@@ -23,9 +23,9 @@ constexpr int kFoldThreads = 256;
 template <int D, int EPI, int MAXP>
 __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnParams p) {
   constexpr int CPRF = D / 4;
-  const int group = (int)blockIdx.x, kv = group / p.members, m = group - kv * p.members;
-  const int b = kv / p.Hkv, hk = kv - b * p.Hkv;
-  const int head0 = p.pack ? 0 : m / p.n_qtiles;
+  const int group = (int)blockIdx.x, kv = divide(p.by_members, group), m = group - kv * p.members;
+  const int b = divide(p.by_hkv, kv), hk = kv - b * p.Hkv;
+  const int head0 = p.pack ? 0 : divide(p.by_qtiles, m);
   const int q0 = (p.n_qtiles - 1 - (m - head0 * p.n_qtiles)) * p.bm, n_tile = min(p.bm, part_rows_total(p) - q0);
   const int r = (int)blockIdx.y * (kFoldThreads / CPRF) + (int)threadIdx.x / CPRF, cc = (int)threadIdx.x % CPRF;
   if (r >= n_tile) return;
@@ -34,7 +34,7 @@ __global__ void __launch_bounds__(kFoldThreads) fold_parts_kernel(const AttnPara
   const int n_live = live_parts(p, hi);
   if (n_live == 1) return;   // written by the attention kernel
 
-  const int head = (q0 + r) / p.Sq, pos = q0 + r - head * p.Sq, hq = hk * p.gq + head0 + head;
+  const int head = divide(p.by_sq, q0 + r), pos = q0 + r - head * p.Sq, hq = hk * p.gq + head0 + head;
   const int64_t l_at = (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (int64_t)pos * p.l_ss;
   const int64_t o_at = (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + (int64_t)pos * p.o_ss + 4 * cc;
   const int64_t slot_row = (int64_t)group * p.n_parts * p.part_rows + r;
@@ -121,7 +121,7 @@ hipError_t launch_attn(const AttnParams& p, int epilogue, dim3 grid, hipStream_t
 
 }  // namespace
 
-hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream_t stream, hipEvent_t fold_done) {
+hipError_t launch_block_attn(AttnParams& p, int D, int epilogue, hipStream_t stream, hipEvent_t fold_done) {
   const int64_t nbh = (int64_t)p.B * p.Hq;
   if (nbh * p.n_qtiles == 0) return hipSuccess;
   if (p.n_qtiles > 65535 || p.bm != shape_rows(p.shape)) return hipErrorInvalidValue;   // grid y limit
@@ -133,6 +133,14 @@ hipError_t launch_block_attn(const AttnParams& p, int D, int epilogue, hipStream
   } else if (p.n_chunks > 0) {
     grid = dim3((unsigned)nbh, (unsigned)((p.chunk_end - p.chunk_begin) * p.n_qtiles));
     if (grid.y > 65535 || epilogue != kEpiMerge) return hipErrorInvalidValue;
+  }
+  if (p.n_parts > 0) {
+    p.by_qtiles = make_divisor(p.n_qtiles);
+    p.by_members = make_divisor(p.members);
+    p.by_parts = make_divisor(p.n_parts);
+    p.by_hkv = make_divisor(p.Hkv);
+    p.by_sq = make_divisor(p.Sq);
+    p.by_part_keys = make_divisor(p.part_keys);
   }
   const hipError_t e = D == 128 ? launch_attn<128>(p, epilogue, grid, stream) : launch_attn<64>(p, epilogue, grid, stream);
   if (e != hipSuccess || p.n_parts <= 1) return e;

@@ -159,14 +159,14 @@ struct PartBlock { int tile, b, hk, hq0, part, group; };
 __device__ __forceinline__ bool decode_part(const AttnParams& p, PartBlock& w) {
   const int per_xcd = (int)gridDim.x >> 3;
   const int at = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
-  const int u = at / p.members, m = at - u * p.members;
+  const int u = divide(p.by_members, at), m = at - u * p.members;
   if (u >= p.units) return false;
-  const int kv = u / p.n_parts;
+  const int kv = divide(p.by_parts, u);
   w.part = u - kv * p.n_parts;
-  w.b = kv / p.Hkv;
+  w.b = divide(p.by_hkv, kv);
   w.hk = kv - w.b * p.Hkv;
   w.group = kv * p.members + m;
-  const int head = p.pack ? 0 : m / p.n_qtiles;
+  const int head = p.pack ? 0 : divide(p.by_qtiles, m);
   w.hq0 = w.hk * p.gq + head;
   w.tile = p.n_qtiles - 1 - (m - head * p.n_qtiles);
   return true;
@@ -180,14 +180,14 @@ using IC = std::integral_constant<int, N>;
 __device__ __forceinline__ int part_rows_total(const AttnParams& p) { return p.pack ? p.gq * p.Sq : p.Sq; }
 __device__ __forceinline__ void pos_span(const AttnParams& p, int first, int n, int& lo, int& hi) {
   const int last = min(first + n, part_rows_total(p)) - 1;
-  const int ha = first / p.Sq, hb = last / p.Sq;
+  const int ha = divide(p.by_sq, first), hb = divide(p.by_sq, last);
   lo = ha == hb ? first - ha * p.Sq : 0;
   hi = ha == hb ? last - hb * p.Sq : p.Sq - 1;
 }
 // Parts of the keys that any row of the tile sees, the first one always counted: parts 0 .. n - 1 are computed.
 __device__ __forceinline__ int live_parts(const AttnParams& p, int pos_last) {
   const int seen = p.causal ? max(0, min(p.Sk, pos_last + p.causal_off + 1)) : p.Sk;
-  return max(1, (seen + p.part_keys - 1) / p.part_keys);
+  return max(1, divide(p.by_part_keys, seen + p.part_keys - 1));
 }
 
 // LDS behind the K/V rings and, once these are dead, behind the waves' transposed 32 x D fp32 tiles (byte offsets
@@ -249,7 +249,7 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
   int* const tab_mode = reinterpret_cast<int*>(lds + Lds<D, R, G>::mode) + rg * 32;
   int64_t* const off = reinterpret_cast<int64_t*>(lds + Lds<D, R, G>::off) + rg * 32;
   if (kgrp == 0 && n_valid > 0) {
-    const int row = min(q0 + rg * 32 + ql, n_rows - 1), head = row / p.Sq, pos = row - head * p.Sq;
+    const int row = min(q0 + rg * 32 + ql, n_rows - 1), head = divide(p.by_sq, row), pos = row - head * p.Sq;
     const int64_t l_at = (int64_t)b * p.l_sb + (int64_t)(hq0 + head) * p.l_sh + (int64_t)pos * p.l_ss;
     const UpdatePlan pl = plan_update(EPI == kEpiMerge ? p.lse[l_at] : -INFINITY, lse_blk);
     if (lane < 32) {
@@ -367,7 +367,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   int lane_head = 0, lane_pos = qrow, pos_first = qw0, pos_last = min(qw0 + 31, p.Sq - 1), pos_last_wg = min(q0 + BM, p.Sq) - 1;
   int n_live = 1;   // parts of the keys that any row of this workgroup sees
   if constexpr (PART) {
-    lane_head = qrow_ld / p.Sq;
+    lane_head = divide(p.by_sq, qrow_ld);
     lane_pos = qrow_ld - lane_head * p.Sq;
     int unused;
     pos_span(p, min(qw0, n_rows - 1), 32, pos_first, pos_last);
