@@ -454,25 +454,50 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     v_left--;
   };
 
-  // ---- prologue: K_0..K_2, V_0, V_1 into the rings, then the Query fragments.  The loads go out
+  // ---- prologue: the wave's Query rows and K_0..K_2, V_0, V_1 into the rings.  The loads go out
   // before the rest of the set-up (this wave's key range, LDS read addresses, cleared accumulators)
   // so that their latency, the longest wait of a workgroup's life, runs under that arithmetic.
+  //
+  // The Query rows take the same way as K: whole rows, 1 KiB an instruction, into the wave's own share of ring slots that are filled
+  // last (V from the top, at D = 128 with two instructions a tile K_3 as well), swizzled alike, and from there into the
+  // B-operand layout.  (Straight into registers a quad of lanes touches four rows, and 64 such loads kept a compute unit's
+  // vector-memory path busy for 1.5 us in front of the later waves' K/V loads: 256 keys in 4 segments x 2 heads 7.93 -> 7.71 us, 500 rows x 32
+  // heads on 12500 keys 97.6 -> 96.1, bf16 blocks of 6008 rows 165.4 -> 164.4; long launches, which the power limit bounds, the same.)  A wave touches its own share
+  // only, so no barrier is needed; what the slots are for is loaded behind it.
+  constexpr int QP = 32 * RB / 1024, Q_SLOTS = (QP + IPW - 1) / IPW;   // instructions, ring slots
+  static_assert(Q_SLOTS <= 4 && (Q_SLOTS <= NS - VA || NS == 4), "Query rows fit into slots that are filled last");
+  constexpr bool V1_LATE = VA == 2 && Q_SLOTS >= 3, K3_LATE = KA == 4 && Q_SLOTS == 4;
+  constexpr int AHEAD = IPW * ((KA == 4 && !K3_LATE ? 4 : 3) + (VA == 2 && !V1_LATE ? 2 : 1)), LATE = IPW * ((V1_LATE ? 1 : 0) + (K3_LATE ? 1 : 0));
+  auto q_slot = [&](int piece) __attribute__((always_inline)) -> int {   // LDS offset of a piece (RPI rows)
+    const int s = piece / IPW;
+    return (2 * NS - 1 - s - (s == 3 ? 1 : 0)) * TILE_BYTES + (wave * IPW + piece % IPW) * 1024;
+  };
+  auto issue_q = [&]() __attribute__((always_inline)) {
+    const __bf16* const qb = p.q + (int64_t)b * p.q_sb + (int64_t)hq * p.q_sh + chunk_row * p.q_ss;
+#pragma unroll
+    for (int i = 0; i < QP; i++) {
+      const int r = i * RPI + lane / CPR, at = min(qw0 + r, n_rows - 1);
+      int head = 0, pos = at;
+      if (PART && p.pack) {
+        head = divide(p.by_sq, at);
+        pos = at - head * p.Sq;
+      }
+      const __bf16* src = qb + (int64_t)pos * p.q_ss + ((lane % CPR) ^ ((r / (256 / RB)) % CPR)) * 8;
+      if (PART) src += (int64_t)head * p.q_sh;
+      const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base + q_slot(i));
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0v), "v"(src) : "memory");
+    }
+  };
+  if (!PART) issue_q();   // (a partitioned launch is bound by its K/V loads, or waits for HBM first; its Query addresses take more arithmetic)
   if (n_tiles > 0) {
     issue_k(0);
     issue_v(0);
     issue_k(1);
-    if (VA == 2) issue_v(1);
+    if (VA == 2 && !V1_LATE) issue_v(1);
     issue_k(2);
-    if (KA == 4) issue_k(3);
+    if (KA == 4 && !K3_LATE) issue_k(3);
   }
-  // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step.
-  bf16x8 qf[KS];
-  {
-    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)(PART ? hq + lane_head : hq) * p.q_sh + (PART ? lane_pos : chunk_row + qrow_ld) * p.q_ss;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * hf);
-  }
-
+  if (PART && qw0 < n_rows) issue_q();
 
   // Key range of this wave (in 32-key sub-tiles).
   int wave_kv_end = 0;
@@ -509,6 +534,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
       v_rd[db] = lds_base + NS * TILE_BYTES + kgrp * (SUB * RB) + v_lds_off<D>(row, 4 * db + 2 * gq) + (i16 & 3) * 8;
   }
 
+  bf16x8 qf[KS];   // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step
   f32x16 o_acc[DB];
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -755,6 +781,20 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     for (int i = 0; i < 16; i++) t = kstart + 8 * (i >> 2) + 4 * hf + (i & 3) <= limit ? fmaxf(t, s[i]) : t;
     return half_swap_max(t);
   };
+  if (!PART && last_tile >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");   // (all of the tiles above are on their way)
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  {
+    const unsigned at = lds_base + q_slot(ql / RPI) + (ql % RPI) * RB;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) qf[ks] = *(const bf16x8 __attribute__((address_space(3)))*)(unsigned long)(at + (((2 * ks + hf) ^ ((ql / (256 / RB)) % CPR)) << 4));
+  }
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(qf[ks]));   // Q is in registers
+  if (n_tiles > 0) {
+    if (K3_LATE) issue_k(3);   // (first: it is read one tile earlier than V_1)
+    if (V1_LATE) issue_v(1);
+  }
+
   if constexpr (G > 1 && RENEW) {
     if (p.renew > 0) {   // at most kMaxRefs of them, see choose_shape
       auto load = [&](int s, bf16x8 (&kf)[KS]) __attribute__((always_inline)) {
@@ -783,9 +823,8 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     }
   }
 
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(qf[ks]));  // Q is in registers before the loop
-  __builtin_amdgcn_s_waitcnt(0);
+  if (LATE > 0 && last_tile >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
+  else __builtin_amdgcn_s_waitcnt(0);
   wg_barrier();  // B_0
 
   // Ring protocol.  Step j = NSW*u + kt is the wave's step kt in tile u; it reads the V operands of
