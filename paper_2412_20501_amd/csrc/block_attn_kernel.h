@@ -347,6 +347,57 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     qt += y * p.n_qtiles;
   }
   const int64_t chunk_row = (int64_t)chunk * p.Sq;
+  f32x16 o_acc[DB];         // O^T of the wave's rows, not yet divided by the sums
+  float m_ref, l_run;       // exponent reference of the lane's row, in raw (unscaled) score units; the lane's share of its sum of exp
+
+  // Chunk form, one key group: the Update of block `done`, whose result is in the registers.  Between two blocks a wave's accumulators lie
+  // in its rows of `out` as they lie in its lanes, 16 bytes of every lane side by side, so blocks before the last need no transposition
+  // through LDS: the rings are free at once and the next block's first loads run under the Update (one after the other the two took 4.8 us of a
+  // block's 20).  A wave with fewer than 32 rows has no place for that and keeps every piece where it belongs.
+  constexpr bool IN_LANES = CHUNKS && G == 1;
+  auto chunk_update = [&](int done, bool last) __attribute__((always_inline)) {
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ql = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), qw0 = qt * BM + wave * 32, n_valid = p.Sq - qw0;
+    if (n_valid <= 0) return;
+    constexpr int CPRF = D / 4, RPI_OUT = 64 / CPRF, NIT = 32 / RPI_OUT;
+    static_assert(NIT == 4 * DB, "as many pieces a lane as rows a lane touches");
+    const bool whole = n_valid >= 32;
+    const int rr = lane / CPRF, cc = lane % CPRF;
+    float* const rows = reinterpret_cast<float*>(p.out) + (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + (chunk_row + qw0) * p.o_ss;
+    float* const place = whole ? rows + (int64_t)rr * p.o_ss + 4 * cc : rows + (int64_t)min(ql, n_valid - 1) * p.o_ss + 4 * hf;
+    const int64_t next = whole ? (int64_t)RPI_OUT * p.o_ss : 8;
+    f32x4 x[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; it++)
+      x[it] = done > 0 ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(place + it * next)) : f32x4{0.f, 0.f, 0.f, 0.f};
+    float* const l_at = p.lse + (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (chunk_row + qw0 + min(ql, n_valid - 1)) * p.l_ss;
+    const float l_tot = half_swap_sum(l_run), inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    UpdatePlan pl = plan_update(done > 0 ? *l_at : -INFINITY, l_tot > 0.f ? m_ref * p.scale + logf(l_tot) : -INFINITY);
+    if (done == 0) pl.mode = 2;   // a first block is stored as it is, also where it is NaN (with lse -inf)
+    if (hf == 0 && ql < n_valid) *l_at = pl.new_lse;
+    char* const my = lds + wave * (32 * 4 * D);
+    const bool round = done > 0 && p.chunk_bf16;
+#pragma unroll
+    for (int it = 0; it < NIT; it++) {
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        o[e] = o_acc[it >> 2][4 * (it & 3) + e] * inv;
+        if (round) o[e] = (float)(__bf16)o[e];
+      }
+      o = apply_update(pl, x[it], o);
+      if (whole && last) *reinterpret_cast<f32x4*>(my + ql * (4 * D) + (((2 * it + hf) ^ (ql & 15)) << 4)) = o;
+      else if (ql < n_valid) __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(place + it * next));
+    }
+    if (whole && last) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
+#pragma unroll
+      for (int it = 0; it < NIT; it++) x[it] = row_piece<D, R, 1>(my, 0, it * RPI_OUT + rr, cc);
+#pragma unroll
+      for (int it = 0; it < NIT; it++) __builtin_nontemporal_store(x[it], reinterpret_cast<f32x4*>(place + it * next));
+    }
+  };
+  int done = -1;   // block whose Update is still to come
   for (int block = 0; block < (CHUNKS ? p.n_chunks : 1); block++) {
   const int kv_chunk = CHUNKS ? (chunk + block < p.n_chunks ? chunk + block : chunk + block - p.n_chunks) : 0;
   if (CHUNKS && p.causal && kv_chunk > chunk) continue;
@@ -498,6 +549,10 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     if (KA == 4 && !K3_LATE) issue_k(3);
   }
   if (PART && qw0 < n_rows) issue_q();
+  if constexpr (IN_LANES) {
+    if (done >= 0) chunk_update(done, false);
+    done = block;
+  }
 
   // Key range of this wave (in 32-key sub-tiles).
   int wave_kv_end = 0;
@@ -535,7 +590,6 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   }
 
   bf16x8 qf[KS];   // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step
-  f32x16 o_acc[DB];
 #pragma unroll
   for (int db = 0; db < DB; db++)
 #pragma unroll
@@ -547,9 +601,9 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // units) before the reference is moved: on all but pathological inputs that happens once, at
   // the row's first keys.
   constexpr float kSumCap = 0x1p80f;
-  float m_ref = -INFINITY;  // exponent reference of this query, in raw (unscaled) score units
+  m_ref = -INFINITY;
   float mc = 0.f;           // m_ref * c2 (0 while m_ref is -inf), kept alongside m_ref
-  float l_run = 0.f;        // this lane's share of the running sum of exp
+  l_run = 0.f;
   float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite and where it is renewed
   constexpr bool RENEW = !CHUNKS;           // (the chunk form ends every segment in a block of its own)
   // Shapes of fewer than 256 rows renew inside a group of inner tiles too: a group of 4 x 1's (192 keys at D 64) may hold a key at which
@@ -969,6 +1023,10 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // swizzled LDS region (the rings are dead by now) and reads it back row-major, one 16-byte
   // chunk per lane, so that every global row is touched as one contiguous segment.
   __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (IN_LANES) {
+    wg_barrier();   // every wave is done with the K/V rings and none of its loads is still landing
+    continue;
+  }
   if (G == 1) __syncthreads();  // every wave is done with the K/V rings and none of its loads is still landing (G > 1: below)
   {
   // The lane is counted anew: held over the loop, it and what follows from it spill at D = 128, and a kernel with
@@ -1129,6 +1187,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   }
   if constexpr (CHUNKS) __syncthreads();  // the next block's loads land where other waves may still read their rows
   }
+  if constexpr (IN_LANES) chunk_update(done, true);
 }
 
 template <int D, int EPI, int FORM, int R, int G>
