@@ -11,7 +11,7 @@ KEPT = 224 << 20
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("extra", [-1, 0, 1, 2, 4099])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-def test_rows_on_both_sides_of_the_kept_ones(tr, D, extra, dtype):
+def test_rows_on_both_sides_of_the_kept_ones(lib, D, extra, dtype):
     rows = KEPT // (4 * D) + extra
     gen = torch.Generator(device="cuda").manual_seed(20600 + D + extra)
     out = torch.full((1, 1, rows, D), float("nan"), device="cuda")
@@ -19,7 +19,7 @@ def test_rows_on_both_sides_of_the_kept_ones(tr, D, extra, dtype):
     blocks = [(torch.randn((1, 1, rows, D), device="cuda", dtype=dtype, generator=gen),
                torch.rand((1, 1, rows), device="cuda", generator=gen) * 20 - 5) for _ in range(2)]
     for o, l in blocks:
-        tr.tr_merge(out, lse, o, l)
+        lib.tr_merge(out, lse, o, l)
     ref = torch.logsumexp(torch.stack([l.double() for _, l in blocks]), 0)
     assert (lse.double() - ref).abs().max().item() <= 1e-5
     worst = 0.0
