@@ -37,7 +37,7 @@ constexpr int64_t kKeptAccBytes = (int64_t)224 << 20;
 // A wave whose rows all have an empty accumulator (the first Update of a fold) does not read it: the
 // block's loads go out first, the accumulator's once the two lse are there.  Eight Updates of
 // 512 MiB fp32 blocks, the first onto an empty accumulator, 2034 -> 1919 us; two of 32 MiB bf16 blocks 62.6 -> 53.2.
-template <bool BLK_BF16>
+template <bool BLK_BF16, bool LARGE>   // LARGE: some rows lie behind the kept ones
 __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams p, int64_t n_rows, int tpr_log2, int64_t kept_rows) {
   const int64_t gtid = (int64_t)blockIdx.x * kMergeThreads + threadIdx.x;
   const int64_t row = gtid >> tpr_log2;
@@ -92,7 +92,9 @@ __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams 
       if (two) store_acc(col2, apply_update(plan, x1, y1));
     }
   };
-  if (__builtin_amdgcn_readfirstlane((int)(row < kept_rows))) {   // (as the wave's first row)
+  if (!LARGE) {
+    update(std::false_type{});
+  } else if (__builtin_amdgcn_readfirstlane((int)(row < kept_rows))) {   // (as the wave's first row)
     asm volatile("; kept");   // sets the branches apart, else the compiler makes one load or store of both and drops the policy
     update(std::false_type{});
     asm volatile("; kept");
@@ -223,8 +225,12 @@ hipError_t launch_merge(const MergeParams& p, bool blk_bf16, hipStream_t stream)
   const int64_t nblocks = (n_threads + kMergeThreads - 1) / kMergeThreads;
   dim3 grid((unsigned)nblocks), block(kMergeThreads);
   const int64_t kept_rows = kKeptAccBytes / (4 * (int64_t)p.D);
-  if (blk_bf16) return launch_kernel(merge_kernel<true>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
-  return launch_kernel(merge_kernel<false>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
+  if (n_rows <= kept_rows) {
+    if (blk_bf16) return launch_kernel(merge_kernel<true, false>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
+    return launch_kernel(merge_kernel<false, false>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
+  }
+  if (blk_bf16) return launch_kernel(merge_kernel<true, true>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
+  return launch_kernel(merge_kernel<false, true>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
 }
 
 }  // namespace tr
