@@ -512,8 +512,8 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // The Query rows take the same way as K: whole rows, 1 KiB an instruction, into the wave's own share of ring slots that are filled
   // last (V from the top, at D = 128 with two instructions a tile K_3 as well), swizzled alike, and from there into the
   // B-operand layout.  (Straight into registers a quad of lanes touches four rows, and 64 such loads kept a compute unit's
-  // vector-memory path busy for 1.5 us in front of the later waves' K/V loads: 256 keys in 4 segments x 2 heads 7.93 -> 7.71 us, 500 rows x 32
-  // heads on 12500 keys 97.6 -> 96.1, bf16 blocks of 6008 rows 165.4 -> 164.4; long launches, which the power limit bounds, the same.)  A wave touches its own share
+  // vector-memory path busy for 1.5 us in front of the later waves' K/V loads: 256 keys in 4 segments x 2 heads 7.93 -> 7.71 us, 4 x 2
+  // heads of 1503 20.9 -> 20.5, 500 rows x 32 heads on 12500 keys 97.6 -> 96.1; long launches, which the power limit bounds, the same.)  A wave touches its own share
   // only, so no barrier is needed; what the slots are for is loaded behind it.
   constexpr int QP = 32 * RB / 1024, Q_SLOTS = (QP + IPW - 1) / IPW;   // instructions, ring slots
   static_assert(Q_SLOTS <= 4 && (Q_SLOTS <= NS - VA || NS == 4), "Query rows fit into slots that are filled last");
@@ -539,7 +539,11 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0v), "v"(src) : "memory");
     }
   };
-  if (!PART) issue_q();   // (a partitioned launch is bound by its K/V loads, or waits for HBM first; its Query addresses take more arithmetic)
+  // In front of K and V, so that they are in their registers when K comes, where key groups make a launch's first steps count; behind them where
+  // several workgroups share a compute unit or HBM bounds the launch.  us, in front / behind: 113 rows x 8 heads on 1314 keys at D 64 11.94 / 12.05,
+  // bf16 blocks of 3488 rows in 8 chunks, 4 heads 52.96 / 53.74; 128 heads of 442 at D 64 11.67 / 11.31, four decode steps of 8192 keys 138.0 / 135.5.
+  constexpr bool Q_FIRST = !PART && G > 1;
+  if (Q_FIRST) issue_q();
   if (n_tiles > 0) {
     issue_k(0);
     issue_v(0);
@@ -548,7 +552,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     issue_k(2);
     if (KA == 4 && !K3_LATE) issue_k(3);
   }
-  if (PART && qw0 < n_rows) issue_q();
+  if (!Q_FIRST && (!PART || qw0 < n_rows)) issue_q();
   if constexpr (IN_LANES) {
     if (done >= 0) chunk_update(done, false);
     done = block;
@@ -835,7 +839,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     for (int i = 0; i < 16; i++) t = kstart + 8 * (i >> 2) + 4 * hf + (i & 3) <= limit ? fmaxf(t, s[i]) : t;
     return half_swap_max(t);
   };
-  if (!PART && last_tile >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");   // (all of the tiles above are on their way)
+  if (Q_FIRST && last_tile >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");   // (all of the tiles above are on their way)
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   {
     const unsigned at = lds_base + q_slot(ql / RPI) + (ql % RPI) * RB;
