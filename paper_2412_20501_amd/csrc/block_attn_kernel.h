@@ -518,7 +518,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   constexpr int QP = 32 * RB / 1024, Q_SLOTS = (QP + IPW - 1) / IPW;   // instructions, ring slots
   static_assert(Q_SLOTS <= 4 && (Q_SLOTS <= NS - VA || NS == 4), "Query rows fit into slots that are filled last");
   constexpr bool V1_LATE = VA == 2 && Q_SLOTS >= 3, K3_LATE = KA == 4 && Q_SLOTS == 4;
-  constexpr int AHEAD = IPW * ((KA == 4 && !K3_LATE ? 4 : 3) + (VA == 2 && !V1_LATE ? 2 : 1)), LATE = IPW * ((V1_LATE ? 1 : 0) + (K3_LATE ? 1 : 0));
+  constexpr int AHEAD = IPW * ((KA == 4 && !K3_LATE ? 3 : 2) + (VA == 2 && !V1_LATE ? 2 : 1)), LATE = IPW * ((V1_LATE ? 1 : 0) + (K3_LATE ? 1 : 0));
   auto q_slot = [&](int piece) __attribute__((always_inline)) -> int {   // LDS offset of a piece (RPI rows)
     const int s = piece / IPW;
     return (2 * NS - 1 - s - (s == 3 ? 1 : 0)) * TILE_BYTES + (wave * IPW + piece % IPW) * 1024;
@@ -539,13 +539,14 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0v), "v"(src) : "memory");
     }
   };
-  // In front of K and V, so that they are in their registers when K comes, where key groups make a launch's first steps count; behind them where
+  // Behind K_0, which the first products need beside them (in front of it too a call of 2 x 6 heads of 340 rows on 652 keys at D 64 takes 8.43 us, behind it
+  // 8.36), and in front of the other tiles, so that they are in their registers when K is there, where key groups make a launch's first steps count; behind all where
   // several workgroups share a compute unit or HBM bounds the launch.  us, in front / behind: 113 rows x 8 heads on 1314 keys at D 64 11.94 / 12.05,
   // bf16 blocks of 3488 rows in 8 chunks, 4 heads 52.96 / 53.74; 128 heads of 442 at D 64 11.67 / 11.31, four decode steps of 8192 keys 138.0 / 135.5.
   constexpr bool Q_FIRST = !PART && G > 1;
+  if (n_tiles > 0) issue_k(0);
   if (Q_FIRST) issue_q();
   if (n_tiles > 0) {
-    issue_k(0);
     issue_v(0);
     issue_k(1);
     if (VA == 2 && !V1_LATE) issue_v(1);
