@@ -198,9 +198,11 @@ struct Lds {
   static constexpr int rings = 2 * ring_depth<D, R, G>() * tile_keys<D, R, G>() * 2 * D, tiles = R * G * 32 * 4 * D, rows = R * 32;
   static constexpr int w = rings > tiles ? rings : tiles, mode = w + rows * 4, off = mode + rows * 4;
   static constexpr int sums = off + rows * 8, refs = sums + (G > 1 ? G * rows * 8 : 0);
-  static constexpr int bytes(int form) {
+  static constexpr int tables(int form) {
     return G > 1 ? (form == kChunks ? refs : refs + kMaxRefs * rows * 4) : form == kPart ? sums : off;
   }
+  static constexpr int query = D == 128 && G == 1 ? R * 2048 : 0;   // a quarter of the Query rows, behind the tables (see the prologue)
+  static constexpr int bytes(int form) { return tables(form) + query; }
 };
 
 // Sixteen bytes of row r of row group rg, from the waves' tiles in LDS (chunk-swizzled, one tile for each key group):
@@ -511,16 +513,23 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   //
   // The Query rows take the same way as K: whole rows, 1 KiB an instruction, into the wave's own share of ring slots that are filled
   // last (V from the top, at D = 128 with two instructions a tile K_3 as well), swizzled alike, and from there into the
-  // B-operand layout.  (Straight into registers a quad of lanes touches four rows, and 64 such loads kept a compute unit's
+  // B-operand layout.  With one key group at D = 128 a quarter of them lies behind the tables, so that K_3 and V_1 need not wait for them (64 heads of 1024,
+  // causal, 0.9 % less, 128 heads of 827 rows on 184 keys 1.7 %).  (Straight into registers a quad of lanes touches four rows, and 64 such loads kept a compute unit's
   // vector-memory path busy for 1.5 us in front of the later waves' K/V loads: 256 keys in 4 segments x 2 heads 7.93 -> 7.71 us, 4 x 2
   // heads of 1503 20.9 -> 20.5, 500 rows x 32 heads on 12500 keys 97.6 -> 96.1; long launches, which the power limit bounds, the same.)  A wave touches its own share
   // only, so no barrier is needed; what the slots are for is loaded behind it.
   constexpr int QP = 32 * RB / 1024, Q_SLOTS = (QP + IPW - 1) / IPW;   // instructions, ring slots
   static_assert(Q_SLOTS <= 4 && (Q_SLOTS <= NS - VA || NS == 4), "Query rows fit into slots that are filled last");
-  constexpr bool V1_LATE = VA == 2 && Q_SLOTS >= 3, K3_LATE = KA == 4 && Q_SLOTS == 4;
+  constexpr bool APART = Lds<D, R, G>::query > 0;   // the last slot's pieces lie behind the tables; the third slot is K_3's of 256-row workgroups
+  static_assert(!APART || (Q_SLOTS == 4 && IPW == 2 && Lds<D, R, G>::tables(FORM) % 1024 == 0), "two pieces of every wave lie apart");
+  constexpr bool V1_LATE = VA == 2 && (APART ? KA == 4 : Q_SLOTS >= 3), K3_LATE = KA == 4 && Q_SLOTS == 4 && !APART;
   constexpr int AHEAD = IPW * ((KA == 4 && !K3_LATE ? 3 : 2) + (VA == 2 && !V1_LATE ? 2 : 1)), LATE = IPW * ((V1_LATE ? 1 : 0) + (K3_LATE ? 1 : 0));
   auto q_slot = [&](int piece) __attribute__((always_inline)) -> int {   // LDS offset of a piece (RPI rows)
     const int s = piece / IPW;
+    if (APART) {
+      const int slot = s == 2 && KA == 3 ? NS - 1 : 2 * NS - 1 - s;
+      return (s == 3 ? Lds<D, R, G>::tables(FORM) : slot * TILE_BYTES) + (wave * IPW + piece % IPW) * 1024;
+    }
     return (2 * NS - 1 - s - (s == 3 ? 1 : 0)) * TILE_BYTES + (wave * IPW + piece % IPW) * 1024;
   };
   auto issue_q = [&]() __attribute__((always_inline)) {
