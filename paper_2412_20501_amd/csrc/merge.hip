@@ -7,8 +7,6 @@
 // element (out = 0, lse = -inf) exact on either side.
 //
 // Pure streaming kernel: per output element it reads 2 values and writes 1, a few flops.
-#include <type_traits>
-
 #include "tr_internal.h"
 
 namespace tr {
@@ -19,12 +17,15 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMergeThreads = 512;
 
-// The rows of the first 224 MiB of an accumulator go through the caches, those behind them past (non-temporal).  Blocks are never read
-// again, so what the chip's 256 MiB memory-side cache is good for is the accumulator of the next Update of a fold (one device's Out between
-// two iterations of Algorithm 1): a fixed share of it, because rows that come round after more than the cache holds evict each other
-// (all of 512 MiB through the caches 2100 us for eight Updates, none 1910, 64 MiB 1886, 128 MiB 1870, 192 MiB 1853, 224 MiB 1842, 256 MiB 1843; 256 MiB, six
-// Updates of fp32 blocks: none 711, 128 MiB 683, 224 MiB 664, all 673; of bf16 blocks 607, 593, 577, 590).
-constexpr int64_t kKeptAccBytes = (int64_t)224 << 20;
+// Accumulators beyond this size cannot stay in the chip's 256 MiB memory-side cache between two
+// Updates, so they are read and written past the caches (non-temporal): measured on the 512 MiB
+// merge-only workload, 5.8 -> 6.5 TB/s.  A smaller accumulator that is updated again soon (one
+// device's Out between two iterations of Algorithm 1) is served from that cache and keeps the
+// ordinary policy, which is the faster one there.  (A share of a large accumulator kept in the cache helps only
+// where one accumulator is updated again and again, and an Update cannot know: with the first 224 MiB kept one of 512 MiB takes 248 us
+// instead of 255, one of 160 MiB 77 instead of 80, but two or more in turn 267 instead of 254 and 85 - 88 instead of 79; bf16 blocks 231 / 214 and
+// 75 - 78 / 67.  Only its loads or only its stores through the cache: the same or worse.)
+constexpr int64_t kStreamAccBytes = (int64_t)128 << 20;
 
 // One row is always handled inside a single wavefront: `tpr` (a power of two <= 64) threads
 // share a row; a thread takes the 16-byte column chunks t and t + tpr (then t + 2 tpr, ... for
@@ -37,8 +38,8 @@ constexpr int64_t kKeptAccBytes = (int64_t)224 << 20;
 // A wave whose rows all have an empty accumulator (the first Update of a fold) does not read it: the
 // block's loads go out first, the accumulator's once the two lse are there.  Eight Updates of
 // 512 MiB fp32 blocks, the first onto an empty accumulator, 2034 -> 1919 us; two of 32 MiB bf16 blocks 62.6 -> 53.2.
-template <bool BLK_BF16, bool LARGE>   // LARGE: some rows lie behind the kept ones
-__global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams p, int64_t n_rows, int tpr_log2, int64_t kept_rows) {
+template <bool BLK_BF16, bool STREAM_ACC>
+__global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams p, int64_t n_rows, int tpr_log2) {
   const int64_t gtid = (int64_t)blockIdx.x * kMergeThreads + threadIdx.x;
   const int64_t row = gtid >> tpr_log2;
   const int tpr = 1 << tpr_log2;
@@ -58,48 +59,36 @@ __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams 
   }
   const UpdatePlan plan = plan_update(p.acc_lse[al], p.blk_lse[bl]);
 
-  auto update = [&](auto stream_c) __attribute__((always_inline)) {
-    constexpr bool STREAM = decltype(stream_c)::value;
-    auto load_acc = [&](int col) __attribute__((always_inline)) -> f32x4 {
-      const f32x4* src = reinterpret_cast<const f32x4*>(p.acc_out + ao + col);
-      return STREAM ? __builtin_nontemporal_load(src) : *src;
-    };
-    auto load_blk = [&](int col) __attribute__((always_inline)) -> f32x4 {
-      if (BLK_BF16) {
-        const bf16x4 yb = __builtin_nontemporal_load(reinterpret_cast<const bf16x4*>(reinterpret_cast<const __bf16*>(p.blk_out) + bo + col));
-        return f32x4{(float)yb[0], (float)yb[1], (float)yb[2], (float)yb[3]};
-      }
-      return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.blk_out) + bo + col));
-    };
-    auto store_acc = [&](int col, f32x4 val) __attribute__((always_inline)) {
-      f32x4* dst = reinterpret_cast<f32x4*>(p.acc_out + ao + col);
-      if (STREAM) __builtin_nontemporal_store(val, dst);
-      else *dst = val;
-    };
-    const bool held = __any(plan.mode == 0 || plan.mode == 3);   // does some row of the wave use what the accumulator holds?
-    for (int col = t * 4; col < p.D; col += tpr * 8) {
-      const int col2 = col + tpr * 4;
-      const bool two = col2 < p.D;
-      const f32x4 y0 = load_blk(col);
-      f32x4 y1 = y0;
-      if (two) y1 = load_blk(col2);
-      f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
-      if (held) {
-        x0 = load_acc(col);
-        if (two) x1 = load_acc(col2);
-      }
-      store_acc(col, apply_update(plan, x0, y0));
-      if (two) store_acc(col2, apply_update(plan, x1, y1));
-    }
+  auto load_acc = [&](int col) __attribute__((always_inline)) -> f32x4 {
+    const f32x4* src = reinterpret_cast<const f32x4*>(p.acc_out + ao + col);
+    return STREAM_ACC ? __builtin_nontemporal_load(src) : *src;
   };
-  if (!LARGE) {
-    update(std::false_type{});
-  } else if (__builtin_amdgcn_readfirstlane((int)(row < kept_rows))) {   // (as the wave's first row)
-    asm volatile("; kept");   // sets the branches apart, else the compiler makes one load or store of both and drops the policy
-    update(std::false_type{});
-    asm volatile("; kept");
-  } else {
-    update(std::true_type{});
+  auto load_blk = [&](int col) __attribute__((always_inline)) -> f32x4 {
+    if (BLK_BF16) {
+      const bf16x4 yb = __builtin_nontemporal_load(reinterpret_cast<const bf16x4*>(reinterpret_cast<const __bf16*>(p.blk_out) + bo + col));
+      return f32x4{(float)yb[0], (float)yb[1], (float)yb[2], (float)yb[3]};
+    }
+    return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.blk_out) + bo + col));
+  };
+  auto store_acc = [&](int col, f32x4 val) __attribute__((always_inline)) {
+    f32x4* dst = reinterpret_cast<f32x4*>(p.acc_out + ao + col);
+    if (STREAM_ACC) __builtin_nontemporal_store(val, dst);
+    else *dst = val;
+  };
+  const bool held = __any(plan.mode == 0 || plan.mode == 3);   // does some row of the wave use what the accumulator holds?
+  for (int col = t * 4; col < p.D; col += tpr * 8) {
+    const int col2 = col + tpr * 4;
+    const bool two = col2 < p.D;
+    const f32x4 y0 = load_blk(col);
+    f32x4 y1 = y0;
+    if (two) y1 = load_blk(col2);
+    f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+    if (held) {
+      x0 = load_acc(col);
+      if (two) x1 = load_acc(col2);
+    }
+    store_acc(col, apply_update(plan, x0, y0));
+    if (two) store_acc(col2, apply_update(plan, x1, y1));
   }
   if (t == 0) p.acc_lse[al] = plan.new_lse;
 }
@@ -224,13 +213,13 @@ hipError_t launch_merge(const MergeParams& p, bool blk_bf16, hipStream_t stream)
   const int64_t n_threads = n_rows << tpr_log2;
   const int64_t nblocks = (n_threads + kMergeThreads - 1) / kMergeThreads;
   dim3 grid((unsigned)nblocks), block(kMergeThreads);
-  const int64_t kept_rows = kKeptAccBytes / (4 * (int64_t)p.D);
-  if (n_rows <= kept_rows) {
-    if (blk_bf16) return launch_kernel(merge_kernel<true, false>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
-    return launch_kernel(merge_kernel<false, false>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
+  const bool stream_acc = n_rows * p.D * 4 > kStreamAccBytes;
+  if (blk_bf16) {
+    if (stream_acc) return launch_kernel(merge_kernel<true, true>, grid, block, 0, stream, p, n_rows, tpr_log2);
+    return launch_kernel(merge_kernel<true, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
   }
-  if (blk_bf16) return launch_kernel(merge_kernel<true, true>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
-  return launch_kernel(merge_kernel<false, true>, grid, block, 0, stream, p, n_rows, tpr_log2, kept_rows);
+  if (stream_acc) return launch_kernel(merge_kernel<false, true>, grid, block, 0, stream, p, n_rows, tpr_log2);
+  return launch_kernel(merge_kernel<false, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
 }
 
 }  // namespace tr
