@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // bf16 blocks of 3488 rows in 8 chunks, 4 heads 52.96 / 53.74; 128 heads of 442 at D 64 11.67 / 11.31, four decode steps of 8192 keys 138.0 / 135.5.
   constexpr bool Q_FIRST = !PART && G > 1;
   if (n_tiles > 0) issue_k(0);
-  if (Q_FIRST) issue_q();
+  if (Q_FIRST && (!CHUNKS || qw0 < n_rows)) issue_q();
   if (n_tiles > 0) {
     issue_v(0);
     issue_k(1);
@@ -563,7 +563,9 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     if (KA == 4 && !K3_LATE) issue_k(3);
   }
   // (A wave without rows loads none, and what it then reads takes part in nothing: with clamped rows loaded all the same 32 rows x 16 heads on 32 keys take
-  // 5.57 us, 5.16 without, 64 rows x 4 heads on 64 keys at D 64 4.58 and 4.34.  In front of the other tiles a test costs as much as it gives: 0.5 - 1 % more.)
+  // 5.57 us, 5.16 without, 64 rows x 4 heads on 64 keys at D 64 4.58 and 4.34.  In front of the other tiles
+  // of a plain launch the test costs as much as it gives, 0.5 - 1 % more; the chunk form, whose blocks load their rows again and again, takes it there too: 4 chunks of 8 rows
+  // x 16 heads 22.25 -> 21.90, of 31 23.42 -> 22.96.)
   if (!Q_FIRST && qw0 < n_rows) issue_q();
   if constexpr (IN_LANES) {
     if (done >= 0) chunk_update(done, false);
