@@ -349,6 +349,12 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     qt += y * p.n_qtiles;
   }
   const int64_t chunk_row = (int64_t)chunk * p.Sq;
+  // Chunk form at D 64 with one key group: what every block can compute anew is not held from block to block, neither in vector registers (168 for
+  // three workgroups a compute unit: 4 spilled, and a kernel with scratch starts later) nor in scalar ones, whose spills take vector registers.  Causal
+  // blocks of 600 rows in 4 chunks, 64 heads 86.7 -> 85.4 us, 96 heads of 300 rows in 4 chunks 99.2 -> 95.7.  (At D 128 nothing but scalars spills, and counting anew costs
+  // more: 6008 rows in 4 chunks, 16 heads 161 -> 168.)
+  constexpr bool LEAN = CHUNKS && G == 1 && D == 64;
+  const int wave_id = LEAN ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
   f32x16 o_acc[DB];         // O^T of the wave's rows, not yet divided by the sums
   float m_ref, l_run;       // exponent reference of the lane's row, in raw (unscaled) score units; the lane's share of its sum of exp
 
@@ -359,28 +365,32 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   constexpr bool IN_LANES = CHUNKS && G == 1;
   auto chunk_update = [&](int done, bool last) __attribute__((always_inline)) {
     const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ql = lane & 31, hf = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), qw0 = qt * BM + wave * 32, n_valid = p.Sq - qw0;
+    int bb = b, hh = hq, wave = LEAN ? wave_id : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if constexpr (LEAN) asm volatile("" : "+s"(bb), "+s"(hh), "+s"(wave));
+    const int qw0 = qt * BM + wave * 32, n_valid = p.Sq - qw0;
     if (n_valid <= 0) return;
     constexpr int CPRF = D / 4, RPI_OUT = 64 / CPRF, NIT = 32 / RPI_OUT;
     static_assert(NIT == 4 * DB, "as many pieces a lane as rows a lane touches");
     const bool whole = n_valid >= 32;
     const int rr = lane / CPRF, cc = lane % CPRF;
-    float* const rows = reinterpret_cast<float*>(p.out) + (int64_t)b * p.o_sb + (int64_t)hq * p.o_sh + (chunk_row + qw0) * p.o_ss;
+    float* const rows = reinterpret_cast<float*>(p.out) + (int64_t)bb * p.o_sb + (int64_t)hh * p.o_sh + (chunk_row + qw0) * p.o_ss;
     float* const place = whole ? rows + (int64_t)rr * p.o_ss + 4 * cc : rows + (int64_t)min(ql, n_valid - 1) * p.o_ss + 4 * hf;
     const int64_t next = whole ? (int64_t)RPI_OUT * p.o_ss : 8;
     f32x4 x[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; it++)
       x[it] = done > 0 ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(place + it * next)) : f32x4{0.f, 0.f, 0.f, 0.f};
-    float* const l_at = p.lse + (int64_t)b * p.l_sb + (int64_t)hq * p.l_sh + (chunk_row + qw0 + min(ql, n_valid - 1)) * p.l_ss;
+    float* const l_at = p.lse + (int64_t)bb * p.l_sb + (int64_t)hh * p.l_sh + (chunk_row + qw0 + min(ql, n_valid - 1)) * p.l_ss;
     const float l_tot = half_swap_sum(l_run), inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     UpdatePlan pl = plan_update(done > 0 ? *l_at : -INFINITY, l_tot > 0.f ? m_ref * p.scale + logf(l_tot) : -INFINITY);
     if (done == 0) pl.mode = 2;   // a first block is stored as it is, also where it is NaN (with lse -inf)
     if (hf == 0 && ql < n_valid) *l_at = pl.new_lse;
     char* const my = lds + wave * (32 * 4 * D);
     const bool round = done > 0 && p.chunk_bf16;
+    float* dst = place;
+    if constexpr (LEAN) asm volatile("" : "+v"(dst));   // the loads' addresses are not held for the stores
 #pragma unroll
-    for (int it = 0; it < NIT; it++) {
+    for (int it = 0; it < NIT; it++, dst += next) {
       f32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; e++) {
@@ -389,7 +399,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
       }
       o = apply_update(pl, x[it], o);
       if (whole && last) *reinterpret_cast<f32x4*>(my + ql * (4 * D) + (((2 * it + hf) ^ (ql & 15)) << 4)) = o;
-      else if (ql < n_valid) __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(place + it * next));
+      else if (ql < n_valid) __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(dst));
     }
     if (whole && last) {
       __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes are visible to all its lanes
@@ -403,10 +413,17 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   for (int block = 0; block < (CHUNKS ? p.n_chunks : 1); block++) {
   const int kv_chunk = CHUNKS ? (chunk + block < p.n_chunks ? chunk + block : chunk + block - p.n_chunks) : 0;
   if (CHUNKS && p.causal && kv_chunk > chunk) continue;
-  int tid = threadIdx.x;
-  if constexpr (CHUNKS) asm volatile("" : "+v"(tid));   // nothing derived from it is held in registers from block to block (179 spills otherwise)
+  int tid = threadIdx.x, wave;
+  if constexpr (LEAN) {
+    unsigned zero = 0;
+    wave = wave_id;
+    asm volatile("" : "+v"(zero), "+s"(wave));
+    tid = wave * 64 + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+  } else {
+    if constexpr (CHUNKS) asm volatile("" : "+v"(tid));   // nothing derived from it is held in registers from block to block (179 spills otherwise)
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept in an SGPR
+  }
   const int lane = tid & 63, ql = lane & 31, hf = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in an SGPR
   const int rg = G == 1 ? wave : wave % R, kgrp = G == 1 ? 0 : wave / R;   // row group, key group
   const bool causal = CHUNKS ? p.causal && block == 0 : p.causal != 0;
   int Sk = p.Sk, causal_off = p.causal_off;
