@@ -571,7 +571,14 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // bf16 blocks of 3488 rows in 8 chunks, 4 heads 52.96 / 53.74; 128 heads of 442 at D 64 11.67 / 11.31, four decode steps of 8192 keys 138.0 / 135.5.
   constexpr bool Q_FIRST = !PART && G > 1;
   if (n_tiles > 0) issue_k(0);
-  if (Q_FIRST && (!CHUNKS || qw0 < n_rows)) issue_q();
+  // At most 16 rows, a decode step's, go straight into registers behind the tiles: of the pieces of 32 rows most would be loaded for nothing, and the way through LDS is
+  // one wait longer.  One row x 8 heads on 2 K/V heads of 2048 keys 12.02 -> 11.55 us (11.85 before the rows went through LDS), 8 heads of 1500
+  // 12.54 -> 12.13; from 24 rows on LDS is faster (24 x 8 heads on 512 keys, which is not cut, 9.23 straight and 9.06).  In the chunk form at D 64: 4 chunks of one row
+  // 16.16 -> 15.78.  Not where the choice costs more than it gives: cut launches at D 64 (4 sequences on 8192 keys 18.23 -> 18.69), uncut ones (64 rows x 4 heads
+  // on 512 keys at D 64 1 %), the chunk form at D 128 (scalar spills, 1 - 2 %).
+  constexpr bool FEW = G > 1 && (D == 128 ? PART : CHUNKS);
+  const bool straight = FEW && n_rows <= 16;
+  if (Q_FIRST && !straight && (!CHUNKS || qw0 < n_rows)) issue_q();
   if (n_tiles > 0) {
     issue_v(0);
     issue_k(1);
@@ -583,7 +590,17 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // 5.57 us, 5.16 without, 64 rows x 4 heads on 64 keys at D 64 4.58 and 4.34.  In front of the other tiles
   // of a plain launch the test costs as much as it gives, 0.5 - 1 % more; the chunk form, whose blocks load their rows again and again, takes it there too: 4 chunks of 8 rows
   // x 16 heads 22.25 -> 21.90, of 31 23.42 -> 22.96.)
-  if (!Q_FIRST && qw0 < n_rows) issue_q();
+  if (!Q_FIRST && !straight && qw0 < n_rows) issue_q();
+  bf16x8 qf[KS];   // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step
+  if (FEW && straight) {
+    if (n_tiles > 0) {   // (nothing lies in their slots)
+      if (K3_LATE) issue_k(3);   // (first: it is read one tile earlier than V_1)
+      if (V1_LATE) issue_v(1);
+    }
+    const __bf16* qp = p.q + (int64_t)b * p.q_sb + (int64_t)(PART ? hq + lane_head : hq) * p.q_sh + (PART ? lane_pos : chunk_row + qrow_ld) * p.q_ss;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * hf);
+  }
   if constexpr (IN_LANES) {
     if (done >= 0) chunk_update(done, false);
     done = block;
@@ -624,7 +641,6 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
       v_rd[db] = lds_base + NS * TILE_BYTES + kgrp * (SUB * RB) + v_lds_off<D>(row, 4 * db + 2 * gq) + (i16 & 3) * 8;
   }
 
-  bf16x8 qf[KS];   // Q^T fragments: lane (q, hf) holds Q[q][16*ks + 8*hf .. +7] for every k-step
 #pragma unroll
   for (int db = 0; db < DB; db++)
 #pragma unroll
@@ -870,18 +886,20 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     for (int i = 0; i < 16; i++) t = kstart + 8 * (i >> 2) + 4 * hf + (i & 3) <= limit ? fmaxf(t, s[i]) : t;
     return half_swap_max(t);
   };
-  if (Q_FIRST && last_tile >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");   // (all of the tiles above are on their way)
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  {
-    const unsigned at = lds_base + q_slot(ql / RPI) + (ql % RPI) * RB;
+  if (!straight) {
+    if (Q_FIRST && last_tile >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD) : "memory");   // (all of the tiles above are on their way)
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    {
+      const unsigned at = lds_base + q_slot(ql / RPI) + (ql % RPI) * RB;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) qf[ks] = *(const bf16x8 __attribute__((address_space(3)))*)(unsigned long)(at + (((2 * ks + hf) ^ ((ql / (256 / RB)) % CPR)) << 4));
-  }
+      for (int ks = 0; ks < KS; ks++) qf[ks] = *(const bf16x8 __attribute__((address_space(3)))*)(unsigned long)(at + (((2 * ks + hf) ^ ((ql / (256 / RB)) % CPR)) << 4));
+    }
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(qf[ks]));   // Q is in registers
-  if (n_tiles > 0) {
-    if (K3_LATE) issue_k(3);   // (first: it is read one tile earlier than V_1)
-    if (V1_LATE) issue_v(1);
+    for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(qf[ks]));   // Q is in registers
+    if (n_tiles > 0) {
+      if (K3_LATE) issue_k(3);   // (first: it is read one tile earlier than V_1)
+      if (V1_LATE) issue_v(1);
+    }
   }
 
   if constexpr (G > 1 && RENEW) {
@@ -912,7 +930,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     }
   }
 
-  if (LATE > 0 && last_tile >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
+  if (LATE > 0 && last_tile >= 3 && !straight) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
   else __builtin_amdgcn_s_waitcnt(0);
   wg_barrier();  // B_0
 

@@ -6,6 +6,8 @@ import math
 import pytest
 import torch
 
+from gpu_util import STEP_F32, attn_plan, attn_shape
+
 pytestmark = pytest.mark.gpu
 
 
@@ -49,7 +51,28 @@ def test_rows_of_a_block_step(lib, D, Sq, B, Hq, Hkv, Sk, token):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("chunk", [1, 32, 45, 127, 128, 131, 300])
+@pytest.mark.parametrize("Hq,Hkv,Sq,Sk", [(8, 8, 1, 1500), (8, 8, 15, 1500), (8, 8, 16, 1500), (8, 8, 17, 1500), (8, 2, 1, 2048), (8, 2, 4, 2048), (8, 2, 5, 2048)])
+@pytest.mark.parametrize("token", [False, True])
+def test_few_rows_of_a_cut_step(lib, D, Hq, Hkv, Sq, Sk, token):
+    """Up to 16 rows of a K/V head, one query head's or its whole group's, and 17 and more."""
+    parts, packed = attn_plan(lib, 1, Hq, Hkv, Sq, Sk, D)
+    assert parts > 1 and packed == int(Hq > Hkv)
+    assert attn_shape(lib, STEP_F32, 1, Hq, Hkv, Sq, Sk, D) == (64, 2)
+    gen = torch.Generator(device="cuda").manual_seed(47 * Sq + Sk + D)
+    q, k, v = rows(gen, 1, Hq, Sq, D, token), rows(gen, 1, Hkv, Sk, D, token), rows(gen, 1, Hkv, Sk, D, token)
+    scale = 1.0 / math.sqrt(D)
+    for causal in (False, True):
+        out, lse = torch.full((1, Hq, Sq, D), float("nan"), device="cuda"), torch.full((1, Hq, Sq), float("nan"), device="cuda")
+        if causal:
+            lib.tr_block_attn_causal_at(q, k, v, Sk - Sq, 0, scale, out, lse)
+        else:
+            lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, scale, out, lse)
+        ref_o, ref_l = attend(q, k, v, scale, causal)
+        assert (out.double() - ref_o).abs().max().item() <= 1e-2 and (lse.double() - ref_l).abs().max().item() <= 1e-3
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [1, 16, 17, 32, 45, 127, 128, 131, 300])
 @pytest.mark.parametrize("n", [1, 2, 3])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("B,H,token", [(1, 3, True), (8, 40, False)])
