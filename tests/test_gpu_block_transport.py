@@ -22,11 +22,39 @@ pytestmark = pytest.mark.gpu
     (1, 2, 1, 320, 1, 128, False),     # a single chunk: nothing is merged
 ])
 def test_bf16_blocks_are_the_steps_one_by_one(lib, B, Hq, Hkv, chunk, n, D, token, causal):
-    S, scale = chunk * n, 1.0 / np.sqrt(D)
-    off = 0 if causal else None
+    S, off = chunk * n, 0 if causal else None
     groups = {attn_shape(lib, RING_BF16, B, Hq, Hkv, S, S, D, off, n)[1], attn_shape(lib, STEP_F32, B, Hq, Hkv, chunk, chunk, D, off)[1]}
     groups |= {attn_shape(lib, STEP_BF16, B, Hq, Hkv, chunk, chunk, D)[1]} if n > 1 else set()
     assert len(groups) == 1 or chunk <= 32               # (a sub-tile belongs to one group)
+    _same_bits(lib, B, Hq, Hkv, chunk, n, D, token, causal)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,chunk,n,D,token,causal,shape", [
+    (16, 16, 16, 20, 3, 64, False, True, (128, 1)),     # no wave has 32 rows
+    (4, 24, 24, 45, 3, 64, False, False, (128, 1)),     # one that has, one of 13
+    (8, 24, 8, 45, 3, 64, True, True, (128, 1)),
+    (4, 24, 24, 45, 3, 128, True, False, (128, 1)),
+    (8, 24, 24, 45, 3, 128, False, True, (128, 1)),
+    (8, 40, 10, 131, 4, 64, True, False, (128, 1)),     # three rows in the second workgroup
+    (8, 40, 10, 131, 4, 128, False, True, (128, 1)),
+    (2, 48, 48, 257, 3, 64, False, True, (128, 1)),
+    (4, 40, 40, 127, 2, 64, True, True, (256, 1)),      # half of the waves have no rows
+    (4, 40, 40, 128, 2, 64, False, True, (256, 1)),
+    (4, 32, 8, 128, 2, 128, False, False, (256, 1)),
+    (1, 40, 8, 768, 2, 128, True, False, (256, 1)),
+    (4, 30, 30, 127, 4, 128, False, True, (256, 1)),
+    (4, 40, 40, 90, 3, 128, True, True, (256, 1)),
+])
+def test_updates_in_the_lanes_are_the_steps_one_by_one(lib, B, Hq, Hkv, chunk, n, D, token, causal, shape):
+    """One key group on either side: between two blocks the accumulators lie in the result as they lie in the lanes."""
+    S, off = chunk * n, 0 if causal else None
+    assert attn_shape(lib, RING_BF16, B, Hq, Hkv, S, S, D, off, n) == shape
+    assert attn_shape(lib, STEP_F32, B, Hq, Hkv, chunk, chunk, D, off)[1] == attn_shape(lib, STEP_BF16, B, Hq, Hkv, chunk, chunk, D)[1] == 1
+    _same_bits(lib, B, Hq, Hkv, chunk, n, D, token, causal)
+
+
+def _same_bits(lib, B, Hq, Hkv, chunk, n, D, token, causal):
+    S, scale = chunk * n, 1.0 / np.sqrt(D)
 
     def tensor(H, seed):
         x = rand_bits((B, H, S, D), seed)
@@ -53,12 +81,13 @@ def test_bf16_blocks_are_the_steps_one_by_one(lib, B, Hq, Hkv, chunk, n, D, toke
     assert torch.equal(out, ref_o) and torch.equal(lse, ref_l)
 
 
-@pytest.mark.parametrize("causal,n", [(False, 1), (True, 3)])
-def test_a_first_block_is_stored_as_it_is(lib, causal, n):
-    chunk, D = 96, 64
-    q, k, v = (bits_to_dev(rand_bits((1, h, chunk * n, D), 530 + i)) for i, h in enumerate((2, 1, 1)))
+@pytest.mark.parametrize("causal,n,B,D", [(False, 1, 1, 64), (True, 3, 1, 64), (True, 3, 150, 64), (True, 2, 150, 128)])   # from 150 on one key group
+def test_a_first_block_is_stored_as_it_is(lib, causal, n, B, D):
+    chunk = 96
+    assert n == 1 or attn_shape(lib, RING_BF16, B, 2, 1, chunk * n, chunk * n, D, 0, n)[1] == (2 if B == 1 else 1)
+    q, k, v = (bits_to_dev(rand_bits((B, h, chunk * n, D), 530 + i)) for i, h in enumerate((2, 1, 1)))
     q[0, 1, 7, 0] = float("nan")                         # a row that meets one block only (chunk 0)
-    out, lse = torch.zeros((1, 2, chunk * n, D), device="cuda"), torch.zeros((1, 2, chunk * n), device="cuda")
+    out, lse = torch.zeros((B, 2, chunk * n, D), device="cuda"), torch.zeros((B, 2, chunk * n), device="cuda")
     ws = torch.empty(lib.tr_ring_attn_blocks_workspace_bytes(q, n, lib.TR_BF16), dtype=torch.uint8, device="cuda")
     lib.tr_ring_attn_blocks(q, k, v, n, causal, out, lse, lib.TR_BF16, ws, 0.1)
     torch.cuda.synchronize()
@@ -66,3 +95,4 @@ def test_a_first_block_is_stored_as_it_is(lib, causal, n):
     keep = torch.ones((2, chunk * n), dtype=torch.bool, device="cuda")
     keep[1, 7] = False
     assert torch.isfinite(out[0][keep]).all() and torch.isfinite(lse[0][keep]).all()
+    assert torch.isfinite(out[1:]).all() and torch.isfinite(lse[1:]).all()
