@@ -4,6 +4,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "divisor.h"
 #include "tokenring.h"
 
 namespace tr {
@@ -15,17 +16,6 @@ constexpr int kMaxParts = 16;  // parts the keys of one partitioned attention la
 constexpr int kShape8x1 = 0, kShape4x1 = 1, kShape4x2 = 2, kShape2x2 = 3;
 constexpr int shape_rows(int shape) { return shape == kShape8x1 ? 256 : shape == kShape2x2 ? 64 : 128; }
 constexpr int shape_key_groups(int shape) { return shape >= kShape4x2 ? 2 : 1; }
-
-// Division of a non-negative 32-bit integer by a divisor the host knows: q = (t + ((n - t) >> s1)) >> s2 with
-// t = mulhi(m, n) (Granlund and Montgomery, "Division by invariant integers using multiplication", PLDI 1994, figure 4.1;
-// exact for every n).  Five instructions for n / d in place of the 20 to 40 dependent ones of a division, up to nine of which stood in front of
-// the first K/V load of a partitioned launch: four decode steps of 4 sequences on 8192 keys 137.8 -> 136.2 us.
-struct Divisor { unsigned m, s1, s2, d; };
-inline Divisor make_divisor(unsigned d) {
-  const unsigned l = d < 2 ? 0 : 32 - __builtin_clz(d - 1);   // ceil(log2 d)
-  const uint64_t m = ((((uint64_t)1 << l) - d) << 32) / d + 1;
-  return Divisor{(unsigned)m, l < 1 ? l : 1, l < 1 ? 0 : l - 1, d};
-}
 
 // Arguments of the block-attention kernel: raw pointers, element strides, sizes.
 struct AttnParams {
@@ -123,11 +113,6 @@ inline hipError_t launch_kernel(Kernel kernel, dim3 grid, dim3 block, size_t lds
 #endif
 
 #if defined(__HIPCC__)
-__device__ __forceinline__ int divide(const Divisor& by, int n) {
-  const unsigned t = __umulhi(by.m, (unsigned)n);
-  return (int)((t + (((unsigned)n - t) >> by.s1)) >> by.s2);
-}
-
 // The Update of Sec. 3.1 for one row, shared by the merge kernel and the fused attention
 // epilogue:  lse' = max + log1p(exp(-|lse - block_lse|)),  w = exp(block_lse - lse')
 // (= sigmoid(block_lse - lse)),  out' = out + w (block_out - out).  The identity element
