@@ -1,12 +1,13 @@
 """Query rows on their way into registers, and Updates that stay in the lanes between two blocks: row counts around the row groups and
 tiles of a workgroup, few and many keys, dense and token-major rows, against the same operation in 64 bits.  Out to 1e-2 and lse
-to 1e-3 (bf16 weights); blocks rounded to bf16 add 2^-8 of the largest value for each that is merged."""
+to 1e-3 (bf16 weights); blocks rounded to bf16 add 2^-8 of the largest value for each that is merged (test_gpu_block_transport.py compares their
+bits).  The shape that a case stands for is asserted."""
 import math
 
 import pytest
 import torch
 
-from gpu_util import STEP_F32, attn_plan, attn_shape
+from gpu_util import RING_BF16, STEP_F32, attn_plan, attn_shape
 
 pytestmark = pytest.mark.gpu
 
@@ -29,25 +30,51 @@ def attend(q, k, v, scale, causal):
     return torch.matmul(torch.softmax(s, -1), v), torch.logsumexp(s, -1)
 
 
-@pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("Sq", [1, 2, 31, 33, 63, 65, 100, 129, 257])
-@pytest.mark.parametrize("B,Hq,Hkv,Sk", [(1, 2, 2, 70), (1, 6, 2, 1100), (4, 16, 16, 200), (2, 48, 12, 333)])
-@pytest.mark.parametrize("token", [False, True])
-def test_rows_of_a_block_step(lib, D, Sq, B, Hq, Hkv, Sk, token):
+def block_step(lib, D, Sq, B, Hq, Hkv, Sk, token, shape, causal):
+    assert attn_shape(lib, STEP_F32, B, Hq, Hkv, Sq, Sk, D, Sk - Sq if causal else None) == shape
     gen = torch.Generator(device="cuda").manual_seed(31 * Sq + Sk + D)
-    Sk = max(Sk, Sq)
     q, k, v = rows(gen, B, Hq, Sq, D, token), rows(gen, B, Hkv, Sk, D, token), rows(gen, B, Hkv, Sk, D, token)
     scale = 1.0 / math.sqrt(D)
-    for causal in (False, True):
-        out = torch.full((B, Hq, Sq, D), float("nan"), device="cuda")
-        lse = torch.full((B, Hq, Sq), float("nan"), device="cuda")
-        if causal:
-            lib.tr_block_attn_causal_at(q, k, v, Sk - Sq, 0, scale, out, lse)
-        else:
-            lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, scale, out, lse)
-        ref_o, ref_l = attend(q, k, v, scale, causal)
-        assert (out.double() - ref_o).abs().max().item() <= max(1e-2, v.abs().max().item() / 256)   # weights rounded to bf16: 2^-8 of a value
-        assert (lse.double() - ref_l).abs().max().item() <= 1e-3
+    out = torch.full((B, Hq, Sq, D), float("nan"), device="cuda")
+    lse = torch.full((B, Hq, Sq), float("nan"), device="cuda")
+    if causal:
+        lib.tr_block_attn_causal_at(q, k, v, Sk - Sq, 0, scale, out, lse)
+    else:
+        lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, scale, out, lse)
+    ref_o, ref_l = attend(q, k, v, scale, causal)
+    assert (out.double() - ref_o).abs().max().item() <= max(1e-2, v.abs().max().item() / 256)   # weights rounded to bf16: 2^-8 of a value
+    assert (lse.double() - ref_l).abs().max().item() <= 1e-3
+
+
+# Query rows of a workgroup, key groups: those that each row count below takes, without a mask and under the causal rule.
+SHAPES = {"a": (256, 1), "b": (128, 1), "c": (128, 2), "d": (64, 2)}
+SQ = [1, 2, 31, 33, 63, 65, 100, 129, 257]
+
+
+@pytest.mark.parametrize("Sq", SQ)
+@pytest.mark.parametrize("D,B,Hq,Hkv,Sk,shapes,causal_shapes", [
+    (64, 1, 2, 2, 70, "aaaaaaadd", "aaaaaaadd"), (64, 1, 6, 2, 1100, "ddddddddd", "ddddddddd"),
+    (64, 4, 16, 16, 200, "dddaaaadb", "dddaaaadb"), (64, 2, 48, 12, 333, "dddddddbb", "dddddddbb"),
+    (128, 1, 2, 2, 70, "aaaaaaadd", "aaaaaaadd"), (128, 1, 6, 2, 1100, "ddddddddd", "ddddddddd"),
+    (128, 4, 16, 16, 200, "dddaaaadb", "dddaaaadd"), (128, 2, 48, 12, 333, "dddddaaba", "dddddaabb"),
+])
+@pytest.mark.parametrize("token", [False, True])
+def test_rows_of_a_block_step(lib, D, Sq, B, Hq, Hkv, Sk, shapes, causal_shapes, token):
+    at = SQ.index(Sq)
+    block_step(lib, D, Sq, B, Hq, Hkv, max(Sk, Sq), token, SHAPES[shapes[at]], False)
+    block_step(lib, D, Sq, B, Hq, Hkv, max(Sk, Sq), token, SHAPES[causal_shapes[at]], True)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,causal", [
+    (2, 48, 12, 129, 1000, False), (2, 48, 12, 129, 1000, True),      # one row in the second workgroup: three of four row groups have none
+    (1, 64, 64, 257, 1000, False), (1, 24, 8, 641, 641, False),
+    (1, 24, 8, 1000, 1000, True),                                     # the first row tiles see one tile of keys to three, which wait for all loads
+    (1, 24, 24, 1300, 1300, True),
+])
+def test_rows_of_128_row_workgroups_with_key_groups(lib, D, B, Hq, Hkv, Sq, Sk, causal):
+    """At D 128 the only workgroups whose K_3 and V_1 both lie where the rows pass through."""
+    block_step(lib, D, Sq, B, Hq, Hkv, Sk, False, SHAPES["c"], causal)
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -57,18 +84,8 @@ def test_few_rows_of_a_cut_step(lib, D, Hq, Hkv, Sq, Sk, token):
     """Up to 16 rows of a K/V head, one query head's or its whole group's, and 17 and more."""
     parts, packed = attn_plan(lib, 1, Hq, Hkv, Sq, Sk, D)
     assert parts > 1 and packed == int(Hq > Hkv)
-    assert attn_shape(lib, STEP_F32, 1, Hq, Hkv, Sq, Sk, D) == (64, 2)
-    gen = torch.Generator(device="cuda").manual_seed(47 * Sq + Sk + D)
-    q, k, v = rows(gen, 1, Hq, Sq, D, token), rows(gen, 1, Hkv, Sk, D, token), rows(gen, 1, Hkv, Sk, D, token)
-    scale = 1.0 / math.sqrt(D)
     for causal in (False, True):
-        out, lse = torch.full((1, Hq, Sq, D), float("nan"), device="cuda"), torch.full((1, Hq, Sq), float("nan"), device="cuda")
-        if causal:
-            lib.tr_block_attn_causal_at(q, k, v, Sk - Sq, 0, scale, out, lse)
-        else:
-            lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, scale, out, lse)
-        ref_o, ref_l = attend(q, k, v, scale, causal)
-        assert (out.double() - ref_o).abs().max().item() <= 1e-2 and (lse.double() - ref_l).abs().max().item() <= 1e-3
+        block_step(lib, D, Sq, 1, Hq, Hkv, Sk, token, SHAPES["d"], causal)
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -79,6 +96,8 @@ def test_few_rows_of_a_cut_step(lib, D, Hq, Hkv, Sq, Sk, token):
 def test_rows_of_bf16_blocks(lib, D, chunk, n, causal, B, H, token):
     gen = torch.Generator(device="cuda").manual_seed(17 * chunk + n + D)
     S = n * chunk
+    rows_wg, groups = attn_shape(lib, RING_BF16, B, H, H, S, S, D, 0 if causal else None, n)
+    assert groups == 1 if B == 8 or (n == 1 and chunk <= 128) else (rows_wg, groups) == (64, 2)
     q, k, v = (rows(gen, B, H, S, D, token) for _ in range(3))
     scale = 1.0 / math.sqrt(D)
     guard = torch.full((B, S + 2, H, D), 7.0, device="cuda")   # rows on both sides of the result, which stay as they are
