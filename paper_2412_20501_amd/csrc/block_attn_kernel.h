@@ -38,7 +38,7 @@
 // D = 64 (158 VGPRs): one's loads, epilogue and waits at barriers run beside another's products, and a launch ends more evenly.
 // What it costs is twice the K/V traffic from L2 into LDS for the same rows.  us, 8 x 1 -> 4 x 1: 512 heads of 256 rows on as many keys
 // 41.8 -> 35.4, at D 64 26.2 -> 19.6; 48 heads of 3000 225 -> 207, at D 64 145 -> 121; 64 of 2048 125.3 -> 126.7, at D 64 77.0 -> 73.8; 32 of
-// 24576 7720 -> 8015, at D 64 4847 -> 4721; bf16 blocks of 6008 rows in 4 chunks, 16 heads 190 -> 169.
+// 24576 7720 -> 8015, at D 64 4847 -> 4721; bf16 blocks of 6008 rows in 4 chunks, 16 heads 167 -> 157.
 #pragma once
 #include <type_traits>
 
@@ -299,7 +299,7 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // scratch buffer in fp32 and fold_parts_kernel adds them up in key order (a fixed
 // order: bitwise reproducible).  Bound: HBM for a decode step, MFMA otherwise, plus the fold.  Four decode steps
 // over 8192 keys each (4 sequences, 32 heads on 8 K/V heads) 355 -> 136 us, 500 Query rows x 32 heads
-// behind 12000 keys 216 -> 102 us against the plain form.
+// behind 12000 keys 216 -> 94 us against the plain form.
 //
 // FORM kChunks replays Algorithm 1 block by block: with block results that are rounded to bf16 on their way to the
 // Update, or (chunks shorter than a sub-tile, which no reference of the running softmax can be kept for) in fp32.
@@ -308,7 +308,7 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // epilogue, the first one unrounded onto an empty accumulator.  One launch instead of two per block: no
 // block result in memory, no idle tail between the blocks (chunks of 1502 rows x 16 heads fill 96 of 256
 // compute units), the longest chunks first.  Bound: as the plain form, plus an epilogue for each block.
-// Causal 6008 rows in 4 chunks, 16 heads: 401 -> 193 us in 256-row workgroups, 157 in shape 4 x 1; the same bits as the steps where both have
+// Causal 6008 rows in 4 chunks, 16 heads: 401 -> 167 us in 256-row workgroups, 157 in shape 4 x 1; the same bits as the steps where both have
 // as many key groups.
 template <int D, int EPI, int FORM, int R, int G>
 __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 2) block_attn_kernel(const AttnParams p) {
@@ -360,8 +360,8 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
 
   // Chunk form, one key group: the Update of block `done`, whose result is in the registers.  Between two blocks a wave's accumulators lie
   // in its rows of `out` as they lie in its lanes, 16 bytes of every lane side by side, so blocks before the last need no transposition
-  // through LDS: the rings are free at once and the next block's first loads run under the Update (one after the other the two took 4.8 us of a
-  // block's 20; causal 6008 rows in 4 chunks, 16 heads 164.4 -> 157.5 us).  A wave with fewer than 32 rows has no place for that and keeps every piece where it belongs.
+  // through LDS: the rings are free at once and the next block's first loads go out in front of the Update, whose accumulator loads come in behind them (one after
+  // the other the two took 4.8 us of a block's 20; causal 6008 rows in 4 chunks, 16 heads 164.4 -> 157.5 us; not to wait for its stores in front of the next block gives nothing).  A wave with fewer than 32 rows has no place for that and keeps every piece where it belongs.
   constexpr bool IN_LANES = CHUNKS && G == 1;
   auto chunk_update = [&](int done, bool last) __attribute__((always_inline)) {
     const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ql = lane & 31, hf = lane >> 5;
@@ -530,10 +530,10 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   //
   // The Query rows take the same way as K: whole rows, 1 KiB an instruction, into the wave's own share of ring slots that are filled
   // last (V from the top, at D = 128 with two instructions a tile K_3 as well), swizzled alike, and from there into the
-  // B-operand layout.  With one key group at D = 128 a quarter of them lies behind the tables, so that K_3 and V_1 need not wait for them (64 heads of 1024,
+  // B-operand layout.  With one key group at D = 128 a quarter of them lies behind the tables, so that K_3 (128-row workgroups) and V_1 (256-row ones) need not wait for them (64 heads of 1024,
   // causal, 0.9 % less, 128 heads of 827 rows on 184 keys 1.7 %).  (Straight into registers a quad of lanes touches four rows, and 64 such loads kept a compute unit's
   // vector-memory path busy for 1.5 us in front of the later waves' K/V loads: 256 keys in 4 segments x 2 heads 7.93 -> 7.71 us, 4 x 2
-  // heads of 1503 20.9 -> 20.5, 500 rows x 32 heads on 12500 keys 97.6 -> 96.1; long launches, which the power limit bounds, the same.)  A wave touches its own share
+  // heads of 1503 20.9 -> 20.5, 500 rows x 32 heads on 12500 keys 95.4 -> 93.8; long launches, which the power limit bounds, the same.)  A wave touches its own share
   // only, so no barrier is needed; what the slots are for is loaded behind it.
   constexpr int QP = 32 * RB / 1024, Q_SLOTS = (QP + IPW - 1) / IPW;   // instructions, ring slots
   static_assert(Q_SLOTS <= 4 && (Q_SLOTS <= NS - VA || NS == 4), "Query rows fit into slots that are filled last");
