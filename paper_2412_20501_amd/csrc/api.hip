@@ -194,7 +194,9 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
     const bool few = std::min<int64_t>(rows, bm) <= bm / 2;
     const double fill = std::min(1.0, n / kCUs * std::min(1.0, total / (n * longest + 1e-9)));   // less than n / kCUs where some workgroups end early
     const double alone = few ? c.few : c.idle + (c.busy - c.idle) * fill * fill;   // (a chip that is not full runs at a higher clock)
-    const double fix = (few ? c.fix_few : c.fix) + (groups ? (0.7 + 0.6 * fill) * refs : 0.0);
+    // (What a later segment costs key groups more than one; us a segment, 4 x 1 and 2 x 2: 8 heads of 1024 in 8 at D 128 0.53 and 0.84, at D 64 0.50 and 0.62.)
+    const double ref = shape == tr::kShape4x2 ? 0.7 + 0.6 * fill : (D == 64 ? 0.3 : 0.5) + 0.3 * fill;
+    const double fix = (few ? c.fix_few : c.fix) + (groups ? ref * refs : 0.0);
     const double rounds = std::ceil(n / kCUs);
     double time;
     if (per_cu > 1 && n > kCUs) {   // workgroups of one compute unit fill each other's gaps

@@ -142,6 +142,7 @@ hipError_t launch_block_attn(AttnParams& p, int D, int epilogue, hipStream_t str
     p.by_sq = make_divisor(p.Sq);
     p.by_part_keys = make_divisor(p.part_keys);
   }
+  if (p.renew > 0) p.by_renew = make_divisor(p.renew);
   const hipError_t e = D == 128 ? launch_attn<128>(p, epilogue, grid, stream) : launch_attn<64>(p, epilogue, grid, stream);
   if (e != hipSuccess || p.n_parts <= 1) return e;
   return D == 128 ? launch_fold<128>(p, epilogue, stream, fold_done) : launch_fold<64>(p, epilogue, stream, fold_done);

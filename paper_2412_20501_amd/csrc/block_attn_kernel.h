@@ -66,7 +66,8 @@ constexpr int tile_keys() { return (D == 64 ? 128 : 64) / (R == 4 && G == 1 ? 2 
 template <int D, int R, int G>
 constexpr int ring_depth() { return D == 64 && R == 4 && G == 1 ? 3 : 4; }   // LDS ring depth (tiles) of K and of V
 constexpr int kEpiBf16 = 0, kEpiF32 = 1, kEpiMerge = 2;
-constexpr int kPlain = 0, kPart = 1, kChunks = 2;   // forms of the kernel, see there
+constexpr int kPlain = 0, kPart = 1, kChunks = 2, kSegments = 3, kPartSegments = 4;   // forms of the kernel, see there
+constexpr bool in_segments(int form) { return form == kSegments || form == kPartSegments; }
 
 // Exchange between the two 32-lane halves of a wave with v_permlane32_swap, which swaps the
 // upper half of its first operand with the lower half of its second: fed (x, x) it leaves
@@ -310,9 +311,14 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // compute units), the longest chunks first.  Bound: as the plain form, plus an epilogue for each block.
 // Causal 6008 rows in 4 chunks, 16 heads: 401 -> 167 us in 256-row workgroups, 157 in shape 4 x 1; the same bits as the steps where both have
 // as many key groups.
+//
+// FORM kSegments and kPartSegments are the plain and the partitioned form for launches that take a row's exponent reference anew
+// every p.renew keys (rings of several segments, and block steps that round as their parts would).  Kernels of their own: the tests for a renewal and the
+// bodies of inner tiles that hold one are a quarter of the code, and a short call runs through most of the code once, from a cold instruction cache
+// (8 heads of 512 rows on as many keys 9.42 -> 9.29 us without them, 16 at D 64 7.42 -> 7.31).
 template <int D, int EPI, int FORM, int R, int G>
-__global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 2) block_attn_kernel(const AttnParams p) {
-  constexpr bool PART = FORM == kPart, CHUNKS = FORM == kChunks;
+__device__ __forceinline__ void attend(const AttnParams& p) {
+  constexpr bool PART = FORM == kPart || FORM == kPartSegments, CHUNKS = FORM == kChunks;
   constexpr int W = R * G, BM = 32 * R;    // waves, Query rows of a workgroup
   static_assert(!CHUNKS || EPI == kEpiMerge, "blocks of the chunk form are merged");
   constexpr int RB = 2 * D;
@@ -579,6 +585,57 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   constexpr bool FEW = G > 1 && (D == 128 ? PART : CHUNKS);
   const bool straight = FEW && n_rows <= 16;
   if (Q_FIRST && !straight && (!CHUNKS || qw0 < n_rows)) issue_q();
+  constexpr bool RENEW = in_segments(FORM);
+  constexpr bool KNOWN = RENEW && G > 1;    // references of later segments are found in the prologue
+  // Key range of this wave (in 32-key sub-tiles): behind the loads, but where rows of K are loaded by it.
+  int wave_kv_end, jw;      // jw: sub-tiles this wave has visible keys in
+  int kmask_from;           // a sub-tile starting at kstart needs masking iff kstart > kmask_from
+  // Where the reference is renewed for a segment that starts at key r: at r, or at the next multiple of 2^renew_log2 keys while that
+  // lies in the stretch (up to renew_end) that no row of the wave needs a mask for, four quarters and more before the keys end.  A
+  // multiple is a group of inner tiles of 256-row workgroups; a function of the wave's rows and the keys alone, so every shape of the
+  // workgroup renews at the same keys and rounds the same weights.
+  const int renew_log2 = p.renew_log2;
+  int renew_end;
+  auto wave_range = [&]() __attribute__((always_inline)) {
+    wave_kv_end = 0;
+    if (qw0 < n_rows) {
+      wave_kv_end = Sk;
+      if (causal) wave_kv_end = max(0, min(Sk, pos_last + causal_off + 1));
+    }
+    jw = (wave_kv_end + SUB - 1) / SUB;
+    int from = Sk - SUB;
+    if (causal) from = min(from, pos_first + causal_off - SUB + 1);
+    kmask_from = __builtin_amdgcn_readfirstlane(from);
+    renew_end = 0;
+    if (RENEW && p.renew >= 1 << renew_log2) {
+      const int j = min(jw, kmask_from >= 0 ? kmask_from / SUB : -1) - (1 << (renew_log2 - 7)) + 1;   // a quarter's last sub-tile must pass both tests
+      const int quarters = j < 0 ? 0 : min(j >> (renew_log2 - 7), ((Sk - 1) >> (renew_log2 - 2)) - 4) + 1;
+      renew_end = __builtin_amdgcn_readfirstlane(max(0, quarters) >> 2 << renew_log2);
+    }
+  };
+  auto renew_key = [&](int r) __attribute__((always_inline)) -> int {
+    return max(r, min((r + (1 << renew_log2) - 1) >> renew_log2 << renew_log2, renew_end));
+  };
+  // The first sub-tiles of later segments, whose largest scores are the references there (see masked_max below): K as it lies in memory is the
+  // A operand, so their rows go straight into registers, two references at a time.  Behind Q and in front of the other tiles, so that the
+  // one wait for Q covers them too (fetched behind it they cost a second latency: 2 heads of 256 rows in 4 segments 10.76 -> 9.72 us at D 128, with the
+  // renewals in front of the stream; at D 64 8.60 -> 7.50, 8 heads of 1024 17.6 -> 16.6 and 13.1 -> 12.3).
+  int n_ref = 0;   // references of later segments that the wave needs, at most kMaxRefs (see choose_shape)
+  bf16x8 ref_a[KNOWN ? KS : 1], ref_b[KNOWN ? KS : 1];
+  auto load_ref = [&](int s, auto& kf) __attribute__((always_inline)) {
+    const __bf16* kp = kg + (int64_t)min(renew_key((s + 1) * p.renew) + ql, Sk - 1) * p.k_ss + 8 * hf;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) kf[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks);
+  };
+  const bool range_first = KNOWN && p.renew > 0;
+  if (range_first) {
+    wave_range();
+    n_ref = __builtin_amdgcn_readfirstlane(divide(p.by_renew, max(0, wave_kv_end - 1)));
+    if (kgrp < n_ref) {
+      load_ref(kgrp, ref_a);
+      if (kgrp + G < n_ref) load_ref(kgrp + G, ref_b);
+    }
+  }
   if (n_tiles > 0) {
     issue_v(0);
     issue_k(1);
@@ -606,21 +663,11 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     done = block;
   }
 
-  // Key range of this wave (in 32-key sub-tiles).
-  int wave_kv_end = 0;
-  if (qw0 < n_rows) {
-    wave_kv_end = Sk;
-    if (causal) wave_kv_end = max(0, min(Sk, pos_last + causal_off + 1));
-  }
-  const int jw = (wave_kv_end + SUB - 1) / SUB;  // sub-tiles this wave has visible keys in
+  if (!range_first) wave_range();
   // wave-uniform loop bounds, forced into scalar registers so that every per-step test is one compare
   const int jw_own = G == 1 ? jw : max(0, jw - kgrp + G - 1) / G;                     // those of this key group: kgrp, kgrp + G, ...
   const int jw_first = __builtin_amdgcn_readfirstlane(jw_own);                        // last allowed step that opens a tile
   const int jw_in = __builtin_amdgcn_readfirstlane(min(jw_own, NSW * n_tiles - 1));   // last allowed step inside a tile
-  // a sub-tile starting at kstart needs masking iff kstart > kmask_from
-  int kmask_from_v = Sk - SUB;
-  if (causal) kmask_from_v = min(kmask_from_v, pos_first + causal_off - SUB + 1);
-  const int kmask_from = __builtin_amdgcn_readfirstlane(kmask_from_v);
 
   // Per-lane LDS read offsets.
   // K operand: lane (key = ql, hf) reads chunk 2*ks + hf of row 32*kt + ql.
@@ -656,32 +703,19 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   float mc = 0.f;           // m_ref * c2 (0 while m_ref is -inf), kept alongside m_ref
   l_run = 0.f;
   float sum_cap = -1.f;     // largest sub-tile sum the fast path accepts; negative until m_ref is finite and where it is renewed
-  constexpr bool RENEW = !CHUNKS;           // (the chunk form ends every segment in a block of its own)
   // Shapes of fewer than 256 rows renew inside a group of inner tiles too: a group of 4 x 1's (192 keys at D 64) may hold a key at which
   // the reference is renewed, and block steps renew at any multiple of 128 keys.  Such a group has a body of its own, whose steps look at
-  // renew_at without a branch: the cap is lowered and the slow path does the rest.  (In every inner step the look costs
+  // renew_at without a branch (one key group): the cap is lowered and the slow path does the rest.  (In every inner step the look costs
   // the DiT shape 0.6 % and 1 head of 9984 rows in 2 segments 4 %; renewed by the general body alone 4 heads of 2048 in 8 at D 64 take 28.2
   // us for 24.8, 2 x 16 heads of 499 rows on 3201 keys 39.4 for 36.0.)
   constexpr bool RENEW_INNER = RENEW && R < 8;
-  // Where the reference is renewed for a segment that starts at key r: at r, or at the next multiple of 2^renew_log2 keys while that
-  // lies in the stretch (up to renew_end) that no row of the wave needs a mask for, four quarters and more before the keys end.  A
-  // multiple is a group of inner tiles of 256-row workgroups; a function of the wave's rows and the keys alone, so every shape of the
-  // workgroup renews at the same keys and rounds the same weights.
-  const int renew_log2 = p.renew_log2;
-  int renew_end = 0;
-  if (RENEW && p.renew >= 1 << renew_log2) {
-    const int j = min(jw, kmask_from >= 0 ? kmask_from / SUB : -1) - (1 << (renew_log2 - 7)) + 1;   // a quarter's last sub-tile must pass both tests
-    const int quarters = j < 0 ? 0 : min(j >> (renew_log2 - 7), ((Sk - 1) >> (renew_log2 - 2)) - 4) + 1;
-    renew_end = __builtin_amdgcn_readfirstlane(max(0, quarters) >> 2 << renew_log2);
-  }
-  auto renew_key = [&](int r) __attribute__((always_inline)) -> int {
-    return max(r, min((r + (1 << renew_log2) - 1) >> renew_log2 << renew_log2, renew_end));
-  };
   int segment_at = RENEW ? p.renew : 0;                                      // key at which the next segment starts
   int renew_at = RENEW && p.renew > 0 ? renew_key(segment_at) : 0x7fffffff;  // the first step that starts here or later renews m_ref
   int segment = -1;         // later segment the wave is in, -1: the first one
+  constexpr bool REF_AHEAD = KNOWN && D == 64;   // read a segment ahead (at D 128 the register for it is one too many)
+  float next_ref = 0.f;
   auto next_segment = [&]() __attribute__((always_inline)) {
-    sum_cap = -1.f;
+    if (!KNOWN) sum_cap = -1.f;
     segment_at += p.renew;
     renew_at = renew_key(segment_at);
     segment++;
@@ -741,6 +775,33 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     constexpr int EPM = 16 / n_mfma;  // softmax elements handled per MFMA slice
     static_assert(16 % n_mfma == 0, "softmax elements must divide evenly over the MFMAs");
     constexpr unsigned v_imm = decltype(v_imm_c)::value, k_imm_next = decltype(k_imm_next_c)::value;
+
+    // Key groups know a segment's reference beforehand: the weights of this sub-tile are taken in it at once (the slow path below would
+    // take them twice, 0.2 us a renewal), and what is summed so far follows behind the stream, whose PV half still adds weights in the old one.
+    float renewed = 1.f;
+    bool renew = false;
+    if constexpr (KNOWN && !FIRST && (!INNER || CHECKED)) {
+      if (__builtin_expect(kstart >= renew_at, 0)) {
+        next_segment();
+        if (segment < n_ref) {   // (else no row of the wave sees the segment)
+          renew = true;
+          const float* const at = reinterpret_cast<const float*>(lds + Lds<D, R, G>::refs) + segment * BM + rg * 32 + ql;
+          const float seg_ref = REF_AHEAD ? next_ref : *at;
+          if (REF_AHEAD) next_ref = at[segment + 1 < n_ref ? BM : 0];
+          // down as well, while the sum stays below 2^40 in the new units, as below; not where the row sees none of the keys
+          const float lowered = half_swap_max(l_run) * __builtin_amdgcn_exp2f((m_ref - seg_ref) * c2);
+          const bool take = seg_ref > m_ref || (seg_ref > -INFINITY && lowered <= 0x1p40f);
+          const float m_new = take ? seg_ref : m_ref;
+          renewed = m_new == m_ref ? 1.f : __builtin_amdgcn_exp2f((m_ref - m_new) * c2);
+          l_run *= renewed;
+          m_ref = m_new;
+          if (m_ref > -INFINITY) {
+            mc = m_ref * c2;
+            sum_cap = kSumCap;
+          }
+        }
+      }
+    }
 
     if (!INNER && kstart > kmask_from) {  // some key of the sub-tile is past Sk or above this wave's first diagonal
       int limit = Sk - 1;
@@ -809,20 +870,21 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
 #pragma unroll
     for (int h = 0; h < 2; h++) p_out[h] = __builtin_bit_cast(bf16x8, u32x4{pw[4 * h], pw[4 * h + 1], pw[4 * h + 2], pw[4 * h + 3]});
     float psum = ps0 + ps1;
+    if (KNOWN && renew) {
+#pragma unroll
+      for (int db = 0; db < DB; db++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) o_acc[db][i] *= renewed;
+    }
     float cap = sum_cap;
-    if (CHECKED) cap = kstart >= renew_at ? -1.f : sum_cap;
+    if (CHECKED && !KNOWN) cap = kstart >= renew_at ? -1.f : sum_cap;
 
     if (__builtin_expect(__any(!(psum <= cap)), 0)) {   // sum_cap < 0 while m_ref is -inf, so that case is included
-      while (CHECKED && kstart >= renew_at) next_segment();   // (once, the keys lie as far apart as a wave's sub-tiles; as an if it spills 31 SGPRs in shape 2 x 2 at D 64)
+      while (CHECKED && !KNOWN && kstart >= renew_at) next_segment();   // (once, the keys lie as far apart as a wave's sub-tiles; as an if it spills 31 SGPRs in shape 2 x 2 at D 64)
       float tmax = s_in[0];
 #pragma unroll
       for (int i = 1; i < 16; i++) tmax = fmaxf(tmax, s_in[i]);
       tmax = half_swap_max(tmax);
-      // The segment's reference, unless this sub-tile lies beyond the fast path's range.
-      if (G > 1 && RENEW && segment >= 0 && sum_cap < 0.f) {
-        const float seg_ref = *reinterpret_cast<const float*>(lds + Lds<D, R, G>::refs + (min(segment, kMaxRefs - 1) * BM + rg * 32 + ql) * 4);
-        if (tmax > -INFINITY && seg_ref > -INFINITY && (tmax - seg_ref) * c2 <= 64.f) tmax = seg_ref;   // (no key visible: perhaps never written)
-      }
       float m_new = fmaxf(m_ref, tmax);
       // Renewed: down as well, while what the row has summed so far stays below 2^40 in the new units (else weights of
       // this sub-tile do not count beside it).  Both halves of a row decide alike.
@@ -879,6 +941,12 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   // group raises its own).  Those of later segments are found here, each by one key group, from K rows
   // that go straight into registers (K is the A operand as it lies in memory).
   auto masked_max = [&](const f32x16& s, int kstart) __attribute__((always_inline)) -> float {
+    if (kstart <= kmask_from) {   // every row sees all of it
+      float t = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; i++) t = fmaxf(t, s[i]);
+      return half_swap_max(t);
+    }
     int limit = Sk - 1;
     if (causal) limit = min(limit, lane_pos + causal_off);
     float t = -INFINITY;
@@ -902,37 +970,28 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     }
   }
 
-  if constexpr (G > 1 && RENEW) {
-    if (p.renew > 0) {   // at most kMaxRefs of them, see choose_shape
-      auto load = [&](int s, bf16x8 (&kf)[KS]) __attribute__((always_inline)) {
-        const __bf16* kp = kg + (int64_t)min(renew_key((s + 1) * p.renew) + ql, Sk - 1) * p.k_ss + 8 * hf;
+  if constexpr (KNOWN) {
+    auto find = [&](int s, const bf16x8 (&kf)[KS]) __attribute__((always_inline)) {
+      f32x16 sr;
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) kf[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks);
-      };
-      auto find = [&](int s, const bf16x8 (&kf)[KS]) __attribute__((always_inline)) {
-        f32x16 sr;
+      for (int i = 0; i < 16; i++) sr[i] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; i++) sr[i] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) sr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sr, 0, 0, 0);
-        const float t = masked_max(sr, renew_key((s + 1) * p.renew));
-        if (hf == 0) *reinterpret_cast<float*>(lds + Lds<D, R, G>::refs + (s * BM + rg * 32 + ql) * 4) = t;
-      };
-      // two at a time: a wait for rows of K costs more than the rest
-      const int n_ref = wave_kv_end > 0 ? (wave_kv_end - 1) / p.renew : 0;
-      for (int s = kgrp; s < n_ref; s += 2 * G) {
-        bf16x8 ka[KS], kb[KS];
-        load(s, ka);
-        load(s + G, kb);   // (past the last: its row is clamped, its result not kept)
-        find(s, ka);
-        if (s + G < n_ref) find(s + G, kb);
-      }
+      for (int ks = 0; ks < KS; ks++) sr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sr, 0, 0, 0);
+      const float t = masked_max(sr, renew_key((s + 1) * p.renew));
+      if (hf == 0) *reinterpret_cast<float*>(lds + Lds<D, R, G>::refs + (s * BM + rg * 32 + ql) * 4) = t;
+    };
+    for (int s = kgrp; s < n_ref; s += 2 * G) {   // (rows past the last reference are clamped, what they give is not kept)
+      find(s, ref_a);
+      if (s + 2 * G < n_ref) load_ref(s + 2 * G, ref_a);
+      if (s + G < n_ref) find(s + G, ref_b);
+      if (s + 3 * G < n_ref) load_ref(s + 3 * G, ref_b);
     }
   }
 
   if (LATE > 0 && last_tile >= 3 && !straight) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
   else __builtin_amdgcn_s_waitcnt(0);
   wg_barrier();  // B_0
+  if (REF_AHEAD && n_ref > 0) next_ref = *reinterpret_cast<const float*>(lds + Lds<D, R, G>::refs + (rg * 32 + ql) * 4);
 
   // Ring protocol.  Step j = NSW*u + kt is the wave's step kt in tile u; it reads the V operands of
   // its sub-tile j-1 and the K operands of its sub-tile j+2.  Barrier B_u sits in front of step NSW*u.
@@ -961,7 +1020,7 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
     const int j = NSW * u + kt;
     const int kstart = G == 1 ? j * SUB : (j * G + kgrp) * SUB;
     if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
-      if (RENEW && !INNER && __builtin_expect(kstart >= renew_at, 0)) next_segment();
+      if (RENEW && !KNOWN && !INNER && __builtin_expect(kstart >= renew_at, 0)) next_segment();
       if (even) step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sA, sB, pB, pA, inner_c);
       else step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sB, sA, pA, pB, inner_c);
     }
@@ -1243,10 +1302,19 @@ __global__ void __launch_bounds__(64 * R * G, D == 64 && R == 4 && G == 1 ? 3 : 
   if constexpr (IN_LANES) chunk_update(done, true);
 }
 
+constexpr int waves_per_simd(int D, int R, int G) { return D == 64 && R == 4 && G == 1 ? 3 : 2; }   // at least
+template <int D, int EPI, int FORM, int R, int G>
+__global__ void __launch_bounds__(64 * R * G, waves_per_simd(D, R, G)) block_attn_kernel(const AttnParams p) { attend<D, EPI, FORM, R, G>(p); }
+template <int D, int EPI, int FORM, int R, int G>
+__global__ void __launch_bounds__(64 * R * G, waves_per_simd(D, R, G)) segments_attn_kernel(const AttnParams p) { attend<D, EPI, FORM, R, G>(p); }
+
 template <int D, int EPI, int FORM, int R, int G>
 hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
   constexpr int lds_bytes = Lds<D, R, G>::bytes(FORM);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget of one CU exceeded");
+  void (*kernel)(const AttnParams);
+  if constexpr (in_segments(FORM)) kernel = segments_attn_kernel<D, EPI, FORM, R, G>;
+  else kernel = block_attn_kernel<D, EPI, FORM, R, G>;
   // Raising the dynamic-LDS limit is a per-function, per-device setting: done once for each
   // device this process launches on (the flags are atomics, a repeated set is harmless).
   constexpr int kMaxDevices = 64;
@@ -1255,12 +1323,11 @@ hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices || !attr_set[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&block_attn_kernel<D, EPI, FORM, R, G>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < kMaxDevices) attr_set[dev].store(true, std::memory_order_release);
   }
-  return launch_kernel(block_attn_kernel<D, EPI, FORM, R, G>, grid, dim3(64 * R * G), lds_bytes, stream, p);
+  return launch_kernel(kernel, grid, dim3(64 * R * G), lds_bytes, stream, p);
 }
 
 template <int D, int FORM, int R, int G>
@@ -1276,8 +1343,13 @@ hipError_t launch_epilogue(const AttnParams& p, int epilogue, dim3 grid, hipStre
 
 template <int D, int R, int G>
 hipError_t launch_attn_shape(const AttnParams& p, int epilogue, dim3 grid, hipStream_t stream) {
-  if (p.n_parts > 0) return launch_epilogue<D, kPart, R, G>(p, epilogue, grid, stream);
   if (p.n_chunks > 0) return launch_epilogue<D, kChunks, R, G>(p, epilogue, grid, stream);
+  if (p.n_parts > 0 && p.renew > 0) {   // rings only, whose heads are packed
+    if (epilogue != kEpiF32 || p.n_parts != 1) return hipErrorInvalidValue;
+    return launch_one<D, kEpiF32, kPartSegments, R, G>(p, grid, stream);
+  }
+  if (p.n_parts > 0) return launch_epilogue<D, kPart, R, G>(p, epilogue, grid, stream);
+  if (p.renew > 0) return launch_epilogue<D, kSegments, R, G>(p, epilogue, grid, stream);
   return launch_epilogue<D, kPlain, R, G>(p, epilogue, grid, stream);
 }
 

@@ -55,7 +55,7 @@ struct AttnParams {
   int part_rows;  // rows of a scratch slot
   float* part_out;       // [row tile][part][part_rows][D], if n_parts > 1
   float* part_lse;       // [row tile][part][part_rows]
-  Divisor by_members, by_parts, by_hkv, by_qtiles, by_sq, by_part_keys;   // of the sizes of those names; set by launch_block_attn
+  Divisor by_members, by_parts, by_hkv, by_qtiles, by_sq, by_part_keys, by_renew;   // of the sizes of those names; set by launch_block_attn
 };
 
 // Arguments of the merge kernel.
