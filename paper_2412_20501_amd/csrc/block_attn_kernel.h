@@ -200,7 +200,7 @@ struct Lds {
   static constexpr int w = rings > tiles ? rings : tiles, mode = w + rows * 4, off = mode + rows * 4;
   static constexpr int sums = off + rows * 8, refs = sums + (G > 1 ? G * rows * 8 : 0);
   static constexpr int tables(int form) {
-    return G > 1 ? (form == kChunks ? refs : refs + kMaxRefs * rows * 4) : form == kPart ? sums : off;
+    return G > 1 ? (in_segments(form) ? refs + kMaxRefs * rows * 4 : refs) : form == kPart || form == kPartSegments ? sums : off;
   }
   static constexpr int query = D == 128 && G == 1 ? R * 2048 : 0;   // a quarter of the Query rows, behind the tables (see the prologue)
   static constexpr int bytes(int form) { return tables(form) + query; }
@@ -336,6 +336,8 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   constexpr int KA = NSW == 1 ? 4 : 3, VA = NS - 2;   // K and V tile issued in tile u: u + KA, u + VA
   static_assert(NSUB % G == 0 && (NSW * NS) % 2 == 0, "the S / P register sets alternate with the step parity");
   static_assert(IPW >= 1, "tile too small for the workgroup");
+  static_assert((!PART || Lds<D, R, G>::tables(FORM) >= Lds<D, R, G>::sums) && (!in_segments(FORM) || G == 1 || Lds<D, R, G>::tables(FORM) > Lds<D, R, G>::refs),
+                "the row offsets and the references lie in the LDS that is asked for");
 
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // K ring | V ring
 

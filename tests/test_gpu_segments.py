@@ -41,3 +41,24 @@ def test_references_of_later_segments(lib, H, seg, n, D, std, causal):
     # weights rounded to bf16: at most 2^-8 of the largest value, where one key has all the weight; lse from fp32 scores and sums
     assert float((out - want).abs().max()) <= 2 ** -8 * float(v.abs().max()) * 1.02 + 1e-4
     assert float((lse - torch.logsumexp(s, -1)).abs().max()) <= 1e-5 * max(1.0, float(s[torch.isfinite(s)].abs().max()) / 8)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_packed_heads(lib, D, causal):
+    """Rings whose query heads share a row space (fewer rounds of workgroups): Query rows of two heads in one workgroup, references renewed."""
+    B, Hq, Hkv, seg, n = 300, 4, 2, 40, 3
+    S, scale = seg * n, D ** -0.5
+    assert attn_shape(lib, RING, B, Hq, Hkv, S, S, D, 0 if causal else None, n)[1] == 1
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v = (torch.randn((B, h, S, D), device="cuda", generator=gen).bfloat16() for h in (Hq, Hkv, Hkv))
+    out, lse = torch.full((B, Hq, S, D), float("nan"), device="cuda"), torch.full((B, Hq, S), float("nan"), device="cuda")
+    lib.tr_ring_attn(q, k, v, n, causal, out, lse)
+    torch.cuda.synchronize()
+    kk, vv = (x.double().repeat_interleave(Hq // Hkv, 1) for x in (k, v))
+    s = (q.double() * scale) @ kk.transpose(-1, -2).contiguous()
+    if causal:
+        s.masked_fill_(torch.ones((S, S), dtype=torch.bool, device="cuda").triu(1), float("-inf"))
+    want = torch.softmax(s, -1) @ vv
+    assert float((out - want).abs().max()) <= 2 ** -8 * float(v.abs().max()) * 1.02 + 1e-4
+    assert float((lse - torch.logsumexp(s, -1)).abs().max()) <= 1e-5
