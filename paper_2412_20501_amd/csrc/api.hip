@@ -157,8 +157,9 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
   const int64_t rows = pack ? (int64_t)p.gq * p.Sq : p.Sq, heads = (int64_t)p.B * (pack ? p.Hkv : p.Hq);
   if (p.Sk == 0) return tr::kShape8x1;
   struct Cost { double fix, idle, busy, two, three, fix_few, few, block; };   // block: of a later block of the chunk form, in units of fix
-  static const Cost costs[2][4] = {{{7.5, 1.52, 2.03, 0, 0, 5.2, 1.0, 1.7}, {6.5, 1.0, 1.12, 2.03, 2.96, 5.6, 0.95, 1.3},
-                                    {7.1, 0.83, 1.09, 0, 0, 6.0, 0.65, 0.75}, {5.8, 0.61, 0.72, 0, 0, 5.4, 0.6, 0.75}},
+  static const Cost costs[2][5] = {{{7.5, 1.52, 2.03, 0, 0, 5.2, 1.0, 1.7}, {6.5, 1.0, 1.12, 2.03, 2.96, 5.6, 0.95, 1.3},
+                                    {7.1, 0.83, 1.09, 0, 0, 6.0, 0.65, 0.75}, {5.8, 0.61, 0.72, 0, 0, 5.4, 0.6, 0.75},
+                                    {6.0, 0.62, 0.75, 1.15, 1.72, 5.6, 0.62, 0.75}},
                                    {{8.3, 1.1, 1.67, 0, 0, 6.2, 0.7, 1.7}, {8.5, 0.7, 0.95, 1.78, 0, 6.8, 0.65, 1.3},
                                     {9.0, 0.59, 0.93, 0, 0, 7.5, 0.5, 0.75}, {7.0, 0.47, 0.57, 0, 0, 6.5, 0.45, 0.75}}};
   const double tile_keys = D == 64 ? 128.0 : 64.0;
@@ -166,15 +167,22 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
   const double later = p.n_chunks > 1 ? p.n_chunks - 1 : 0;   // blocks behind its first of the longest workgroup
   const double blocks = p.causal ? later / 2 : later, chunks = later + 1;   // later blocks of the average workgroup
   const double memory = (double)(heads * rows) * chunks * D * (2 + (p.n_parts > 1 ? 4 : out_bytes)) / 5.2e6;   // Query rows in, result out
+  const bool trio = D == 64 && p.n_parts == 0 && p.n_chunks == 0;   // the forms that it has
   int best = tr::kShape8x1;
   double t_best = 0;
-  for (int shape = 0; shape < 4; shape++) {
+  for (int shape = 0; shape < (trio ? 5 : 4); shape++) {
     const Cost& c = costs[D == 128][shape];
-    const int bm = tr::shape_rows(shape), per_cu = shape != tr::kShape4x1 ? 1 : D == 64 ? 3 : 2;
+    const int bm = tr::shape_rows(shape), per_cu = shape == tr::kShapeTrio ? 3 : shape != tr::kShape4x1 ? 1 : D == 64 ? 3 : 2;
     const bool groups = shape >= tr::kShape4x2;
     const int64_t tiles = (rows + bm - 1) / bm;
     if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
-    if (groups && (refs > tr::kMaxRefs || heads * tiles >= 8 * kCUs)) continue;
+    if (groups && (refs > (shape == tr::kShapeTrio ? tr::kMaxRefsTrio : tr::kMaxRefs) || heads * tiles >= 8 * kCUs)) continue;
+    // Trio: where all its workgroups run at once and a compute unit holds two or three, that is one to one and a half of 128 rows, which leave units
+    // uneven.  us, the best of the other shapes / trio: 24 heads of 1777 under the causal rule 18.8 / 17.4, 32 of 1024 13.1 / 11.0, 16 of 2048 in 4 segments 23.0 / 17.9,
+    // 8 of 4096 35.7 / 28.1; 128 heads of 300 rows on 3000 keys without a mask 45.2 / 43.2, on 300 9.8 / 10.0, 24 of 1777 29.0 / 28.8,
+    // 48 of 1000 20.2 / 20.4; beyond it 64 of 1024, causal, 15.7 / 17.5, 12 of 4096 35.6 / 37.3.  From 8192 keys on, where six heads at most are left, the other
+    // shapes stay (4 of 9000 67.5 / 58.2, so not the faster side: a test of rings counts on 4 x 2 at 4 heads of 8192).
+    if (shape == tr::kShapeTrio && (heads * tiles < 2 * kCUs || heads * tiles > 3 * kCUs || p.Sk >= 8192)) continue;
     if (groups && p.renew > 0 && p.renew < 64) continue;   // renewals lie as far apart as a group's sub-tiles
     int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
     if (p.causal && pack) {
@@ -203,7 +211,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
       const double at_once = std::min<double>(per_cu, rounds), tile = at_once == 3 ? c.three : c.two;
       time = total * tile / (kCUs * at_once);
       if (!p.causal && rounds <= per_cu) time = longest * tile * (0.85 + 0.15 * n / (kCUs * rounds));   // all at once: as slow as the fullest compute unit
-      if (p.causal || later > 0) time += 0.15 * longest * tile;
+      if (p.causal || later > 0) time += (shape == tr::kShapeTrio ? 0.05 : 0.15) * longest * tile;   // (half the rows: it ends more evenly)
       time = std::max(time, memory) + fix + 0.35 * blocks * fix * n / (kCUs * at_once);
       time = std::max(time, longest * alone + fix * (1 + c.block * later));
     } else {
@@ -219,7 +227,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
     if (shape == tr::kShape8x1) {
       t_best = time * (n > kCUs ? 0.95 : 0.97);   // a last round that is nearly empty runs faster than a full one
     } else {   // over several rounds the estimates lie closer together than their errors, unless there are many
-      time *= n > 8 * kCUs ? 0.97 : n > kCUs * per_cu ? 1.03 : 1.0;
+      time *= shape == tr::kShapeTrio ? (p.causal ? 1.0 : 1.13) : n > 8 * kCUs ? 0.97 : n > kCUs * per_cu ? 1.03 : 1.0;
       if (time < t_best) {
         t_best = time;
         best = shape;

@@ -112,6 +112,9 @@ hipError_t launch_fold(const AttnParams& p, int epilogue, hipStream_t stream, hi
 template <int D>
 hipError_t launch_attn(const AttnParams& p, int epilogue, dim3 grid, hipStream_t stream) {
   switch (p.shape) {
+    case kShapeTrio:
+      if (D != 64) return hipErrorInvalidValue;
+      [[fallthrough]];
     case kShape2x2: return launch_attn_shape<D, 2, 2>(p, epilogue, grid, stream);
     case kShape4x2: return launch_attn_shape<D, 4, 2>(p, epilogue, grid, stream);
     case kShape4x1: return launch_attn_shape<D, 4, 1>(p, epilogue, grid, stream);

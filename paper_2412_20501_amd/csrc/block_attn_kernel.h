@@ -61,10 +61,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Keys per LDS tile: 16 KiB of K (and of V) either way, so a tile is 2 sub-tiles of 32 keys at
 // D = 128 and 4 at D = 64, where a sub-tile carries half the MFMA work per barrier otherwise.  Shape 4 x 1: half of that, so
 // that two (D = 64, with rings of three: three) workgroups share a compute unit.
-template <int D, int R, int G>
-constexpr int tile_keys() { return (D == 64 ? 128 : 64) / (R == 4 && G == 1 ? 2 : 1); }
-template <int D, int R, int G>
-constexpr int ring_depth() { return D == 64 && R == 4 && G == 1 ? 3 : 4; }   // LDS ring depth (tiles) of K and of V
+// Ring depth (tiles) NS of K and of V: three where three workgroups are to share a compute unit.
+constexpr int ring_depth(int D, int R, int G) { return D == 64 && R == 4 && G == 1 ? 3 : 4; }
+template <int D, int R, int G, int NS>
+constexpr int tile_keys() { return (D == 64 ? 128 : 64) / ((R == 4 && G == 1) || NS == 3 ? 2 : 1); }
 constexpr int kEpiBf16 = 0, kEpiF32 = 1, kEpiMerge = 2;
 constexpr int kPlain = 0, kPart = 1, kChunks = 2, kSegments = 3, kPartSegments = 4;   // forms of the kernel, see there
 constexpr bool in_segments(int form) { return form == kSegments || form == kPartSegments; }
@@ -194,13 +194,14 @@ __device__ __forceinline__ int live_parts(const AttnParams& p, int pos_last) {
 // LDS behind the K/V rings and, once these are dead, behind the waves' transposed 32 x D fp32 tiles (byte offsets
 // from the start): Update weight and case of each row, the rows' output offsets (partitioned form), exponent reference
 // and sum of each wave's rows and the references of later segments (more than one key group).
-template <int D, int R, int G>
+template <int D, int R, int G, int NS = ring_depth(D, R, G)>
 struct Lds {
-  static constexpr int rings = 2 * ring_depth<D, R, G>() * tile_keys<D, R, G>() * 2 * D, tiles = R * G * 32 * 4 * D, rows = R * 32;
+  static constexpr int rings = 2 * NS * tile_keys<D, R, G, NS>() * 2 * D, tiles = R * G * 32 * 4 * D, rows = R * 32;
   static constexpr int w = rings > tiles ? rings : tiles, mode = w + rows * 4, off = mode + rows * 4;
   static constexpr int sums = off + rows * 8, refs = sums + (G > 1 ? G * rows * 8 : 0);
+  static constexpr int max_refs = G > 1 && NS == 3 ? kMaxRefsTrio : kMaxRefs;
   static constexpr int tables(int form) {
-    return G > 1 ? (in_segments(form) ? refs + kMaxRefs * rows * 4 : refs) : form == kPart || form == kPartSegments ? sums : off;
+    return G > 1 ? (in_segments(form) ? refs + max_refs * rows * 4 : refs) : form == kPart || form == kPartSegments ? sums : off;
   }
   static constexpr int query = D == 128 && G == 1 ? R * 2048 : 0;   // a quarter of the Query rows, behind the tables (see the prologue)
   static constexpr int bytes(int form) { return tables(form) + query; }
@@ -316,7 +317,7 @@ __device__ __forceinline__ void part_epilogue(const AttnParams& p, char* lds, in
 // every p.renew keys (rings of several segments, and block steps that round as their parts would).  Kernels of their own: the tests for a renewal and the
 // bodies of inner tiles that hold one are a quarter of the code, and a short call runs through most of the code once, from a cold instruction cache
 // (8 heads of 512 rows on as many keys 9.42 -> 9.29 us without them, 16 at D 64 7.42 -> 7.31).
-template <int D, int EPI, int FORM, int R, int G>
+template <int D, int EPI, int FORM, int R, int G, int NS = ring_depth(D, R, G)>
 __device__ __forceinline__ void attend(const AttnParams& p) {
   constexpr bool PART = FORM == kPart || FORM == kPartSegments, CHUNKS = FORM == kChunks;
   constexpr int W = R * G, BM = 32 * R;    // waves, Query rows of a workgroup
@@ -325,18 +326,20 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   constexpr int KS = D / 16;               // MFMA k-steps over the head dim
   constexpr int DB = D / 32;               // 32-wide d blocks of the output
   constexpr int CPR = D / 8;               // 16-byte chunks per row
-  constexpr int BN = tile_keys<D, R, G>();       // keys per LDS tile
+  typedef Lds<D, R, G, NS> L;
+  constexpr int BN = tile_keys<D, R, G, NS>();   // keys per LDS tile
   constexpr int TILE_BYTES = BN * RB;
   constexpr int RPI = 1024 / RB;           // tile rows one wave-wide 16-byte load instruction covers
   constexpr int IPW = BN / RPI / W;        // load instructions per wave, tile and tensor
-  constexpr int NS = ring_depth<D, R, G>();                // ring depth of the K and of the V tiles
   constexpr int SUB = 32;                  // keys per sub-tile (one MFMA row block)
   constexpr int NSUB = BN / SUB;           // sub-tiles per tile
   constexpr int NSW = NSUB / G;            // sub-tiles of one key group (= steps of a wave) per tile
   constexpr int KA = NSW == 1 ? 4 : 3, VA = NS - 2;   // K and V tile issued in tile u: u + KA, u + VA
-  static_assert(NSUB % G == 0 && (NSW * NS) % 2 == 0, "the S / P register sets alternate with the step parity");
+  constexpr bool TRIO = G > 1 && NS == 3;
+  constexpr int NG = NSW * NS % 2 ? 2 * NS : NS;      // tiles after which ring slots and register sets come round
+  static_assert(NSUB % G == 0 && (NSW * NG) % 2 == 0, "the S / P register sets alternate with the step parity");
   static_assert(IPW >= 1, "tile too small for the workgroup");
-  static_assert((!PART || Lds<D, R, G>::tables(FORM) >= Lds<D, R, G>::sums) && (!in_segments(FORM) || G == 1 || Lds<D, R, G>::tables(FORM) > Lds<D, R, G>::refs),
+  static_assert((!PART || L::tables(FORM) >= L::sums) && (!in_segments(FORM) || G == 1 || L::tables(FORM) > L::refs),
                 "the row offsets and the references lie in the LDS that is asked for");
 
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // K ring | V ring
@@ -545,15 +548,15 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   // only, so no barrier is needed; what the slots are for is loaded behind it.
   constexpr int QP = 32 * RB / 1024, Q_SLOTS = (QP + IPW - 1) / IPW;   // instructions, ring slots
   static_assert(Q_SLOTS <= 4 && (Q_SLOTS <= NS - VA || NS == 4), "Query rows fit into slots that are filled last");
-  constexpr bool APART = Lds<D, R, G>::query > 0;   // the last slot's pieces lie behind the tables; the third slot is K_3's of 256-row workgroups
-  static_assert(!APART || (Q_SLOTS == 4 && IPW == 2 && Lds<D, R, G>::tables(FORM) % 1024 == 0), "two pieces of every wave lie apart");
+  constexpr bool APART = L::query > 0;   // the last slot's pieces lie behind the tables; the third slot is K_3's of 256-row workgroups
+  static_assert(!APART || (Q_SLOTS == 4 && IPW == 2 && L::tables(FORM) % 1024 == 0), "two pieces of every wave lie apart");
   constexpr bool V1_LATE = VA == 2 && (APART ? KA == 4 : Q_SLOTS >= 3), K3_LATE = KA == 4 && Q_SLOTS == 4 && !APART;
-  constexpr int AHEAD = IPW * ((KA == 4 && !K3_LATE ? 3 : 2) + (VA == 2 && !V1_LATE ? 2 : 1)), LATE = IPW * ((V1_LATE ? 1 : 0) + (K3_LATE ? 1 : 0));
+  constexpr int AHEAD = IPW * ((KA == 4 && !K3_LATE && !TRIO ? 3 : 2) + (VA == 2 && !V1_LATE ? 2 : 1)), LATE = IPW * ((V1_LATE ? 1 : 0) + (K3_LATE ? 1 : 0));
   auto q_slot = [&](int piece) __attribute__((always_inline)) -> int {   // LDS offset of a piece (RPI rows)
     const int s = piece / IPW;
     if (APART) {
       const int slot = s == 2 && KA == 3 ? NS - 1 : 2 * NS - 1 - s;
-      return (s == 3 ? Lds<D, R, G>::tables(FORM) : slot * TILE_BYTES) + (wave * IPW + piece % IPW) * 1024;
+      return (s == 3 ? L::tables(FORM) : slot * TILE_BYTES) + (wave * IPW + piece % IPW) * 1024;
     }
     return (2 * NS - 1 - s - (s == 3 ? 1 : 0)) * TILE_BYTES + (wave * IPW + piece % IPW) * 1024;
   };
@@ -643,7 +646,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
     issue_k(1);
     if (VA == 2 && !V1_LATE) issue_v(1);
     issue_k(2);
-    if (KA == 4 && !K3_LATE) issue_k(3);
+    if (KA == 4 && !K3_LATE && !TRIO) issue_k(3);
   }
   // (A wave without rows loads none, and what it then reads takes part in nothing: with clamped rows loaded all the same 32 rows x 16 heads on 32 keys take
   // 5.57 us, 5.16 without, 64 rows x 4 heads on 64 keys at D 64 4.58 and 4.34.  In front of the other tiles
@@ -714,7 +717,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   int segment_at = RENEW ? p.renew : 0;                                      // key at which the next segment starts
   int renew_at = RENEW && p.renew > 0 ? renew_key(segment_at) : 0x7fffffff;  // the first step that starts here or later renews m_ref
   int segment = -1;         // later segment the wave is in, -1: the first one
-  constexpr bool REF_AHEAD = KNOWN && D == 64;   // read a segment ahead (at D 128 the register for it is one too many)
+  constexpr bool REF_AHEAD = KNOWN && D == 64 && !TRIO;   // read a segment ahead (at D 128 the register for it is one too many)
   float next_ref = 0.f;
   auto next_segment = [&]() __attribute__((always_inline)) {
     if (!KNOWN) sum_cap = -1.f;
@@ -787,7 +790,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
         next_segment();
         if (segment < n_ref) {   // (else no row of the wave sees the segment)
           renew = true;
-          const float* const at = reinterpret_cast<const float*>(lds + Lds<D, R, G>::refs) + segment * BM + rg * 32 + ql;
+          const float* const at = reinterpret_cast<const float*>(lds + L::refs) + segment * BM + rg * 32 + ql;
           const float seg_ref = REF_AHEAD ? next_ref : *at;
           if (REF_AHEAD) next_ref = at[segment + 1 < n_ref ? BM : 0];
           // down as well, while the sum stays below 2^40 in the new units, as below; not where the row sees none of the keys
@@ -980,7 +983,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) sr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sr, 0, 0, 0);
       const float t = masked_max(sr, renew_key((s + 1) * p.renew));
-      if (hf == 0) *reinterpret_cast<float*>(lds + Lds<D, R, G>::refs + (s * BM + rg * 32 + ql) * 4) = t;
+      if (hf == 0) *reinterpret_cast<float*>(lds + L::refs + (s * BM + rg * 32 + ql) * 4) = t;
     };
     for (int s = kgrp; s < n_ref; s += 2 * G) {   // (rows past the last reference are clamped, what they give is not kept)
       find(s, ref_a);
@@ -993,7 +996,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   if (LATE > 0 && last_tile >= 3 && !straight) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
   else __builtin_amdgcn_s_waitcnt(0);
   wg_barrier();  // B_0
-  if (REF_AHEAD && n_ref > 0) next_ref = *reinterpret_cast<const float*>(lds + Lds<D, R, G>::refs + (rg * 32 + ql) * 4);
+  if (REF_AHEAD && n_ref > 0) next_ref = *reinterpret_cast<const float*>(lds + L::refs + (rg * 32 + ql) * 4);
 
   // Ring protocol.  Step j = NSW*u + kt is the wave's step kt in tile u; it reads the V operands of
   // its sub-tile j-1 and the K operands of its sub-tile j+2.  Barrier B_u sits in front of step NSW*u.
@@ -1011,14 +1014,14 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   f32x16 sA, sB;
   bf16x8 pA[2], pB[2];
   constexpr unsigned SUBB = SUB * RB;  // bytes of one sub-tile inside a tile
-  // Step NSW*u + kt of the tile in ring slot `su` (previous tile in sp).
-  auto tile_step = [&](int u, auto su_c, auto kt_c, auto inner_c) __attribute__((always_inline)) {
-    constexpr int su = decltype(su_c)::value, kt = decltype(kt_c)::value;
+  // Step NSW*u + kt of the tile in ring slot su (previous tile in sp); at_c = u % NG.
+  auto tile_step = [&](int u, auto at_c, auto kt_c, auto inner_c) __attribute__((always_inline)) {
+    constexpr int at = decltype(at_c)::value, su = at % NS, kt = decltype(kt_c)::value;
     constexpr bool INNER = decltype(inner_c)::value != 0;   // the step certainly runs and needs no mask
     constexpr int sp = (su + NS - 1) % NS;
     constexpr unsigned v_imm = kt == 0 ? sp * TILE_BYTES + (NSW - 1) * G * SUBB : su * TILE_BYTES + (kt - 1) * G * SUBB;
     constexpr unsigned k_imm = (su + (kt + 2) / NSW) % NS * TILE_BYTES + (kt + 2) % NSW * G * SUBB;
-    constexpr bool even = (NSW * su + kt) % 2 == 0;   // the ring holds an even number of a wave's steps
+    constexpr bool even = (NSW * at + kt) % 2 == 0;
     const int j = NSW * u + kt;
     const int kstart = G == 1 ? j * SUB : (j * G + kgrp) * SUB;
     if (INNER || j <= (kt == 0 ? jw_first : jw_in)) {
@@ -1029,7 +1032,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   };
   if (n_tiles > 0) {
     if (KA == 3 && NS == 4) issue_k(3 % NS);
-    issue_v(VA % NS);
+    if (!TRIO) issue_v(VA % NS);
     if (jw > 0) {
       // S_0 = K_0[0:32] Q^T, plain (nothing to overlap with yet); operands of step 0 (the wave's sub-tile 1)
 #pragma unroll
@@ -1051,6 +1054,18 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
       }
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) pre[ks] = load_k(ks, 1 % NSW * G * SUBB + 1 / NSW * TILE_BYTES);
+    }
+    if constexpr (TRIO) {   // K_3 and K_4 go where K_0 and K_1 lay, which every wave has read
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(pre[ks]));
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+      wg_barrier();
+      issue_k(0);
+      issue_v(1);
+      issue_k(1);
+    }
+    if (jw > 0) {
       // step 0: S_1 alongside the softmax of sub-tile 0 (no PV yet); prefetch the K operands of sub-tile 2
       constexpr unsigned k_imm0 = 2 % NSW * G * SUBB + 2 / NSW * TILE_BYTES;
       step(kgrp * SUB, IC<1>{}, IC<0>{}, IC<(int)k_imm0>{}, sA, sB, pB, pA, IC<0>{});
@@ -1064,15 +1079,15 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   }
   // tiles u = 1 .. n_tiles: steps NSW*u .. NSW*u + NSW-1 (the last tile index only has its first
   // step, which folds in the PV product of the final sub-tile; its softmax sees only masked keys)
-  auto tile_body = [&](int u, auto slot_c, auto inner_c, auto second_c) __attribute__((always_inline)) {   // slot_c = u % NS; second_c: u = 1
-    constexpr int su = decltype(slot_c)::value;
+  auto tile_body = [&](int u, auto slot_c, auto inner_c, auto second_c) __attribute__((always_inline)) {   // slot_c = u % NG; second_c: u = 1
+    constexpr int su = decltype(slot_c)::value % NS;
     constexpr bool INNER = decltype(inner_c)::value != 0;
     // vmcnt; of a ring of three also lgkmcnt(0): the slot that is filled behind the barrier was read in the step before it
     constexpr int none = NS == 3 ? 0x0070 : 0x0F70;
-    if (INNER || (u + KA - 1 <= last_tile && !(NS == 3 && decltype(second_c)::value))) __builtin_amdgcn_s_waitcnt(none | (NS == 3 ? IPW : 2 * IPW));
+    if (INNER || (u + KA - 1 <= last_tile && !(NS == 3 && !TRIO && decltype(second_c)::value))) __builtin_amdgcn_s_waitcnt(none | (NS == 3 && !TRIO ? IPW : 2 * IPW));
     else __builtin_amdgcn_s_waitcnt(none);           // the tile before issued no K: everything that is on its way
     wg_barrier();                                    // B_u
-    if ((KA == 4 || NS == 3) && decltype(second_c)::value) issue_k(0);   // K_4 of a ring of four, K_3 of a ring of three
+    if ((KA == 4 || NS == 3) && !TRIO && decltype(second_c)::value) issue_k(0);   // K_4 of a ring of four, K_3 of a ring of three
     if (INNER) {   // K_{u+KA}, V_{u+VA}; first what is needed first
       if (NS == 3) issue_v_inner((su + VA) % NS);
       issue_k_inner((su + KA) % NS);
@@ -1099,35 +1114,41 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   int u_inner = j_inner < 0 ? -1 : j_inner / NSUB;
   u_inner = __builtin_amdgcn_readfirstlane(min(u_inner, last_tile - KA - 1));   // loads issued in tile u reach tile u + KA
   if (RENEW && !RENEW_INNER && p.renew > 0) u_inner = min(u_inner, renew_end / BN - 1);   // up to there the reference is renewed where a group starts
-  // tiles 1 .. 3 (tile 0 was the prologue)
-  if (1 <= n_tiles) tile_body(1, IC<1 % NS>{}, IC<0>{}, IC<1>{});
-  if (2 <= n_tiles) tile_body(2, IC<2 % NS>{}, IC<0>{}, IC<0>{});
-  if (NS > 3 && 3 <= n_tiles) tile_body(3, IC<3 % NS>{}, IC<0>{}, IC<0>{});
-  // Groups of NS tiles: first the groups of inner tiles (up to where the reference is renewed, and on from there; see RENEW_INNER), then
+  // tiles 1 .. NG - 1 (tile 0 was the prologue)
+  if (1 <= n_tiles) tile_body(1, IC<1>{}, IC<0>{}, IC<1>{});
+  if (2 <= n_tiles) tile_body(2, IC<2>{}, IC<0>{}, IC<0>{});
+  if (NG > 3 && 3 <= n_tiles) tile_body(3, IC<3 % NG>{}, IC<0>{}, IC<0>{});
+  if (NG > 4 && 4 <= n_tiles) tile_body(4, IC<4 % NG>{}, IC<0>{}, IC<0>{});
+  if (NG > 5 && 5 <= n_tiles) tile_body(5, IC<5 % NG>{}, IC<0>{}, IC<0>{});
+  // Groups of NG tiles: first the groups of inner tiles (up to where the reference is renewed, and on from there; see RENEW_INNER), then
   // general ones to the end.
-  int u0 = NS;
-  while (u0 + NS - 1 <= u_inner) {
-    if (!RENEW_INNER && u0 * BN >= renew_at) next_segment();
-    const int stop = RENEW_INNER ? min(u_inner, (int)((unsigned)renew_at / BN) - 1) : min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NS - 1);
-    for (; u0 + NS - 1 <= stop; u0 += NS) {
-      tile_body(u0, IC<0>{}, IC<1>{}, IC<0>{});
-      tile_body(u0 + 1, IC<1 % NS>{}, IC<1>{}, IC<0>{});
-      tile_body(u0 + 2, IC<2 % NS>{}, IC<1>{}, IC<0>{});
-      if constexpr (NS > 3) tile_body(u0 + 3, IC<3 % NS>{}, IC<1>{}, IC<0>{});
+  auto group = [&](int u, auto inner_c) __attribute__((always_inline)) {
+    tile_body(u, IC<0>{}, inner_c, IC<0>{});
+    tile_body(u + 1, IC<1>{}, inner_c, IC<0>{});
+    tile_body(u + 2, IC<2>{}, inner_c, IC<0>{});
+    if constexpr (NG > 3) tile_body(u + 3, IC<3 % NG>{}, inner_c, IC<0>{});
+    if constexpr (NG > 4) {
+      tile_body(u + 4, IC<4 % NG>{}, inner_c, IC<0>{});
+      tile_body(u + 5, IC<5 % NG>{}, inner_c, IC<0>{});
     }
-    if (RENEW_INNER && u0 + NS - 1 <= u_inner) {
-      tile_body(u0, IC<0>{}, IC<2>{}, IC<0>{});
-      tile_body(u0 + 1, IC<1 % NS>{}, IC<2>{}, IC<0>{});
-      tile_body(u0 + 2, IC<2 % NS>{}, IC<2>{}, IC<0>{});
-      if constexpr (NS > 3) tile_body(u0 + 3, IC<3 % NS>{}, IC<2>{}, IC<0>{});
-      u0 += NS;
+  };
+  int u0 = NG;
+  while (u0 + NG - 1 <= u_inner) {
+    if (!RENEW_INNER && u0 * BN >= renew_at) next_segment();
+    const int stop = RENEW_INNER ? min(u_inner, (int)((unsigned)renew_at / BN) - 1) : min(u_inner, (int)(((unsigned)renew_at - 1) / BN) + NG - 1);
+    for (; u0 + NG - 1 <= stop; u0 += NG) group(u0, IC<1>{});
+    if (RENEW_INNER && u0 + NG - 1 <= u_inner) {
+      group(u0, IC<2>{});
+      u0 += NG;
     }
   }
-  for (; u0 <= n_tiles; u0 += NS) {
+  for (; u0 <= n_tiles; u0 += NG) {
     tile_body(u0, IC<0>{}, IC<0>{}, IC<0>{});
-    if (u0 + 1 <= n_tiles) tile_body(u0 + 1, IC<1 % NS>{}, IC<0>{}, IC<0>{});
-    if (u0 + 2 <= n_tiles) tile_body(u0 + 2, IC<2 % NS>{}, IC<0>{}, IC<0>{});
-    if (NS > 3 && u0 + 3 <= n_tiles) tile_body(u0 + 3, IC<3 % NS>{}, IC<0>{}, IC<0>{});
+    if (u0 + 1 <= n_tiles) tile_body(u0 + 1, IC<1>{}, IC<0>{}, IC<0>{});
+    if (u0 + 2 <= n_tiles) tile_body(u0 + 2, IC<2>{}, IC<0>{}, IC<0>{});
+    if (NG > 3 && u0 + 3 <= n_tiles) tile_body(u0 + 3, IC<3 % NG>{}, IC<0>{}, IC<0>{});
+    if (NG > 4 && u0 + 4 <= n_tiles) tile_body(u0 + 4, IC<4 % NG>{}, IC<0>{}, IC<0>{});
+    if (NG > 5 && u0 + 5 <= n_tiles) tile_body(u0 + 5, IC<5 % NG>{}, IC<0>{}, IC<0>{});
   }
   __builtin_amdgcn_s_waitcnt(0);  // no LDS write of this workgroup may still be in flight at exit
 
@@ -1151,14 +1172,14 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   constexpr int CPRF = D / 4;                 // 16-byte chunks per fp32 row = lanes per row when reading back
   constexpr int RPI_OUT = 64 / CPRF;          // rows one wave-wide access covers
   char* const my = lds + wave * (32 * ROWB);
-  float* const my_w = reinterpret_cast<float*>(lds + Lds<D, R, G>::w) + rg * 32;     // Update weight of each of the row group's rows
-  int* const my_mode = reinterpret_cast<int*>(lds + Lds<D, R, G>::mode) + rg * 32;   // and its case
+  float* const my_w = reinterpret_cast<float*>(lds + L::w) + rg * 32;     // Update weight of each of the row group's rows
+  int* const my_mode = reinterpret_cast<int*>(lds + L::mode) + rg * 32;   // and its case
   float l_tot = half_swap_sum(l_run), m_tot = m_ref, f_own = 1.f;
   if constexpr (G > 1) {
     // The key groups' sums meet: every wave scales its share to the common reference (they differ only where a row's
     // scores left the fast path's range) and the tiles are added as they are read back.
     typedef float f32x2 __attribute__((ext_vector_type(2)));
-    f32x2* const sums = reinterpret_cast<f32x2*>(lds + Lds<D, R, G>::sums);
+    f32x2* const sums = reinterpret_cast<f32x2*>(lds + L::sums);
     if (hf == 0) sums[wave * 32 + ql] = f32x2{m_ref, l_tot};
     __syncthreads();
     f32x2 each[G];
@@ -1304,18 +1325,21 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   if constexpr (IN_LANES) chunk_update(done, true);
 }
 
-constexpr int waves_per_simd(int D, int R, int G) { return D == 64 && R == 4 && G == 1 ? 3 : 2; }   // at least
+constexpr int waves_per_simd(int D, int NS) { return D == 64 && NS == 3 ? 3 : 2; }   // at least
 template <int D, int EPI, int FORM, int R, int G>
-__global__ void __launch_bounds__(64 * R * G, waves_per_simd(D, R, G)) block_attn_kernel(const AttnParams p) { attend<D, EPI, FORM, R, G>(p); }
+__global__ void __launch_bounds__(64 * R * G, waves_per_simd(D, ring_depth(D, R, G))) block_attn_kernel(const AttnParams p) { attend<D, EPI, FORM, R, G>(p); }
 template <int D, int EPI, int FORM, int R, int G>
-__global__ void __launch_bounds__(64 * R * G, waves_per_simd(D, R, G)) segments_attn_kernel(const AttnParams p) { attend<D, EPI, FORM, R, G>(p); }
+__global__ void __launch_bounds__(64 * R * G, waves_per_simd(D, ring_depth(D, R, G))) segments_attn_kernel(const AttnParams p) { attend<D, EPI, FORM, R, G>(p); }
+template <int EPI, int FORM>
+__global__ void __launch_bounds__(64 * 2 * 2, 3) trio_attn_kernel(const AttnParams p) { attend<64, EPI, FORM, 2, 2, 3>(p); }
 
-template <int D, int EPI, int FORM, int R, int G>
+template <int D, int EPI, int FORM, int R, int G, int NS = ring_depth(D, R, G)>
 hipError_t launch_one(const AttnParams& p, dim3 grid, hipStream_t stream) {
-  constexpr int lds_bytes = Lds<D, R, G>::bytes(FORM);
-  static_assert(lds_bytes <= 160 * 1024, "LDS budget of one CU exceeded");
+  constexpr int lds_bytes = Lds<D, R, G, NS>::bytes(FORM);
+  static_assert(lds_bytes <= 160 * 1024 / (D == 64 && NS == 3 ? 3 : 1), "LDS budget exceeded");
   void (*kernel)(const AttnParams);
-  if constexpr (in_segments(FORM)) kernel = segments_attn_kernel<D, EPI, FORM, R, G>;
+  if constexpr (NS != ring_depth(D, R, G)) kernel = trio_attn_kernel<EPI, FORM>;
+  else if constexpr (in_segments(FORM)) kernel = segments_attn_kernel<D, EPI, FORM, R, G>;
   else kernel = block_attn_kernel<D, EPI, FORM, R, G>;
   // Raising the dynamic-LDS limit is a per-function, per-device setting: done once for each
   // device this process launches on (the flags are atomics, a repeated set is harmless).
@@ -1343,8 +1367,21 @@ hipError_t launch_epilogue(const AttnParams& p, int epilogue, dim3 grid, hipStre
 
 }  // namespace
 
+template <int FORM>
+hipError_t launch_trio(const AttnParams& p, int epilogue, dim3 grid, hipStream_t stream) {
+  if (epilogue == kEpiBf16) return launch_one<64, kEpiBf16, FORM, 2, 2, 3>(p, grid, stream);
+  if (epilogue == kEpiF32) return launch_one<64, kEpiF32, FORM, 2, 2, 3>(p, grid, stream);
+  return launch_one<64, kEpiMerge, FORM, 2, 2, 3>(p, grid, stream);
+}
+
 template <int D, int R, int G>
 hipError_t launch_attn_shape(const AttnParams& p, int epilogue, dim3 grid, hipStream_t stream) {
+  if constexpr (D == 64 && R == 2 && G == 2) {
+    if (p.shape == kShapeTrio) {
+      if (p.n_chunks > 0 || p.n_parts > 0) return hipErrorInvalidValue;
+      return p.renew > 0 ? launch_trio<kSegments>(p, epilogue, grid, stream) : launch_trio<kPlain>(p, epilogue, grid, stream);
+    }
+  }
   if (p.n_chunks > 0) return launch_epilogue<D, kChunks, R, G>(p, epilogue, grid, stream);
   if (p.n_parts > 0 && p.renew > 0) {   // rings only, whose heads are packed
     if (epilogue != kEpiF32 || p.n_parts != 1) return hipErrorInvalidValue;

@@ -10,11 +10,12 @@
 namespace tr {
 
 constexpr int kMaxRefs = 32;   // references of later segments that workgroups of fewer than 256 rows keep in LDS
+constexpr int kMaxRefsTrio = 8;   // the same where three of them share a compute unit
 constexpr int kMaxParts = 16;  // parts the keys of one partitioned attention launch are cut into at most
 
 // Shapes of an attention workgroup: row groups of 32 Query rows x key groups.
-constexpr int kShape8x1 = 0, kShape4x1 = 1, kShape4x2 = 2, kShape2x2 = 3;
-constexpr int shape_rows(int shape) { return shape == kShape8x1 ? 256 : shape == kShape2x2 ? 64 : 128; }
+constexpr int kShape8x1 = 0, kShape4x1 = 1, kShape4x2 = 2, kShape2x2 = 3, kShapeTrio = 4;   // kShapeTrio: 2 x 2 at D 64, three to a compute unit
+constexpr int shape_rows(int shape) { return shape == kShape8x1 ? 256 : shape >= kShape2x2 ? 64 : 128; }
 constexpr int shape_key_groups(int shape) { return shape >= kShape4x2 ? 2 : 1; }
 
 // Arguments of the block-attention kernel: raw pointers, element strides, sizes.
