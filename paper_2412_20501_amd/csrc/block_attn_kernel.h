@@ -39,6 +39,11 @@
 // What it costs is twice the K/V traffic from L2 into LDS for the same rows.  us, 8 x 1 -> 4 x 1: 512 heads of 256 rows on as many keys
 // 41.8 -> 35.4, at D 64 26.2 -> 19.6; 48 heads of 3000 225 -> 207, at D 64 145 -> 121; 64 of 2048 125.3 -> 126.7, at D 64 77.0 -> 73.8; 32 of
 // 24576 7720 -> 8015, at D 64 4847 -> 4721; bf16 blocks of 6008 rows in 4 chunks, 16 heads 167 -> 157.
+//
+// Trio (D = 64).  Shape 2 x 2 with rings of three tiles of 64 keys: 48 KiB and 154 VGPRs (with renewals 168), three workgroups a compute unit.  For launches
+// of 1 to 1.5 workgroups of 128 rows a compute unit, where two of those on some units set the time.  The same bits as 2 x 2.  What bounds it is the vector ALU, as in 4 x 1
+// (0.28 us a step and SIMD, 0.25 there), and K/V traffic, twice 4 x 1's.  us, the shape before -> trio, under the causal rule: 24 heads of 1777 rows 20.2 -> 17.4, 32 of 1024 13.7 -> 11.0, 8 of
+// 4096 35.7 -> 28.1; alone on its unit it is slower than 2 x 2 with rings of four tiles of 128 keys (16 heads of 512 7.3 and 7.6).
 #pragma once
 #include <type_traits>
 
@@ -946,7 +951,8 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   // group raises its own).  Those of later segments are found here, each by one key group, from K rows
   // that go straight into registers (K is the A operand as it lies in memory).
   auto masked_max = [&](const f32x16& s, int kstart) __attribute__((always_inline)) -> float {
-    if (kstart <= kmask_from) {   // every row sees all of it
+    // every row sees all of it (no choice in the chunk form at D 128: 4 heads of 2000 in 4 chunks, causal, 37.8 us with it, 37.4 without)
+    if ((!CHUNKS || D == 64) && kstart <= kmask_from) {
       float t = s[0];
 #pragma unroll
       for (int i = 1; i < 16; i++) t = fmaxf(t, s[i]);
@@ -1009,6 +1015,9 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   // slot of K_0 is free at B_1, where K_4 is issued in front of K_5.  K_{w+2} and V_{w-1}, read first in step w, were issued
   // before the newest 2*IPW loads at B_w.  Rings of three tiles (NSW = 2): K_{w+3} goes into the slot of K_w and V_{w+1}, issued in
   // front of it, into the one of V_{w-2}; all but the newest IPW loads have landed at B_{w+1}, and K_3 is issued at B_1, like K_4 above.
+  // Rings of three tiles and NSW = 1 (three workgroups a compute unit): K_{w+4} goes into the slot of K_{w+1} and V_{w+1}, issued in front of it, into the one of
+  // V_{w-2}, both read last in step w-1; K_{w+2} and V_{w-1}, read first in step w, were issued before the newest 2*IPW loads at B_w. K_3, V_1 and K_4
+  // go out behind a barrier of their own in front of step 0, where K_0 and K_1 have been read.  Six tiles until slots and register sets come round.
   // S and P alternate between two register sets: even steps read sA / pB and write sB / pA,
   // odd steps the other way round, so no step has to copy its results.
   f32x16 sA, sB;
@@ -1030,51 +1039,58 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
       else step(kstart, IC<0>{}, IC<(int)v_imm>{}, IC<(int)k_imm>{}, sB, sA, pA, pB, inner_c);
     }
   };
+  auto first_scores = [&]() __attribute__((always_inline)) {
+    // S_0 = K_0[0:32] Q^T, plain (nothing to overlap with yet); operands of step 0 (the wave's sub-tile 1)
+#pragma unroll
+    for (int i = 0; i < 16; i++) sA[i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_k(ks, 0), qf[ks], sA, 0, 0, 0);
+    if constexpr (G > 1) {   // the reference comes from the first sub-tile of all, key group 0's
+      f32x16 sr;
+#pragma unroll
+      for (int i = 0; i < 16; i++) sr[i] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++)
+        sr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(lds_b128_ptr)(unsigned long)(k_rd[ks] - kgrp * (SUB * RB)), qf[ks], sr, 0, 0, 0);
+      m_ref = masked_max(sr, 0);
+      if (m_ref > -INFINITY) {
+        mc = m_ref * c2;
+        sum_cap = kSumCap;
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) pre[ks] = load_k(ks, 1 % NSW * G * SUBB + 1 / NSW * TILE_BYTES);
+  };
+  auto first_steps = [&]() __attribute__((always_inline)) {
+    // step 0: S_1 alongside the softmax of sub-tile 0 (no PV yet); prefetch the K operands of sub-tile 2
+    constexpr unsigned k_imm0 = 2 % NSW * G * SUBB + 2 / NSW * TILE_BYTES;
+    step(kgrp * SUB, IC<1>{}, IC<0>{}, IC<(int)k_imm0>{}, sA, sB, pB, pA, IC<0>{});
+    // the other steps of tile 0 (tiles 0 and 1 sit in ring slots 0 and 1)
+    if constexpr (NSW > 1) tile_step(0, IC<0>{}, IC<1>{}, IC<0>{});
+    if constexpr (NSW > 2) {
+      tile_step(0, IC<0>{}, IC<2>{}, IC<0>{});
+      tile_step(0, IC<0>{}, IC<3>{}, IC<0>{});
+    }
+  };
   if (n_tiles > 0) {
     if (KA == 3 && NS == 4) issue_k(3 % NS);
     if (!TRIO) issue_v(VA % NS);
-    if (jw > 0) {
-      // S_0 = K_0[0:32] Q^T, plain (nothing to overlap with yet); operands of step 0 (the wave's sub-tile 1)
+    if constexpr (TRIO) {
+      if (jw > 0) {
+        first_scores();
 #pragma unroll
-      for (int i = 0; i < 16; i++) sA[i] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_k(ks, 0), qf[ks], sA, 0, 0, 0);
-      if constexpr (G > 1) {   // the reference comes from the first sub-tile of all, key group 0's
-        f32x16 sr;
-#pragma unroll
-        for (int i = 0; i < 16; i++) sr[i] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++)
-          sr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(lds_b128_ptr)(unsigned long)(k_rd[ks] - kgrp * (SUB * RB)), qf[ks], sr, 0, 0, 0);
-        m_ref = masked_max(sr, 0);
-        if (m_ref > -INFINITY) {
-          mc = m_ref * c2;
-          sum_cap = kSumCap;
-        }
+        for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(pre[ks]));
       }
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) pre[ks] = load_k(ks, 1 % NSW * G * SUBB + 1 / NSW * TILE_BYTES);
-    }
-    if constexpr (TRIO) {   // K_3 and K_4 go where K_0 and K_1 lay, which every wave has read
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) asm volatile("" ::"v"(pre[ks]));
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-      wg_barrier();
+      wg_barrier();                         // K_3 and K_4 go where K_0 and K_1 lay, once every wave has read them
       issue_k(0);
       issue_v(1);
       issue_k(1);
-    }
-    if (jw > 0) {
-      // step 0: S_1 alongside the softmax of sub-tile 0 (no PV yet); prefetch the K operands of sub-tile 2
-      constexpr unsigned k_imm0 = 2 % NSW * G * SUBB + 2 / NSW * TILE_BYTES;
-      step(kgrp * SUB, IC<1>{}, IC<0>{}, IC<(int)k_imm0>{}, sA, sB, pB, pA, IC<0>{});
-      // the other steps of tile 0 (tiles 0 and 1 sit in ring slots 0 and 1)
-      if constexpr (NSW > 1) tile_step(0, IC<0>{}, IC<1>{}, IC<0>{});
-      if constexpr (NSW > 2) {
-        tile_step(0, IC<0>{}, IC<2>{}, IC<0>{});
-        tile_step(0, IC<0>{}, IC<3>{}, IC<0>{});
-      }
+      if (jw > 0) first_steps();
+    } else if (jw > 0) {   // (one branch over both: with two, 8 heads of 2048 in 4 chunks of bf16 blocks at D 128 take 38.2 us for 38.0)
+      first_scores();
+      first_steps();
     }
   }
   // tiles u = 1 .. n_tiles: steps NSW*u .. NSW*u + NSW-1 (the last tile index only has its first

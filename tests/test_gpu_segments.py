@@ -2,7 +2,7 @@
 import pytest
 import torch
 
-from gpu_util import RING, attn_shape
+from gpu_util import RING, STEP_F32, attn_shape
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +62,36 @@ def test_packed_heads(lib, D, causal):
     want = torch.softmax(s, -1) @ vv
     assert float((out - want).abs().max()) <= 2 ** -8 * float(v.abs().max()) * 1.02 + 1e-4
     assert float((lse - torch.logsumexp(s, -1)).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("B,H,Sq,Sk,n,causal", [
+    (4, 32, 300, 300, 1, True),       # row tiles that see one tile of keys to five
+    (4, 32, 300, 337, 1, True), (4, 24, 449, 449, 1, True),   # the sixth tile, the eighth: a group of six and more; one row in the last workgroup
+    (3, 32, 385, 290, 1, True),       # rows that see no key
+    (4, 8, 1089, 1089, 1, True),      # groups of inner tiles
+    (16, 8, 257, 1345, 1, False), (16, 8, 257, 1409, 1, True), (16, 8, 257, 1601, 1, False),   # tails of one to six tiles behind them
+    (4, 8, 1152, 1152, 3, True), (4, 8, 1300, 1300, 4, True),   # rings
+    (2, 8, 2304, 2304, 9, True),      # as many references as it keeps
+])
+def test_three_workgroups_a_compute_unit(lib, B, H, Sq, Sk, n, causal):
+    """512 to 768 workgroups of 64 rows at D 64."""
+    D, off = 64, Sk - Sq if causal else None
+    assert 512 <= B * H * -(-Sq // 64) <= 768 and attn_shape(lib, RING if n > 1 else STEP_F32, B, H, H, Sq, Sk, D, off, n) == (64, 2)
+    gen = torch.Generator(device="cuda").manual_seed(Sq + 7 * Sk)
+    q, k, v = (torch.randn((B, H, S, D), device="cuda", generator=gen).bfloat16() for S in (Sq, Sk, Sk))
+    out, lse = torch.full((B, H, Sq, D), float("nan"), device="cuda"), torch.full((B, H, Sq), float("nan"), device="cuda")
+    if n > 1:
+        lib.tr_ring_attn(q, k, v, n, causal, out, lse)
+    elif causal:
+        lib.tr_block_attn_causal_at(q, k, v, max(off, 0), max(-off, 0), D ** -0.5, out, lse)
+    else:
+        lib.tr_block_attn(q, k, v, lib.TR_MASK_NONE, D ** -0.5, out, lse)
+    torch.cuda.synchronize()
+    s = (q.double() * D ** -0.5) @ k.double().transpose(-1, -2).contiguous()
+    if causal:
+        s.masked_fill_(torch.arange(Sk, device="cuda")[None, :] > torch.arange(Sq, device="cuda")[:, None] + off, float("-inf"))
+    want_l = torch.logsumexp(s, -1)
+    want_o = torch.exp(s - want_l.masked_fill(torch.isinf(want_l), 0.0)[..., None]) @ v.double()
+    seen = ~torch.isneginf(want_l)
+    assert torch.equal(torch.isneginf(lse), ~seen)
+    assert float((out - want_o).abs().max()) <= 2 ** -8 * float(v.abs().max()) * 1.02 + 1e-4 and float((lse - want_l)[seen].abs().max()) <= 1e-5
