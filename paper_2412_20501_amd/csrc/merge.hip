@@ -27,6 +27,13 @@ constexpr int kMergeThreads = 512;
 // 75 - 78 / 67.  Only its loads or only its stores through the cache: the same or worse.)
 constexpr int64_t kStreamAccBytes = (int64_t)128 << 20;
 
+// Up to this many threads, a third more than the chip holds at once, the accumulator is requested together with the block and both lse: the launch is
+// two memory latencies long otherwise (one for the lse that say whether the accumulator is used), and nothing else runs beside the first. us an Update of
+// fp32 blocks, behind the lse / at once: 16384 rows of 128 5.4 / 5.0, 42648 of 64 6.5 / 6.2, of 128 10.7 / 10.0 (682368 threads), bf16 blocks 10.5 / 9.5; onto an
+// empty accumulator, whose reading is then for nothing, the same or less.  Beyond it the bytes count: 65536 of 128 17.3 / 16.4, but onto an empty
+// accumulator 15.4 / 18.4.
+constexpr int64_t kAtOnceThreads = 256 * 2048 * 4 / 3;
+
 // One row is always handled inside a single wavefront: `tpr` (a power of two <= 64) threads
 // share a row; a thread takes the 16-byte column chunks t and t + tpr (then t + 2 tpr, ... for
 // long rows), both loads of a pair issued before the first store, so the lse arithmetic of a
@@ -38,7 +45,7 @@ constexpr int64_t kStreamAccBytes = (int64_t)128 << 20;
 // A wave whose rows all have an empty accumulator (the first Update of a fold) does not read it: the
 // block's loads go out first, the accumulator's once the two lse are there.  Eight Updates of
 // 512 MiB fp32 blocks, the first onto an empty accumulator, 2034 -> 1919 us; two of 32 MiB bf16 blocks 62.6 -> 53.2.
-template <bool BLK_BF16, bool STREAM_ACC>
+template <bool BLK_BF16, bool STREAM_ACC, bool AT_ONCE>
 __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams p, int64_t n_rows, int tpr_log2) {
   const int64_t gtid = (int64_t)blockIdx.x * kMergeThreads + threadIdx.x;
   const int64_t row = gtid >> tpr_log2;
@@ -57,7 +64,7 @@ __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams 
     bo = b * p.bo_sb + h * p.bo_sh + s * p.bo_ss;
     bl = b * p.bl_sb + h * p.bl_sh + s * p.bl_ss;
   }
-  const UpdatePlan plan = plan_update(p.acc_lse[al], p.blk_lse[bl]);
+  const float old_lse = p.acc_lse[al], blk_lse = p.blk_lse[bl];
 
   auto load_acc = [&](int col) __attribute__((always_inline)) -> f32x4 {
     const f32x4* src = reinterpret_cast<const f32x4*>(p.acc_out + ao + col);
@@ -75,6 +82,25 @@ __global__ void __launch_bounds__(kMergeThreads) merge_kernel(const MergeParams 
     if (STREAM_ACC) __builtin_nontemporal_store(val, dst);
     else *dst = val;
   };
+  if constexpr (AT_ONCE) {   // one pair of chunks a thread (see launch_merge): everything is requested before the first wait
+    const int col = t * 4, col2 = col + tpr * 4;
+    const bool one = col < p.D, two = col2 < p.D;
+    f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0, y0 = x0, y1 = x0;
+    if (one) {
+      y0 = load_blk(col);
+      x0 = load_acc(col);
+    }
+    if (two) {
+      y1 = load_blk(col2);
+      x1 = load_acc(col2);
+    }
+    const UpdatePlan plan = plan_update(old_lse, blk_lse);
+    if (one) store_acc(col, apply_update(plan, x0, y0));
+    if (two) store_acc(col2, apply_update(plan, x1, y1));
+    if (t == 0) p.acc_lse[al] = plan.new_lse;
+    return;
+  }
+  const UpdatePlan plan = plan_update(old_lse, blk_lse);
   const bool held = __any(plan.mode == 0 || plan.mode == 3);   // does some row of the wave use what the accumulator holds?
   for (int col = t * 4; col < p.D; col += tpr * 8) {
     const int col2 = col + tpr * 4;
@@ -214,12 +240,15 @@ hipError_t launch_merge(const MergeParams& p, bool blk_bf16, hipStream_t stream)
   const int64_t nblocks = (n_threads + kMergeThreads - 1) / kMergeThreads;
   dim3 grid((unsigned)nblocks), block(kMergeThreads);
   const bool stream_acc = n_rows * p.D * 4 > kStreamAccBytes;
+  const bool at_once = n_threads <= kAtOnceThreads && p.D <= (8 << tpr_log2);
   if (blk_bf16) {
-    if (stream_acc) return launch_kernel(merge_kernel<true, true>, grid, block, 0, stream, p, n_rows, tpr_log2);
-    return launch_kernel(merge_kernel<true, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
+    if (stream_acc) return launch_kernel(merge_kernel<true, true, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
+    if (at_once) return launch_kernel(merge_kernel<true, false, true>, grid, block, 0, stream, p, n_rows, tpr_log2);
+    return launch_kernel(merge_kernel<true, false, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
   }
-  if (stream_acc) return launch_kernel(merge_kernel<false, true>, grid, block, 0, stream, p, n_rows, tpr_log2);
-  return launch_kernel(merge_kernel<false, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
+  if (stream_acc) return launch_kernel(merge_kernel<false, true, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
+  if (at_once) return launch_kernel(merge_kernel<false, false, true>, grid, block, 0, stream, p, n_rows, tpr_log2);
+  return launch_kernel(merge_kernel<false, false, false>, grid, block, 0, stream, p, n_rows, tpr_log2);
 }
 
 }  // namespace tr
