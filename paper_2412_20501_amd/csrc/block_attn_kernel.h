@@ -637,8 +637,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) kf[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks);
   };
-  const bool range_first = KNOWN && p.renew > 0;
-  if (range_first) {
+  if constexpr (KNOWN) {   // (launched with p.renew > 0 only)
     wave_range();
     n_ref = __builtin_amdgcn_readfirstlane(divide(p.by_renew, max(0, wave_kv_end - 1)));
     if (kgrp < n_ref) {
@@ -673,7 +672,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
     done = block;
   }
 
-  if (!range_first) wave_range();
+  if constexpr (!KNOWN) wave_range();
   // wave-uniform loop bounds, forced into scalar registers so that every per-step test is one compare
   const int jw_own = G == 1 ? jw : max(0, jw - kgrp + G - 1) / G;                     // those of this key group: kgrp, kgrp + G, ...
   const int jw_first = __builtin_amdgcn_readfirstlane(jw_own);                        // last allowed step that opens a tile
