@@ -999,7 +999,10 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
     }
   }
 
-  if (LATE > 0 && last_tile >= 3 && !straight) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
+  // (Where K rows were loaded into registers this is a wait that the compiler knows: it does not see that the one for Q covers them, takes rows of a reference
+  // to be on their way still, and waits for everything in each group of inner tiles, where it needs their registers again.  With that wait / without, us at D 128:
+  // 1 head of 28948 rows in 2 segments 394 / 384, a block step of 4 x 16 heads of 373 rows on 9183 keys, renewed at its parts, 141 / 125.)
+  if (LATE > 0 && !KNOWN && last_tile >= 3 && !straight) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LATE) : "memory");
   else __builtin_amdgcn_s_waitcnt(0);
   wg_barrier();  // B_0
   if (REF_AHEAD && n_ref > 0) next_ref = *reinterpret_cast<const float*>(lds + L::refs + (rg * 32 + ql) * 4);
