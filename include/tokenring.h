@@ -132,6 +132,12 @@ int tr_attn_workgroup(const tr_tensor* q, const tr_tensor* k, int causal, int64_
                       int32_t* key_groups);
 
 /*
+ * Host-only, the same arguments: how many of those workgroups a compute unit holds at once (1, 2 or 3), -1 on invalid arguments.
+ * 64 rows in two key groups are one a unit, or at head dim 64 three, with rings of three tiles of 64 keys.
+ */
+int tr_attn_workgroups_per_unit(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int form, int n_chunks);
+
+/*
  * Out, Lse <- Update(block_out, block_lse), the two equations of Sec. 3.1, in place:
  *   out_acc <- out_acc - sigmoid(block_lse - lse_acc) * (out_acc - block_out)
  *   lse_acc <- lse_acc - ln(sigmoid(lse_acc - block_lse))

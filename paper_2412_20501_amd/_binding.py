@@ -58,6 +58,8 @@ def _load():
     lib.tr_block_attn_plan.restype = ctypes.c_int
     lib.tr_attn_workgroup.argtypes = [P, P, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int32)]
     lib.tr_attn_workgroup.restype = ctypes.c_int
+    lib.tr_attn_workgroups_per_unit.argtypes = lib.tr_attn_workgroup.argtypes[:-1]
+    lib.tr_attn_workgroups_per_unit.restype = ctypes.c_int
     lib.tr_merge.argtypes = [P, P, P, P, ctypes.c_void_p]
     lib.tr_merge.restype = ctypes.c_int
     lib.tr_ring_attn.argtypes = [P, P, P, ctypes.c_int, ctypes.c_int, P, P, ctypes.c_float,

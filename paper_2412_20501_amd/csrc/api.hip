@@ -172,7 +172,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
   double t_best = 0;
   for (int shape = 0; shape < (trio ? 5 : 4); shape++) {
     const Cost& c = costs[D == 128][shape];
-    const int bm = tr::shape_rows(shape), per_cu = shape == tr::kShapeTrio ? 3 : shape != tr::kShape4x1 ? 1 : D == 64 ? 3 : 2;
+    const int bm = tr::shape_rows(shape), per_cu = tr::shape_per_unit(shape, D);
     const bool groups = shape >= tr::kShape4x2;
     const int64_t tiles = (rows + bm - 1) / bm;
     if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
@@ -779,13 +779,13 @@ int tr_block_attn_plan(const tr_tensor* q, const tr_tensor* k, int causal, int64
   return planned ? plan.parts : 1;
 }
 
-int tr_attn_workgroup(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int form, int n_chunks, int32_t* key_groups) {
-  tr::AttnParams p;
-  if (!view_sizes(p, q, k, causal, q_pos0, k_pos0)) return -1;
+// The launch of a call on these shapes (tr_attn_workgroup); true: it is in p.
+static bool view_launch(tr::AttnParams& p, const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int form, int n_chunks) {
+  if (!view_sizes(p, q, k, causal, q_pos0, k_pos0)) return false;
   const int D = (int)q->D;
   if (form < TR_FORM_STEP_BF16 || form > TR_FORM_RING_BF16 || n_chunks < 1 || (form >= TR_FORM_RING && (q->S % n_chunks || k->S != q->S))) {
     fail(TR_ERR_SHAPE, "unknown form %d, or a sequence that is no multiple of %d chunks", form, n_chunks);
-    return -1;
+    return false;
   }
   const int64_t seg = q->S / n_chunks;
   if (form == TR_FORM_RING_BF16 || (form == TR_FORM_RING && n_chunks > 1 && seg < 32)) {
@@ -798,8 +798,20 @@ int tr_attn_workgroup(const tr_tensor* q, const tr_tensor* k, int causal, int64_
     const bool planned = plan_parts(p, D, form != TR_FORM_RING, plan);
     settle_launch(p, plan, planned, D, form == TR_FORM_RING ? 1 : form, true);
   }
+  return true;
+}
+
+int tr_attn_workgroup(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int form, int n_chunks, int32_t* key_groups) {
+  tr::AttnParams p;
+  if (!view_launch(p, q, k, causal, q_pos0, k_pos0, form, n_chunks)) return -1;
   if (key_groups) *key_groups = tr::shape_key_groups(p.shape);
   return p.bm;
+}
+
+int tr_attn_workgroups_per_unit(const tr_tensor* q, const tr_tensor* k, int causal, int64_t q_pos0, int64_t k_pos0, int form, int n_chunks) {
+  tr::AttnParams p;
+  if (!view_launch(p, q, k, causal, q_pos0, k_pos0, form, n_chunks)) return -1;
+  return tr::shape_per_unit(p.shape, (int)q->D);
 }
 
 tr_status tr_merge(const tr_tensor* out_acc, const tr_tensor* lse_acc, const tr_tensor* block_out, const tr_tensor* block_lse,

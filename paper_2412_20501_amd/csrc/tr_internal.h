@@ -17,6 +17,7 @@ constexpr int kMaxParts = 16;  // parts the keys of one partitioned attention la
 constexpr int kShape8x1 = 0, kShape4x1 = 1, kShape4x2 = 2, kShape2x2 = 3, kShapeTrio = 4;   // kShapeTrio: 2 x 2 at D 64, three to a compute unit
 constexpr int shape_rows(int shape) { return shape == kShape8x1 ? 256 : shape >= kShape2x2 ? 64 : 128; }
 constexpr int shape_key_groups(int shape) { return shape >= kShape4x2 ? 2 : 1; }
+constexpr int shape_per_unit(int shape, int D) { return shape == kShapeTrio ? 3 : shape != kShape4x1 ? 1 : D == 64 ? 3 : 2; }   // workgroups that share a compute unit
 
 // Arguments of the block-attention kernel: raw pointers, element strides, sizes.
 struct AttnParams {

@@ -33,6 +33,15 @@ def attn_shape(lib, form, B, Hq, Hkv, Sq, Sk, D, offset=None, n=1):
     return rows, groups.value
 
 
+def attn_per_unit(lib, form, B, Hq, Hkv, Sq, Sk, D, offset=None, n=1):
+    """How many workgroups of that call share a compute unit: it tells the two launches of 64 rows and two key groups apart.  Host only."""
+    def t(H, S, ptr):
+        return lib.TrTensor(ptr, lib.TR_BF16, B, H, S, D, H * S * D, S * D, D)
+    off = offset or 0
+    return lib.raw_lib().tr_attn_workgroups_per_unit(ctypes.byref(t(Hq, Sq, 0x7F0000000000)), ctypes.byref(t(Hkv, Sk, 0x7F8000000000)),
+                                                     int(offset is not None), max(off, 0), max(-off, 0), form, n)
+
+
 def bits_to_dev(bits: np.ndarray) -> torch.Tensor:
     """bf16 bit patterns (uint16 numpy) -> bf16 torch tensor on cuda:0 with the same bits."""
     return torch.from_numpy(bits.view(np.int16)).to("cuda").view(torch.bfloat16)

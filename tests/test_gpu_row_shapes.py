@@ -9,7 +9,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, STEP_MERGE, attn_plan, attn_shape, bits_to_dev, f64, max_abs, rand_bits, to_np
+from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, STEP_MERGE, attn_per_unit, attn_plan, attn_shape, bits_to_dev, f64, max_abs, rand_bits, to_np
 
 pytestmark = pytest.mark.gpu
 MANY = 2048      # (batch, head, row tile) triples of 256 rows from which on the launches here take 128 rows and one key group
@@ -74,15 +74,19 @@ def test_rings_renew_at_the_same_keys(lib, seg, n, D, causal):
     few = _new(1, 1, seg * n, D)
     lib.tr_ring_attn(q, k, v, n, causal, *few)
     shapes = [attn_shape(lib, RING, 1, 1, 1, seg * n, seg * n, D, 0 if causal else None, n)]
+    compared = {(*shapes[0], 1)}
     for heads in (2, 4, 8, 12, 16, 24, 32, 96):
         shapes.append(attn_shape(lib, RING, 1, heads, heads, seg * n, seg * n, D, 0 if causal else None, n))
-        if shapes[-1] in shapes[:-1]:
+        launch = (*shapes[-1], attn_per_unit(lib, RING, 1, heads, heads, seg * n, seg * n, D, 0 if causal else None, n))
+        if launch in compared:
             continue
+        compared.add(launch)
         many = _new(1, heads, seg * n, D)
         lib.tr_ring_attn(*(x.expand(-1, heads, -1, -1) for x in (q, k, v)), n, causal, *many)
         torch.cuda.synchronize()
         _agree(few, [x.transpose(0, 1) for x in many])
     assert shapes[0] == ROWS_64_GROUPS and ROWS_128 in shapes
+    assert (64, 2, 3) in compared or D == 128 or seg == 4096 or not causal
     assert ROWS_256 in shapes or (causal and (seg, n) in ((1024, 2), (545, 4), (478, 4)))
     assert ROWS_128_GROUPS in shapes or (seg, n) not in ((4096, 2), (2000, 2)) or (seg, causal) == (2000, False)
 

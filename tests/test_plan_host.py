@@ -2,7 +2,7 @@
 packed heads, shape of the workgroups."""
 import pytest
 
-from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, attn_plan as plan, attn_shape as shape
+from gpu_util import RING, RING_BF16, STEP_BF16, STEP_F32, attn_per_unit as per_unit, attn_plan as plan, attn_shape as shape
 
 
 @pytest.fixture(scope="module")
@@ -66,10 +66,19 @@ def test_shapes_of_a_workgroup(tr):
     assert shape(tr, STEP_BF16, 4, 32, 8, 1, 8192, 128) == (64, 2)
 
 
+def test_workgroups_that_share_a_compute_unit(tr):
+    for D, small in ((64, 3), (128, 2)):
+        assert shape(tr, RING, 4, 96, 96, 1024, 1024, D, 0) == (128, 1) and per_unit(tr, RING, 4, 96, 96, 1024, 1024, D, 0) == small
+        assert per_unit(tr, RING, 1, 1, 1, 8192, 8192, D) == 1                     # 64 rows, two key groups, a unit each
+        assert per_unit(tr, RING, 1, 32, 32, 32768, 32768, 128, 0, 8) == 1         # 256 rows
+    assert shape(tr, STEP_F32, 2, 12, 12, 1777, 1777, 64, 0) == (64, 2) and per_unit(tr, STEP_F32, 2, 12, 12, 1777, 1777, 64, 0) == 3
+
+
 def test_invalid_arguments(tr):
     assert shape(tr, 5, 1, 2, 2, 8, 8, 64)[0] == -1 and shape(tr, STEP_F32, 1, 3, 2, 8, 8, 64)[0] == -1
     assert shape(tr, RING, 1, 2, 2, 8, 8, 64, None, 3)[0] == -1 and shape(tr, RING_BF16, 1, 2, 2, 8, 16, 64)[0] == -1
     assert tr.raw_lib().tr_attn_workgroup(None, None, 0, 0, 0, 0, 1, None) == -1
+    assert tr.raw_lib().tr_attn_workgroups_per_unit(None, None, 0, 0, 0, 0, 1) == -1 and per_unit(tr, RING, 1, 2, 2, 8, 8, 64, None, 3) == -1
     assert plan(tr, 1, 3, 2, 8, 8, 64)[0] == -1 and plan(tr, 1, 2, 2, 8, 8, 96)[0] == -1
     assert tr.raw_lib().tr_block_attn_plan(None, None, 0, 0, 0, None) == -1
     q = tr.TrTensor(0x7F0000000000, tr.TR_BF16, 1, 2, 8, 64, 1024, 512, 64)
