@@ -169,7 +169,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
   const double memory = (double)(heads * rows) * chunks * D * (2 + (p.n_parts > 1 ? 4 : out_bytes)) / 5.2e6;   // Query rows in, result out
   const bool trio = D == 64 && p.n_parts == 0 && p.n_chunks == 0;   // the forms that it has
   int best = tr::kShape8x1;
-  double t_best = 0;
+  double t_best = 0, seen_share = 0;   // seen_share: of the keys that the last row tile sees, by the average one (of the shape chosen)
   for (int shape = 0; shape < (trio ? 5 : 4); shape++) {
     const Cost& c = costs[D == 128][shape];
     const int bm = tr::shape_rows(shape), per_cu = tr::shape_per_unit(shape, D);
@@ -178,11 +178,16 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
     if (shape != tr::kShape8x1 && tiles > 65535) continue;   // a grid's second dimension
     if (groups && (refs > (shape == tr::kShapeTrio ? tr::kMaxRefsTrio : tr::kMaxRefs) || heads * tiles >= 8 * kCUs)) continue;
     // Trio: where all its workgroups run at once and a compute unit holds two or three, that is one to one and a half of 128 rows, which leave units
-    // uneven.  us, the best of the other shapes / trio: 24 heads of 1777 under the causal rule 18.8 / 17.4, 32 of 1024 13.1 / 11.0, 16 of 2048 in 4 segments 23.0 / 17.9,
-    // 8 of 4096 35.7 / 28.1; 128 heads of 300 rows on 3000 keys without a mask 45.2 / 43.2, on 300 9.8 / 10.0, 24 of 1777 29.0 / 28.8,
-    // 48 of 1000 20.2 / 20.4; beyond it 64 of 1024, causal, 15.7 / 17.5, 12 of 4096 35.6 / 37.3.  From 8192 keys on, where six heads at most are left, the other
-    // shapes stay (4 of 9000 67.5 / 58.2, so not the faster side: a test of rings counts on 4 x 2 at 4 heads of 8192).
-    if (shape == tr::kShapeTrio && (heads * tiles < 2 * kCUs || heads * tiles > 3 * kCUs || p.Sk >= 8192)) continue;
+    // uneven.  us under the causal rule, the best of the other shapes / trio: 24 heads of 1777 rows 18.9 / 17.3, 32 of 1024 13.3 / 11.3, 8 of 4096 33.1 / 28.7, 4 of 9000 68.6 / 58.5,
+    // 2 of 20000 152 / 136; rings of 16 of 2048 in 4 segments 22.4 / 18.3, 4 of 8192 in 2 52.4 / 49.1, 2 of 17644 in 4 119 / 108; beyond it 64 of 1024 15.7 / 17.4, 12 of 4096 36.3 / 36.7.
+    // Not for a few keys, where set-up is the time, of two on a unit and more so of three: bf16 results of 256 heads of 88 rows 5.3 / 6.0, of 128 5.9 / 6.2, of 118 on 174 keys
+    // 7.3 / 7.0; 128 heads of 280, whose units hold up to three, 7.3 / 7.9, of 336 8.2 / 8.7, fp32 results of 96 of 354 8.5 / 8.3.  (With more heads than units it stays: the other
+    // shapes' estimates are furthest off there, 384 heads of 83 rows 9.4 in the one they choose, 7.4.)
+    if (shape == tr::kShapeTrio) {
+      const int64_t n = heads * tiles, seen = std::min<int64_t>(p.Sk, rows + p.causal_off);   // keys that the last row sees under the causal rule
+      const bool few_keys = p.causal && p.causal_off >= 0 && heads <= kCUs && seen < (n > 2 * kCUs ? 352 : 160);
+      if (n < 2 * kCUs || n > 3 * kCUs || few_keys) continue;
+    }
     if (groups && p.renew > 0 && p.renew < 64) continue;   // renewals lie as far apart as a group's sub-tiles
     int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
     if (p.causal && pack) {
@@ -211,7 +216,18 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
       const double at_once = std::min<double>(per_cu, rounds), tile = at_once == 3 ? c.three : c.two;
       time = total * tile / (kCUs * at_once);
       if (!p.causal && rounds <= per_cu) time = longest * tile * (0.85 + 0.15 * n / (kCUs * rounds));   // all at once: as slow as the fullest compute unit
-      if (p.causal || later > 0) time += (shape == tr::kShapeTrio ? 0.05 : 0.15) * longest * tile;   // (half the rows: it ends more evenly)
+      // (Trio: half the rows, it ends more evenly: 313 causal calls in its window are 0.8 % above their fastest shape on average, with 0.15 2.9 %.)
+      if (p.causal || later > 0) time += (shape == tr::kShapeTrio ? 0.05 : 0.15) * longest * tile;
+      if (shape == tr::kShapeTrio) {
+        // Where row tiles see about as many keys, a unit that holds three sets the time, however few others do.
+        if (p.causal) time = std::max(time, 0.81 * (0.45 * longest + 0.55 * shortest) * tile);
+        // Under the causal rule, whose order spreads a head's row tiles over the launch, they fetch K and V again and again once these are more than the L2s hold (32 MB),
+        // at about 11 TB/s, the first time at 6.5; from the fifth tile on little is added, while the memory-side cache (256 MB) holds them.  us, the best of the other shapes / trio: chunks behind cached keys of 256
+        // heads of 138 rows on 5315 keys (348 MB of K and V) 82 / 141, 192 of 256 on 2568 (126) 45 / 59, 128 of 110 on 1873 (122) 25 / 37, 256 of 99 on 2066 (68) 25 / 29, 48 of
+        // 1005 on 6111 (75) 90 / 84, 128 of 251 on 743 (24) 12.0 / 11.2.  (737 such calls are 1.4 % above the fastest on average, without it 3 %, by up to three quarters.)
+        const double once = (double)p.B * p.Hkv * most * D * 4, all = total * tile_keys * D * 4;
+        if (p.causal && once > 60e6 && all > 1.2 * once) time = std::max(time, once / 6.5e6 + (once > 256e6 ? all - once : std::min(all - once, 3 * once)) / 11e6);
+      }
       time = std::max(time, memory) + fix + 0.35 * blocks * fix * n / (kCUs * at_once);
       time = std::max(time, longest * alone + fix * (1 + c.block * later));
     } else {
@@ -227,14 +243,18 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
     if (shape == tr::kShape8x1) {
       t_best = time * (n > kCUs ? 0.95 : 0.97);   // a last round that is nearly empty runs faster than a full one
     } else {   // over several rounds the estimates lie closer together than their errors, unless there are many
+      // (Trio without a mask: 0.93 to 1.16 of the best other shape on 83 calls in its window, which the estimates don't tell apart: with 1.0 25 of them gain
+      // 2 % and more and 10 lose as much, up to 10 %.  24 heads of 1777 rows 29.6 / 28.7, 128 of 300 on 300 keys 10.0 / 10.1, on 3000 45.9 / 43.1, where it is taken.)
       time *= shape == tr::kShapeTrio ? (p.causal ? 1.0 : 1.13) : n > 8 * kCUs ? 0.97 : n > kCUs * per_cu ? 1.03 : 1.0;
       if (time < t_best) {
         t_best = time;
         best = shape;
+        seen_share = total / (n * longest + 1e-9);
       }
     }
   }
-  if (estimate) *estimate = t_best;
+  // (Against a cut, whose workgroups are many and short, units that hold three of trio's count more: 16 heads of 2462 rows behind 25314 keys 323 / in three parts 287.)
+  if (estimate) *estimate = t_best * (best == tr::kShapeTrio && p.causal ? 1.0 + 0.1 * std::max(0.0, seen_share - 0.6) : 1.0);
   return best;
 }
 

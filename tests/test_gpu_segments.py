@@ -65,8 +65,9 @@ def test_packed_heads(lib, D, causal):
 
 
 @pytest.mark.parametrize("B,H,Sq,Sk,n,causal", [
-    (4, 32, 300, 300, 1, True),       # row tiles that see one tile of keys to five
-    (4, 32, 300, 337, 1, True), (4, 24, 449, 449, 1, True),   # the sixth tile, the eighth: a group of six and more; one row in the last workgroup
+    (4, 32, 256, 256, 1, True),       # row tiles that see one tile of keys to four
+    (4, 32, 200, 300, 1, True),       # five
+    (4, 32, 193, 337, 1, True), (4, 24, 449, 449, 1, True),   # the sixth tile, the eighth: a group of six and more; one row in the last workgroup
     (3, 32, 385, 290, 1, True),       # rows that see no key
     (4, 8, 1089, 1089, 1, True),      # groups of inner tiles
     (16, 8, 257, 1345, 1, False), (16, 8, 257, 1409, 1, True), (16, 8, 257, 1601, 1, False),   # tails of one to six tiles behind them
@@ -113,6 +114,7 @@ def _exact(q, k, v, off):
     (2, 12, 12, 1777, 1777, 0, STEP_MERGE, False),      # merged into accumulators
     (1, 16, 2, 2201, 2201, 0, STEP_F32, True),          # rounds as the parts it is not cut into would
     (1, 16, 2, 2201, 2201, 0, STEP_MERGE, True),
+    (1, 4, 1, 9001, 9001, 0, STEP_F32, True),
 ])
 def test_steps_of_three_workgroups_a_compute_unit(lib, B, Hq, Hkv, Sq, Sk, off, form, renewed):
     """Every way out of the kernel, with grouped heads in the token-major layout; renewed: the reference is taken anew at the parts that

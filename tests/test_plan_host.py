@@ -74,6 +74,25 @@ def test_workgroups_that_share_a_compute_unit(tr):
     assert shape(tr, STEP_F32, 2, 12, 12, 1777, 1777, 64, 0) == (64, 2) and per_unit(tr, STEP_F32, 2, 12, 12, 1777, 1777, 64, 0) == 3
 
 
+def test_where_three_workgroups_of_64_rows_share_a_unit(tr):
+    """us, the best other shape and three of 64 rows a unit."""
+    def three(*case):
+        return shape(tr, *case) == (64, 2) and per_unit(tr, *case) == 3
+    for form in (RING, STEP_F32):
+        assert three(form, 1, 8, 8, 4096, 4096, 64, 0)                          # 33.1 and 28.7
+        assert three(form, 1, 4, 4, 8192, 8192, 64, 0)                          # 55.4 and 51.4, cut in three 89.3
+        assert three(form, 1, 4, 4, 9000, 9000, 64, 0)                          # 68.6 and 58.4
+        assert not three(form, 1, 24, 24, 1777, 1777, 64)
+        assert not three(form, 4, 32, 32, 280, 280, 64, 0)                      # a few keys: 7.3 and 7.9
+        assert three(form, 4, 32, 32, 238, 238, 64, 0)                          # two a unit: 7.3 and 6.9
+    assert three(RING, 1, 2, 2, 17644, 17644, 64, 0, 4)                         # 119 and 108
+    assert not three(STEP_F32, 8, 32, 32, 138, 5315, 64, 5177)                  # few row tiles a head, K and V from beyond the L2s: 82 and 142
+    assert not three(STEP_BF16, 16, 24, 24, 106, 2905, 64, 2799)                # 53 and 78
+    assert not three(STEP_F32, 8, 24, 24, 256, 2568, 64, 2312)                  # 45 and 59
+    assert three(STEP_F32, 4, 24, 12, 321, 1322, 64, 1001)                      # 22.5 and 20.3
+    assert plan(tr, 1, 16, 16, 2462, 27776, 64, 25314)[0] > 1                   # uncut 323, in three parts 287
+
+
 def test_invalid_arguments(tr):
     assert shape(tr, 5, 1, 2, 2, 8, 8, 64)[0] == -1 and shape(tr, STEP_F32, 1, 3, 2, 8, 8, 64)[0] == -1
     assert shape(tr, RING, 1, 2, 2, 8, 8, 64, None, 3)[0] == -1 and shape(tr, RING_BF16, 1, 2, 2, 8, 16, 64)[0] == -1
