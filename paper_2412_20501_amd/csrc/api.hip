@@ -346,10 +346,11 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     q.part_keys = (int)best.part_keys;
     choose_shape(q, D, false, 4, &cut);
     cut += 5.0 + 0.25 * best.parts + (double)best.out_elems * 4 / 3.5e6;
-    // The line with the least regret of those tried, on 371 calls near it and 125 long ones: 0.3 % and 0.8 % above the faster side on average,
-    // 2 and 4 calls by more than a tenth; the estimates as they are 1.7 % and 30, 1.2 % and 6.  (What it adds is the renewals of short calls.)
+    // The line with the least regret of those tried, on 1350 calls near it of either head dim: 0.6 % above the faster side on average, 19 of them by more than a tenth; the estimates
+    // as they are 1.9 % and 91.  (What it adds is the renewals of short calls: 3 heads of 1251 rows at D 64 12.4 cut and 14.3, 2 of 1053 at D 128 15.0 and 17.0; with 3.0 in the place of
+    // 4.0 0.8 % and 36, these two among them.)
     whole = std::max(whole, stream + fix);
-    if (std::max(0.85 * whole + 3.0 + 0.6 * (best.parts - 1), 0.95 * whole) < cut) {
+    if (std::max(0.85 * whole + 4.0 + 0.6 * (best.parts - 1), 0.95 * whole) < cut) {
       best = c;
       best.renew = w.renew;
       return false;

@@ -38,6 +38,15 @@ def test_workgroups_of_fewer_rows_make_a_cut_needless(tr):
     assert plan(tr, 1, 3, 3, 1307, 27907, 64, 26600)[0] > 1
 
 
+def test_short_calls_of_few_heads_are_cut(tr):
+    """us, cut and in one piece whose reference is renewed where the parts would begin."""
+    assert plan(tr, 1, 3, 3, 1251, 1251, 64)[0] > 1                             # 12.4 and 14.3
+    assert plan(tr, 1, 12, 12, 286, 1282, 64)[0] > 1                            # 12.3 and 14.7
+    assert plan(tr, 1, 4, 1, 1694, 1906, 64, 212)[0] > 1                        # 14.7 and 17.2
+    assert plan(tr, 1, 2, 2, 1053, 1053, 128)[0] > 1                            # 15.0 and 17.0
+    assert plan(tr, 1, 1, 1, 6762, 1812, 128, -4950)[0] > 1                     # 17.6 and 21.8
+
+
 def test_a_packed_grid_stays_within_the_dispatch_limit(tr):
     """2^32 threads in one dimension: the plain form's second grid dimension holds what a packed launch would not."""
     assert plan(tr, 2_700_000, 2, 1, 257, 8, 64) == (1, 1)
