@@ -188,7 +188,7 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
       const bool few_keys = p.causal && p.causal_off >= 0 && heads <= kCUs && seen < (n > 2 * kCUs ? 352 : 160);
       if (n < 2 * kCUs || n > 3 * kCUs || few_keys) continue;
     }
-    if (groups && p.renew > 0 && p.renew < 64) continue;   // renewals lie as far apart as a group's sub-tiles
+    if (groups && p.renew > 0 && (p.renew < 64 || pack)) continue;   // renewals lie as far apart as a group's sub-tiles; packed rings fill the chip and never gain from key groups
     int64_t least = p.Sk, most = p.Sk, sum = p.Sk * tiles;   // keys that the first, the last, all row tiles of a head see
     if (p.causal && pack) {
       least = most = std::max<int64_t>(0, std::min<int64_t>(p.Sk, (int64_t)p.Sq + p.causal_off));

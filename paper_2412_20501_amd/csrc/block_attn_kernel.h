@@ -344,6 +344,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   constexpr int NG = NSW * NS % 2 ? 2 * NS : NS;      // tiles after which ring slots and register sets come round
   static_assert(NSUB % G == 0 && (NSW * NG) % 2 == 0, "the S / P register sets alternate with the step parity");
   static_assert(IPW >= 1, "tile too small for the workgroup");
+  static_assert(FORM != kPartSegments || G == 1, "packed rings: one key group (see choose_shape)");
   static_assert((!PART || L::tables(FORM) >= L::sums) && (!in_segments(FORM) || G == 1 || L::tables(FORM) > L::refs),
                 "the row offsets and the references lie in the LDS that is asked for");
 
@@ -1402,9 +1403,11 @@ hipError_t launch_attn_shape(const AttnParams& p, int epilogue, dim3 grid, hipSt
     }
   }
   if (p.n_chunks > 0) return launch_epilogue<D, kChunks, R, G>(p, epilogue, grid, stream);
-  if (p.n_parts > 0 && p.renew > 0) {   // rings only, whose heads are packed
-    if (epilogue != kEpiF32 || p.n_parts != 1) return hipErrorInvalidValue;
-    return launch_one<D, kEpiF32, kPartSegments, R, G>(p, grid, stream);
+  if (p.n_parts > 0 && p.renew > 0) {   // rings only, whose heads are packed and whose workgroups have one key group
+    if constexpr (G == 1) {
+      if (epilogue == kEpiF32 && p.n_parts == 1) return launch_one<D, kEpiF32, kPartSegments, R, G>(p, grid, stream);
+    }
+    return hipErrorInvalidValue;
   }
   if (p.n_parts > 0) return launch_epilogue<D, kPart, R, G>(p, epilogue, grid, stream);
   if (p.renew > 0) return launch_epilogue<D, kSegments, R, G>(p, epilogue, grid, stream);

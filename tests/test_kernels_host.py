@@ -19,6 +19,7 @@ def test_no_kernel_has_scratch(library):
     found = re.findall(rb"\.name\xd9.(_ZN2tr\w+)\xbb\.private_segment_fixed_size(.)", library, re.S)
     kernels = {name.decode(): size[0] for name, size in found}
     assert sum("block_attn_kernel" in name for name in kernels) == 56 and sum("merge" in name for name in kernels) > 4
+    assert sum("segments_attn_kernel" in name for name in kernels) == 28 and sum("trio_attn_kernel" in name for name in kernels) == 6
     assert {name: size for name, size in kernels.items() if size} == {}
 
 
@@ -66,7 +67,7 @@ def waits_in_steps(library, tmp_path_factory):
     return found
 
 
-@pytest.mark.parametrize("family,kernels", [("segments_attn_kernel", 32), ("trio_attn_kernel", 6)])
+@pytest.mark.parametrize("family,kernels", [("segments_attn_kernel", 28), ("trio_attn_kernel", 6)])
 def test_steps_do_not_wait_for_loads(waits_in_steps, family, kernels):
     mine = {name: waits for name, waits in waits_in_steps.items() if family in name}
     assert len(mine) == kernels

@@ -102,6 +102,14 @@ def test_where_three_workgroups_of_64_rows_share_a_unit(tr):
     assert plan(tr, 1, 16, 16, 2462, 27776, 64, 25314)[0] > 1                   # uncut 323, in three parts 287
 
 
+def test_packed_rings_have_one_key_group(tr):
+    """Rings whose heads share a row space, which fills the chip: no kernel with key groups is there for them."""
+    for D in (64, 128):
+        for off in (None, 0):
+            for B, g, seg, n in ((300, 2, 40, 3), (64, 4, 32, 2), (32, 8, 33, 4), (200, 16, 65, 2), (64, 2, 150, 2), (300, 3, 100, 8)):
+                assert shape(tr, RING, B, 2 * g, 2, seg * n, seg * n, D, off, n)[1] == 1
+
+
 def test_invalid_arguments(tr):
     assert shape(tr, 5, 1, 2, 2, 8, 8, 64)[0] == -1 and shape(tr, STEP_F32, 1, 3, 2, 8, 8, 64)[0] == -1
     assert shape(tr, RING, 1, 2, 2, 8, 8, 64, None, 3)[0] == -1 and shape(tr, RING_BF16, 1, 2, 2, 8, 16, 64)[0] == -1
