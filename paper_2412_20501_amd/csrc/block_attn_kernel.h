@@ -40,10 +40,10 @@
 // 41.8 -> 35.4, at D 64 26.2 -> 19.6; 48 heads of 3000 225 -> 207, at D 64 145 -> 121; 64 of 2048 125.3 -> 126.7, at D 64 77.0 -> 73.8; 32 of
 // 24576 7720 -> 8015, at D 64 4847 -> 4721; bf16 blocks of 6008 rows in 4 chunks, 16 heads 167 -> 157.
 //
-// Trio (D = 64).  Shape 2 x 2 with rings of three tiles of 64 keys: 48 KiB and 154 VGPRs (with renewals 168), three workgroups a compute unit.  For launches
-// of 1 to 1.5 workgroups of 128 rows a compute unit, where two of those on some units set the time.  The same bits as 2 x 2.  What bounds it is the vector ALU, as in 4 x 1
-// (0.28 us a step and SIMD, 0.25 there), and K/V traffic, twice 4 x 1's.  us, the shape before -> trio, under the causal rule: 24 heads of 1777 rows 20.2 -> 17.4, 32 of 1024 13.7 -> 11.0, 8 of
-// 4096 35.7 -> 28.1; alone on its unit it is slower than 2 x 2 with rings of four tiles of 128 keys (16 heads of 512 7.3 and 7.6).
+// Trio (D = 64).  Shape 2 x 2 with rings of three tiles of 64 keys: 50 KiB of LDS (with references 52) and 154 VGPRs (with renewals 168), three workgroups a compute
+// unit.  For launches of 1 to 1.5 workgroups of 128 rows a compute unit, where two of those on some units set the time.  The same bits as 2 x 2.  What bounds it is the vector
+// ALU, as in 4 x 1 (0.28 us a step and SIMD, 0.25 there), and K/V traffic, twice 4 x 1's.  us, the shape that would be chosen without it -> trio, under the causal rule:
+// 24 heads of 1777 rows 20.3 -> 17.4, 32 of 1024 13.6 -> 11.3, 8 of 4096 36.2 -> 28.8; alone on its unit it is slower than 2 x 2 with rings of four tiles of 128 keys (16 heads of 512 7.4 and 7.7).
 #pragma once
 #include <type_traits>
 
@@ -631,7 +631,7 @@ __device__ __forceinline__ void attend(const AttnParams& p) {
   // A operand, so their rows go straight into registers, two references at a time.  Behind Q and in front of the other tiles, so that the
   // one wait for Q covers them too (fetched behind it they cost a second latency: 2 heads of 256 rows in 4 segments 10.76 -> 9.72 us at D 128, with the
   // renewals in front of the stream; at D 64 8.60 -> 7.50, 8 heads of 1024 17.6 -> 16.6 and 13.1 -> 12.3).
-  int n_ref = 0;   // references of later segments that the wave needs, at most kMaxRefs (see choose_shape)
+  int n_ref = 0;   // references of later segments that the wave needs, at most L::max_refs (see choose_shape)
   bf16x8 ref_a[KNOWN ? KS : 1], ref_b[KNOWN ? KS : 1];
   auto load_ref = [&](int s, auto& kf) __attribute__((always_inline)) {
     const __bf16* kp = kg + (int64_t)min(renew_key((s + 1) * p.renew) + ql, Sk - 1) * p.k_ss + 8 * hf;

@@ -29,9 +29,11 @@ constexpr int64_t kStreamAccBytes = (int64_t)128 << 20;
 
 // Up to this many threads, a third more than the chip holds at once, the accumulator is requested together with the block and both lse: the launch is
 // two memory latencies long otherwise (one for the lse that say whether the accumulator is used), and nothing else runs beside the first. us an Update of
-// fp32 blocks, behind the lse / at once: 16384 rows of 128 5.4 / 5.0, 42648 of 64 6.5 / 6.2, of 128 10.7 / 10.0 (682368 threads), bf16 blocks 10.5 / 9.5; onto an
-// empty accumulator, whose reading is then for nothing, the same or less.  Beyond it the bytes count: 65536 of 128 17.3 / 16.4, but onto an empty
-// accumulator 15.4 / 18.4.
+// fp32 blocks in a train, behind the lse / at once: 16384 rows of 128 (262144 threads) 5.8 / 5.4, 42648 of 64 (341184) 6.5 / 6.2, of 128 (682368) 10.7 / 10.0, bf16 blocks 10.5 / 9.5.
+// An empty accumulator is then read for nothing: one in a cache the same, one from memory 4.7 / 5.0 at 131072 threads, 6.7 / 9.1 at 341000, 11.1 / 15.2 at 690000, which
+// the next Update makes up for: folds of two from memory 12.0 / 11.0, 16.9 / 16.6, 27.2 / 26.4, of six 30.2 / 26.5, 44.7 / 44.1, 72.3 / 67.9; about 500000, just
+// below what the chip holds, 20.5 / 20.8 and 54.8 / 54.9.  Beyond the line full accumulators gain up to a million threads (18.4 / 16.5 at 800000, 21.1 / 19.8 at
+// 1048576, from memory) and empty ones lose more (12.2 / 16.8, 14.7 / 20.3).
 constexpr int64_t kAtOnceThreads = 256 * 2048 * 4 / 3;
 
 // One row is always handled inside a single wavefront: `tpr` (a power of two <= 64) threads
@@ -42,7 +44,7 @@ constexpr int64_t kAtOnceThreads = 256 * 2048 * 4 / 3;
 // program order within one wave guarantees.  Neighbouring thread groups take neighbouring
 // rows, so a wave touches one contiguous span of each stream.  (Giving a group several rows,
 // near or far apart, measured slower; so did one or four chunks per thread.)
-// A wave whose rows all have an empty accumulator (the first Update of a fold) does not read it: the
+// Where not everything is requested at once (AT_ONCE), a wave whose rows all have an empty accumulator (the first Update of a fold) does not read it: the
 // block's loads go out first, the accumulator's once the two lse are there.  Eight Updates of
 // 512 MiB fp32 blocks, the first onto an empty accumulator, 2034 -> 1919 us; two of 32 MiB bf16 blocks 62.6 -> 53.2.
 template <bool BLK_BF16, bool STREAM_ACC, bool AT_ONCE>
