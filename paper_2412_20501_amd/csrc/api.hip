@@ -209,7 +209,10 @@ int choose_shape(const tr::AttnParams& p, int D, bool pack, int out_bytes, doubl
     const double alone = few ? c.few : c.idle + (c.busy - c.idle) * fill * fill;   // (a chip that is not full runs at a higher clock)
     // (What a later segment costs key groups more than one; us a segment, 4 x 1 and 2 x 2: 8 heads of 1024 in 8 at D 128 0.53 and 0.84, at D 64 0.50 and 0.62.)
     const double ref = shape == tr::kShape4x2 ? 0.7 + 0.6 * fill : (D == 64 ? 0.3 : 0.5) + 0.3 * fill;
-    const double fix = (few ? c.fix_few : c.fix) + (groups ? ref * refs : 0.0);
+    // (An odd number of sub-tiles is a step more for one of the key groups, which counts where there are few.  us, 4 x 1 and 2 x 2: rings without a mask of 288 keys in 4 at D 128 10.6
+    // and 11.3, of 292 11.7 and 11.5, of 412 12.6 and 13.1, of 464 13.9 and 13.7, at D 64 of 156 in 2 6.3 and 6.9, of 280 in 4 8.4 and 8.8, of 324 9.4 and 9.4, of 408 10.0 and 9.6.)
+    const bool odd = refs > 0 && !p.causal && p.Sk <= (D == 64 ? 288 : 416) && (p.Sk + 31) / 32 % 2 == 1;
+    const double fix = (few ? c.fix_few : c.fix) + (groups ? ref * refs + (odd ? (D == 64 ? 0.6 : 0.8) : 0.0) : 0.0);
     const double rounds = std::ceil(n / kCUs);
     double time;
     if (per_cu > 1 && n > kCUs) {   // workgroups of one compute unit fill each other's gaps

@@ -20,7 +20,7 @@ def lib():
 @pytest.mark.parametrize("H,seg,n,D", [
     (2, 64, 4, 64),       # as short as segments of key groups can be: every step but the first renews
     (2, 64, 4, 128),
-    (2, 95, 3, 64),       # renewed every 64 keys, rows and keys end inside a sub-tile
+    (2, 75, 4, 64),       # renewed every 64 keys, rows and keys end inside a sub-tile
     (1, 97, 5, 128),      # an odd number of sub-tiles a segment: either key group holds its first one
     (2, 161, 2, 128),     # one reference, for one key group
     (3, 260, 4, 64),      # references beyond the tiles that are loaded before the loop

@@ -102,6 +102,15 @@ def test_where_three_workgroups_of_64_rows_share_a_unit(tr):
     assert plan(tr, 1, 16, 16, 2462, 27776, 64, 25314)[0] > 1                   # uncut 323, in three parts 287
 
 
+def test_short_rings_of_an_odd_number_of_sub_tiles(tr):
+    """One of two key groups has a step more then; us, one key group and two."""
+    for H, S, n, D, groups in ((6, 288, 4, 128, 1), (2, 292, 4, 128, 2),        # 10.6 and 11.3, 11.7 and 11.5
+                               (8, 412, 4, 128, 1), (4, 464, 4, 128, 2),        # 12.6 and 13.1, 13.9 and 13.7
+                               (4, 156, 2, 64, 1), (4, 280, 4, 64, 1), (4, 408, 4, 64, 2)):   # 6.3 and 6.9, 8.4 and 8.8, 10.0 and 9.6
+        assert shape(tr, RING, 1, H, H, S, S, D, None, n)[1] == groups
+    assert shape(tr, RING, 1, 2, 2, 256, 256, 64, None, 4) == (64, 2)
+
+
 def test_packed_rings_have_one_key_group(tr):
     """Rings whose heads share a row space, which fills the chip: no kernel with key groups is there for them."""
     for D in (64, 128):
