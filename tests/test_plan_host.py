@@ -47,6 +47,14 @@ def test_short_calls_of_few_heads_are_cut(tr):
     assert plan(tr, 1, 1, 1, 6762, 1812, 128, -4950)[0] > 1                     # 17.6 and 21.8
 
 
+def test_long_calls_of_few_rows_are_cut_at_head_dim_128(tr):
+    """us, cut and in one piece."""
+    assert plan(tr, 2, 32, 32, 165, 8866, 128, 8701)[0] > 1                     # 73 and 90
+    assert plan(tr, 2, 32, 32, 147, 7438, 128)[0] > 1                           # 62 and 81
+    assert plan(tr, 4, 4, 2, 889, 8060, 128)[0] > 1                             # 67 and 80
+    assert plan(tr, 2, 12, 3, 419, 4343, 128, 3924)[0] > 1                      # 37 and 42
+
+
 def test_a_packed_grid_stays_within_the_dispatch_limit(tr):
     """2^32 threads in one dimension: the plain form's second grid dimension holds what a packed launch would not."""
     assert plan(tr, 2_700_000, 2, 1, 257, 8, 64) == (1, 1)
