@@ -351,7 +351,7 @@ bool plan_parts(const tr::AttnParams& p, int D, bool may_cut, PartPlan& best) {
     cut += 5.0 + 0.25 * best.parts + (double)best.out_elems * 4 / 3.5e6;
     // The line with the least regret of those tried, on 1970 calls near it: 0.6 % (D 64) and 0.4 % (D 128) above the faster side on average, 15 and 9 of them by more than a tenth;
     // the estimates as they are 1.9 % and one in fifteen.  (What it adds is the renewals of short calls: 3 heads of 1251 rows at D 64 12.4 cut and 14.3, 2 of 1053 at D 128 15.0 and 17.0;
-    // with 3.0 0.9 % and 31.  With 0.85 and 4.0 at D 128 0.55 % and 15, long calls above all: 2 x 32 heads of 165 rows behind 8701 keys 73 and 90, 2 x 32 of 147 on 7438 62 and 81, 8 of 889 on
+    // with 3.0 0.9 % and 31.  With 0.85 and 4.0 at D 128 0.55 % and 15, long calls above all: 2 x 32 heads of 165 rows behind 8701 keys 73 and 90, 2 x 32 of 147 on 7438 62 and 81, 16 of 889 on
     // 8060 67 and 80.)
     whole = std::max(whole, stream + fix);
     if (std::max((D == 64 ? 0.85 * whole + 4.0 : 0.92 * whole + 2.5) + 0.6 * (best.parts - 1), 0.95 * whole) < cut) {
